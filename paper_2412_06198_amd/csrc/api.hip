@@ -38,7 +38,7 @@ void carve(sa_ctx *c) {
   c->off[5] = o; o += align256(kvg);
   c->off[6] = o; o += align256(kvg);
   c->off[7] = o; o += 256;
-  c->off[8] = o; o += align256(sa::index_scratch_bytes(s.Hq));
+  c->off[8] = o; o += align256(sa::index_scratch_bytes(s));
   c->off[9] = o; o += align256((size_t)s.Hq * (s.N / 32) * 4);
   c->off[10] = o; o += align256(sa::decode_partial_bytes(s));
   c->off[11] = o; o += align256((size_t)(s.Hq + s.Hkv) * 4);
@@ -301,10 +301,9 @@ sa_status sa_estimate_and_index(sa_ctx *c, const void *Q, const void *K, sa_scor
     const uint16_t *q = (const uint16_t *)Q, *k = (const uint16_t *)K;
     using sa::IndexStage;
     using sa::EstimatePart;
-    hipError_t e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, IndexStage::Zero, st);
+    hipError_t e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, IndexStage::Zero, st, true);
     if (e == hipSuccess) e = sa::launch_estimate_part(c->sh, c->ws, q, k, scores, EstimatePart::KChain, nullptr, st);
-    if (e == hipSuccess) e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, IndexStage::ColumnsDiagonals, st);
-    if (e == hipSuccess) e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, IndexStage::Decide, st);
+    if (e == hipSuccess) e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, IndexStage::ColumnsDiagonals, st, true);
     if (e == hipSuccess)
       e = sa::launch_estimate_part(c->sh, c->ws, q, k, scores, EstimatePart::QChain, out.pattern, st);
     if (e == hipSuccess) e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, IndexStage::Blocks, st, true);

@@ -8,23 +8,33 @@
 //
 // Five selections run side by side for every head, so that nothing waits on the
 // pattern decision: the probe_v / probe_s best of v and s (pattern rule), the
-// k_v best columns, the k_s best diagonals, the k_b - nb best blocks.  Each is a
-// radix select in three levels (11 + 10 + 10 key bits; the sign bit is clear).  Every level is a
-// launch of P workgroups per head (LDS histograms, flushed to global memory with
-// integer atomics) followed by a one-workgroup-per-head launch that reads the
-// merged histogram and fixes the next digit: kernel boundaries are the only
-// synchronisation between workgroups, no fences or spin waits.  Two more
-// launches count and then emit the selected entries in index order (wave
-// ballots), so the result is sorted without any sort.
+// k_v best columns, the k_s best diagonals, the k_b - nb best blocks.  Five launches:
+//   zero    clears the head's counters;
+//   hist    one pass over the scores: 2048 logarithmic bins (64 per octave);
+//   refine  a second pass that splits a bin in 1024, only for selections whose boundary bin holds
+//           more keys than a list can take (it returns at once otherwise, which is the rule);
+//   count   a pass that counts, per wave, the keys above the boundary bin and appends the few
+//           inside it to a list, from which the exact threshold follows;
+//   emit    a pass that writes the selected entries in index order (wave ballots), so the result
+//           is sorted without any sort; only the pattern's own arrays are read.
+// Small steps between the passes (finding a bin, resolving a list, prefixes, the pattern decision)
+// are done by the workgroup of a head and array that arrives last, not by launches of their own:
+// an integer ticket says who that is, nobody waits.  What it reads from the others travels in
+// atomic operations and agent-scope loads and stores (which pass the L2 caches by), each completed
+// before the ticket is drawn, so that no cache has to be written back or invalidated on the way.
+// Every launch costs 3 to 8 us whatever it does, and a pass over the scores of 32 heads 10 to 40 us.
+// Short prompts take two launches, see idx_select_kernel.  With ten launches and five passes before,
+// 32 heads took 85 us at 16K tokens, 105 at 32K, 113 at 64K and 170 at 128K; now 41, 54, 59 and 103
+// (4 heads at 4K: 70 and 14).
 //
 // With the per-row block rule (every row block of a Block-Cluster head keeps the
 // same fraction of its causal blocks) the fifth selection is switched off and
-// one more launch selects inside each row instead: one wave per row, keys in
+// the emission selects inside each row instead: one wave per row, keys in
 // registers, the threshold found bit by bit.
 //
-// With block-granular diagonals four launches after the emission turn the selected
+// With block-granular diagonals two launches after the emission turn the selected
 // offsets of the Interval-Slash heads into rows of the block CSR (bitmap per row,
-// count, prefix, ordered write) and empty the offset list.
+// count and prefix, ordered write).
 #include <cstddef>
 
 #include "sa_internal.h"
@@ -34,235 +44,923 @@ namespace {
 
 constexpr int BT = 256;            // threads per workgroup
 constexpr int WPB = BT / 64;       // waves per workgroup
-constexpr int kMaxParts = 64;      // workgroups per head
-constexpr int kMaxPW = kMaxParts * WPB;
+constexpr int kUnit = 256;         // keys a wave takes with one load: 16 bytes per lane
+constexpr int kVsUnits = 4;        // units of v or s per wave (one where a workgroup walks a whole array)
+constexpr int kMaxVsParts = kMaxSeq / (kVsUnits * kUnit);
+constexpr int kMaxBlkParts = 512;  // waves that share the block map of a head
 constexpr int kMaxNb = kMaxSeq / 64;
 constexpr int NSEL = 5;            // 0: v probe, 1: s probe, 2: v top k_v, 3: s top k_s, 4: blk top k_b - nb
-constexpr int L1BINS = 2048, L2BINS = 1024, L3BINS = 1024;  // 11 + 10 + 10 key bits below the sign bit
+constexpr int kBins = 2048, kSubBins = 1024;
+constexpr int kBinShift = 17;      // key bits below a bin: 6 mantissa bits count
+// Bin 0 takes everything up to 2^-25 (2^-19), the last bin everything from 2^7 (2^13) on: window
+// sums stay below 64 and block weights below 1, or below the row length where they are scaled by it.
+constexpr int kBase = ((127 + 7) << 6) - kBins, kBaseRowNorm = ((127 + 13) << 6) - kBins;
+constexpr int kListVs = 4096, kListBlk = 16384;  // boundary keys a list takes
+
+typedef unsigned long long u64;
+typedef unsigned u32x4a __attribute__((ext_vector_type(4), aligned(4)));
 
 // per-head scratch in the workspace
 struct IdxScratch {
-  alignas(16) unsigned hist1[3][L1BINS];  // level 1 per array: v, s, blk
-  alignas(16) unsigned hist2[NSEL][L2BINS];
-  alignas(16) unsigned hist3[NSEL][L3BINS];
-  unsigned long long vtot, ct, topsum[2];
+  alignas(16) unsigned hist1[3][kBins];   // per array: v, s, blk
+  alignas(16) unsigned hist2[NSEL][kSubBins];
+  u64 vtot, ct, topsum[2];
+  unsigned nlist[NSEL];                   // boundary keys appended so far
+  unsigned ticket[3][3];                  // per launch (hist, refine, count) and array
+  unsigned ticket_vs;                     // v and s resolved
   // everything above is zeroed at the start of a call
-  unsigned prefix[NSEL], remaining[NSEL];
+  alignas(16) u64 psum[2];                // sums of the probe best of v and s
+  unsigned lo[NSEL], last[NSEL];          // key range that holds the k-th key of a selection ...
+  unsigned rem[NSEL], pop[NSEL];          // ... its rank inside, and the keys in the range
   unsigned thr[NSEL], need[NSEL];
-  unsigned wgt[2][kMaxPW], weq[2][kMaxPW];  // v / s: counts per wave part, then exclusive prefixes
-  unsigned rowgt[kMaxNb], roweq[kMaxNb];    // blk: counts per row, then exclusive prefixes
-  int pattern;
+  unsigned wgt[2][kMaxVsParts], weq[2][kMaxVsParts];  // v / s: counts per wave part, then exclusive prefixes
+  unsigned bgt[kMaxBlkParts], beq[kMaxBlkParts];      // blk: likewise
+  unsigned ticket_rows;                   // block-granular diagonals: cleared by the emission
+  unsigned rowcnt[kMaxNb];                // block-granular diagonals: blocks per row
 };
-constexpr size_t kZeroWords = offsetof(IdxScratch, prefix) / 4;
+constexpr size_t kZeroBytes = offsetof(IdxScratch, psum);
+static_assert(kZeroBytes % 16 == 0, "cleared 16 bytes at a time");
 
 struct IdxArgs {
   const unsigned *v, *s, *blk;     // fp32 scores as bit patterns
   IdxScratch *scratch;
+  u64 *list_vs, *list_blk;         // [Hq][4][cap_vs], [Hq][cap_blk]: boundary keys, (key << 32) | wave part
+  int32_t *doffs;                  // [Hq][k_s] selected offsets when they are kept as blocks
+  int cap_vs, cap_blk;
   Shape sh;
   Override ov;
   sa_index out;
-  int P, PW, seg;                  // workgroups per head, wave parts per head, keys of v / s per wave part
+  int Pv, Pb;                      // workgroups per head for v (and for s), and for the block map
+  int vpart, bpart;                // entries of v and s, and of the block map (row-major, upper half included) per wave
+  int first;                       // array v of a launch starts at workgroup -first (see Role)
+  int decide_here;                 // 1: the launches before the emission write the patterns, 0: it decides by itself
   int ksel[NSEL];                  // clamped k of every selection
-  // Which part of the work a launch does: bit 0 = the selections on v and s, bit 1 = the selection
-  // on the block map (the two parts touch disjoint fields of the scratch and may run side by side).
-  int mask;
+  u64 nb_magic;                    // ceil(2^40 / nb)
+  unsigned wrap_magic;             // ceil(2^20 / nb)
+  u64 share_magic;                 // floor(2^64 / (nb (nb + 1) / 2)) + 1
+  u64 E, ET;                       // causal window entries; those in the sink + band region
   // Heads (bit h) whose pattern override makes the v/s selections, or the block selection, unnecessary.
   uint32_t skip_vs[kMaxHeads / 32], skip_blk[kMaxHeads / 32];
   // Not null: the patterns an earlier launch decided ([Hq], device); the block-map part of the work
   // is then done for the Block-Cluster heads only (the block map of the others was never computed).
   const int32_t *decided;
+  const HeadBudget *hb;            // not null: budgets per head instead of the configuration's
 };
+
+// What crosses workgroups inside a launch: agent-scope accesses, see the top of the file.
+__device__ inline unsigned agent_load(const unsigned *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline u64 agent_load(const u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void agent_store(unsigned *p, unsigned x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void agent_store(u64 *p, u64 x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// True in the workgroup that draws ticket n - 1: every access of the others has completed by then.
+// Called by all threads.
+__device__ inline bool arrives_last(unsigned *ticket, unsigned n) {
+  __shared__ unsigned s_last;
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this thread's stores and atomics have been performed
+  __syncthreads();
+  if (threadIdx.x == 0) s_last = atomicAdd(ticket, 1u) == n - 1;
+  __syncthreads();
+  asm volatile("" ::: "memory");
+  return s_last != 0;
+}
+
+__device__ inline HeadBudget head_budget(const IdxArgs &a, int h) {
+  if (a.hb) return a.hb[h];
+  HeadBudget b;
+  b.k_v = a.ksel[2]; b.k_s = a.ksel[3]; b.k_b = a.sh.k_b; b.local = a.sh.local;
+  return b;
+}
+
+// k of selection q, never more than there are candidates
+__device__ inline int ksel(const IdxArgs &a, int h, int q) {
+  if (!a.hb || q < 2) return a.ksel[q];
+  const HeadBudget b = a.hb[h];
+  if (q < 4) return min(q == 2 ? b.k_v : b.k_s, a.sh.N);
+  const long long ncand = (long long)a.sh.nb * (a.sh.nb - 1) / 2, k = (long long)b.k_b - a.sh.nb;
+  return (int)(k < 0 ? 0 : k < ncand ? k : ncand);
+}
 
 // Whether a launch has to touch one part of a head's work (the selections on v and s, or the one on
 // the block map): with a pattern override only the overridden pattern's own selection is needed,
-// none for Triangular.  (Skipping the rest of a head as soon as it passes the Triangular test was
-// tried too: the flag costs every later workgroup one more dependent read, more than it saves.)
+// none for Triangular.
 __device__ inline bool head_wants(const IdxArgs &a, int h, bool blk_part) {
   const int w = h >> 5;  // four words: selected without indexing the argument block dynamically
   const uint32_t *m = blk_part ? a.skip_blk : a.skip_vs;
   const uint32_t bits = w == 0 ? m[0] : w == 1 ? m[1] : w == 2 ? m[2] : m[3];
   if ((bits >> (h & 31)) & 1u) return false;
-  return !(blk_part && a.decided) || a.decided[h] == SA_BLOCK_CLUSTER;
+  if (!blk_part) return true;
+  if (a.decided && a.decided[h] != SA_BLOCK_CLUSTER) return false;
+  return !a.sh.row_select && ksel(a, h, 4) > 0;
 }
 
-// floor(x * 2^30) of a finite fp32 x >= 0 given by its bits.
-__device__ inline unsigned long long fx30(unsigned bits) {
-  const int e = (int)(bits >> 23) & 0xFF;
-  if (e == 0) return 0ull;  // denormals are far below 2^-30
-  const unsigned long long m = (unsigned long long)((bits & 0x7FFFFFu) | 0x800000u);
-  const int sh = e - 120;   // (e - 127) - 23 + 30
-  if (sh >= 0) return sh < 40 ? (m << sh) : ~0ull;
-  return (-sh) < 64 ? (m >> (-sh)) : 0ull;
+// A workgroup's array and its number among the workgroups of that array.
+struct Role { int arr, p, n; };
+__device__ inline Role role_of(const IdxArgs &a) {
+  const int x = (int)blockIdx.x + a.first;
+  if (x < a.Pv) return {0, x, a.Pv};
+  if (x < 2 * a.Pv) return {1, x - a.Pv, a.Pv};
+  return {2, x - 2 * a.Pv, a.Pb};
+}
+// Selections of an array: 0 and 2 on v, 1 and 3 on s, 4 on the block map.
+__device__ inline int n_sel(int arr) { return arr < 2 ? 2 : 1; }
+__device__ inline int sel_of(int arr, int k) { return arr < 2 ? arr + 2 * k : 4; }
+
+// floor(x * 2^30) of a finite fp32 x >= 0 given by its bits: the scaling is exact, the conversion
+// truncates, and from 2^32 on the value is a multiple of 2^9.
+__device__ inline u64 fx30(unsigned bits) {
+  const float f = __uint_as_float(bits) * 1073741824.f;
+  const bool big = f >= 4294967296.f;
+  const u64 u = (unsigned)(big ? f * 0.00390625f : f);
+  return big ? u << 8 : u;
 }
 
-// The Triangular test of the pattern rule on the sums of the level-1 histogram launch; E receives
-// the number of causal window entries.
-__device__ inline bool triangular_test(const IdxArgs &a, const IdxScratch *G, unsigned long long &E) {
+// Pattern of head h by the integer lift tests, from the sums of the hist launch (vtot, ct) and the
+// sums sv, ss of the probe best of v and s.
+__device__ inline int decide_pattern(const IdxArgs &a, const IdxScratch *G, u64 sv, u64 ss) {
   const Shape &sh = a.sh;
-  const int N = sh.N, nb = sh.nb;
-  long long sbnd = (long long)sh.sink * sh.b;
-  if (sbnd > N) sbnd = N;
-  long long lb0 = (long long)(nb - sh.local) * sh.b;
-  if (lb0 < sbnd) lb0 = sbnd;
-  unsigned long long ET = 0;
-  E = 0;
-  for (int i = 0; i < sh.w; ++i) {
-    const long long qi1 = (long long)N - sh.w + i + 1;
-    E += (unsigned long long)qi1;
-    ET += (unsigned long long)(qi1 < sbnd ? qi1 : sbnd);
-    if (qi1 > lb0) ET += (unsigned long long)(qi1 - lb0);
-  }
   typedef unsigned __int128 u128;
-  return (u128)sh.lift_den * G->ct * E >= (u128)sh.lift_num * G->vtot * ET;
-}
-
-// Pattern of head h: the caller's override, else the integer lift tests on the sums that the level-1
-// histogram launch (vtot, ct) and the counting launch (topsum) left in the scratch.
-__device__ inline int decide_pattern(const IdxArgs &a, const IdxScratch *G, int h) {
-  const Shape &sh = a.sh;
-  const int pat = a.ov.pat[h];
-  if (pat >= 0) return pat;
-  unsigned long long E;
-  if (triangular_test(a, G, E)) return SA_TRIANGULAR;
-  typedef unsigned __int128 u128;
-  // sum over the probe best = sum over keys above the threshold + ties at the threshold
-  const unsigned long long sv =
-      a.ksel[0] > 0 ? G->topsum[0] + (unsigned long long)G->need[0] * fx30(G->thr[0]) : 0ull;
-  const unsigned long long ss =
-      a.ksel[1] > 0 ? G->topsum[1] + (unsigned long long)G->need[1] * fx30(G->thr[1]) : 0ull;
-  if ((u128)sh.lift_den * (sv + ss) * E >=
-      (u128)sh.lift_num * G->vtot * (unsigned long long)(sh.probe_v + sh.probe_s) * (unsigned long long)sh.w)
+  const u64 vtot = agent_load(&G->vtot);
+  if ((u128)sh.lift_den * agent_load(&G->ct) * a.E >= (u128)sh.lift_num * vtot * a.ET) return SA_TRIANGULAR;
+  if ((u128)sh.lift_den * (sv + ss) * a.E >=
+      (u128)sh.lift_num * vtot * (u64)(sh.probe_v + sh.probe_s) * (u64)sh.w)
     return SA_INTERVAL_SLASH;
   return SA_BLOCK_CLUSTER;
 }
 
 // Blocks that row block R keeps under the per-row rule: the same fraction k_b / (nb (nb+1) / 2) of
-// its R + 1 causal blocks, rounded up (the diagonal block is one of them).
-__device__ inline int row_share(const Shape &sh, int R) {
-  const long long all = (long long)sh.nb * (sh.nb + 1) / 2;
-  const long long k = ((long long)sh.k_b * (R + 1) + all - 1) / all;
-  return (int)(k < R + 1 ? k : R + 1);
+// its R + 1 causal blocks, rounded up (the diagonal block is one of them).  The quotient by a product
+// with the reciprocal: exact, dividends stay below 2^36 and the divisor below 2^23.
+__device__ inline int row_share(const IdxArgs &a, int R) {
+  const u64 all = (u64)a.sh.nb * (a.sh.nb + 1) / 2;
+  const u64 k = all == 1 ? 1 : __umul64hi((u64)min((u64)a.sh.k_b, all) * (R + 1) + all - 1, a.share_magic);
+  return (int)(k < (u64)R + 1 ? k : R + 1);
+}
+
+// Triangular rows: row R keeps the blocks C < min(sink, band start) and the band of `local` blocks.
+__device__ inline int tri_prefix(int sink, int local, int R) {  // blocks in the rows above R
+  if (R <= local) return R * (R + 1) / 2;
+  const int m = R - local;  // rows whose band starts at 1 .. m
+  const int s = m <= sink ? m * (m + 1) / 2 : sink * (sink + 1) / 2 + (m - sink) * sink;
+  return local * (local + 1) / 2 + m * local + s;
 }
 
 // ---- candidate walks ---------------------------------------------------------------------------
-// Score arrays are read four keys per lane (16-byte loads when the segment start is 16-byte
-// aligned) with several independent loads in flight per thread: these loops are latency-bound.
-// fn(k, i0, lim) receives keys k[0..3] of indices i0..i0+3; entries with i0 + j >= lim are padding.
-struct Keys4 { unsigned k[4]; };
+// Four entries of an array per lane: keys, their place (v and s: R = 0 and C = the index), which of
+// them lie in the array (bit j of `in`) and which are candidates (`ok`).
+struct Four {
+  unsigned k[4];
+  int R[4], C[4];
+  unsigned in, ok;
+};
 
-__device__ inline Keys4 load4(const unsigned *p, int i, int lim, bool vec) {
-  Keys4 r;
-  if (i + 3 < lim && vec) {
-    const uint4 v = *(const uint4 *)(p + i);
-    r.k[0] = v.x; r.k[1] = v.y; r.k[2] = v.z; r.k[3] = v.w;
-  } else {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) r.k[j] = (i + j < lim) ? p[i + j] : 0u;
-  }
-  return r;
-}
-
-// one wave, indices [lo,hi) in increasing groups of 256: lane l holds lo + 256g + 4l .. +3
+// One wave part of an array, a unit of 256 entries at a time, two units' loads ahead.  v and s are
+// plain; the block map is walked as a run of the row-major map, of which the entries C < R are the
+// candidates and units above the diagonal are passed over unread.  Most units of long rows are all
+// candidates, which is wave-uniform and carries no tests per entry.  fn is called by all 64 lanes
+// (and compiled in once: in the short launches of this file the cold fetch of the code itself
+// counts).  With row_norm the key of an entry of row R is its value times R + 1 (one fp32
+// multiplication; all values are >= +0, so the products order like their bit patterns too).
+// part: wave-uniform.
 template <class Fn>
-__device__ inline void wave_visit4(const unsigned *p, int lo, int hi, bool vec, Fn fn) {
-  constexpr int U = 4;
-  const int lane = threadIdx.x & 63;
-  for (int g0 = lo; g0 < hi; g0 += 256 * U) {
-    Keys4 v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = load4(p, g0 + 256 * u + 4 * lane, hi, vec);
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (g0 + 256 * u < hi) fn(v[u], g0 + 256 * u + 4 * lane, hi);
-  }
-}
-
-// The strictly-lower part (C < R) of the rows R = first, first + stride, ... of the nb x nb block
-// map, walked by one wave in units of 1024 keys with the next unit's loads issued before the
-// current one is processed: short rows would otherwise expose one memory round trip each.
-// begin(R) / end(R) bracket a row.
-// With scale_rows the key of an entry of row R is its value times R + 1 (one fp32 multiplication;
-// all values are >= +0, so the products order like their bit patterns too).
-template <class Begin, class Fn, class End>
-__device__ inline void wave_rows_visit4(const unsigned *blk, int nb, int first, int stride, bool vec,
-                                        bool scale_rows, Begin begin, Fn fn, End end) {
-  constexpr int U = 4;
-  const int lane = threadIdx.x & 63;
-  int R = first, c0 = 0;    // unit being processed
-  int Rn = first, cn = 0;   // unit being loaded
-  Keys4 cur[U], nxt[U];
-  auto load_unit = [&](Keys4 (&dst)[U], int row, int col) {
-    const unsigned *p = blk + (size_t)row * nb;
-#pragma unroll
-    for (int u = 0; u < U; ++u) dst[u] = load4(p, col + 256 * u + 4 * lane, row, vec);
-  };
-  auto advance = [&](int &row, int &col) {
-    col += 256 * U;
-    if (col >= row) { row += stride; col = 0; }
-  };
-  if (Rn < nb) load_unit(nxt, Rn, cn);
-  while (R < nb) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) cur[u] = nxt[u];
-    advance(Rn, cn);
-    if (Rn < nb) load_unit(nxt, Rn, cn);
-    if (c0 == 0) begin(R);
-    if (scale_rows) {
-      const float len = (float)(R + 1);
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) cur[u].k[j] = __float_as_uint(__uint_as_float(cur[u].k[j]) * len);
+__device__ inline void visit(const IdxArgs &a, int arr, const unsigned *src, int part, Fn fn) {
+  const int lane = threadIdx.x & 63, nb = a.sh.nb;
+  const unsigned total = arr == 2 ? (unsigned)nb * (unsigned)nb : (unsigned)a.sh.N;
+  const unsigned len = (unsigned)(arr == 2 ? a.bpart : a.vpart);
+  const unsigned begin = (unsigned)part * len, end = min(begin + len, total);
+  struct Unit { u32x4a x; int R0, C0, kind; };  // kind 0: nothing to see, 1: mixed, 2: all candidates
+  auto fetch = [&](unsigned u0, Unit &u) {
+    u.kind = u.R0 = 0;
+    u.C0 = (int)u0;
+    if (u0 >= end) return;
+    if (arr == 2) {
+      u.R0 = (int)(((u64)u0 * a.nb_magic) >> 40);
+      u.C0 = (int)u0 - u.R0 * nb;
+      u.kind = u.C0 + kUnit > nb ? 1 : u.C0 + kUnit <= u.R0 ? 2 : u.C0 > u.R0 ? 0 : 1;
+      if (u.kind == 0) return;
+    } else {
+      u.kind = u0 + kUnit <= total ? 2 : 1;
     }
+    const unsigned e = u0 + 4 * lane;
+    if (e + 3 < total) {
+      u.x = *(const u32x4a *)(src + e);
+    } else {
+      u.x.x = e < total ? src[e] : 0u;
+      u.x.y = e + 1 < total ? src[e + 1] : 0u;
+      u.x.z = e + 2 < total ? src[e + 2] : 0u;
+      u.x.w = 0u;
+    }
+  };
+  Unit cur, n1, n2;
+  fetch(begin, n1);
+  fetch(begin + kUnit, n2);
+#pragma unroll 1
+  for (unsigned u0 = begin; u0 < end; u0 += kUnit) {
+    cur = n1;
+    n1 = n2;
+    fetch(u0 + 2 * kUnit, n2);
+    if (cur.kind == 0) continue;
+    Four f;
+    f.k[0] = cur.x.x; f.k[1] = cur.x.y; f.k[2] = cur.x.z; f.k[3] = cur.x.w;
+    int c = cur.C0 + 4 * lane, r = cur.R0;
+    if (cur.kind == 2) {
+      f.in = f.ok = 15u;
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (c0 + 256 * u < R) fn(cur[u], c0 + 256 * u + 4 * lane, R);
-    if (c0 + 256 * U >= R) end(R);
-    advance(R, c0);
+      for (int j = 0; j < 4; ++j) { f.R[j] = r; f.C[j] = c + j; }
+    } else if (arr != 2) {
+      f.in = f.ok = c < (int)total ? 15u : 0u;  // N is a multiple of 4
+#pragma unroll
+      for (int j = 0; j < 4; ++j) { f.R[j] = r; f.C[j] = c + j; }
+    } else {
+      // rows passed: one at most where a unit is no longer than a row, else by c / nb (c < nb + 256)
+      const int w = nb >= kUnit ? (c >= nb ? 1 : 0) : (int)(((unsigned)c * a.wrap_magic) >> 20);
+      r += w;
+      c -= w * nb;
+      if ((nb & 3) == 0) {  // the four entries share their row
+        f.in = u0 + 4 * lane < total ? 15u : 0u;
+        f.ok = f.in & ((1u << min(max(r - c, 0), 4)) - 1u);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { f.R[j] = r; f.C[j] = c + j; }
+      } else {
+        f.in = f.ok = 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          f.R[j] = r; f.C[j] = c;
+          if (u0 + 4 * lane + j < total) {
+            f.in |= 1u << j;
+            if (c < r) f.ok |= 1u << j;
+          }
+          const bool wrap = c + 1 >= nb;
+          r += wrap ? 1 : 0;
+          c = wrap ? 0 : c + 1;
+        }
+      }
+    }
+    if (arr == 2 && a.sh.row_norm) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) f.k[j] = __float_as_uint(__uint_as_float(f.k[j]) * (float)(f.R[j] + 1));
+    }
+    fn(f);
   }
 }
 
-// Adds one count per valid lane to an LDS histogram.  Same-address LDS atomics are serialised
-// lane by lane, and the scores of a head share their leading bits, so the bin of the first valid
-// lane is added once with its lane count (two such peels); what is left goes one atomic per lane.
-// Must be called by all 64 lanes.
-__device__ inline void hist_add(unsigned *h, unsigned bin, bool valid) {
-#pragma unroll
-  for (int peel = 0; peel < 2; ++peel) {
-    const unsigned long long mv = __ballot(valid);
-    if (mv == 0) return;
-    const int first = __ffsll((long long)mv) - 1;
-    const unsigned b0 = __builtin_amdgcn_readlane(bin, first);
-    const bool same = valid && bin == b0;
-    const unsigned long long ms = __ballot(same);
-    if ((int)(threadIdx.x & 63) == first) atomicAdd(&h[b0], (unsigned)__popcll(ms));
-    valid = valid && !same;
-  }
-  if (valid) atomicAdd(&h[bin], 1u);
+// Prefix sums and sums over a wave on the data-parallel lane moves (row shifts inside 16 lanes, then
+// two broadcasts): a shuffle through LDS per step is a round trip of some 60 cycles.
+template <int CTRL, int ROWS>
+__device__ inline unsigned lane_move(unsigned x) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
+}
+__device__ inline unsigned wave_inclusive_sum(unsigned x) {
+  x += lane_move<0x111, 0xF>(x);  // row_shr:1
+  x += lane_move<0x112, 0xF>(x);  // row_shr:2
+  x += lane_move<0x114, 0xF>(x);  // row_shr:4
+  x += lane_move<0x118, 0xF>(x);  // row_shr:8
+  x += lane_move<0x142, 0xA>(x);  // row_bcast:15 into rows 1 and 3
+  x += lane_move<0x143, 0xC>(x);  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+template <int CTRL, int ROWS>
+__device__ inline u64 lane_move64(u64 x) {
+  return (u64)lane_move<CTRL, ROWS>((unsigned)x) | ((u64)lane_move<CTRL, ROWS>((unsigned)(x >> 32)) << 32);
+}
+// The sum over the wave, in lane 63.
+__device__ inline u64 wave_sum63(u64 x) {
+  x += lane_move64<0x111, 0xF>(x);
+  x += lane_move64<0x112, 0xF>(x);
+  x += lane_move64<0x114, 0xF>(x);
+  x += lane_move64<0x118, 0xF>(x);
+  x += lane_move64<0x142, 0xA>(x);
+  x += lane_move64<0x143, 0xC>(x);
+  return x;
 }
 
-// Ordered emission for one 256-key group of a wave: an element is selected if its key is above the
-// threshold, or equal to it and among the first `need` such elements in index order.  put(pos, idx)
-// stores the selection; grun / erun count the greater / equal elements seen so far.
-template <class Put>
-__device__ inline void emit_group(const Keys4 &v, int i0, int lim, unsigned thr, unsigned need,
-                                  unsigned &grun, unsigned &erun, Put put) {
+// Exclusive prefixes of two values per thread over the 64 * NW threads of a workgroup: lane moves inside
+// the waves, the wave totals through LDS (wsum: 2 * NW words).  Called by all threads.
+template <int NW>
+__device__ inline void block_exclusive_scan2(unsigned &a, unsigned &b, unsigned *wsum) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const unsigned ia = wave_inclusive_sum(a), ib = wave_inclusive_sum(b);
+  if (lane == 63) { wsum[wv] = ia; wsum[NW + wv] = ib; }
+  __syncthreads();
+  const unsigned ta = wave_inclusive_sum(lane < NW ? wsum[lane] : 0u);
+  const unsigned tb = wave_inclusive_sum(lane < NW ? wsum[NW + lane] : 0u);
+  const unsigned ba = wv ? __builtin_amdgcn_readlane(ta, wv - 1) : 0u, bb = wv ? __builtin_amdgcn_readlane(tb, wv - 1) : 0u;
+  __syncthreads();
+  a = ba + ia - a;
+  b = bb + ib - b;
+}
+
+// The bins of a workgroup's histogram (NB bins of COPIES interleaved counters: the weights of a map's
+// row are nearly equal, so a wave's additions meet in a few bins, and lanes of different copies at least
+// do not wait for each other) that hold the k-th keys counted from the top bin down, for ns values of k
+// (1 <= k <= total), with the rank of that key inside the bin and the bin's count.  All threads; pick is
+// valid after the call.
+struct Pick { unsigned bin, rank, count; };
+
+template <int NT, int NB, int COPIES>
+__device__ inline void block_find_kth(const unsigned *hist, int ns, unsigned k0, unsigned k1, Pick *pick, unsigned *wsum) {
+  constexpr int PER = NB / NT;  // thread t owns PER bins, the first threads the top ones
+  const int top = NB - 1 - (int)threadIdx.x * PER;
+  unsigned c[PER], tot = 0, unused = 0;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    c[i] = hist[(top - i) * COPIES];
+#pragma unroll
+    for (int y = 1; y < COPIES; ++y) c[i] += hist[(top - i) * COPIES + y];
+    tot += c[i];
+  }
+  unsigned above = tot;
+  block_exclusive_scan2<NT / 64>(above, unused, wsum);
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    if (above < k0 && k0 <= above + c[i]) pick[0] = {(unsigned)(top - i), k0 - above, c[i]};
+    if (ns > 1 && above < k1 && k1 <= above + c[i]) pick[1] = {(unsigned)(top - i), k1 - above, c[i]};
+    above += c[i];
+  }
+  __syncthreads();
+}
+
+// grid (Hq, parts): clears the counters of a head
+__global__ __launch_bounds__(BT) void idx_zero_kernel(IdxScratch *scratch) {
+  uint4 *p = (uint4 *)(scratch + blockIdx.x);
+  for (unsigned i = blockIdx.y * BT + threadIdx.x; i < kZeroBytes / 16; i += gridDim.y * BT)
+    p[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// Shift that brings the offsets of a key range into kSubBins digits.
+__device__ inline int digit_shift(unsigned width_minus_1) {
+  const int bits = 32 - __clz((int)width_minus_1);  // __clz(0) = 32
+  return bits > 10 ? bits - 10 : 0;
+}
+
+// ---- building blocks of the passes -----------------------------------------------------------------
+constexpr int kCopies = 2;
+constexpr int kL1Words = kBins * kCopies, kSubWords = kSubBins;
+constexpr int kList = 512;        // boundary keys of a selection that a workgroup holds in LDS
+
+__device__ inline int first_bin(const IdxArgs &a, int arr) { return arr == 2 && a.sh.row_norm ? kBaseRowNorm : kBase; }
+__device__ inline const unsigned *array_of(const IdxArgs &a, int arr, int h) {
+  return arr == 2 ? a.blk + (size_t)h * a.sh.nb * a.sh.nb : (arr ? a.s : a.v) + (size_t)h * a.sh.N;
+}
+
+// One wave part into the level-1 histogram; of v also the fixed-point sums over all keys and over
+// those of the Triangular region.
+__device__ inline void hist_part(const IdxArgs &a, int arr, const unsigned *src, int part, unsigned *hist,
+                                 u64 &vt, u64 &ct) {
+  const Shape &sh = a.sh;
+  const int base = first_bin(a, arr), copy = threadIdx.x & (kCopies - 1);
+  int sbnd = (int)min((long long)sh.sink * sh.b, (long long)sh.N);
+  int lb0 = max((sh.nb - sh.local) * sh.b, sbnd);
+  visit(a, arr, src, part, [&](const Four &f) {
+    int bin[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bin[j] = min(max((int)(f.k[j] >> kBinShift) - base, 0), kBins - 1);
+    // the neighbours of a lane often share their bin
+    if (f.ok == 15u && bin[0] == bin[1] && bin[0] == bin[2] && bin[0] == bin[3]) {
+      atomicAdd(&hist[bin[0] * kCopies + copy], 4u);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if ((f.ok >> j) & 1u) atomicAdd(&hist[bin[j] * kCopies + copy], 1u);
+    }
+    if (arr == 0) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if ((f.ok >> j) & 1u) {
+          const u64 x = fx30(f.k[j]);
+          vt += x;
+          if (f.C[j] < sbnd || f.C[j] >= lb0) ct += x;
+        }
+    }
+  });
+}
+
+// The range of keys that bin `bin` of the level-1 histogram stands for.
+__device__ inline void bin_range(unsigned bin, int base, unsigned &lo, unsigned &last) {
+  lo = bin == 0 ? 0u : (bin + base) << kBinShift;
+  last = bin == kBins - 1 ? 0xFFFFFFFFu : ((bin + 1 + base) << kBinShift) - 1u;
+}
+
+// The selections of one array on their way to a threshold: the k-th key lies in lo .. last, has rank
+// `rank` from the top there, and n keys lie in that range.
+struct Ranges {
+  unsigned lo[2], last[2], rank[2], n[2];
+  __device__ inline bool open(int k, unsigned most) const { return n[k] > most && lo[k] != last[k]; }
+};
+// The digit of every wanted selection from its histogram of digits, and the narrower ranges.
+template <int NT>
+__device__ inline void narrow_step(int ns, unsigned (*hist)[kSubWords], Pick *pick, unsigned *wsum,
+                                   const bool (&want)[2], Ranges &r) {
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    if (want[k]) {
+      block_find_kth<NT, kSubBins, 1>(hist[k], 1, r.rank[k], 0u, &pick[k], wsum);
+      const int shift = digit_shift(r.last[k] - r.lo[k]);
+      r.lo[k] += pick[k].bin << shift;
+      r.last[k] = min(r.last[k], r.lo[k] + ((1u << shift) - 1u));
+      r.rank[k] = pick[k].rank;
+      r.n[k] = pick[k].count;
+    }
+}
+
+// One workgroup narrows the ranges by walks over the whole array until at most kList keys are left or
+// a single one, ...
+template <int NT>
+__device__ inline void narrow(const IdxArgs &a, int arr, const unsigned *src, int nparts, int ns,
+                              unsigned (*hist)[kSubWords], Pick *pick, unsigned *wsum, Ranges &r) {
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  while (r.open(0, kList) || r.open(1, kList)) {
+    const bool want[2] = {r.open(0, kList), r.open(1, kList)};
+    __syncthreads();
+    for (int i = threadIdx.x; i < 2 * kSubWords; i += NT) (&hist[0][0])[i] = 0u;
+    __syncthreads();
+    for (int pt = wv; pt < nparts; pt += NT / 64)
+      visit(a, arr, src, pt, [&](const Four &f) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+          if (want[k]) {
+            const int shift = digit_shift(r.last[k] - r.lo[k]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (((f.ok >> j) & 1u) && f.k[j] >= r.lo[k] && f.k[j] <= r.last[k])
+                atomicAdd(&hist[k][(f.k[j] - r.lo[k]) >> shift], 1u);
+          }
+      });
+    narrow_step<NT>(ns, hist, pick, wsum, want, r);
+  }
+  __syncthreads();
+}
+
+// ... and then, per part, counts the keys above them (up to `top`) and puts the keys inside them on
+// the lists.  A range of a single key needs no list, its keys are counted.  Selection ns - 1 is the
+// one whose entries are emitted; of the other, a probe, only the sum of the keys matters.
+template <int NT>
+__device__ inline void collect(const IdxArgs &a, int arr, const unsigned *src, int nparts, int ns, const Ranges &r,
+                               const unsigned (&top)[2], u64 (*list)[kList], unsigned *n_list, unsigned *pgt,
+                               unsigned *peq, u64 &ts) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), km = ns - 1;
+  const unsigned lom = km ? r.lo[1] : r.lo[0], lastm = km ? r.last[1] : r.last[0], topm = km ? top[1] : top[0];
+  for (int pt = wv; pt < nparts; pt += NT / 64) {
+    unsigned gt = 0, eq = 0;
+    visit(a, arr, src, pt, [&](const Four &f) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if ((f.ok >> j) & 1u) {
+          const unsigned key = f.k[j];
+          if (key > lastm) {
+            gt += key <= topm;
+          } else if (key >= lom) {
+            if (lom == lastm) ++eq;
+            else list[km][atomicAdd(&n_list[km], 1u)] = ((u64)key << 32) | (unsigned)pt;
+          }
+          if (arr < 2 && key >= r.lo[0] && key <= top[0]) {
+            if (key > r.last[0]) ts += fx30(key);
+            else if (r.lo[0] != r.last[0]) list[0][atomicAdd(&n_list[0], 1u)] = ((u64)key << 32) | (unsigned)pt;
+          }
+        }
+    });
+    gt = wave_inclusive_sum(gt);
+    eq = wave_inclusive_sum(eq);
+    if (lane == 63) { pgt[pt] = gt; peq[pt] = eq; }
+  }
+  __syncthreads();
+}
+
+// Last steps of one array, by one workgroup: thresholds from the lists (each(k, fn) calls fn(key,
+// part) for every key of list k on some thread), per-part prefixes of the counts (own: parts 2 tid and
+// 2 tid + 1 counted elsewhere), and of v and s the sum of the probe best (ts: this thread's share of
+// the keys above the probe's list, above: the workgroup's).  Both selections step together: a step
+// is a chain of barriers and LDS round trips.
+template <int NT, class Each>
+__device__ inline u64 finish_array(const IdxArgs &a, IdxScratch *G, int arr, int nparts, int ns,
+                                   const u64 (*list)[kList], Each each,
+                                   unsigned (*hist)[kSubWords], Pick *pick, Ranges &r, const unsigned (&own)[2],
+                                   unsigned *pgt, unsigned *peq, unsigned *wsum, u64 *red, u64 ts) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  // A list of up to 64 keys, the usual case, by one wave: each lane counts the keys above its own.
+  if (wv < ns) {
+    const unsigned n = wv ? r.n[1] : r.n[0], rank = wv ? r.rank[1] : r.rank[0];
+    if (n <= 64 && (wv ? r.lo[1] != r.last[1] : r.lo[0] != r.last[0])) {
+      const unsigned key = lane < (int)n ? (unsigned)(list[wv][lane] >> 32) : 0u;
+      unsigned g = 0, e = 0;
+      for (unsigned i = 0; i < n; ++i) {
+        const unsigned o = __builtin_amdgcn_readlane(key, i);
+        g += o > key;
+        e += o == key;
+      }
+      if (lane < (int)n && g < rank && rank <= g + e) pick[wv] = {key, rank - g, e};  // equal lanes write the same
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    if (k < ns && r.n[k] <= 64 && r.lo[k] != r.last[k]) {
+      r.lo[k] = r.last[k] = pick[k].bin;
+      r.rank[k] = pick[k].rank;
+    }
+  while (r.lo[0] != r.last[0] || r.lo[1] != r.last[1]) {
+    const bool want[2] = {r.lo[0] != r.last[0], r.lo[1] != r.last[1]};
+    __syncthreads();
+    for (int i = tid; i < ns * kSubWords; i += NT) (&hist[0][0])[i] = 0u;
+    __syncthreads();
+    for (int k = 0; k < ns; ++k) {
+      const unsigned l = k ? r.lo[1] : r.lo[0], e = k ? r.last[1] : r.last[0];
+      const int shift = digit_shift(e - l);
+      if (l != e)
+        each(k, [&](unsigned key, int) {
+          if (key >= l && key <= e) atomicAdd(&hist[k][(key - l) >> shift], 1u);
+        });
+    }
+    narrow_step<NT>(ns, hist, pick, wsum, want, r);
+  }
+  const unsigned thr_p = r.lo[0], thr = ns > 1 ? r.lo[1] : r.lo[0], need = ns > 1 ? r.rank[1] : r.rank[0];
+  for (int k = 0; k < ns; ++k) {
+    const bool probe = k < ns - 1;
+    each(k, [&](unsigned key, int pt) {
+      if (probe) {
+        if (key > thr_p) ts += fx30(key);
+      } else {
+        if (key > thr) atomicAdd(&pgt[pt], 1u);
+        else if (key == thr) atomicAdd(&peq[pt], 1u);
+      }
+    });
+  }
+  if (arr < 2) {
+    ts = wave_sum63(ts);
+    if (lane == 63) red[wv] = ts;
+  }
+  __syncthreads();
+  unsigned *wg = arr == 2 ? G->bgt : G->wgt[arr], *we = arr == 2 ? G->beq : G->weq[arr];
+  unsigned g[2], e[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const bool in = 2 * tid + j < nparts;
+    g[j] = own[j] + (in ? pgt[2 * tid + j] : 0u);
+    e[j] = in ? peq[2 * tid + j] : 0u;
+  }
+  unsigned xg = g[0] + g[1], xe = e[0] + e[1];
+  block_exclusive_scan2<NT / 64>(xg, xe, wsum);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    if (2 * tid + j < nparts) { wg[2 * tid + j] = xg; we[2 * tid + j] = xe; }
+    xg += g[j]; xe += e[j];
+  }
+  if (tid == 0) {
+    G->thr[sel_of(arr, ns - 1)] = thr;
+    G->need[sel_of(arr, ns - 1)] = need;
+  }
+  u64 sum = 0;
+  if (arr < 2 && tid == 0) {
+    sum = (u64)r.rank[0] * fx30(thr_p);  // ties at the threshold
+    for (int w = 0; w < NT / 64; ++w) sum += red[w];
+  }
+  return sum;
+}
+
+// Thread 0 of the workgroup that has finished v or s: the second of the two decides the pattern.
+__device__ inline void finish_vs(const IdxArgs &a, IdxScratch *G, int arr, int h) {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  asm volatile("" ::: "memory");
+  if (atomicAdd(&G->ticket_vs, 1u) == 1u && a.ov.pat[h] < 0)
+    a.out.pattern[h] = decide_pattern(a, G, agent_load(&G->psum[0]), agent_load(&G->psum[1]));
+}
+
+// ---- pass 1: histograms ------------------------------------------------------------------------
+// grid (workgroups of v, s and the block map, Hq)
+__global__ __launch_bounds__(BT) void idx_hist_kernel(IdxArgs a) {
+  __shared__ __attribute__((aligned(16))) unsigned hist[kL1Words];
+  __shared__ u64 red[2][WPB];
+  __shared__ Pick pick[2];
+  __shared__ unsigned wsum[2 * WPB];
+  const Role ro = role_of(a);
+  const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (!head_wants(a, h, ro.arr == 2)) return;
+  IdxScratch *G = a.scratch + h;
+  for (int i = tid; i < kL1Words / 4; i += BT) ((uint4 *)hist)[i] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+  u64 vt = 0, ct = 0;
+  hist_part(a, ro.arr, array_of(a, ro.arr, h), ro.p * WPB + wv, hist, vt, ct);
+  if (ro.arr == 0) {
+    vt = wave_sum63(vt);
+    ct = wave_sum63(ct);
+    if (lane == 63) { red[0][wv] = vt; red[1][wv] = ct; }
+  }
+  __syncthreads();
+  unsigned *gh = G->hist1[ro.arr];
+  static_assert(kCopies == 2, "copies of a bin are read as one uint2");
+  for (int i = tid; i < kBins; i += BT) {
+    const uint2 c = ((const uint2 *)hist)[i];
+    const unsigned n = c.x + c.y;
+    if (n) atomicAdd(&gh[i], n);
+  }
+  if (ro.arr == 0 && tid < 2) {
+    u64 t = 0;
+    for (int w = 0; w < WPB; ++w) t += red[tid][w];
+    atomicAdd(tid ? &G->ct : &G->vtot, t);
+  }
+  if (!arrives_last(&G->ticket[0][ro.arr], ro.n)) return;
+  // the merged histogram: the bin of every selection on this array
+  for (int i = tid; i < kBins; i += BT) hist[i] = agent_load(&gh[i]);
+  __syncthreads();
+  const int ns = n_sel(ro.arr);
+  block_find_kth<BT, kBins, 1>(hist, ns, (unsigned)ksel(a, h, sel_of(ro.arr, 0)), (unsigned)ksel(a, h, sel_of(ro.arr, ns - 1)),
+                               pick, wsum);
+  if (tid < ns) {
+    const int q = sel_of(ro.arr, tid);
+    bin_range(pick[tid].bin, first_bin(a, ro.arr), G->lo[q], G->last[q]);
+    G->rem[q] = pick[tid].rank;
+    G->pop[q] = pick[tid].count;
+  }
+}
+
+// ---- pass 2, where it is needed: a boundary bin with more keys than its list takes is split --------
+// grid (kRefineVs + kRefineVs + kRefineBlk, Hq): few workgroups, since most have nothing to do
+constexpr int kRefineVs = 4, kRefineBlk = 24;
+
+__global__ __launch_bounds__(BT) void idx_refine_kernel(IdxArgs a) {
+  __shared__ unsigned hist[2][kSubWords];
+  __shared__ Pick pick[2];
+  __shared__ unsigned wsum[2 * WPB];
+  const int h = blockIdx.y, tid = threadIdx.x;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int x = (int)blockIdx.x, arr = 2, nwg = kRefineBlk;
+  if (a.first == 0) {
+    if (x < 2 * kRefineVs) { arr = x / kRefineVs; x %= kRefineVs; nwg = kRefineVs; }
+    else x -= 2 * kRefineVs;
+  }
+  if (!head_wants(a, h, arr == 2)) return;
+  IdxScratch *G = a.scratch + h;
+  const int ns = n_sel(arr);
+  const unsigned cap = arr == 2 ? (unsigned)a.cap_blk : (unsigned)a.cap_vs;
+  unsigned lo[2], last[2];
+  int shift[2];
+  bool want[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int q = sel_of(arr, k < ns ? k : 0);
+    want[k] = k < ns && G->pop[q] > cap;
+    lo[k] = G->lo[q]; last[k] = G->last[q];
+    shift[k] = digit_shift(last[k] - lo[k]);
+  }
+  if (!want[0] && !want[1]) return;
+  for (int i = tid; i < 2 * kSubWords; i += BT) (&hist[0][0])[i] = 0u;
+  __syncthreads();
+  const int nparts = (arr == 2 ? a.Pb : a.Pv) * WPB;
+  for (int part = x * WPB + wv; part < nparts; part += nwg * WPB)
+    visit(a, arr, array_of(a, arr, h), part, [&](const Four &f) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (want[k] && ((f.ok >> j) & 1u) && f.k[j] >= lo[k] && f.k[j] <= last[k])
+            atomicAdd(&hist[k][(f.k[j] - lo[k]) >> shift[k]], 1u);
+    });
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    if (want[k])
+      for (int i = tid; i < kSubBins; i += BT) {
+        const unsigned c = hist[k][i];
+        if (c) atomicAdd(&G->hist2[sel_of(arr, k)][i], c);
+      }
+  if (!arrives_last(&G->ticket[1][arr], nwg)) return;
+  Ranges r;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) { r.lo[k] = lo[k]; r.last[k] = last[k]; r.rank[k] = G->rem[sel_of(arr, k < ns ? k : 0)]; }
+  for (int k = 0; k < ns; ++k)
+    for (int i = tid; i < kSubBins; i += BT) hist[k][i] = agent_load(&G->hist2[sel_of(arr, k)][i]);
+  narrow_step<BT>(ns, hist, pick, wsum, want, r);
+  if (tid == 0) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      if (want[k]) {
+        const int q = sel_of(arr, k);
+        G->lo[q] = r.lo[k]; G->last[q] = r.last[k]; G->rem[q] = r.rank[k]; G->pop[q] = r.n[k];
+      }
+  }
+}
+
+// ---- pass 3: counts, thresholds, pattern ---------------------------------------------------------
+__global__ __launch_bounds__(BT) void idx_count_kernel(IdxArgs a) {
+  __shared__ u64 list[2][kList];   // the workgroup's boundary keys; later the head's
+  __shared__ unsigned n_list[2], s_base[2];
+  __shared__ u64 red[WPB];
+  __shared__ unsigned hist[2][kSubWords];
+  __shared__ Pick pick[2];
+  __shared__ unsigned pgt[kMaxBlkParts], peq[kMaxBlkParts];
+  __shared__ unsigned wsum[2 * WPB];
+  const Role ro = role_of(a);
+  const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, arr = ro.arr;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (arr == 0 && ro.p == 0 && tid == 0 && a.ov.pat[h] >= 0) a.out.pattern[h] = a.ov.pat[h];
+  if (!head_wants(a, h, arr == 2)) return;
+  IdxScratch *G = a.scratch + h;
+  const int ns = n_sel(arr), km = ns - 1;
+  const unsigned cap = arr == 2 ? (unsigned)a.cap_blk : (unsigned)a.cap_vs;
+  const unsigned *src = array_of(a, arr, h);
+  auto list_of = [&](int k) { return arr == 2 ? a.list_blk + (size_t)h * cap : a.list_vs + ((size_t)h * 4 + arr + 2 * k) * cap; };
+  if (tid < 2) n_list[tid] = 0u;
+  Ranges r;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int q = sel_of(arr, k < ns ? k : 0);
+    r.lo[k] = G->lo[q]; r.last[k] = G->last[q]; r.rank[k] = G->rem[q]; r.n[k] = G->pop[q];
+  }
+  __syncthreads();
+
+  const int part = ro.p * WPB + wv;
+  {
+    const unsigned lom = km ? r.lo[1] : r.lo[0], lastm = km ? r.last[1] : r.last[0];
+    const bool fitm = (km ? r.n[1] : r.n[0]) <= cap, fitp = arr < 2 && r.n[0] <= cap;  // no list where it would not hold them all
+    unsigned gt = 0;
+    u64 ts = 0;
+    visit(a, arr, src, part, [&](const Four &f) {
+      unsigned inm = 0u, inp = 0u;  // keys for the lists
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bool ok = (f.ok >> j) & 1u;
+        const unsigned key = f.k[j];
+        gt += ok && key > lastm;
+        if (ok && key >= lom && key <= lastm) inm |= 1u << j;
+        if (arr < 2 && ok && key >= r.lo[0]) {
+          if (key > r.last[0]) ts += fx30(key);
+          else inp |= 1u << j;
+        }
+      }
+      inm = fitm ? inm : 0u;
+      inp = fitp ? inp : 0u;
+      unsigned k0 = f.k[0], k1 = f.k[1], k2 = f.k[2], k3 = f.k[3];
+      while (inm | inp) {
+#pragma unroll 1
+        for (int s2 = 0; s2 < 2; ++s2) {
+          const int k = s2 ? 0 : km;
+          if (!((s2 ? inp : inm) & 1u)) continue;
+          const u64 item = ((u64)k0 << 32) | (unsigned)part;
+          const unsigned n = atomicAdd(&n_list[k], 1u);
+          if (n < kList) list[k][n] = item;
+          else agent_store(&list_of(k)[atomicAdd(&G->nlist[sel_of(arr, k)], 1u)], item);
+        }
+        inm >>= 1; inp >>= 1;
+        k0 = k1; k1 = k2; k2 = k3;
+      }
+    });
+    gt = wave_inclusive_sum(gt);
+    if (lane == 63) agent_store(arr == 2 ? &G->bgt[part] : &G->wgt[arr][part], gt);
+    if (arr < 2) {
+      ts = wave_sum63(ts);
+      if (lane == 63) red[wv] = ts;
+    }
+  }
+  __syncthreads();
+  if (tid < ns) s_base[tid] = n_list[tid] ? atomicAdd(&G->nlist[sel_of(arr, tid)], min(n_list[tid], (unsigned)kList)) : 0u;
+  if (arr < 2 && tid == 64) {
+    u64 t = 0;
+    for (int w = 0; w < WPB; ++w) t += red[w];
+    if (t) atomicAdd(&G->topsum[arr], t);
+  }
+  __syncthreads();
+  for (int k = 0; k < ns; ++k) {
+    const unsigned n = min(n_list[k], (unsigned)kList), b = s_base[k];
+    u64 *to = list_of(k);
+    for (unsigned i = tid; i < n; i += BT) agent_store(&to[b + i], list[k][i]);
+  }
+  if (!arrives_last(&G->ticket[2][arr], ro.n)) return;
+
+  // ---- one workgroup: the exact threshold of every selection on this array.  All reads that pass the
+  // L2 caches by are issued together.
+  const int nparts = ro.n * WPB;
+  unsigned own[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+    own[j] = 2 * tid + j < nparts ? agent_load(arr == 2 ? &G->bgt[2 * tid + j] : &G->wgt[arr][2 * tid + j]) : 0u;
+  u64 ts = tid == 0 && arr < 2 ? agent_load(&G->topsum[arr]) : 0ull;
+  const bool listed = r.n[0] <= cap && r.n[1] <= cap;
+  const unsigned n0 = r.n[0], n1 = r.n[1];
+  if (listed)
+    for (int k = 0; k < ns; ++k)
+      for (unsigned i = tid; i < min(k ? n1 : n0, (unsigned)kList); i += BT) list[k][i] = agent_load(&list_of(k)[i]);
+  for (int i = tid; i < nparts; i += BT) { pgt[i] = 0u; peq[i] = 0u; }
+  if (tid < 2) n_list[tid] = 0u;
+  if (ns == 1) r.lo[1] = r.last[1] = r.n[1] = 0u;
+  __syncthreads();
+  if (!listed) {
+    // Even the refined range of a selection did not fit its list: whole stretches of equal scores.
+    const unsigned top[2] = {r.last[0], r.last[1]};
+    narrow<BT>(a, arr, src, nparts, ns, hist, pick, wsum, r);
+    collect<BT>(a, arr, src, nparts, ns, r, top, list, n_list, pgt, peq, ts);
+  }
+  const unsigned m0 = listed ? n0 : n_list[0], m1 = listed ? n1 : n_list[1];
+  auto each = [&](int k, auto fn) {
+    for (unsigned i = tid; i < (k ? m1 : m0); i += BT) {
+      const u64 it = i < kList ? list[k][i] : agent_load(&list_of(k)[i]);
+      fn((unsigned)(it >> 32), (int)(unsigned)it);
+    }
+  };
+  const u64 sum = finish_array<BT>(a, G, arr, nparts, ns, list, each, hist, pick, r, own, pgt, peq, wsum, red, ts);
+  if (arr == 2 || tid != 0) return;
+  agent_store(&G->psum[arr], sum);
+  finish_vs(a, G, arr, h);
+}
+
+// ---- passes 1 to 3 of short prompts in one launch ------------------------------------------------
+// grid (arrays, Hq), 1024 threads: one workgroup walks a whole array, two or three times out of L2,
+// and needs nothing from the others: no counters to clear, no tickets, no merging.  Taken while the
+// walks are short against the launches and round trips they replace (see one_launch).
+constexpr int ST = 1024, SW = ST / 64;
+
+__global__ __launch_bounds__(ST) void idx_select_kernel(IdxArgs a, int first_array) {
+  __shared__ __attribute__((aligned(16))) union {
+    unsigned l1[kL1Words];
+    unsigned sub[2][kSubWords];
+  } hist;
+  __shared__ u64 list[2][kList];
+  __shared__ unsigned n_list[2];
+  __shared__ Pick pick[2];
+  __shared__ unsigned pgt[kMaxBlkParts], peq[kMaxBlkParts];
+  __shared__ unsigned wsum[2 * SW];
+  __shared__ u64 red[2][SW];
+  const int arr = first_array + (int)blockIdx.x, h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (arr == 0 && tid == 0 && a.ov.pat[h] >= 0) a.out.pattern[h] = a.ov.pat[h];
+  if (!head_wants(a, h, arr == 2)) return;
+  IdxScratch *G = a.scratch + h;
+  const int ns = n_sel(arr), nparts = (arr == 2 ? a.Pb : a.Pv) * WPB;
+  const unsigned *src = array_of(a, arr, h);
+  for (int i = tid; i < kL1Words / 4; i += ST) ((uint4 *)hist.l1)[i] = make_uint4(0u, 0u, 0u, 0u);
+  if (tid < 2) n_list[tid] = 0u;
+  __syncthreads();
+  u64 vt = 0, ct = 0;
+  for (int pt = wv; pt < nparts; pt += SW) hist_part(a, arr, src, pt, hist.l1, vt, ct);
+  if (arr == 0) {
+    vt = wave_sum63(vt);
+    ct = wave_sum63(ct);
+    if (lane == 63) { red[0][wv] = vt; red[1][wv] = ct; }
+  }
+  __syncthreads();
+  u64 sum_v = 0, sum_c = 0;  // thread 0, array v
+  if (arr == 0 && tid == 0)
+    for (int w = 0; w < SW; ++w) { sum_v += red[0][w]; sum_c += red[1][w]; }
+  block_find_kth<ST, kBins, kCopies>(hist.l1, ns, (unsigned)ksel(a, h, sel_of(arr, 0)),
+                                     (unsigned)ksel(a, h, sel_of(arr, ns - 1)), pick, wsum);
+  Ranges r;
+  unsigned top[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    r.lo[k] = r.last[k] = r.rank[k] = r.n[k] = 0u;
+    top[k] = 0xFFFFFFFFu;
+    if (k < ns) {
+      bin_range(pick[k].bin, first_bin(a, arr), r.lo[k], r.last[k]);
+      r.rank[k] = pick[k].rank; r.n[k] = pick[k].count;
+    }
+  }
+  u64 ts = 0;
+  narrow<ST>(a, arr, src, nparts, ns, hist.sub, pick, wsum, r);
+  collect<ST>(a, arr, src, nparts, ns, r, top, list, n_list, pgt, peq, ts);
+  auto each = [&](int k, auto fn) {
+    for (unsigned i = tid; i < n_list[k]; i += ST) {
+      const u64 it = list[k][i];
+      fn((unsigned)(it >> 32), (int)(unsigned)it);
+    }
+  };
+  const unsigned own[2] = {0u, 0u};
+  const u64 sum = finish_array<ST>(a, G, arr, nparts, ns, list, each, hist.sub, pick, r, own, pgt, peq, wsum, red[0], ts);
+  if (arr == 2 || tid != 0) return;
+  if (arr == 0) {
+    agent_store(&G->vtot, sum_v);
+    agent_store(&G->ct, sum_c);
+  }
+  agent_store(&G->psum[arr], sum);
+  if (a.decide_here) finish_vs(a, G, arr, h);
+}
+
+// ---- pass 4: emission ------------------------------------------------------------------------------
+// One 256-key group of a wave: an element is selected if its key is above the threshold, or equal to
+// it and among the first `need` such elements in index order.  visit(j, pos, sel) receives every
+// element with the number of selected elements before it; grun / erun count the greater / equal
+// elements seen so far.
+template <class Visit>
+__device__ inline void emit_group(const Four &f, unsigned thr, unsigned need,
+                                  unsigned &grun, unsigned &erun, Visit visit) {
   const int lane = threadIdx.x & 63;
-  const unsigned long long below = (1ull << lane) - 1ull;
+  const u64 below = (1ull << lane) - 1ull;
   unsigned gl = 0, el = 0, gtot = 0, etot = 0;
   bool isgt[4], iseq[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    isgt[j] = i0 + j < lim && v.k[j] > thr;
-    iseq[j] = i0 + j < lim && v.k[j] == thr;
-    const unsigned long long bg = __ballot(isgt[j]), be = __ballot(iseq[j]);
+    isgt[j] = ((f.ok >> j) & 1u) && f.k[j] > thr;
+    iseq[j] = ((f.ok >> j) & 1u) && f.k[j] == thr;
+    const u64 bg = __ballot(isgt[j]), be = __ballot(iseq[j]);
     gl += __popcll(bg & below); el += __popcll(be & below);
     gtot += __popcll(bg); etot += __popcll(be);
   }
   unsigned G = grun + gl, E = erun + el;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    if (isgt[j] || (iseq[j] && E < need)) put(G + min(E, need), i0 + j);
+    visit(j, G + min(E, need), isgt[j] || (iseq[j] && E < need));
     G += isgt[j];
     E += iseq[j];
   }
@@ -270,328 +968,6 @@ __device__ inline void emit_group(const Keys4 &v, int i0, int lim, unsigned thr,
   erun += etot;
 }
 
-// In a histogram of nbins (a multiple of 64) counts held in LDS, the bin that holds the k-th key
-// counted from the top bin down (1 <= k <= total), and the rank of that key inside the bin.
-// One wave.
-__device__ inline void wave_find_kth(const unsigned *hist, int nbins, unsigned k, unsigned &bin,
-                                     unsigned &rank) {
-  const int lane = threadIdx.x & 63;
-  const int per = nbins / 64;  // lane l owns bins [l*per, (l+1)*per)
-  unsigned tot = 0;
-  for (int i = 0; i < per; ++i) tot += hist[lane * per + i];
-  unsigned incl = tot;  // inclusive suffix sum over lanes >= l
-  for (int d = 1; d < 64; d <<= 1) {
-    const unsigned o = __shfl_down(incl, d);
-    if (lane + d < 64) incl += o;
-  }
-  const unsigned above = incl - tot;
-  const bool mine = above < k && k <= above + tot;
-  const unsigned long long m = __ballot(mine);
-  const int owner = m ? __ffsll((long long)m) - 1 : 0;
-  unsigned b = 0, r = 0;
-  if (lane == owner) {
-    unsigned ab = above;
-    for (int i = per - 1; i >= 0; --i) {
-      const unsigned c = hist[lane * per + i];
-      if (ab < k && k <= ab + c) { b = (unsigned)(lane * per + i); r = k - ab; break; }
-      ab += c;
-    }
-  }
-  bin = __shfl(b, owner);
-  rank = __shfl(r, owner);
-}
-
-// Exclusive prefixes of two values per thread over the BT threads of a workgroup: shuffles inside
-// the waves, the wave totals through LDS (wsum: 2 * WPB words).  Called by all threads.
-__device__ inline void block_exclusive_scan2(unsigned &a, unsigned &b, unsigned *wsum) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  unsigned ia = a, ib = b;
-  for (int d = 1; d < 64; d <<= 1) {
-    const unsigned oa = __shfl_up(ia, d), ob = __shfl_up(ib, d);
-    if (lane >= d) { ia += oa; ib += ob; }
-  }
-  if (lane == 63) { wsum[wv] = ia; wsum[WPB + wv] = ib; }
-  __syncthreads();
-  unsigned ba = 0, bb = 0;
-  for (int w = 0; w < wv; ++w) { ba += wsum[w]; bb += wsum[WPB + w]; }
-  __syncthreads();
-  a = ba + ia - a;
-  b = bb + ib - b;
-}
-
-__global__ void idx_zero_kernel(IdxScratch *scratch) {
-  unsigned *p = (unsigned *)(scratch + blockIdx.x);
-  for (size_t i = threadIdx.x; i < kZeroWords; i += blockDim.x) p[i] = 0u;
-}
-
-// ---- level histograms ------------------------------------------------------------------------------
-// LEVEL 1: bits 30..20 of every key (scores are >= +0: bit 31 is clear), one histogram per array.
-// LEVEL 2: bits 19..10 of the keys whose bits 30..20 equal the selection's prefix.
-// LEVEL 3: bits  9..0 of the keys whose bits 31..10 equal the selection's prefix.
-template <int LEVEL>
-__global__ __launch_bounds__(BT) void idx_hist_kernel(IdxArgs a) {
-  constexpr int NH = LEVEL == 1 ? 3 : NSEL;
-  constexpr int BINS = LEVEL == 1 ? L1BINS : L2BINS;
-  // levels 2 and 3: 20 KB, nothing else in LDS, so that eight workgroups (every wave slot) fit a CU
-  __shared__ __attribute__((aligned(16))) unsigned hist[NH][BINS];
-  const Shape &sh = a.sh;
-  const int p = blockIdx.x, h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int N = sh.N, nb = sh.nb;
-  IdxScratch *G = a.scratch + h;
-  const bool do_vs = (a.mask & 1) && head_wants(a, h, false);
-  const bool do_blk = (a.mask & 2) && a.ksel[4] > 0 && head_wants(a, h, true);
-  if (!do_vs && !do_blk) return;
-  const unsigned *vb = a.v + (size_t)h * N, *sb = a.s + (size_t)h * N;
-  const unsigned *bb = a.blk + (size_t)h * nb * nb;
-  for (int i = tid; i < NH * BINS; i += BT) (&hist[0][0])[i] = 0u;
-  unsigned pre[NSEL];
-  bool act[NSEL];
-#pragma unroll
-  for (int q = 0; q < NSEL; ++q) {
-    pre[q] = LEVEL == 1 ? 0u : G->prefix[q];
-    act[q] = a.ksel[q] > 0;
-  }
-  __syncthreads();
-  const int gw = p * WPB + wv;
-  const int lo = min(gw * a.seg, N), hi = min(lo + a.seg, N);
-  unsigned long long vt = 0, ct = 0;
-  long long sbnd = (long long)sh.sink * sh.b;
-  if (sbnd > N) sbnd = N;
-  long long lb0 = (long long)(nb - sh.local) * sh.b;
-  if (lb0 < sbnd) lb0 = sbnd;
-
-  auto visit = [&](const Keys4 &v, int i0, int lim, int arr) {
-    // arr 0: v (selections 0, 2), 1: s (selections 1, 3), 2: blk (selection 4)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const bool ok = i0 + j < lim;
-      const unsigned key = v.k[j];
-      if (LEVEL == 1) {
-        hist_add(hist[arr], min(key >> 20, (unsigned)L1BINS - 1u), ok);  // the sign bit of a score is 0
-      } else {
-        const unsigned hi_bits = LEVEL == 2 ? key >> 20 : key >> 10;
-        const unsigned bin = LEVEL == 2 ? (key >> 10) & 1023u : key & 1023u;
-        if (arr == 2) {
-          hist_add(hist[NH - 1], bin, ok && act[4] && hi_bits == pre[4]);
-        } else {
-          hist_add(hist[arr % NH], bin, ok && act[arr] && hi_bits == pre[arr]);
-          hist_add(hist[(arr + 2) % NH], bin, ok && act[arr + 2] && hi_bits == pre[arr + 2]);
-        }
-      }
-    }
-  };
-  if (do_vs) wave_visit4(vb, lo, hi, true, [&](const Keys4 &v, int i0, int lim) {
-    visit(v, i0, lim, 0);
-    if (LEVEL == 1) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (i0 + j < lim) {
-          const unsigned long long f = fx30(v.k[j]);
-          vt += f;
-          if (i0 + j < sbnd || i0 + j >= lb0) ct += f;
-        }
-    }
-  });
-  if (do_vs) wave_visit4(sb, lo, hi, true, [&](const Keys4 &v, int i0, int lim) { visit(v, i0, lim, 1); });
-  if (do_blk)
-    wave_rows_visit4(bb, nb, gw, a.PW, (nb & 3) == 0, sh.row_norm != 0, [](int) {},
-                     [&](const Keys4 &v, int i0, int lim) { visit(v, i0, lim, 2); }, [](int) {});
-  __syncthreads();
-  unsigned *gh = LEVEL == 1 ? &G->hist1[0][0] : (LEVEL == 2 ? &G->hist2[0][0] : &G->hist3[0][0]);
-  for (int i = tid; i < NH * BINS; i += BT) {
-    const unsigned c = (&hist[0][0])[i];
-    if (c) atomicAdd(&gh[i], c);
-  }
-  if (LEVEL == 1 && do_vs) {
-    // the two 64-bit sums of the workgroup, through the histogram's LDS once it is flushed
-    for (int d = 32; d >= 1; d >>= 1) { vt += __shfl_xor(vt, d); ct += __shfl_xor(ct, d); }
-    unsigned long long *red64 = (unsigned long long *)&hist[0][0];
-    __syncthreads();
-    if (lane == 0) { red64[wv] = vt; red64[WPB + wv] = ct; }
-    __syncthreads();
-    if (tid == 0) {
-      unsigned long long tv = 0, tc = 0;
-      for (int w = 0; w < WPB; ++w) { tv += red64[w]; tc += red64[WPB + w]; }
-      atomicAdd(&G->vtot, tv);
-      atomicAdd(&G->ct, tc);
-    }
-  }
-}
-
-// One workgroup per head: fixes the next digit of every selection from the merged histograms.
-template <int LEVEL>
-__global__ __launch_bounds__(BT) void idx_select_kernel(IdxArgs a) {
-  constexpr int NH = LEVEL == 1 ? 3 : NSEL;
-  constexpr int BINS = LEVEL == 1 ? L1BINS : L2BINS;
-  __shared__ __attribute__((aligned(16))) unsigned hist[NH][BINS];
-  const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  IdxScratch *G = a.scratch + h;
-  const unsigned *gh = LEVEL == 1 ? &G->hist1[0][0] : (LEVEL == 2 ? &G->hist2[0][0] : &G->hist3[0][0]);
-  for (int i = tid * 4; i < NH * BINS; i += BT * 4)
-    *(uint4 *)&(&hist[0][0])[i] = *(const uint4 *)&gh[i];
-  __syncthreads();
-  for (int q = wv; q < NSEL; q += WPB) {  // wave w takes selections w and w + 4
-    if (!(a.mask & (q < 4 ? 1 : 2)) || !head_wants(a, h, q == 4)) continue;
-    if (a.ksel[q] <= 0) {
-      if (LEVEL == 3 && lane == 0) { G->thr[q] = 0xFFFFFFFFu; G->need[q] = 0u; }
-      continue;
-    }
-    const unsigned *hsel = LEVEL == 1 ? hist[(q == 4 ? 2 : (q & 1)) % NH] : hist[q % NH];
-    const unsigned pre = LEVEL == 1 ? 0u : G->prefix[q];
-    const unsigned k = LEVEL == 1 ? (unsigned)a.ksel[q] : G->remaining[q];
-    unsigned bin, rank;
-    wave_find_kth(hsel, BINS, k, bin, rank);
-    if (lane == 0) {
-      if (LEVEL == 1) {
-        G->prefix[q] = bin;
-        G->remaining[q] = rank;
-      } else if (LEVEL == 2) {
-        G->prefix[q] = (pre << 10) | bin;
-        G->remaining[q] = rank;
-      } else {
-        G->thr[q] = (pre << 10) | bin;
-        G->need[q] = rank;
-      }
-    }
-  }
-}
-
-// ---- counts, pattern, prefixes ---------------------------------------------------------------------
-__global__ __launch_bounds__(BT) void idx_count_kernel(IdxArgs a) {
-  __shared__ unsigned long long red64[2][WPB];
-  const Shape &sh = a.sh;
-  const int p = blockIdx.x, h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int N = sh.N, nb = sh.nb;
-  IdxScratch *G = a.scratch + h;
-  const unsigned *vb = a.v + (size_t)h * N, *sb = a.s + (size_t)h * N;
-  const unsigned *bb = a.blk + (size_t)h * nb * nb;
-  unsigned thr[NSEL], need[NSEL];
-#pragma unroll
-  for (int q = 0; q < NSEL; ++q) { thr[q] = G->thr[q]; need[q] = G->need[q]; }
-  const int gw = p * WPB + wv;
-  const int lo = min(gw * a.seg, N), hi = min(lo + a.seg, N);
-  const bool do_vs = (a.mask & 1) && head_wants(a, h, false);
-  for (int arr = 0; arr < 2 && do_vs; ++arr) {
-    unsigned gt = 0, eq = 0;
-    unsigned long long ts = 0;
-    const unsigned tp = thr[arr], tk = thr[arr + 2];
-    wave_visit4(arr ? sb : vb, lo, hi, true, [&](const Keys4 &v, int i0, int lim) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (i0 + j < lim) {
-          gt += v.k[j] > tk;
-          eq += v.k[j] == tk;
-          if (v.k[j] > tp) ts += fx30(v.k[j]);
-        }
-    });
-    for (int d = 32; d >= 1; d >>= 1) {
-      gt += __shfl_xor(gt, d); eq += __shfl_xor(eq, d); ts += __shfl_xor(ts, d);
-    }
-    if (lane == 0) { G->wgt[arr][gw] = gt; G->weq[arr][gw] = eq; red64[arr][wv] = ts; }
-  }
-  if (!sh.row_select && (a.mask & 2) && head_wants(a, h, true)) {
-    unsigned gt = 0, eq = 0;
-    wave_rows_visit4(
-        bb, nb, gw, a.PW, (nb & 3) == 0, sh.row_norm != 0, [&](int) { gt = 0; eq = 0; },
-        [&](const Keys4 &v, int i0, int lim) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            gt += i0 + j < lim && v.k[j] > thr[4];
-            eq += i0 + j < lim && v.k[j] == thr[4];
-          }
-        },
-        [&](int R) {
-          unsigned g2 = gt, e2 = eq;
-          for (int d = 32; d >= 1; d >>= 1) { g2 += __shfl_xor(g2, d); e2 += __shfl_xor(e2, d); }
-          if (lane == 0) { G->rowgt[R] = g2; G->roweq[R] = e2; }
-        });
-  }
-  __syncthreads();
-  if (tid < 2 && do_vs) {
-    unsigned long long t = 0;
-    for (int w = 0; w < WPB; ++w) t += red64[tid][w];
-    atomicAdd(&G->topsum[tid], t);
-  }
-}
-
-// The pattern decision by itself, one thread per head, for a caller that needs it before the block
-// map exists (the scan launch below takes the same decision again from the same sums).
-__global__ void idx_decide_kernel(IdxArgs a) {
-  const int h = blockIdx.x * blockDim.x + threadIdx.x;
-  if (h < a.sh.Hq) a.out.pattern[h] = decide_pattern(a, a.scratch + h, h);
-}
-
-// One workgroup per head: pattern decision, prefixes of the per-part and per-row counts, rowptr.
-__global__ __launch_bounds__(BT) void idx_scan_kernel(IdxArgs a) {
-  __shared__ unsigned s_wsum[2 * WPB];
-  __shared__ int s_pat;
-  const Shape &sh = a.sh;
-  const int h = blockIdx.x, tid = threadIdx.x;
-  const int N = sh.N, nb = sh.nb;
-  IdxScratch *G = a.scratch + h;
-  unsigned thr[NSEL], need[NSEL];
-#pragma unroll
-  for (int q = 0; q < NSEL; ++q) { thr[q] = G->thr[q]; need[q] = G->need[q]; }
-  // ---- pattern of the head --------------------------------------------------------------------------
-  if (tid == 0) {
-    const int pat = decide_pattern(a, G, h);
-    G->pattern = pat;
-    a.out.pattern[h] = pat;
-    s_pat = pat;
-  }
-  // ---- exclusive prefixes of the wave-part counts of v and s (PW <= 256 = one per thread) --------
-  for (int arr = 0; arr < 2; ++arr) {
-    unsigned pg = tid < a.PW ? G->wgt[arr][tid] : 0u, pe = tid < a.PW ? G->weq[arr][tid] : 0u;
-    block_exclusive_scan2(pg, pe, s_wsum);
-    if (tid < a.PW) { G->wgt[arr][tid] = pg; G->weq[arr][tid] = pe; }
-  }
-  const int pat = s_pat;  // written before the barriers of the scans above
-  const bool bc_global = pat == SA_BLOCK_CLUSTER && !sh.row_select;
-  // ---- row prefixes: thread t owns RP consecutive rows (nb <= kMaxNb) ------------------------------
-  constexpr int RP = kMaxNb / BT;
-  unsigned g16[RP], e16[RP], gs = 0, es = 0;
-#pragma unroll
-  for (int j = 0; j < RP; ++j) {
-    const int R = RP * tid + j;
-    unsigned g = 0, e = 0;
-    if (R < nb) {
-      if (bc_global) {
-        g = G->rowgt[R];
-        e = G->roweq[R];
-      } else if (pat == SA_BLOCK_CLUSTER) {
-        g = (unsigned)row_share(sh, R);
-      } else if (pat == SA_TRIANGULAR) {
-        const int bs = max(R - sh.local + 1, 0);  // row R keeps C < min(sink, band start) and the band
-        g = (unsigned)(min(sh.sink, bs) + (R - bs + 1));
-      } else {
-        g = 1u;
-      }
-    }
-    g16[j] = g; e16[j] = e;
-    gs += g; es += e;
-  }
-  unsigned eg = gs, ee = es;
-  block_exclusive_scan2(eg, ee, s_wsum);
-  int32_t *rp = a.out.rowptr + (size_t)h * (nb + 1);
-#pragma unroll
-  for (int j = 0; j < RP; ++j) {
-    const int R = RP * tid + j;
-    if (R < nb) {
-      if (bc_global) {
-        G->rowgt[R] = eg;
-        G->roweq[R] = ee;
-        rp[R] = (int)(eg + min(ee, need[4]) + (unsigned)R);  // R forced diagonals above this row
-      } else {
-        rp[R] = (int)eg;
-      }
-    }
-    eg += g16[j];
-    ee += e16[j];
-    if (R == nb - 1) rp[nb] = bc_global ? a.ksel[4] + nb : (int)eg;
-  }
-}
-
-// ---- emission ------------------------------------------------------------------------------------------
 // Per-row block rule, one wave per row: out[0..kr) = the kr candidates C < R with the largest keys
 // (ties to the lower C) in ascending order, out[kr] = R (the forced diagonal block).  Lane l holds
 // the keys of the candidates l, l + 64, ... in registers (T of them, R <= 64 T); slots past the
@@ -618,14 +994,14 @@ __device__ inline void emit_row_select(const unsigned *row, int R, int kr, int32
     }
     const unsigned gt = thr == 0xFFFFFFFFu ? 0u : count_ge(thr + 1u);
     const unsigned need = (unsigned)kr - gt;  // ties at the threshold, taken in index order
-    const unsigned long long below = (1ull << lane) - 1ull;
+    const u64 below = (1ull << lane) - 1ull;
     unsigned grun = 0, erun = 0;
 #pragma unroll
     for (int t = 0; t < T; ++t)
       if (64 * t < R) {
         const bool ok = 64 * t + lane < R;
         const bool isgt = ok && key[t] > thr, iseq = ok && key[t] == thr;
-        const unsigned long long bg = __ballot(isgt), be = __ballot(iseq);
+        const u64 bg = __ballot(isgt), be = __ballot(iseq);
         const unsigned gb = grun + __popcll(bg & below), eb = erun + __popcll(be & below);
         if (isgt || (iseq && eb < need)) out[gb + min(eb, need)] = 64 * t + lane;
         grun += __popcll(bg);
@@ -635,105 +1011,130 @@ __device__ inline void emit_row_select(const unsigned *row, int R, int kr, int32
   if (lane == 0) out[kr] = R;
 }
 
+// grid as in the passes above.  T: 64-key slices of a row under the per-row rule (nb <= 64 T), 0 for
+// the rules with one selection per head.
+template <int T>
 __global__ __launch_bounds__(BT) void idx_emit_kernel(IdxArgs a) {
+  __shared__ unsigned s_wsum[2 * WPB];
   const Shape &sh = a.sh;
-  const int p = blockIdx.x, h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const Role ro = role_of(a);
+  const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int N = sh.N, nb = sh.nb;
   IdxScratch *G = a.scratch + h;
-  const int pat = G->pattern;
-  const int gw = p * WPB + wv;
-  const int gtid = p * BT + tid, gthreads = a.P * BT;
-  int32_t *cols = a.out.cols + (size_t)h * sh.k_v, *offs = a.out.offs + (size_t)h * sh.k_s;
+  int pat = a.ov.pat[h];
+  if (pat < 0) pat = a.decide_here ? a.out.pattern[h] : decide_pattern(a, G, G->psum[0], G->psum[1]);
+  pat = __builtin_amdgcn_readfirstlane(pat);
+  const int part = ro.p * WPB + wv, nparts = ro.n * WPB;
+  const int gtid = ro.p * BT + tid, gthreads = ro.n * BT;
+  if (ro.arr < 2) {  // columns and diagonals: Interval-Slash only
+    const int q = ro.arr + 2, width = ro.arr ? sh.k_s : sh.k_v;
+    const int k = pat == SA_INTERVAL_SLASH ? ksel(a, h, q) : 0;
+    int32_t *idx = (ro.arr ? a.out.offs : a.out.cols) + (size_t)h * width;
+    const bool aside = ro.arr == 1 && sh.diag_blocks;  // the offsets become blocks: the list stays empty
+    if (k > 0) {
+      int32_t *dst = aside ? a.doffs + (size_t)h * width : idx;
+      const unsigned thr = G->thr[q], need = G->need[q];
+      unsigned grun = G->wgt[ro.arr][part], erun = G->weq[ro.arr][part];
+      visit(a, ro.arr, array_of(a, ro.arr, h), part, [&](const Four &f) {
+        emit_group(f, thr, need, grun, erun, [&](int j, unsigned pos, bool sel) {
+          if (sel) dst[pos] = f.C[j];
+        });
+      });
+    }
+    const int shown = aside ? 0 : k;
+    for (int i = shown + gtid; i < width; i += gthreads) idx[i] = -1;
+    if (gtid == 0) {
+      (ro.arr ? a.out.n_offs : a.out.n_cols)[h] = shown;
+      if (ro.arr == 0 && !a.decide_here) a.out.pattern[h] = pat;
+      if (aside) G->ticket_rows = 0u;
+    }
+    return;
+  }
+  // block CSR
   int32_t *rp = a.out.rowptr + (size_t)h * (nb + 1);
   int32_t *bc = a.out.blkcols + (size_t)h * sh.cap_b;
-  // columns and diagonals (Interval-Slash only)
-  const int kv = pat == SA_INTERVAL_SLASH ? a.ksel[2] : 0, ks = pat == SA_INTERVAL_SLASH ? a.ksel[3] : 0;
-  if (pat == SA_INTERVAL_SLASH) {
-    const int lo = min(gw * a.seg, N), hi = min(lo + a.seg, N);
-    for (int arr = 0; arr < 2; ++arr) {
-      const unsigned thr = G->thr[arr + 2], need = G->need[arr + 2];
-      unsigned grun = G->wgt[arr][gw], erun = G->weq[arr][gw];
-      int32_t *out = arr ? offs : cols;
-      if (a.ksel[arr + 2] > 0)
-        wave_visit4((arr ? a.s : a.v) + (size_t)h * N, lo, hi, true, [&](const Keys4 &v, int i0, int lim) {
-          emit_group(v, i0, lim, thr, need, grun, erun, [&](unsigned pos, int idx) { out[pos] = idx; });
-        });
-    }
-  }
-  for (int i = kv + gtid; i < sh.k_v; i += gthreads) cols[i] = -1;
-  for (int i = ks + gtid; i < sh.k_s; i += gthreads) offs[i] = -1;
-  if (gtid == 0) { a.out.n_cols[h] = kv; a.out.n_offs[h] = ks; }
-  // block CSR
+  const unsigned *hb = a.blk + (size_t)h * nb * nb;
   int total;
-  if (pat == SA_BLOCK_CLUSTER && sh.row_select) {
-    total = rp[nb];  // the rows themselves are written by idx_emit_rows_kernel
-  } else if (pat == SA_BLOCK_CLUSTER) {
-    const unsigned thr = G->thr[4], need = G->need[4];
-    unsigned grun = 0, erun = 0;
-    wave_rows_visit4(
-        a.blk + (size_t)h * nb * nb, nb, gw, a.PW, (nb & 3) == 0, sh.row_norm != 0,
-        [&](int R) { grun = G->rowgt[R]; erun = G->roweq[R]; },
-        [&](const Keys4 &v, int i0, int lim) {
-          // lim is the row index R: a selected entry lands after the R diagonals of the rows above
-          if (a.ksel[4] > 0)
-            emit_group(v, i0, lim, thr, need, grun, erun, [&](unsigned pos, int C) { bc[pos + lim] = C; });
-        },
-        [&](int R) {
-          if (lane == 0) bc[grun + min(erun, need) + R] = R;  // the forced diagonal block closes the row
-        });
-    total = a.ksel[4] + nb;
-  } else if (pat == SA_TRIANGULAR) {
-    for (int R = gtid; R < nb; R += gthreads) {
-      const int run = rp[R];
-      const int bs = max(R - sh.local + 1, 0);
-      const int ns = min(sh.sink, bs);
-      for (int C = 0; C < ns; ++C) bc[run + C] = C;
-      for (int C = bs; C <= R; ++C) bc[run + ns + (C - bs)] = C;
+  if (pat == SA_BLOCK_CLUSTER && T > 0) {
+    // every workgroup finds its rows' pointers for itself: thread t sums the shares of RP rows
+    __shared__ int s_at[kMaxNb + 1];
+    constexpr int RP = kMaxNb / BT;
+    const int per = (nb + BT - 1) / BT;  // <= RP
+    unsigned sum = 0, unused = 0;
+    for (int j = 0; j < per; ++j)
+      if (per * tid + j < nb) sum += (unsigned)row_share(a, per * tid + j);
+    unsigned run = sum;
+    static_assert(RP * BT == kMaxNb, "rows per thread");
+    block_exclusive_scan2<WPB>(run, unused, s_wsum);
+    for (int j = 0; j < per; ++j) {
+      const int R = per * tid + j;
+      if (R < nb) {
+        s_at[R] = (int)run;
+        run += (unsigned)row_share(a, R);
+        if (R == nb - 1) s_at[nb] = (int)run;
+      }
     }
-    total = rp[nb];
+    __syncthreads();
+    for (int R = part; R < nb; R += nparts) {
+      const int at = __builtin_amdgcn_readfirstlane(s_at[R]), end = __builtin_amdgcn_readfirstlane(s_at[R + 1]);
+      if (lane == 0) rp[R] = at;
+      emit_row_select<T == 0 ? 1 : T>(hb + (size_t)R * nb, R, end - at - 1, bc + at);
+    }
+    total = s_at[nb];
+  } else if (pat == SA_BLOCK_CLUSTER) {
+    const int k = ksel(a, h, 4);
+    // no block below the diagonal is selected: no key is above this threshold, and no tie is taken
+    const unsigned thr = k > 0 ? G->thr[4] : 0xFFFFFFFFu, need = k > 0 ? G->need[4] : 0u;
+    unsigned grun = k > 0 ? G->bgt[part] : 0u, erun = k > 0 ? G->beq[part] : 0u;
+    // An entry of row R lands after the R diagonal blocks of the rows above; the first column of a
+    // row knows the row pointer, the diagonal entry the end of the row.
+    visit(a, 2, hb, part, [&](const Four &f) {
+      emit_group(f, thr, need, grun, erun, [&](int j, unsigned pos, bool sel) {
+        if (!((f.in >> j) & 1u)) return;
+        if (f.C[j] == 0) rp[f.R[j]] = (int)pos + f.R[j];
+        if (sel || f.C[j] == f.R[j]) bc[pos + f.R[j]] = f.C[j];
+      });
+    });
+    total = k + nb;
+  } else if (pat == SA_TRIANGULAR) {
+    const int local = head_budget(a, h).local;
+    for (int R = part; R < nb; R += nparts) {
+      const int at = tri_prefix(sh.sink, local, R);
+      const int bs = max(R - local + 1, 0), ns = min(sh.sink, bs), n = ns + R - bs + 1;
+      if (lane == 0) rp[R] = at;
+      for (int i = lane; i < n; i += 64) bc[at + i] = i < ns ? i : bs + i - ns;
+    }
+    total = tri_prefix(sh.sink, local, nb);
   } else {
-    for (int R = gtid; R < nb; R += gthreads) bc[R] = R;
+    for (int R = gtid; R < nb; R += gthreads) { rp[R] = R; bc[R] = R; }
     total = nb;
   }
+  if (gtid == 0) rp[nb] = total;
   for (int i = total + gtid; i < sh.cap_b; i += gthreads) bc[i] = -1;
-}
-
-// Per-row block rule: the rows of the Block-Cluster heads, wave gw of a head taking the rows
-// gw, gw + PW, ...  T = 64-key slices a row can have (nb <= 64 T).
-template <int T>
-__global__ __launch_bounds__(BT) void idx_emit_rows_kernel(IdxArgs a) {
-  const Shape &sh = a.sh;
-  const int h = blockIdx.y, nb = sh.nb;
-  if ((a.scratch + h)->pattern != SA_BLOCK_CLUSTER) return;
-  const int gw = blockIdx.x * WPB + (threadIdx.x >> 6);
-  const unsigned *hb = a.blk + (size_t)h * nb * nb;
-  const int32_t *rp = a.out.rowptr + (size_t)h * (nb + 1);
-  int32_t *bc = a.out.blkcols + (size_t)h * sh.cap_b;
-  for (int R = gw; R < nb; R += a.PW)
-    emit_row_select<T>(hb + (size_t)R * nb, R, row_share(sh, R) - 1, bc + rp[R]);
 }
 
 // ---- diagonals at block granularity -----------------------------------------------------------------
 // Interval-Slash heads when the selected diagonals are kept as whole blocks.  Runs after the
-// emission, which has left the selected offsets in the index: one wave per row block R collects the
+// emission, which has left the selected offsets in doffs: one wave per row block R collects the
 // key blocks that hold a key i - o of a query i of the row (at most two per offset) and the diagonal
-// block in a bitmap (the wave's own LDS slice).  PASS 0 stores the number of blocks of the row,
-// PASS 1 writes them in ascending order behind the row pointer.
+// block in a bitmap (the wave's own LDS slice).  PASS 0 counts the blocks of the rows, and its last
+// workgroup turns the counts into row pointers; PASS 1 writes the blocks in ascending order.
 template <int PASS>
 __global__ __launch_bounds__(BT) void idx_diag_rows_kernel(IdxArgs a) {
   __shared__ unsigned bm[WPB][kMaxNb / 32];
+  __shared__ unsigned s_wsum[2 * WPB];
   const Shape &sh = a.sh;
-  const int h = blockIdx.y, nb = sh.nb, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int h = blockIdx.y, nb = sh.nb, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   IdxScratch *G = a.scratch + h;
-  if (G->pattern != SA_INTERVAL_SLASH) return;
-  const int gw = blockIdx.x * WPB + wv;
-  const int n_offs = a.out.n_offs[h];
-  const int32_t *offs = a.out.offs + (size_t)h * sh.k_s;
-  const int32_t *rp = a.out.rowptr + (size_t)h * (nb + 1);
+  if (a.out.pattern[h] != SA_INTERVAL_SLASH) return;
+  const int n_offs = ksel(a, h, 3);
+  const int32_t *offs = a.doffs + (size_t)h * sh.k_s;
+  int32_t *rp = a.out.rowptr + (size_t)h * (nb + 1);
   int32_t *bc = a.out.blkcols + (size_t)h * sh.cap_b;
   const int shift = sh.b == 128 ? 7 : 6;
   unsigned *w = bm[wv];
-  for (int R = gw; R < nb; R += a.PW) {
+  for (int R = blockIdx.x * WPB + wv; R < nb; R += gridDim.x * WPB) {
     const int words = (R >> 5) + 1;  // bits 0..R
     for (int i = lane; i < words; i += 64) w[i] = 0u;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -768,67 +1169,89 @@ __global__ __launch_bounds__(BT) void idx_diag_rows_kernel(IdxArgs a) {
       }
       run += __shfl(incl, 63);
     }
-    if (PASS == 0 && lane == 0) G->rowgt[R] = (unsigned)run;
+    if (PASS == 0 && lane == 0) agent_store(&G->rowcnt[R], (unsigned)run);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();  // the slice is cleared again for the next row
   }
-}
-
-// One workgroup per head: row pointers of the Interval-Slash heads from the per-row counts above.
-__global__ __launch_bounds__(BT) void idx_diag_scan_kernel(IdxArgs a) {
-  __shared__ unsigned s_wsum[2 * WPB];
-  const int h = blockIdx.x, tid = threadIdx.x, nb = a.sh.nb;
-  IdxScratch *G = a.scratch + h;
-  if (G->pattern != SA_INTERVAL_SLASH) return;
+  if (PASS == 1 || !arrives_last(&G->ticket_rows, gridDim.x)) return;
+  // row pointers: thread t owns RP consecutive rows
   constexpr int RP = kMaxNb / BT;
+  const int per = (nb + BT - 1) / BT;  // <= RP
   unsigned g[RP], sum = 0;
 #pragma unroll
   for (int j = 0; j < RP; ++j) {
-    const int R = RP * tid + j;
-    g[j] = R < nb ? G->rowgt[R] : 0u;
+    const int R = per * tid + j;
+    g[j] = j < per && R < nb ? agent_load(&G->rowcnt[R]) : 0u;
     sum += g[j];
   }
   unsigned run = sum, unused = 0;
-  block_exclusive_scan2(run, unused, s_wsum);
-  int32_t *rp = a.out.rowptr + (size_t)h * (nb + 1);
+  block_exclusive_scan2<WPB>(run, unused, s_wsum);
 #pragma unroll
   for (int j = 0; j < RP; ++j) {
-    const int R = RP * tid + j;
-    if (R < nb) rp[R] = (int)run;
-    run += g[j];
-    if (R == nb - 1) rp[nb] = (int)run;
+    const int R = per * tid + j;
+    if (j < per && R < nb) {
+      rp[R] = (int)run;
+      run += g[j];
+      if (R == nb - 1) rp[nb] = (int)run;
+    }
   }
 }
 
-// The offsets are part of the block CSR now: hand back an empty list.
-__global__ void idx_diag_done_kernel(IdxArgs a) {
-  const int h = blockIdx.x;
-  if ((a.scratch + h)->pattern != SA_INTERVAL_SLASH) return;
-  int32_t *offs = a.out.offs + (size_t)h * a.sh.k_s;
-  for (int i = threadIdx.x; i < a.sh.k_s; i += blockDim.x) offs[i] = -1;
-  if (threadIdx.x == 0) a.out.n_offs[h] = 0;
+int list_cap_vs(const Shape &sh) { return sh.N < kListVs ? sh.N : kListVs; }
+int list_cap_blk(const Shape &sh) {
+  const long long all = (long long)sh.nb * (sh.nb - 1) / 2 + 1;
+  return all < kListBlk ? (int)all : kListBlk;
 }
+size_t round16(size_t x) { return (x + 15) & ~(size_t)15; }
 
 }  // namespace
 
-size_t index_scratch_bytes(int n_heads) { return sizeof(IdxScratch) * (size_t)n_heads; }
+size_t index_scratch_bytes(const Shape &sh) {
+  const size_t H = (size_t)sh.Hq;
+  return H * sizeof(IdxScratch) + H * 4 * list_cap_vs(sh) * 8 + H * list_cap_blk(sh) * 8 +
+         (sh.diag_blocks ? round16(H * (size_t)sh.k_s * 4) : 0);
+}
 
 namespace {
 
-IdxArgs index_args(const Shape &sh, const Workspace &ws, sa_scores in, const Override &ov, sa_index out) {
+// Prompts whose arrays one workgroup walks faster than several merge: see idx_select_kernel.  Measured
+// with 32 heads, one launch against four: 4096 keys and a 64 x 64 map 10 us against 29; a 256 x 256
+// map 37 against 27 (one compute unit then spends 13 us per walk), so the line lies between.
+constexpr int kSelectMaxKeys = 32768, kSelectMaxEntries = 32768;
+bool one_launch(const Shape &sh) {
+  return sh.N <= kSelectMaxKeys && (sh.row_select || sh.nb * sh.nb <= kSelectMaxEntries);
+}
+
+IdxArgs index_args(const Shape &sh, const Workspace &ws, sa_scores in, const Override &ov, sa_index out,
+                   const HeadBudget *hb, bool lazy) {
   IdxArgs a;
   a.v = (const unsigned *)in.v; a.s = (const unsigned *)in.s; a.blk = (const unsigned *)in.blk;
   a.scratch = (IdxScratch *)ws.idx;
+  a.cap_vs = list_cap_vs(sh); a.cap_blk = list_cap_blk(sh);
+  a.list_vs = (u64 *)(a.scratch + sh.Hq);
+  a.list_blk = a.list_vs + (size_t)sh.Hq * 4 * a.cap_vs;
+  a.doffs = (int32_t *)(a.list_blk + (size_t)sh.Hq * a.cap_blk);
   a.sh = sh; a.ov = ov; a.out = out;
-  // Workgroups per head.  Every launch is a chain of dependent memory round trips per wave, so more,
-  // shorter waves win until the per-workgroup costs (clearing and flushing the LDS histograms) take
-  // over: measured best at 32 per head up to 64K tokens and 64 at 128K, 256 keys per wave at least.
-  int P = sh.N / 256;
-  const int pmax = sh.N <= 65536 ? 32 : kMaxParts;
-  if (P < 1) P = 1;
-  if (P > pmax) P = pmax;
-  a.P = P; a.PW = P * WPB;
-  a.seg = ((sh.N + a.PW - 1) / a.PW + 255) / 256 * 256;
+  // A wave takes 1024 keys of v or s; of the block map it takes 1024 entries or a 512th of the map,
+  // whichever is more (a 256th at 128K tokens: 119 us for the index, a 512th 103; more, shorter waves
+  // hide more latency until merging their histograms takes over).  Where a workgroup walks a whole
+  // array, parts are single units: its waves share the work evenly from 4096 keys on.
+  const bool whole = one_launch(sh);
+  a.vpart = (whole ? 1 : kVsUnits) * kUnit;
+  a.Pv = (sh.N + WPB * a.vpart - 1) / (WPB * a.vpart);
+  const long long entries = (long long)sh.nb * sh.nb, units = (entries + kUnit - 1) / kUnit;
+  long long per = whole ? 1 : (units + kMaxBlkParts - 1) / kMaxBlkParts;
+  if (!whole && per < 4) per = 4;
+  a.bpart = (int)per * kUnit;
+  a.Pb = (int)(((units + per - 1) / per + WPB - 1) / WPB);
+  // under the per-row rule a wave of the emission takes whole rows
+  if (sh.row_select) a.Pb = (sh.nb + WPB - 1) / WPB < 128 ? (sh.nb + WPB - 1) / WPB : 128;
+  a.first = 0;
+  a.decide_here = lazy || !one_launch(sh);
+  a.nb_magic = ((1ull << 40) + sh.nb - 1) / sh.nb;
+  a.wrap_magic = ((1u << 20) + sh.nb - 1) / sh.nb;
+  const u64 all = (u64)sh.nb * (sh.nb + 1) / 2;
+  a.share_magic = all == 1 ? 0 : ~0ull / all + 1;
   const long long ncand = (long long)sh.nb * (sh.nb - 1) / 2;
   long long kb = (long long)sh.k_b - sh.nb;
   if (kb < 0) kb = 0;
@@ -838,8 +1261,20 @@ IdxArgs index_args(const Shape &sh, const Workspace &ws, sa_scores in, const Ove
   a.ksel[2] = sh.k_v < sh.N ? sh.k_v : sh.N;
   a.ksel[3] = sh.k_s < sh.N ? sh.k_s : sh.N;
   a.ksel[4] = sh.row_select ? 0 : (int)kb;   // per-row rule: selected row by row while emitting
-  a.mask = 3;
   a.decided = nullptr;
+  a.hb = hb;
+  // causal window entries, and those inside the Triangular region (sinks and band)
+  long long sbnd = (long long)sh.sink * sh.b;
+  if (sbnd > sh.N) sbnd = sh.N;
+  long long lb0 = (long long)(sh.nb - sh.local) * sh.b;
+  if (lb0 < sbnd) lb0 = sbnd;
+  a.E = a.ET = 0;
+  for (int i = 0; i < sh.w; ++i) {
+    const long long qi1 = (long long)sh.N - sh.w + i + 1;
+    a.E += (u64)qi1;
+    a.ET += (u64)(qi1 < sbnd ? qi1 : sbnd);
+    if (qi1 > lb0) a.ET += (u64)(qi1 - lb0);
+  }
   static_assert(kMaxHeads == 128, "four mask words");
   for (int w = 0; w < kMaxHeads / 32; ++w) a.skip_vs[w] = a.skip_blk[w] = 0u;
   for (int h = 0; h < sh.Hq; ++h) {
@@ -850,71 +1285,65 @@ IdxArgs index_args(const Shape &sh, const Workspace &ws, sa_scores in, const Ove
   return a;
 }
 
-void launch_levels(const IdxArgs &a, hipStream_t st) {
-  const dim3 grid(a.P, a.sh.Hq);
-  idx_hist_kernel<1><<<grid, BT, 0, st>>>(a);
-  idx_select_kernel<1><<<a.sh.Hq, BT, 0, st>>>(a);
-  idx_hist_kernel<2><<<grid, BT, 0, st>>>(a);
-  idx_select_kernel<2><<<a.sh.Hq, BT, 0, st>>>(a);
-  idx_hist_kernel<3><<<grid, BT, 0, st>>>(a);
-  idx_select_kernel<3><<<a.sh.Hq, BT, 0, st>>>(a);
+void launch_zero(const IdxArgs &a, hipStream_t st) {
+  if (a.decide_here) idx_zero_kernel<<<dim3(a.sh.Hq, 3), BT, 0, st>>>(a.scratch);
+}
+
+// The passes before the emission, for the selections on v and s, the one on the block map, or both.
+void launch_levels(IdxArgs a, bool vs, bool blk, hipStream_t st) {
+  if (a.sh.row_select || (a.ksel[4] <= 0 && !a.hb)) blk = false;
+  if (!vs && !blk) return;
+  if (one_launch(a.sh)) {
+    idx_select_kernel<<<dim3((vs ? 2 : 0) + (blk ? 1 : 0), a.sh.Hq), ST, 0, st>>>(a, vs ? 0 : 2);
+    return;
+  }
+  a.first = vs ? 0 : 2 * a.Pv;
+  const dim3 grid((vs ? 2 * a.Pv : 0) + (blk ? a.Pb : 0), a.sh.Hq);
+  idx_hist_kernel<<<grid, BT, 0, st>>>(a);
+  idx_refine_kernel<<<dim3((vs ? 2 * kRefineVs : 0) + (blk ? kRefineBlk : 0), a.sh.Hq), BT, 0, st>>>(a);
   idx_count_kernel<<<grid, BT, 0, st>>>(a);
 }
 
 void launch_finish(const IdxArgs &a, hipStream_t st) {
-  const dim3 grid(a.P, a.sh.Hq);
-  idx_scan_kernel<<<a.sh.Hq, BT, 0, st>>>(a);
-  idx_emit_kernel<<<grid, BT, 0, st>>>(a);
-  if (a.sh.row_select) {
-    if (a.sh.nb <= 256) idx_emit_rows_kernel<4><<<grid, BT, 0, st>>>(a);
-    else if (a.sh.nb <= 1024) idx_emit_rows_kernel<16><<<grid, BT, 0, st>>>(a);
-    else idx_emit_rows_kernel<kMaxNb / 64><<<grid, BT, 0, st>>>(a);
-  }
+  const dim3 grid(2 * a.Pv + a.Pb, a.sh.Hq);
+  if (!a.sh.row_select) idx_emit_kernel<0><<<grid, BT, 0, st>>>(a);
+  else if (a.sh.nb <= 256) idx_emit_kernel<4><<<grid, BT, 0, st>>>(a);
+  else if (a.sh.nb <= 1024) idx_emit_kernel<16><<<grid, BT, 0, st>>>(a);
+  else idx_emit_kernel<kMaxNb / 64><<<grid, BT, 0, st>>>(a);
   if (a.sh.diag_blocks) {
-    idx_diag_rows_kernel<0><<<grid, BT, 0, st>>>(a);
-    idx_diag_scan_kernel<<<a.sh.Hq, BT, 0, st>>>(a);
-    idx_diag_rows_kernel<1><<<grid, BT, 0, st>>>(a);
-    idx_diag_done_kernel<<<a.sh.Hq, BT, 0, st>>>(a);
+    // a row per wave, up to 64 workgroups per head
+    int P = (a.sh.nb + WPB - 1) / WPB;
+    if (P > 64) P = 64;
+    const dim3 rows(P, a.sh.Hq);
+    idx_diag_rows_kernel<0><<<rows, BT, 0, st>>>(a);
+    idx_diag_rows_kernel<1><<<rows, BT, 0, st>>>(a);
   }
 }
 
 }  // namespace
 
 hipError_t launch_build_index(const Shape &sh, const Workspace &ws, sa_scores in, const Override &ov,
-                              sa_index out, hipStream_t st) {
-  const IdxArgs a = index_args(sh, ws, in, ov, out);
-  idx_zero_kernel<<<sh.Hq, 256, 0, st>>>(a.scratch);
-  launch_levels(a, st);
+                              sa_index out, hipStream_t st, const HeadBudget *budgets) {
+  const IdxArgs a = index_args(sh, ws, in, ov, out, budgets, false);
+  launch_zero(a, st);
+  launch_levels(a, true, true, st);
   launch_finish(a, st);
   return hipGetLastError();
 }
 
 // The same work in parts, so that it can run beside the estimator: the selections on v and s as
-// soon as the window passes are done, the block-map selection as soon as the block map is (on
-// another stream), and the emission once both are.  Decide (after ColumnsDiagonals) writes the
-// patterns early, for a caller that computes the block map only where it is needed.
+// soon as the window passes are done (they also write the patterns, for a caller that computes the
+// block map only where it is needed), the block-map selection as soon as the block map is (on
+// another stream), and the emission once both are.
 hipError_t launch_index_stage(const Shape &sh, const Workspace &ws, sa_scores in, const Override &ov,
                               sa_index out, IndexStage stage, hipStream_t st, bool lazy) {
-  IdxArgs a = index_args(sh, ws, in, ov, out);
+  IdxArgs a = index_args(sh, ws, in, ov, out, nullptr, lazy);
   if (lazy) a.decided = out.pattern;
   switch (stage) {
-    case IndexStage::Zero:
-      idx_zero_kernel<<<sh.Hq, 256, 0, st>>>(a.scratch);
-      break;
-    case IndexStage::ColumnsDiagonals:
-      a.mask = 1;
-      launch_levels(a, st);
-      break;
-    case IndexStage::Decide:
-      idx_decide_kernel<<<(sh.Hq + 63) / 64, 64, 0, st>>>(a);
-      break;
-    case IndexStage::Blocks:
-      a.mask = 2;
-      if (!sh.row_select) launch_levels(a, st);
-      break;
-    case IndexStage::Emit:
-      launch_finish(a, st);
-      break;
+    case IndexStage::Zero: launch_zero(a, st); break;
+    case IndexStage::ColumnsDiagonals: launch_levels(a, true, false, st); break;
+    case IndexStage::Blocks: launch_levels(a, false, true, st); break;
+    case IndexStage::Emit: launch_finish(a, st); break;
   }
   return hipGetLastError();
 }

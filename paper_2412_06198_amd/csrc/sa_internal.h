@@ -14,6 +14,9 @@ constexpr int kMaxSeq = 262144;   // key-tile bitmaps of the attention kernel co
 
 struct Override { int8_t pat[kMaxHeads]; };
 
+// Budgets of one head, for index builds whose heads differ in them (device arrays of these).
+struct HeadBudget { int32_t k_v, k_s, k_b, local; };
+
 // Everything the kernels need, resolved from sa_config at sa_create time.
 struct Shape {
   int Hq, Hkv, g, N, b, nb, w;
@@ -42,7 +45,7 @@ struct Workspace {
   int32_t *hperm;                 // [Hkv][g + 1] order of a KV head's query heads in the attention kernel's queues
 };
 
-size_t index_scratch_bytes(int n_heads);
+size_t index_scratch_bytes(const Shape &sh);
 
 // Side stream of a context with the events that fork it from and join it back into the caller's
 // stream inside one call (the estimator runs its Q chain beside its K chain).  aux == nullptr:
@@ -50,7 +53,7 @@ size_t index_scratch_bytes(int n_heads);
 struct Fork { hipStream_t aux; hipEvent_t fork, mid, join; };
 
 // Parts of the index builder when it runs interleaved with the estimator.
-enum class IndexStage { Zero, ColumnsDiagonals, Decide, Blocks, Emit };
+enum class IndexStage { Zero, ColumnsDiagonals, Blocks, Emit };
 
 // Which of the estimator's two chains a call enqueues.
 enum class EstimatePart { Both, KChain, QChain };
@@ -83,10 +86,12 @@ hipError_t launch_estimate(const Shape &sh, const Workspace &ws, const uint16_t 
 hipError_t launch_estimate_part(const Shape &sh, const Workspace &ws, const uint16_t *Q, const uint16_t *K,
                                 sa_scores out, EstimatePart part, const int32_t *only_block_cluster,
                                 hipStream_t st);
+// budgets: device array of one entry per head, none above the shape's own, or nullptr = the shape's
 hipError_t launch_build_index(const Shape &sh, const Workspace &ws, sa_scores in,
-                              const Override &ov, sa_index out, hipStream_t st);
+                              const Override &ov, sa_index out, hipStream_t st,
+                              const HeadBudget *budgets = nullptr);
 // lazy: the block-map part of the work is done only for the heads whose out.pattern (written by
-// the Decide stage) is SA_BLOCK_CLUSTER.
+// the ColumnsDiagonals stage) is SA_BLOCK_CLUSTER.
 hipError_t launch_index_stage(const Shape &sh, const Workspace &ws, sa_scores in, const Override &ov,
                               sa_index out, IndexStage stage, hipStream_t st, bool lazy = false);
 size_t decode_partial_bytes(const Shape &sh);
