@@ -19,9 +19,9 @@
  *     workspace).  Sizes come from the *_bytes queries.  The library never
  *     allocates or frees device memory and the compute calls never synchronise
  *     the host: they enqueue kernels on the given HIP stream and return.  The
- *     offline search is the exception on the host side: the host steers it, so
- *     it waits for the stream after every probe and creates and frees small
- *     host-memory contexts on the way (still no device memory), see there.
+ *     offline search is the exception on the host side: its results go to host
+ *     memory, so it waits for the stream (once per batch of heads) and uses host
+ *     memory of its own on the way (still no device memory), see there.
  *     sa_estimate_patterns (and sa_estimate_and_index) runs part of its kernels on a side stream that the
  *     context owns (created by sa_create, default priority); that stream waits
  *     for the given stream at entry and the given stream waits for it at exit,
@@ -214,8 +214,8 @@ sa_status sa_sparse_decode(sa_ctx *ctx, const void *q, const void *K, const void
 sa_status sa_sparse_decode_static(sa_ctx *ctx, const void *q, const void *K, const void *V, sa_index idx,
                                   int64_t pos, void *o, void *hip_stream);
 
-/* Offline pattern search, "Kernel-Aware Sparse Pattern Search Algorithm" (Alg. 1), one head at a
- * time.  Candidates: the three patterns, each with one integer size (its search space):
+/* Offline pattern search, "Kernel-Aware Sparse Pattern Search Algorithm" (Alg. 1), for every head by
+ * itself.  Candidates: the three patterns, each with one integer size (its search space):
  *   SA_TRIANGULAR      local_blocks = x,                       1 <= x <= nb
  *   SA_INTERVAL_SLASH  k_slash = x, k_vertical = min(N, 32 x), 1 <= x <= max(1, N/32)
  *   SA_BLOCK_CLUSTER   k_blocks = x,                           nb <= x <= nb (nb+1)/2
@@ -229,9 +229,9 @@ sa_status sa_sparse_decode_static(sa_ctx *ctx, const void *q, const void *K, con
  * Q, K, V, scores: device, as for the other calls (scores from sa_estimate_patterns).  scratch:
  * DEVICE, 256-byte aligned, sa_search_scratch_bytes bytes, owned by the caller.  out_host: HOST
  * array of n_q_heads results, candidates in pattern-id order.  The call runs the index builder and
- * the attention kernel of this library on one-head contexts it creates and destroys, waits for the
- * stream after every probe (do not capture it in a graph) and returns when all results are in
- * out_host.  ctx's own workspace is not used. */
+ * the attention kernel of this library on batches of heads (as many as 2 GiB of scratch hold, one at
+ * least), waits for the stream after each batch (do not capture it in a graph) and returns when all
+ * results are in out_host.  ctx's own workspace is not used. */
 typedef struct {
   int32_t pattern;   /* argmin of err */
   int32_t param[3];  /* refined size x of each candidate */

@@ -11,15 +11,6 @@ namespace {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-long long triangular_count(int nb, int sink, int local) {
-  long long n = 0;
-  for (int R = 0; R < nb; ++R) {
-    const int bs = R - local + 1 > 0 ? R - local + 1 : 0;
-    n += (sink < bs ? sink : bs) + (R - bs + 1);
-  }
-  return n;
-}
-
 sa_status fail(sa_ctx *c, sa_status st, const char *msg) {
   if (c) snprintf(c->err, sizeof(c->err), "%s", msg);
   return st;
@@ -46,6 +37,15 @@ void carve(sa_ctx *c) {
 }
 
 }  // namespace
+
+long long sa::triangular_count(int nb, int sink, int local) {
+  long long n = 0;
+  for (int R = 0; R < nb; ++R) {
+    const int bs = R - local + 1 > 0 ? R - local + 1 : 0;
+    n += (sink < bs ? sink : bs) + (R - bs + 1);
+  }
+  return n;
+}
 
 extern "C" {
 
@@ -115,7 +115,7 @@ sa_status sa::create_context(const sa_config *cfg, sa_ctx **out, bool side_strea
   s.probe_s = cfg->probe_s ? cfg->probe_s : 4;
   s.lift_num = cfg->lift_num ? cfg->lift_num : 4;
   s.lift_den = cfg->lift_den ? cfg->lift_den : 1;
-  const long long tri = triangular_count(nb, s.sink, s.local);
+  const long long tri = sa::triangular_count(nb, s.sink, s.local);
   s.row_select = cfg->block_select == SA_BLOCKS_PER_ROW;
   s.row_norm = cfg->block_select == SA_BLOCKS_GLOBAL_ROW_NORMALISED;
   // the per-row rule rounds every row's share up: at most one block per row above k_b
@@ -139,6 +139,8 @@ sa_status sa::create_context(const sa_config *cfg, sa_ctx **out, bool side_strea
   s.q_hs = cfg->q_head_stride ? cfg->q_head_stride : (int64_t)s.N * s.q_rs;
   s.kv_rs = cfg->kv_row_stride ? cfg->kv_row_stride : sa::kHeadDim;
   s.kv_hs = cfg->kv_head_stride ? cfg->kv_head_stride : (int64_t)s.N * s.kv_rs;
+  s.o_hs = s.q_hs;
+  s.o_rs = s.q_rs;
   if (s.q_rs % 8 || s.kv_rs % 8 || s.q_hs % 8 || s.kv_hs % 8 || s.q_rs < sa::kHeadDim ||
       s.kv_rs < sa::kHeadDim) {
     delete c;

@@ -29,6 +29,7 @@ struct Shape {
   int chunk, nchunks;             // keys per estimator workgroup (window passes), ceil(N / chunk)
   int n_cu;                       // compute units of the device the context was created on
   int64_t q_hs, q_rs, kv_hs, kv_rs;
+  int64_t o_hs, o_rs;             // output of the attention: as Q's, except inside the search
   float scale;
 };
 
@@ -74,6 +75,8 @@ struct sa_ctx {
 
 namespace sa {
 
+// key blocks of a Triangular index
+long long triangular_count(int nb, int sink, int local);
 // sa_create, optionally without the estimator's side stream and its events
 sa_status create_context(const sa_config *cfg, sa_ctx **out, bool side_stream);
 

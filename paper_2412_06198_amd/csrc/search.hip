@@ -1,34 +1,45 @@
-// Offline pattern search (Kernel-Aware Sparse Pattern Search Algorithm, Alg. 1), head by head:
+// Offline pattern search (Kernel-Aware Sparse Pattern Search Algorithm, Alg. 1):
 //   Initialize Search Space - each candidate pattern has one integer size (Triangular: band
 //     blocks; Interval-Slash: diagonals, with 32 columns per diagonal; Block-Cluster: blocks);
 //     RefineSearchSpace is a bisection on it until the kept (query, key) pairs - FLOPs / (4 d) -
 //     meet the target within the tolerance, or the two sizes around the target are adjacent;
 //   Evaluate Patterns - the head's dense causal output against the sparse output of every
 //     refined candidate, Frobenius norm of the difference, smallest wins (ties: lowest id).
-// Every evaluation runs the library's own index builder and attention kernel on a one-head
-// context, so the cost that is matched is the cost of these kernels' masks; the host only steers.
+// All heads of a batch go through every step together, with budgets of their own each, and the host
+// waits once per batch.  The pairs of a Triangular or Block-Cluster candidate follow from its number
+// of blocks alone; those of an Interval-Slash candidate are counted from the selected columns and
+// offsets (slash_step_kernel), which also takes the head's next bisection step, so a probe is an
+// index build and one small kernel, and no attention runs before the sizes are known.  (With one
+// head at a time, an attention call per probe to count its pairs and a wait after each, 8 heads of
+// 4096 tokens took 24 ms; this takes 1.)
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <vector>
 
 #include "sa_internal.h"
 
 namespace {
 
 constexpr int kNormBlocks = 1024;
+constexpr size_t kBatchBytes = (size_t)2 << 30;  // scratch that a batch of heads may take (one head always may)
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// partial[blockIdx.x] = sum over the block's rows of (A - B)^2, A and B [N][128] bf16 with row
-// stride rs (elements); fp64 accumulation, fixed order: bit-reproducible.
+// partial[head][blockIdx.x] = sum over the block's rows of (A - B)^2, A and B [heads][N][128] bf16; fp64
+// accumulation, fixed order: bit-reproducible.  grid (blocks, heads)
 __global__ __launch_bounds__(256) void sq_diff_kernel(const uint16_t *__restrict__ A,
-                                                      const uint16_t *__restrict__ B, int N, int64_t rs,
+                                                      const uint16_t *__restrict__ B, int N,
                                                       double *__restrict__ partial) {
   __shared__ double red[256];
   const int cc = threadIdx.x & 15, rg = threadIdx.x >> 4;
+  const size_t head = (size_t)blockIdx.y * N * sa::kHeadDim;
   double acc = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * 16 + rg; i < N; i += (int64_t)gridDim.x * 16) {
-    const uint4 a = *(const uint4 *)(A + i * rs + cc * 8), b = *(const uint4 *)(B + i * rs + cc * 8);
+  // the rows of a block: kNormBlocks blocks' worth apart, whatever the grid (the sums of the blocks that
+  // a short sequence leaves without rows are zero)
+  for (int64_t i = (int64_t)blockIdx.x * 16 + rg; i < N; i += (int64_t)kNormBlocks * 16) {
+    const size_t o = head + (size_t)i * sa::kHeadDim + cc * 8;
+    const uint4 a = *(const uint4 *)(A + o), b = *(const uint4 *)(B + o);
     const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -43,62 +54,174 @@ __global__ __launch_bounds__(256) void sq_diff_kernel(const uint16_t *__restrict
     if ((int)threadIdx.x < d) red[threadIdx.x] += red[threadIdx.x + d];
     __syncthreads();
   }
-  if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) partial[(size_t)blockIdx.y * kNormBlocks + blockIdx.x] = red[0];
 }
 
-struct Sizes {
-  int64_t x_lo[3], x_hi[3];
-  int kv_max, ks_max;
-  int64_t cap_max;
-  size_t ws_child, o_bytes, off[12], total;
+// RefineSearchSpace of one candidate, a step per evaluated size: the smallest size, the largest, then
+// bisection between sizes whose pairs lie on either side of the target.
+struct Refine {
+  int64_t lo, hi, p_lo, p_hi;  // sizes around the target and their pairs
+  int64_t x, px;               // size to evaluate next, or (done) the answer and its pairs
+  int32_t stage, done;
+  __host__ __device__ void start(int64_t x_lo, int64_t x_hi) {
+    lo = x = x_lo; hi = x_hi;
+    p_lo = p_hi = px = 0;
+    stage = done = 0;
+  }
+  __host__ __device__ void step(int64_t pairs, int64_t target, int64_t eps) {
+    if (done) return;
+    const int64_t off = pairs < target ? target - pairs : pairs - target;
+    const bool hit = off <= eps;
+    px = pairs;
+    if (stage == 0) {
+      p_lo = pairs;
+      if (pairs >= target || hit || lo == hi) { done = 1; return; }
+      x = hi;
+      stage = 1;
+      return;
+    }
+    if (stage == 1) {
+      p_hi = pairs;
+      if (pairs <= target || hit) { done = 1; return; }
+      stage = 2;
+    } else {
+      if (hit) { done = 1; return; }
+      if (pairs < target) { lo = x; p_lo = pairs; } else { hi = x; p_hi = pairs; }
+    }
+    if (hi - lo > 1) { x = (lo + hi) / 2; return; }
+    done = 1;  // adjacent sizes: the closer one, the smaller on a tie
+    if (target - p_lo <= p_hi - target) { x = lo; px = p_lo; } else { x = hi; px = p_hi; }
+  }
 };
 
-void candidate_config(const sa_config &parent, int pattern, int64_t x, sa_config *c) {
-  *c = parent;
-  c->n_q_heads = c->n_kv_heads = 1;
-  const int nb = parent.seq_len / parent.block;
-  c->local_blocks = 1; c->k_vertical = 1; c->k_slash = 1; c->k_blocks = nb;
-  c->block_select = SA_BLOCKS_GLOBAL;  // the search's Block-Cluster candidate is the one-top-k rule,
-  c->diagonal_select = SA_DIAGONALS_EXACT;  // its Interval-Slash candidate the element-exact one
-  c->lazy_block_map = 0;
-  if (pattern == SA_TRIANGULAR) {
-    c->local_blocks = (int32_t)x;
-  } else if (pattern == SA_INTERVAL_SLASH) {
-    c->k_slash = (int32_t)x;
-    const int64_t kv = 32 * x;
-    c->k_vertical = (int32_t)(kv < parent.seq_len ? kv : parent.seq_len);
-  } else {
-    c->k_blocks = (int32_t)x;
+__host__ __device__ inline sa::HeadBudget slash_budget(int64_t x, int N, int nb) {
+  sa::HeadBudget b;
+  b.k_s = (int32_t)x;
+  b.k_v = (int32_t)(32 * x < N ? 32 * x : N);
+  b.k_b = nb;
+  b.local = 1;
+  return b;
+}
+
+// One workgroup per head: the kept pairs of the head's Interval-Slash index (its diagonal blocks, the
+// selected columns, the selected diagonals; each pair once), then the next step of its refinement.
+//   diagonal blocks: nb b (b + 1) / 2
+//   column c: the queries behind its key block
+//   offset o: the pairs (i, i - o) in different blocks, less those whose key is a selected column,
+//     i.e. the columns c < N - o with c % b >= b - o
+__global__ __launch_bounds__(256) void slash_step_kernel(const int32_t *cols, const int32_t *offs, int k_v,
+                                                         int k_s, int N, int b, Refine *state,
+                                                         sa::HeadBudget *budget, int64_t target, int64_t eps) {
+  __shared__ int by_pos[128];            // columns outside the last key block by their position in the block
+  __shared__ int from[129];              // ... at position p or behind
+  __shared__ long long red[256];
+  const int h = blockIdx.x, tid = threadIdx.x, nb = N / b;
+  if (state[h].done) return;
+  const int nc = min(budget[h].k_v, N), no = min(budget[h].k_s, N);
+  const int32_t *c = cols + (size_t)h * k_v, *o = offs + (size_t)h * k_s;
+  if (tid < b) by_pos[tid] = 0;
+  __syncthreads();
+  long long sum = 0;
+  for (int i = tid; i < nc; i += 256) {
+    const int key = c[i], blk = key / b;
+    sum += N - (blk + 1) * b;
+    if (blk < nb - 1) atomicAdd(&by_pos[key - blk * b], 1);
+  }
+  __syncthreads();
+  if (tid <= b) {
+    int n = 0;
+    for (int p = tid; p < b; ++p) n += by_pos[p];
+    from[tid] = n;
+  }
+  __syncthreads();
+  for (int i = tid; i < no; i += 256) {
+    const int off = o[i];
+    if (off >= b) {
+      int lo = 0, hi = nc;  // the first column that is not below N - off
+      while (lo < hi) {
+        const int m = (lo + hi) >> 1;
+        if (c[m] < N - off) lo = m + 1;
+        else hi = m;
+      }
+      sum += N - off - lo;
+    } else {
+      sum += (long long)(N - off) - (long long)nb * (b - off) - from[b - off];
+    }
+  }
+  red[tid] = sum;
+  __syncthreads();
+  for (int d = 128; d >= 1; d >>= 1) {
+    if (tid < d) red[tid] += red[tid + d];
+    __syncthreads();
+  }
+  if (tid == 0) {
+    Refine r = state[h];
+    r.step(red[0] + (long long)nb * b * (b + 1) / 2, target, eps);
+    state[h] = r;
+    budget[h] = slash_budget(r.x, N, nb);
   }
 }
 
-sa_status plan(const sa_ctx *ctx, Sizes *z) {
+// Heads that go through the search together, and the scratch they take.
+struct Plan {
+  int heads, kv_heads;  // query heads of a batch (whole KV groups, or a part of one), their KV heads
+  sa_config cfg;        // of a batch: budgets as large as any candidate's
+  int64_t x_lo[3], x_hi[3];
+  size_t off[12], total;
+};
+
+sa_status plan_batch(const sa_ctx *ctx, int heads, Plan *z) {
   const sa_config &p = ctx->cfg;
-  const int N = p.seq_len, nb = N / p.block;
+  const int N = p.seq_len, nb = N / p.block, g = ctx->sh.g;
+  z->heads = heads;
+  z->kv_heads = heads > g ? heads / g : 1;
   z->x_lo[0] = 1; z->x_hi[0] = nb;
   z->x_lo[1] = 1; z->x_hi[1] = N / 32 > 1 ? N / 32 : 1;
   z->x_lo[2] = nb; z->x_hi[2] = (int64_t)nb * (nb + 1) / 2;
   if (z->x_hi[2] > 0x7FFFFFFFll) return SA_ERR_UNSUPPORTED;
-  z->ks_max = (int)z->x_hi[1];
-  z->kv_max = 32 * (int64_t)z->ks_max < N ? 32 * z->ks_max : N;
-  z->cap_max = z->x_hi[2];
-  // the largest child workspace is the one with the most gathered columns
-  sa_config c;
-  candidate_config(p, SA_INTERVAL_SLASH, z->x_hi[1], &c);
+  sa_config &c = z->cfg;
+  c = p;
+  c.n_q_heads = heads; c.n_kv_heads = z->kv_heads;
+  const sa::HeadBudget most = slash_budget(z->x_hi[1], N, nb);
+  c.k_vertical = most.k_v; c.k_slash = most.k_s;
+  c.local_blocks = nb; c.k_blocks = (int32_t)z->x_hi[2];
+  c.block_select = SA_BLOCKS_GLOBAL;        // the search's Block-Cluster candidate is the one-top-k rule,
+  c.diagonal_select = SA_DIAGONALS_EXACT;   // its Interval-Slash candidate the element-exact one
+  c.lazy_block_map = 0;
+  if (!c.q_head_stride) c.q_head_stride = ctx->sh.q_hs;
+  if (!c.kv_head_stride) c.kv_head_stride = ctx->sh.kv_hs;
   sa_ctx *child = nullptr;
-  sa_status st = sa::create_context(&c, &child, false);
+  sa_status st = sa::create_context(&c, &child, false);  // host memory only: no stream, no events
   if (st != SA_OK) return st;
-  st = sa_workspace_bytes(child, &z->ws_child);
+  size_t ws = 0, ix[7];
+  st = sa_workspace_bytes(child, &ws);
+  if (st == SA_OK) st = sa_index_bytes(child, ix);
   sa_destroy(child);
   if (st != SA_OK) return st;
-  z->o_bytes = (size_t)N * (size_t)ctx->sh.q_rs * 2;
-  const size_t parts[12] = {z->ws_child, z->o_bytes, z->o_bytes, (size_t)nb * nb * 4, 256, 256,
-                            (size_t)z->kv_max * 4, 256, (size_t)z->ks_max * 4, (size_t)(nb + 1) * 4,
-                            (size_t)z->cap_max * 4, 256 + (size_t)kNormBlocks * 8};
+  const size_t o_bytes = (size_t)heads * N * sa::kHeadDim * 2;
+  const size_t parts[12] = {ws, o_bytes, o_bytes, (size_t)heads * 4 * sizeof(sa::HeadBudget) + (size_t)heads * sizeof(Refine),
+                            (size_t)heads * 3 * kNormBlocks * 8, ix[0], ix[1], ix[2], ix[3], ix[4], ix[5], ix[6]};
   size_t o = 0;
   for (int i = 0; i < 12; ++i) { z->off[i] = o; o += align256(parts[i]); }
   z->total = o;
   return SA_OK;
+}
+
+// The largest batch whose scratch stays within kBatchBytes: whole KV groups, else an even part of one.
+sa_status plan(const sa_ctx *ctx, Plan *z) {
+  const int g = ctx->sh.g;
+  sa_status st = SA_OK;
+  for (int kv = ctx->sh.Hkv; kv >= 1; --kv) {
+    if (ctx->sh.Hkv % kv) continue;
+    if ((st = plan_batch(ctx, kv * g, z)) != SA_OK) return st;
+    if (z->total <= kBatchBytes) return SA_OK;
+  }
+  for (int n = g - 1; n >= 1; --n) {
+    if (g % n) continue;
+    if ((st = plan_batch(ctx, n, z)) != SA_OK) return st;
+    if (z->total <= kBatchBytes) return SA_OK;
+  }
+  return SA_OK;  // one head at a time
 }
 
 sa_status failp(sa_ctx *c, sa_status st, const char *msg) {
@@ -112,7 +235,7 @@ extern "C" {
 
 sa_status sa_search_scratch_bytes(const sa_ctx *ctx, size_t *bytes) {
   if (!ctx || !bytes) return SA_ERR_INVALID_ARG;
-  Sizes z;
+  Plan z;
   const sa_status st = plan(ctx, &z);
   if (st == SA_OK) *bytes = z.total;
   return st;
@@ -126,115 +249,118 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
     return failp(ctx, SA_ERR_INVALID_ARG, "null pointer");
   if (target_pairs < 0 || eps_pairs < 0) return failp(ctx, SA_ERR_INVALID_ARG, "negative target or tolerance");
   if ((uintptr_t)scratch & 255) return failp(ctx, SA_ERR_INVALID_ARG, "scratch must be 256-byte aligned");
-  Sizes z;
+  if (((uintptr_t)Q | (uintptr_t)K | (uintptr_t)V | (uintptr_t)scores.v | (uintptr_t)scores.s) & 15)
+    return failp(ctx, SA_ERR_INVALID_ARG, "search: Q, K, V, v, s must be 16-byte aligned");
+  Plan z;
   sa_status st = plan(ctx, &z);
   if (st != SA_OK) return failp(ctx, st, "search: sizes not supported");
   if (scratch_bytes < z.total) return failp(ctx, SA_ERR_BUFFER_TOO_SMALL, "scratch smaller than sa_search_scratch_bytes");
   hipStream_t stream = (hipStream_t)hip_stream;
   const sa::Shape &sh = ctx->sh;
-  const int N = sh.N, nb = sh.nb;
+  const int N = sh.N, nb = sh.nb, b = sh.b, B = z.heads;
   char *base = (char *)scratch;
-  void *ws = base + z.off[0];
   uint16_t *o_dense = (uint16_t *)(base + z.off[1]), *o_sparse = (uint16_t *)(base + z.off[2]);
-  float *blk1 = (float *)(base + z.off[3]);
+  sa::HeadBudget *budgets = (sa::HeadBudget *)(base + z.off[3]);  // dense, then the three candidates
+  Refine *state = (Refine *)(budgets + (size_t)4 * B);
+  double *partial = (double *)(base + z.off[4]);
   sa_index ix;
-  ix.pattern = (int32_t *)(base + z.off[4]); ix.n_cols = (int32_t *)(base + z.off[5]);
-  ix.cols = (int32_t *)(base + z.off[6]); ix.n_offs = (int32_t *)(base + z.off[7]);
-  ix.offs = (int32_t *)(base + z.off[8]); ix.rowptr = (int32_t *)(base + z.off[9]);
-  ix.blkcols = (int32_t *)(base + z.off[10]);
-  uint64_t *counters = (uint64_t *)(base + z.off[11]);
-  double *partial = (double *)(base + z.off[11] + 256);
+  int32_t **part[7] = {&ix.pattern, &ix.n_cols, &ix.cols, &ix.n_offs, &ix.offs, &ix.rowptr, &ix.blkcols};
+  for (int i = 0; i < 7; ++i) *part[i] = (int32_t *)(base + z.off[5 + i]);
+
+  sa_ctx *child = nullptr;
+  if ((st = sa::create_context(&z.cfg, &child, false)) != SA_OK) return failp(ctx, st, "search: batch rejected by sa_create");
+  st = sa_set_workspace(child, base + z.off[0], child->ws_bytes);
+  sa::Shape cs = child->sh;
+  const sa::Workspace ws = child->ws;
+  sa_destroy(child);
+  if (st != SA_OK) return failp(ctx, st, "search: workspace");
+  cs.o_hs = (int64_t)N * sa::kHeadDim;  // outputs are compared here: contiguous whatever Q's layout
+  cs.o_rs = sa::kHeadDim;
+
+  // pairs of an index made of whole blocks, the nb diagonal ones among them
+  auto block_pairs = [&](int64_t blocks) { return (blocks - nb) * b * b + (int64_t)nb * b * (b + 1) / 2; };
+  // The sizes of the candidates whose pairs are known without an index are the same for every head.
+  Refine tri, clu;
+  tri.start(z.x_lo[0], z.x_hi[0]);
+  while (!tri.done) tri.step(block_pairs(sa::triangular_count(nb, sh.sink, (int)tri.x)), target_pairs, eps_pairs);
+  clu.start(z.x_lo[2], z.x_hi[2]);
+  while (!clu.done) clu.step(block_pairs(clu.x), target_pairs, eps_pairs);
+  int rounds = 2;  // evaluations a bisection can take
+  for (int64_t w = z.x_hi[1] - z.x_lo[1]; w > 1; w = (w + 1) / 2) ++rounds;
+
+  std::vector<char> head((size_t)B * (4 * sizeof(sa::HeadBudget) + sizeof(Refine)));
+  sa::HeadBudget *hb = (sa::HeadBudget *)head.data();
+  Refine *hr = (Refine *)(hb + (size_t)4 * B);
+  for (int i = 0; i < B; ++i) {
+    const sa::HeadBudget least = slash_budget(z.x_lo[1], N, nb);
+    hb[i] = hb[B + i] = hb[2 * B + i] = hb[3 * B + i] = least;
+    hb[i].local = nb;
+    hb[B + i].local = (int32_t)tri.x;
+    hb[3 * B + i].k_b = (int32_t)clu.x;
+    hr[i].start(z.x_lo[1], z.x_hi[1]);
+  }
+  const size_t norms = (size_t)B * 3 * kNormBlocks;
+  std::vector<double> hp(norms);
+  const int nblocks = (N + 15) / 16 < kNormBlocks ? (N + 15) / 16 : kNormBlocks;
 
   hipError_t he = hipSuccess;
-  auto hip_fail = [&](hipError_t e) {
-    snprintf(ctx->err, sizeof(ctx->err), "HIP: %s", hipGetErrorString(e));
-    return SA_ERR_HIP;
+  auto ok = [&](hipError_t e) {
+    if (e != hipSuccess && he == hipSuccess) he = e;
+    return he == hipSuccess;
   };
-
-  for (int h = 0; h < sh.Hq; ++h) {
-    const uint16_t *Qh = (const uint16_t *)Q + (size_t)h * sh.q_hs;
-    const uint16_t *Kh = (const uint16_t *)K + (size_t)(h / sh.g) * sh.kv_hs;
-    const uint16_t *Vh = (const uint16_t *)V + (size_t)(h / sh.g) * sh.kv_hs;
-    // the head's block map goes to an aligned copy (its slice need not be 16-byte aligned)
-    if ((he = hipMemcpyAsync(blk1, scores.blk + (size_t)h * nb * nb, (size_t)nb * nb * 4,
-                             hipMemcpyDeviceToDevice, stream)) != hipSuccess)
-      return hip_fail(he);
-    const sa_scores sc{scores.v + (size_t)h * N, scores.s + (size_t)h * N, blk1};
-
-    // one evaluation: index of candidate (pattern, x), sparse output into O, kept pairs
-    auto evaluate = [&](int pattern, int64_t x, uint16_t *O, bool count, int64_t *pairs) -> sa_status {
-      sa_config c;
-      candidate_config(ctx->cfg, pattern, x, &c);
-      sa_ctx *child = nullptr;
-      sa_status s_ = sa::create_context(&c, &child, false);  // host memory only: no stream, no events
-      if (s_ != SA_OK) return failp(ctx, s_, "search: candidate rejected by sa_create");
-      const int32_t ov = pattern;
-      s_ = sa_set_workspace(child, ws, z.ws_child);
-      if (s_ == SA_OK) s_ = sa_build_index(child, sc, &ov, ix, stream);
-      if (s_ == SA_OK && count) {
-        if ((he = hipMemsetAsync(counters, 0, 16, stream)) != hipSuccess) s_ = hip_fail(he);
-        if (s_ == SA_OK) s_ = sa_sparse_prefill_counted(child, Qh, Kh, Vh, ix, O, counters, stream);
-      } else if (s_ == SA_OK) {
-        s_ = sa_sparse_prefill(child, Qh, Kh, Vh, ix, O, stream);
-      }
-      if (s_ != SA_OK && s_ != SA_ERR_HIP) snprintf(ctx->err, sizeof(ctx->err), "search: %s", sa_last_error(child));
-      if (s_ == SA_OK && count) {
-        uint64_t hc[2];
-        if ((he = hipMemcpyAsync(hc, counters, 16, hipMemcpyDeviceToHost, stream)) != hipSuccess ||
-            (he = hipStreamSynchronize(stream)) != hipSuccess)
-          s_ = hip_fail(he);
-        else
-          *pairs = (int64_t)hc[1];
-      } else if (s_ == SA_OK) {
-        if ((he = hipStreamSynchronize(stream)) != hipSuccess) s_ = hip_fail(he);
-      }
-      sa_destroy(child);  // the stream is idle: nothing of the child is in flight
-      return s_;
+  for (int h0 = 0; h0 < sh.Hq && he == hipSuccess; h0 += B) {
+    const uint16_t *Qh = (const uint16_t *)Q + (size_t)h0 * sh.q_hs;
+    const uint16_t *Kh = (const uint16_t *)K + (size_t)(h0 / sh.g) * sh.kv_hs;
+    const uint16_t *Vh = (const uint16_t *)V + (size_t)(h0 / sh.g) * sh.kv_hs;
+    const sa_scores sc{scores.v + (size_t)h0 * N, scores.s + (size_t)h0 * N, scores.blk + (size_t)h0 * nb * nb};
+    auto build = [&](int pattern, int which) {  // every head's index of one pattern from budget row `which`
+      sa::Override ov;
+      for (int h = 0; h < sa::kMaxHeads; ++h) ov.pat[h] = (int8_t)pattern;
+      return ok(sa::launch_build_index(cs, ws, sc, ov, ix, stream, budgets + (size_t)which * B));
     };
-
-    // dense reference: the band as wide as the sequence
-    if ((st = evaluate(SA_TRIANGULAR, nb, o_dense, false, nullptr)) != SA_OK) return st;
-
-    sa_search_head &r = out_host[h];
-    for (int p = 0; p < 3; ++p) {
-      int64_t lo = z.x_lo[p], hi = z.x_hi[p], p_lo = 0, p_hi = 0, x = lo, px = 0;
-      // RefineSearchSpace: bisection, the pair count does not decrease with the size
-      if ((st = evaluate(p, lo, o_sparse, true, &p_lo)) != SA_OK) return st;
-      x = lo; px = p_lo;
-      bool done = p_lo >= target_pairs || llabs(p_lo - target_pairs) <= eps_pairs || lo == hi;
-      if (!done) {
-        if ((st = evaluate(p, hi, o_sparse, true, &p_hi)) != SA_OK) return st;
-        if (p_hi <= target_pairs || llabs(p_hi - target_pairs) <= eps_pairs) { x = hi; px = p_hi; done = true; }
-      }
-      while (!done && hi - lo > 1) {
-        const int64_t mid = (lo + hi) / 2;
-        int64_t pm = 0;
-        if ((st = evaluate(p, mid, o_sparse, true, &pm)) != SA_OK) return st;
-        if (llabs(pm - target_pairs) <= eps_pairs) { x = mid; px = pm; done = true; break; }
-        if (pm < target_pairs) { lo = mid; p_lo = pm; } else { hi = mid; p_hi = pm; }
-      }
-      if (!done) {
-        if (target_pairs - p_lo <= p_hi - target_pairs) { x = lo; px = p_lo; } else { x = hi; px = p_hi; }
-      }
-      // Evaluate Patterns: sparse output of the refined candidate against the dense one
-      if ((st = evaluate(p, x, o_sparse, false, nullptr)) != SA_OK) return st;
-      sq_diff_kernel<<<kNormBlocks, 256, 0, stream>>>(o_sparse, o_dense, N, sh.q_rs, partial);
-      if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he);
-      double hp[kNormBlocks];
-      if ((he = hipMemcpyAsync(hp, partial, sizeof(hp), hipMemcpyDeviceToHost, stream)) != hipSuccess ||
-          (he = hipStreamSynchronize(stream)) != hipSuccess)
-        return hip_fail(he);
-      double sum = 0.0;
-      for (int i = 0; i < kNormBlocks; ++i) sum += hp[i];
-      r.param[p] = (int32_t)x;
-      r.pairs[p] = px;
-      r.err[p] = std::sqrt(sum);
+    auto attend = [&](uint16_t *O) {
+      return ok(sa::launch_sparse_prefill(cs, ws, Qh, Kh, Vh, ix, O, nullptr, stream));
+    };
+    ok(hipMemcpyAsync(budgets, head.data(), head.size(), hipMemcpyHostToDevice, stream));
+    // RefineSearchSpace of the Interval-Slash candidate, all heads a step per round (a head that is done
+    // repeats its last index)
+    for (int r = 0; r < rounds && he == hipSuccess; ++r) {
+      if (!build(SA_INTERVAL_SLASH, 2)) break;
+      slash_step_kernel<<<B, 256, 0, stream>>>(ix.cols, ix.offs, cs.k_v, cs.k_s, N, b, state, budgets + 2 * (size_t)B,
+                                               target_pairs, eps_pairs);
+      ok(hipGetLastError());
     }
-    r.pattern = 0;
-    for (int p = 1; p < 3; ++p)
-      if (r.err[p] < r.err[r.pattern]) r.pattern = p;
+    // dense reference: the band as wide as the sequence; then every refined candidate against it
+    if (he == hipSuccess && build(SA_TRIANGULAR, 0)) attend(o_dense);
+    for (int p = 0; p < 3 && he == hipSuccess; ++p) {
+      if (!build(p, 1 + p) || !attend(o_sparse)) break;
+      sq_diff_kernel<<<dim3(nblocks, B), 256, 0, stream>>>(o_sparse, o_dense, N, partial + (size_t)p * B * kNormBlocks);
+      ok(hipGetLastError());
+    }
+    std::vector<Refine> slash(B);
+    ok(hipMemcpyAsync(slash.data(), state, (size_t)B * sizeof(Refine), hipMemcpyDeviceToHost, stream));
+    ok(hipMemcpyAsync(hp.data(), partial, norms * 8, hipMemcpyDeviceToHost, stream));
+    // also after an error: nothing of this call is in flight when it returns
+    const hipError_t last = hipStreamSynchronize(stream);
+    if (!ok(last)) break;
+    for (int i = 0; i < B; ++i) {
+      sa_search_head &r = out_host[h0 + i];
+      const Refine *c[3] = {&tri, &slash[i], &clu};
+      for (int p = 0; p < 3; ++p) {
+        double sum = 0.0;
+        for (int k = 0; k < nblocks; ++k) sum += hp[((size_t)p * B + i) * kNormBlocks + k];
+        r.param[p] = (int32_t)c[p]->x;
+        r.pairs[p] = c[p]->px;
+        r.err[p] = std::sqrt(sum);
+      }
+      r.pattern = 0;
+      for (int p = 1; p < 3; ++p)
+        if (r.err[p] < r.err[r.pattern]) r.pattern = p;
+    }
   }
-  return SA_OK;
+  if (he == hipSuccess) return SA_OK;
+  snprintf(ctx->err, sizeof(ctx->err), "HIP: %s", hipGetErrorString(he));
+  return SA_ERR_HIP;
 }
 
 }  // extern "C"
