@@ -22,11 +22,6 @@
  *     offline search is the exception on the host side: its results go to host
  *     memory, so it waits for the stream (once per batch of heads) and uses host
  *     memory of its own on the way (still no device memory), see there.
- *     sa_estimate_patterns (and sa_estimate_and_index) runs part of its kernels on a side stream that the
- *     context owns (created by sa_create, default priority); that stream waits
- *     for the given stream at entry and the given stream waits for it at exit,
- *     so work enqueued on the given stream before and after the call is
- *     ordered with all of it.
  *   - Errors are return codes.  Argument checks are synchronous;
  *     SA_ERR_HIP wraps a failed launch; sa_last_error gives a text.
  *     Unsupported shapes are rejected, nothing is silently padded.
@@ -155,11 +150,8 @@ sa_status sa_build_index(sa_ctx *ctx, sa_scores in, const int32_t *pattern_overr
 
 /* sa_estimate_patterns followed by sa_build_index as one call: same score
  * buffers, same index, byte for byte (Alg. 2 l.1-7 on the last-query window,
- * Alg. 3 l.1-6, and the categorisation of the heads).  The two are interleaved
- * on the caller's stream and the context's side stream: the selections on v
- * and s run while the block map is still being computed, and the block
- * selection runs beside them.  Towards the caller it behaves like a sequence
- * of kernels on `stream`.  Arguments as in the two calls; errors likewise.
+ * Alg. 3 l.1-6, and the categorisation of the heads).  Arguments as in the two
+ * calls; errors likewise.
  * With cfg.lazy_block_map = 1 the call follows the order of the categorisation
  * instead (the blocked representation of Alg. 3 belongs to the Block-Cluster
  * branch only): window passes, selections on v and s, pattern decision, and

@@ -20,19 +20,18 @@ void carve(sa_ctx *c) {
   const sa::Shape &s = c->sh;
   size_t o = 0;
   const size_t nb16 = (size_t)(s.nb + 15) / 16 * 16;  // block means are stored in tiles of 16 rows
-  c->off[0] = o; o += align256((size_t)s.Hq * nb16 * sa::kHeadDim * 4);
-  c->off[1] = o; o += align256((size_t)s.Hkv * nb16 * sa::kHeadDim * 4);
-  c->off[2] = o; o += align256((size_t)s.Hq * s.nchunks * sa::kWin * 8);
-  c->off[3] = o; o += align256((size_t)s.Hq * sa::kWin * 8);
-  c->off[4] = o; o += align256((size_t)s.Hq * (s.N / 32) * 4);
+  c->off[0] = o; o += align256((size_t)s.Hkv * nb16 * sa::kHeadDim * 4);
+  c->off[1] = o; o += align256((size_t)s.Hq * s.nchunks * sa::kWin * 8);
+  c->off[2] = o; o += align256((size_t)s.Hq * sa::kWin * 8);
+  c->off[3] = o; o += align256((size_t)s.Hq * (s.N / 32) * 4);
   const size_t kvg = (size_t)s.Hq * ((s.k_v + 63) / 64 * 64) * (size_t)s.kv_rs * 2;
+  c->off[4] = o; o += align256(kvg);
   c->off[5] = o; o += align256(kvg);
-  c->off[6] = o; o += align256(kvg);
-  c->off[7] = o; o += 256;
-  c->off[8] = o; o += align256(sa::index_scratch_bytes(s));
-  c->off[9] = o; o += align256((size_t)s.Hq * (s.N / 32) * 4);
-  c->off[10] = o; o += align256(sa::decode_partial_bytes(s));
-  c->off[11] = o; o += align256((size_t)(s.Hq + s.Hkv) * 4);
+  c->off[6] = o; o += 256;
+  c->off[7] = o; o += align256(sa::index_scratch_bytes(s));
+  c->off[8] = o; o += align256((size_t)s.Hq * (s.N / 32) * 4);
+  c->off[9] = o; o += align256(sa::decode_partial_bytes(s));
+  c->off[10] = o; o += align256((size_t)(s.Hq + s.Hkv) * 4);
   c->ws_bytes = o;
 }
 
@@ -77,13 +76,7 @@ sa_status sa_default_budgets(sa_config *cfg, double keep) {
   return SA_OK;
 }
 
-sa_status sa_create(const sa_config *cfg, sa_ctx **out) { return sa::create_context(cfg, out, true); }
-
-}  // extern "C"
-
-// side_stream == false: a context for callers inside the library that never run the estimator (the
-// probes of the offline search): no stream and no events are created.
-sa_status sa::create_context(const sa_config *cfg, sa_ctx **out, bool side_stream) {
+sa_status sa_create(const sa_config *cfg, sa_ctx **out) {
   if (!cfg || !out) return SA_ERR_INVALID_ARG;
   *out = nullptr;
   if (cfg->head_dim != sa::kHeadDim) return SA_ERR_UNSUPPORTED;
@@ -131,16 +124,10 @@ sa_status sa::create_context(const sa_config *cfg, sa_ctx **out, bool side_strea
   }
   if (cap > 0x7FFFFFFFll) { delete c; return SA_ERR_UNSUPPORTED; }
   s.cap_b = (int)cap;
-  // keys per workgroup of the window passes: 1024 measured 3 % faster than 512 at 128K, equal at
-  // 32K-64K; short sequences keep 512 for the sake of parallelism
-  s.chunk = s.N >= 32768 ? 1024 : 512;
-  s.nchunks = (s.N + s.chunk - 1) / s.chunk;
   s.q_rs = cfg->q_row_stride ? cfg->q_row_stride : sa::kHeadDim;
   s.q_hs = cfg->q_head_stride ? cfg->q_head_stride : (int64_t)s.N * s.q_rs;
   s.kv_rs = cfg->kv_row_stride ? cfg->kv_row_stride : sa::kHeadDim;
   s.kv_hs = cfg->kv_head_stride ? cfg->kv_head_stride : (int64_t)s.N * s.kv_rs;
-  s.o_hs = s.q_hs;
-  s.o_rs = s.q_rs;
   if (s.q_rs % 8 || s.kv_rs % 8 || s.q_hs % 8 || s.kv_hs % 8 || s.q_rs < sa::kHeadDim ||
       s.kv_rs < sa::kHeadDim) {
     delete c;
@@ -157,26 +144,14 @@ sa_status sa::create_context(const sa_config *cfg, sa_ctx **out, bool side_strea
     }
     s.n_cu = ncu;
   }
+  // Keys per workgroup of the window passes: as many as make one round of the three workgroups a compute
+  // unit holds of the first pass, in steps of 128 (the larger block; two tiles, and a shorter walk
+  // would be mostly prologue).
+  const int64_t walks = (int64_t)s.Hkv * ((s.g + 3) / 4);
+  s.chunk = (int)(((int64_t)s.N * walks + 3 * s.n_cu * 128 - 1) / (3 * s.n_cu * 128)) * 128;
+  if ((s.N + s.chunk - 1) / s.chunk * walks > 3 * s.n_cu) s.chunk += 128;  // ragged ends
+  s.nchunks = (s.N + s.chunk - 1) / s.chunk;
   s.scale = cfg->softmax_scale > 0.f ? cfg->softmax_scale : 1.0f / std::sqrt((float)sa::kHeadDim);
-  // Side stream of the estimator (default priority).  Without a usable device the creation
-  // fails and the context simply enqueues everything on the caller's stream.
-  c->fork = sa::Fork{nullptr, nullptr, nullptr, nullptr};
-  if (!side_stream) {
-    // everything is enqueued on the caller's stream
-  } else if (hipStreamCreateWithFlags(&c->fork.aux, hipStreamNonBlocking) == hipSuccess) {
-    if (hipEventCreateWithFlags(&c->fork.fork, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&c->fork.mid, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&c->fork.join, hipEventDisableTiming) != hipSuccess) {
-      if (c->fork.fork) (void)hipEventDestroy(c->fork.fork);
-      if (c->fork.mid) (void)hipEventDestroy(c->fork.mid);
-      if (c->fork.join) (void)hipEventDestroy(c->fork.join);
-      (void)hipStreamDestroy(c->fork.aux);
-      c->fork = sa::Fork{nullptr, nullptr, nullptr, nullptr};
-    }
-  } else {
-    c->fork.aux = nullptr;
-  }
-  (void)hipGetLastError();
   c->have_ws = false;
   c->err[0] = 0;
   carve(c);
@@ -184,16 +159,8 @@ sa_status sa::create_context(const sa_config *cfg, sa_ctx **out, bool side_strea
   return SA_OK;
 }
 
-extern "C" {
-
 void sa_destroy(sa_ctx *ctx) {
   if (!ctx) return;
-  if (ctx->fork.aux) {
-    (void)hipEventDestroy(ctx->fork.fork);
-    (void)hipEventDestroy(ctx->fork.mid);
-    (void)hipEventDestroy(ctx->fork.join);
-    (void)hipStreamDestroy(ctx->fork.aux);
-  }
   delete ctx;
 }
 
@@ -228,18 +195,17 @@ sa_status sa_set_workspace(sa_ctx *c, void *dev, size_t bytes) {
   if (!dev || ((uintptr_t)dev & 255)) return fail(c, SA_ERR_INVALID_ARG, "workspace must be a 256-byte aligned device pointer");
   if (bytes < c->ws_bytes) return fail(c, SA_ERR_BUFFER_TOO_SMALL, "workspace smaller than sa_workspace_bytes");
   char *p = (char *)dev;
-  c->ws.qblk = (float *)(p + c->off[0]);
-  c->ws.kblk = (float *)(p + c->off[1]);
-  c->ws.part = (float2 *)(p + c->off[2]);
-  c->ws.stats = (float2 *)(p + c->off[3]);
-  c->ws.colbits = (uint32_t *)(p + c->off[4]);
-  c->ws.kg = (uint16_t *)(p + c->off[5]);
-  c->ws.vg = (uint16_t *)(p + c->off[6]);
-  c->ws.queue = (unsigned int *)(p + c->off[7]);
-  c->ws.idx = (void *)(p + c->off[8]);
-  c->ws.colprefix = (int32_t *)(p + c->off[9]);
-  c->ws.dec_part = (float *)(p + c->off[10]);
-  c->ws.hperm = (int32_t *)(p + c->off[11]);
+  c->ws.kblk = (float *)(p + c->off[0]);
+  c->ws.part = (float2 *)(p + c->off[1]);
+  c->ws.stats = (float2 *)(p + c->off[2]);
+  c->ws.colbits = (uint32_t *)(p + c->off[3]);
+  c->ws.kg = (uint16_t *)(p + c->off[4]);
+  c->ws.vg = (uint16_t *)(p + c->off[5]);
+  c->ws.queue = (unsigned int *)(p + c->off[6]);
+  c->ws.idx = (void *)(p + c->off[7]);
+  c->ws.colprefix = (int32_t *)(p + c->off[8]);
+  c->ws.dec_part = (float *)(p + c->off[9]);
+  c->ws.hperm = (int32_t *)(p + c->off[10]);
   c->have_ws = true;
   return SA_OK;
 }
@@ -255,8 +221,8 @@ sa_status sa_estimate_patterns(sa_ctx *c, const void *Q, const void *K, sa_score
   if (!Q || !K || !out.v || !out.s || !out.blk) return fail(c, SA_ERR_INVALID_ARG, "null pointer");
   if (((uintptr_t)Q | (uintptr_t)K | (uintptr_t)out.blk) & 15) return fail(c, SA_ERR_INVALID_ARG, "Q, K, blk must be 16-byte aligned");
   if (!c->have_ws) return fail(c, SA_ERR_INVALID_ARG, "no workspace attached");
-  return hip_result(c, sa::launch_estimate(c->sh, c->ws, (const uint16_t *)Q, (const uint16_t *)K, out,
-                                           (hipStream_t)stream, c->fork));
+  return hip_result(c, sa::launch_estimate_part(c->sh, c->ws, (const uint16_t *)Q, (const uint16_t *)K, out,
+                                                sa::EstimatePart::All, nullptr, (hipStream_t)stream));
 }
 
 static sa_status check_index_args(sa_ctx *c, sa_scores in, const int32_t *override_host, sa_index out,
@@ -296,38 +262,23 @@ sa_status sa_estimate_and_index(sa_ctx *c, const void *Q, const void *K, sa_scor
   const sa_status s = check_index_args(c, scores, override_host, out, &ov);
   if (s != SA_OK) return s;
   hipStream_t st = (hipStream_t)stream;
-  const sa::Fork &fk = c->fork;
-  if (c->sh.lazy_blk) {
-    // In the order of the categorisation, on one stream: what the Block-Cluster branch needs is
-    // computed once the heads that take it are known.
-    const uint16_t *q = (const uint16_t *)Q, *k = (const uint16_t *)K;
-    using sa::IndexStage;
-    using sa::EstimatePart;
-    hipError_t e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, IndexStage::Zero, st, true);
-    if (e == hipSuccess) e = sa::launch_estimate_part(c->sh, c->ws, q, k, scores, EstimatePart::KChain, nullptr, st);
-    if (e == hipSuccess) e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, IndexStage::ColumnsDiagonals, st, true);
-    if (e == hipSuccess)
-      e = sa::launch_estimate_part(c->sh, c->ws, q, k, scores, EstimatePart::QChain, out.pattern, st);
-    if (e == hipSuccess) e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, IndexStage::Blocks, st, true);
-    if (e == hipSuccess) e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, IndexStage::Emit, st, true);
+  const uint16_t *q = (const uint16_t *)Q, *k = (const uint16_t *)K;
+  using sa::IndexStage;
+  using sa::EstimatePart;
+  hipError_t e;
+  if (!c->sh.lazy_blk) {
+    e = sa::launch_estimate_part(c->sh, c->ws, q, k, scores, EstimatePart::All, nullptr, st);
+    if (e == hipSuccess) e = sa::launch_build_index(c->sh, c->ws, scores, ov, out, st);
     return hip_result(c, e);
   }
-  // Caller's stream: window passes -> selections on v and s; side stream: block means and block
-  // map -> block selection; joined before the pattern decision and the emission.
-  hipError_t e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, sa::IndexStage::Zero, st);
-  if (e == hipSuccess)
-    e = sa::launch_estimate(c->sh, c->ws, (const uint16_t *)Q, (const uint16_t *)K, scores, st, fk, false);
-  if (e == hipSuccess)
-    e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, sa::IndexStage::ColumnsDiagonals, st);
-  if (e == hipSuccess)
-    e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, sa::IndexStage::Blocks, fk.aux ? fk.aux : st);
-  if (fk.aux) {
-    // join even after an error above, so that the side stream never outlives the call unjoined
-    hipError_t j = hipEventRecord(fk.join, fk.aux);
-    if (j == hipSuccess) j = hipStreamWaitEvent(st, fk.join, 0);
-    if (e == hipSuccess) e = j;
-  }
-  if (e == hipSuccess) e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, sa::IndexStage::Emit, st);
+  // In the order of the categorisation: what the Block-Cluster branch needs is computed once the heads
+  // that take it are known.
+  e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, IndexStage::Zero, st);
+  if (e == hipSuccess) e = sa::launch_estimate_part(c->sh, c->ws, q, k, scores, EstimatePart::Windows, nullptr, st);
+  if (e == hipSuccess) e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, IndexStage::ColumnsDiagonals, st);
+  if (e == hipSuccess) e = sa::launch_estimate_part(c->sh, c->ws, q, k, scores, EstimatePart::BlockMap, out.pattern, st);
+  if (e == hipSuccess) e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, IndexStage::Blocks, st);
+  if (e == hipSuccess) e = sa::launch_index_stage(c->sh, c->ws, scores, ov, out, IndexStage::Emit, st);
   return hip_result(c, e);
 }
 

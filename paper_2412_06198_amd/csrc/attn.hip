@@ -40,7 +40,7 @@ struct AttnArgs {
   uint16_t *Kg, *Vg;  // [Hq][kvg_rows][kv_rs] selected key columns, gathered once per call
   int kvg_rows;
   int Hq, Hkv, g, N, b, nb, nT, k_v, k_s, cap_b;
-  int64_t q_hs, q_rs, kv_hs, kv_rs, o_hs, o_rs;
+  int64_t q_hs, q_rs, kv_hs, kv_rs;
   float c;  // softmax scale * log2(e)
   unsigned int *queue;           // [8] work-queue heads, zeroed by index_prepare_kernel
   int n_items;  // (head, row block) items in all
@@ -787,7 +787,7 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
       const int r = 4 * n + rr;
       const uint4 v = *(const uint4 *)(ow + r * 256 + (pc << 4));
       if (r0 + r < N)
-        *(uint4 *)(p.O + (size_t)h * p.o_hs + (size_t)(r0 + r) * p.o_rs + ((pc ^ (r & 15)) << 3)) = v;
+        *(uint4 *)(p.O + (size_t)h * p.q_hs + (size_t)(r0 + r) * p.q_rs + ((pc ^ (r & 15)) << 3)) = v;
     }
   }
   }  // work-queue loop
@@ -812,7 +812,6 @@ hipError_t launch_sparse_prefill(const Shape &sh, const Workspace &ws, const uin
   a.nT = (sh.N + BQ - 1) / BQ;
   a.k_v = sh.k_v; a.k_s = sh.k_s; a.cap_b = sh.cap_b;
   a.q_hs = sh.q_hs; a.q_rs = sh.q_rs; a.kv_hs = sh.kv_hs; a.kv_rs = sh.kv_rs;
-  a.o_hs = sh.o_hs; a.o_rs = sh.o_rs;
   a.c = sh.scale * 1.4426950408889634f;
   a.counters = counters;
   a.hperm = ws.hperm;

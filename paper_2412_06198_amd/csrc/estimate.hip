@@ -1,18 +1,23 @@
-// Pattern estimator for gfx950.
+// Pattern estimator for gfx950: two launches.
 //
 //  * window scores (Alg. 2 "Compute Dense Attention Scores" on the last w query
 //    rows only, then SumRows -> v and SumDiagonals -> s).  The softmax of a
 //    window row needs its maximum and normaliser over ALL keys before any
 //    column can be summed, so K is streamed twice:
 //      pass 1  S^T = K Qwin^T  (lane = query)  -> per-chunk (max, sum) partials,
-//                                                 and the block sums of K on the way
+//                                                 and the block means of K on the way
 //      pass 2  S   = Qwin K^T  (lane = key)    -> normalised weights, column sums in
 //                                                 the lane, diagonal sums by lane shifts
 //    The 4 query heads of a GQA group ride on one K stream: wave w = head w.
-//    K tiles go global -> LDS directly (global_load_lds_dwordx4), double-buffered.
-//  * block map (Alg. 3 "Compute Blocked Representation"): fp32 block means of Q
-//    and K, then one kernel that forms a 16-row strip of block logits with fp32
-//    MFMA, keeps it in registers, and writes its causal row softmax once.
+//    K tiles go global -> LDS directly (global_load_lds_dwordx4).
+//  * block map (Alg. 3 "Compute Blocked Representation"): a workgroup streams the
+//    queries of 16 row blocks of a head, keeps their fp32 means in LDS, forms the
+//    16-row strip of block logits on the matrix pipe, keeps it in registers, and
+//    writes its causal row softmax once.
+// The first launch is pass 1; the second holds the workgroups of pass 2 (bound by exp and vector
+// ALU) spread among those of the block map (bound by the HBM stream of Q), which needs the K means of
+// pass 1.  One stream, no events: with five launches on two streams 4 heads of 4096 tokens took 59 us,
+// now 18; 32 heads at 10K, 16K and 32K tokens 62, 74 and 122, now 54, 63 and 113; at 128K both take 390.
 #include "sa_internal.h"
 
 namespace sa {
@@ -21,6 +26,8 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
 
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -47,50 +54,81 @@ __device__ inline void store_split(float *means_head, int R, int d, float x) {
 }
 
 // ------------------------------------------------------------------ Q block means
-// grid (nb, Hq), 256 threads: thread = (row group of 16, 16-byte column); all RPT = b/16 loads of
-// a thread are in flight before the first sum.  The kernel is pure HBM streaming and runs beside
-// the window passes (vector ALU bound): it is launched with kQMeanLdsPad* bytes of unused dynamic
-// LDS so that it never holds more than a few wave slots of a compute unit.
-constexpr int kQMeanLdsPad128 = 32 * 1024, kQMeanLdsPad64 = 32 * 1024;  // measured best (16-96 KB swept)
+constexpr int kMapWaves = 4;
 
-template <int RPT>
-__global__ __launch_bounds__(256) void q_block_mean_kernel(const uint16_t *__restrict__ Q, Shape sh,
-                                                           float *__restrict__ qblk,
-                                                           const int32_t *__restrict__ only_bc) {
-  __shared__ float red[16][kHeadDim + 4];
-  const int R = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
-  if (only_bc && only_bc[h] != SA_BLOCK_CLUSTER) return;  // this head's block map is not wanted
-  const uint16_t *src = Q + (size_t)h * sh.q_hs + (size_t)R * sh.b * sh.q_rs;
-  const int cc = tid & 15, rg = tid >> 4;
-  uint4 x[RPT];
-#pragma unroll
-  for (int n = 0; n < RPT; ++n) {
-    // read once: a streaming (non-temporal) load leaves the caches to K, which the second window
-    // pass reads again
-    typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-    const u32x4_t v = __builtin_nontemporal_load((const u32x4_t *)(src + (size_t)(rg + 16 * n) * sh.q_rs + cc * 8));
-    x[n] = make_uint4(v.x, v.y, v.z, v.w);
-  }
+// The means of the queries of a strip's row blocks first, first + step, ... (up to rows), split, into the
+// strip's operand tile (LDS, laid out like the K means).  One wave.
+__device__ __forceinline__ void strip_means(const uint16_t *__restrict__ src, const Shape &sh, uint16_t *tile, int first,
+                                            int step, int rows) {
+  const int lane = threadIdx.x & 63, cc = lane & 15, rg = lane >> 4;
+  typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+  const int64_t q_rs = sh.q_rs;
+  const uint16_t *lane_src = src + (size_t)rg * q_rs + cc * 8;
   float acc[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+  // A batch is eight loads of four query rows; a row block has two or four.  The next batch is always
+  // under way while one is summed, across the row blocks too: 8 to 16 KB in flight per wave.  Read once:
+  // streaming (non-temporal) loads leave the caches to K, which the second window pass reads again, and
+  // to the K means.
+  const int per = sh.b >> 5, total = ((rows - first + step - 1) / step) * per;
+  u32x4_t x0[8], x1[8];
+  auto fetch = [&](u32x4_t (&x)[8], int it) {
+    const int blk = first + step * (it / per), bt = it % per;
+    const uint16_t *p = lane_src + ((size_t)blk * sh.b + 32 * bt) * q_rs;
 #pragma unroll
-  for (int n = 0; n < RPT; ++n) {
-    const uint32_t wds[4] = {x[n].x, x[n].y, x[n].z, x[n].w};
+    for (int k = 0; k < 8; ++k) x[k] = __builtin_nontemporal_load((const u32x4_t *)(p + (size_t)(4 * k) * q_rs));
+  };
+  auto add = [&](const u32x4_t (&x)[8]) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      acc[2 * e] += bf16_bits_to_f32(wds[e] & 0xFFFFu);
-      acc[2 * e + 1] += bf16_bits_to_f32(wds[e] >> 16);
+    for (int k = 0; k < 8; ++k) {
+      const uint32_t wds[4] = {x[k].x, x[k].y, x[k].z, x[k].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        acc[2 * e] += bf16_bits_to_f32(wds[e]);
+        acc[2 * e + 1] += __uint_as_float(wds[e] & 0xFFFF0000u);
+      }
     }
+  };
+  if (total > 0) fetch(x0, 0);
+#pragma unroll 1
+  for (int it = 0; it < total; it += 2) {
+    fetch(x1, it + 1);
+    add(x0);
+    if (it + 2 < total) fetch(x0, it + 2);
+    add(x1);
+    if ((it + 2) % per) continue;
+    bf16x8 hi, lo;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      float s = acc[e];
+      s += __shfl_xor(s, 16);
+      s += __shfl_xor(s, 32);
+      s *= 1.0f / (float)sh.b;
+      hi[e] = (__bf16)s;
+      lo[e] = (__bf16)(s - (float)hi[e]);
+      acc[e] = 0.f;
+    }
+    // elements 8 cc .. 8 cc + 7: k-step cc / 4, g = cc % 4
+    uint16_t *dst = tile + (cc >> 2) * 512 + (cc & 3) * 128 + (first + step * (it / per)) * 8;
+    if (rg == 0) *(bf16x8 *)dst = hi;
+    if (rg == 1) *(bf16x8 *)(dst + 2048) = lo;
   }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) red[rg][cc * 8 + e] = acc[e];
-  __syncthreads();
-  if (tid < kHeadDim) {
-    float sum = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sum += red[r][tid];
-    store_split(qblk + (size_t)h * means_tiles(sh.nb) * 2048, R, tid, sum * (1.0f / (float)sh.b));
+}
+
+// The L-th strip to be taken, the longest ones first.  Consecutive workgroup ids land on consecutive XCDs.
+// While Hkv is a multiple of 8, KV head k is served by XCD k % 8 only, so that the L2 of an XCD holds the
+// K means of one KV head at a time instead of all of them.
+__device__ inline void strip_of(int L, const Shape &sh, int &strip, int &h) {
+  const int nstrips = (sh.nb + 15) / 16;
+  if (sh.Hkv % 8 == 0) {
+    const int x = L & 7, s = L >> 3, hx = sh.Hq / 8;  // hx heads per XCD
+    const int hl = s % hx;
+    strip = nstrips - 1 - s / hx;
+    h = (x + 8 * (hl / sh.g)) * sh.g + hl % sh.g;
+  } else {
+    strip = nstrips - 1 - L % nstrips;
+    h = L / nstrips;
   }
 }
 
@@ -155,31 +193,87 @@ struct KTileCopy {
   }
 };
 
-// fragment (rows 32*kh + q, logical chunk 2*ks + gg) of a swizzled tile
-__device__ inline bf16x8 k_frag(const uint16_t *tile, unsigned kbase, int gg, int kh, int ks) {
-  return *(const bf16x8 *)((const char *)tile + ((kbase ^ (unsigned)((2 * ks + gg) << 4)) + kh * 32 * 256));
+// Fragment addresses of a swizzled tile: rows 32 kh + q, logical chunk 2 ks + gg.  One per-lane address
+// per ks, shared by both halves of the tile and, with the tile's buffer added, by all buffers.
+typedef const __attribute__((address_space(3))) bf16x8 lds_frag;
+struct KFrags {
+  unsigned at[8];
+  __device__ inline void init(const uint16_t *ks0, int lane) {
+    const int q = lane & 31, gg = lane >> 5;
+    const unsigned base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) const uint16_t *)ks0 + (unsigned)(q * 256);
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) at[ks] = base + (unsigned)((((2 * ks + gg) ^ (q & 15)) & 15) << 4);
+  }
+};
+
+// Products of one 32-key half of a tile with the two halves of the window (pass 1: K is the A operand).  The
+// fragments go through a ring of four registers: the read of fragment i + 4 follows the products with
+// fragment i.
+__device__ inline void half_tile(const unsigned (&at)[8], int kh, const bf16x8 (&qf)[2][8], f32x16 (&acc)[2]) {
+#pragma unroll
+  for (int qh = 0; qh < 2; ++qh)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[qh][r] = 0.f;
+  bf16x8 kf[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) kf[ks] = *(lds_frag *)(uintptr_t)(at[ks] + kh * 32 * 256);
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) {
+#pragma unroll
+    for (int qh = 0; qh < 2; ++qh)
+      acc[qh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks & 3], qf[qh][ks], acc[qh], 0, 0, 0);
+    if (ks + 4 < 8) kf[ks & 3] = *(lds_frag *)(uintptr_t)(at[ks + 4] + kh * 32 * 256);
+  }
+  __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+  }
+  __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
 }
 
-// pass 1: grid (nchunks, Hkv, ceil(g/4)), 256 threads.
-__global__ __launch_bounds__(256, 2) void window_stats_kernel(const uint16_t *__restrict__ Q,
-                                                           const uint16_t *__restrict__ K, Shape sh,
-                                                           float c, float2 *__restrict__ part,
-                                                           float *__restrict__ s_out,
-                                                           float *__restrict__ kblk) {
-  __shared__ __attribute__((aligned(16))) uint16_t Ks[kStages][64 * 128];
-  __shared__ float ksum[2][4][kHeadDim];
+// Products of 32 window rows with both halves of a tile (pass 2: K is the B operand), likewise.
+__device__ inline void rows_tile(const unsigned (&at)[8], const bf16x8 (&qf)[8], f32x16 (&acc)[2]) {
+#pragma unroll
+  for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[kh][r] = 0.f;
+  bf16x8 kf[4];
+  auto frag = [&](int i) { return *(lds_frag *)(uintptr_t)(at[i >> 1] + (i & 1) * 32 * 256); };
+#pragma unroll
+  for (int i = 0; i < 4; ++i) kf[i] = frag(i);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    acc[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[i >> 1], kf[i & 3], acc[i & 1], 0, 0, 0);
+    if (i + 4 < 16) kf[i & 3] = frag(i + 4);
+  }
+  __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+  for (int i = 0; i < 12; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+  }
+  __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+}
+
+// pass 1, workgroup L of nchunks * Hkv * ceil(g/4), 256 threads.
+__device__ inline void window_stats(int L, uint16_t (*Ks)[64 * 128], const uint16_t *__restrict__ Q,
+                                    const uint16_t *__restrict__ K, const Shape &sh, float c,
+                                    float2 *__restrict__ part, float *__restrict__ s_out,
+                                    float *__restrict__ kblk) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q = lane & 31, gg = lane >> 5;
-  const int chunk = blockIdx.x, kvh = blockIdx.y;
-  const int hsub = 4 * blockIdx.z + wv;
+  const int chunk = L % sh.nchunks, kvh = L / sh.nchunks % sh.Hkv, z0 = L / (sh.nchunks * sh.Hkv);
+  const int hsub = 4 * z0 + wv;
   const bool head_ok = hsub < sh.g;
   const int hq = kvh * sh.g + (head_ok ? hsub : 0);
   const int jc0 = chunk * sh.chunk;
   const int jc1 = min(jc0 + sh.chunk, sh.N);
   const int nt = (jc1 - jc0) >> 6;  // N is a multiple of 64: whole tiles only
   const uint16_t *Kh = K + (size_t)kvh * sh.kv_hs + (size_t)jc0 * sh.kv_rs;
-  const bool do_means = blockIdx.z == 0;
+  const bool do_means = z0 == 0;
 
   KTileCopy cp;
   cp.init(&Ks[0][0], wv, lane, sh.kv_rs);
@@ -195,13 +289,27 @@ __global__ __launch_bounds__(256, 2) void window_stats_kernel(const uint16_t *__
   for (int s2 = 1; s2 < kStages - 1; ++s2)
     if (s2 < nt) cp.issue(Kh + (size_t)s2 * 64 * sh.kv_rs, s2);
   float m[2] = {-INFINITY, -INFINITY}, z[2] = {0.f, 0.f};
-  const unsigned kbase = (unsigned)(q * 256) | (unsigned)((q & 15) << 4);
+  KFrags kfr;
+  kfr.init(&Ks[0][0], lane);
 
-  // block sums of K: thread = (dword column cd of the 256-byte rows, rows 16*wv .. 16*wv+15)
-  const int cd = tid & 63;
+  // Block sums of K on the matrix pipe: ones (16 x 32 keys) times K (32 keys x 16 elements) in
+  // v_mfma_f32_16x16x32_bf16 leaves the sum of the 32 keys in every row; wave w takes elements 32 w ..
+  // 32 w + 31.  Its B operand, lane (n = element, group lane/16) = keys 8 group .. + 7, is K transposed,
+  // which two transposing reads of four keys each deliver.  Their source lane r = lane % 16 supplies
+  // the 8-byte piece (key r/4, elements 4(r%4)..+3); the piece of key row y sits in chunk
+  // (2 blk16 + (r%4)/2) ^ (y & 15).  (Adding the rows on the vector ALU took a fifth of this pass, which
+  // is bound there.)
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
   const int tpb = sh.b >> 6;  // tiles per block: 1 or 2
-  float ks_lo = 0.f, ks_hi = 0.f;
-  int pending = -1;           // block whose four partial sums wait in ksum[pending & 1]
+  f32x4 ksum[2] = {};
+  unsigned tr[2];             // byte offsets of the two reads of element block 2 wv, key step 0
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const int r = lane & 15, y = 8 * (lane >> 4) + 4 * p + (r >> 2);
+    tr[p] = (unsigned)(y * 256 + (((4 * wv + ((r & 3) >> 1)) ^ (y & 15)) << 4) + ((r & 1) << 3));
+  }
+  const __bf16 one = (__bf16)1.f;
+  const bf16x8 ones = {one, one, one, one, one, one, one, one};
 
   for (int t = 0; t < nt; ++t) {
     const int cur = t % kStages;
@@ -213,79 +321,65 @@ __global__ __launch_bounds__(256, 2) void window_stats_kernel(const uint16_t *__
     const int j0 = jc0 + 64 * t;
 
     if (do_means) {
-      if (pending >= 0 && tid < kHeadDim) {
-        const float(*ps)[kHeadDim] = ksum[pending & 1];
-        store_split(kblk + (size_t)kvh * means_tiles(sh.nb) * 2048, pending, tid,
-                    ((ps[0][tid] + ps[1][tid]) + (ps[2][tid] + ps[3][tid])) * (1.0f / (float)sh.b));
-      }
-      pending = -1;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = 16 * wv + r;
-        const uint32_t x = *(const uint32_t *)((const char *)Kt + row * 256 +
-                                               ((((cd >> 2) ^ r) << 4) | ((cd & 3) << 2)));
-        ks_lo += bf16_bits_to_f32(x & 0xFFFFu);
-        ks_hi += bf16_bits_to_f32(x >> 16);
-      }
-      if ((t + 1) % tpb == 0) {
-        const int C = j0 / sh.b;
-        *(float2 *)&ksum[C & 1][wv][2 * cd] = make_float2(ks_lo, ks_hi);
-        ks_lo = 0.f; ks_hi = 0.f;
-        pending = C;
+      for (int eb = 0; eb < 2; ++eb)
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          const char *base = (const char *)Kt + ks * 32 * 256;
+          const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(base + (tr[0] ^ (unsigned)(eb << 5))));
+          const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(base + (tr[1] ^ (unsigned)(eb << 5))));
+          const s16x8 kt = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+          ksum[eb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, __builtin_bit_cast(bf16x8, kt), ksum[eb], 0, 0, 0);
+        }
+      if ((t + 1) % tpb == 0) {  // every lane of a column holds its sum: lanes 0..15 write one block, 16..31 the other
+        if (lane < 32)
+          store_split(kblk + (size_t)kvh * means_tiles(sh.nb) * 2048, j0 / sh.b, 32 * wv + lane,
+                      (lane < 16 ? ksum[0][0] : ksum[1][0]) * (1.0f / (float)sh.b));
+        ksum[0] = ksum[1] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
     }
 
     // One 32-key half of the tile at a time: its scores are reduced to (max, sum) before the next
-    // half is multiplied, so only 32 accumulator registers are live (two waves per SIMD fit).
+    // half is multiplied, so only 32 accumulator registers are live (three waves per SIMD fit).
     // lane = query 32qh+q ; acc[qh][r] <-> key j0 + 32kh + 8(r/4) + 4gg + r%4
     const bool tail = j0 + 63 > sh.N - sh.w;  // causal masking only in the last tile of the sequence
+    unsigned at[8];
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) at[ks] = kfr.at[ks] + cur * (64 * 256);
 #pragma unroll
     for (int kh = 0; kh < 2; ++kh) {
       f32x16 acc[2];  // [query half]
-#pragma unroll
-      for (int qh = 0; qh < 2; ++qh)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[qh][r] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        const bf16x8 a = k_frag(Kt, kbase, gg, kh, ks);
-#pragma unroll
-        for (int qh = 0; qh < 2; ++qh)
-          acc[qh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[qh][ks], acc[qh], 0, 0, 0);
-      }
+      half_tile(at, kh, qf, acc);
 #pragma unroll
       for (int qh = 0; qh < 2; ++qh) {
-        float tmax = -INFINITY;
         if (tail) {
-          const int jmax = sh.N - sh.w + 32 * qh + q;  // last visible key of this window row
+          // last visible key of this window row, relative to the lane's first key of the half
+          const int lim = sh.N - sh.w + 32 * qh + q - (j0 + 32 * kh + 4 * gg);
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int j = j0 + 32 * kh + 8 * (r / 4) + 4 * gg + (r % 4);
-            if (j > jmax) acc[qh][r] = -INFINITY;
-          }
+          for (int r = 0; r < 16; ++r)
+            if (8 * (r / 4) + (r % 4) > lim) acc[qh][r] = -INFINITY;
         }
+        // The reference of a row only has to keep 2^(logit - reference) inside the fp32 range, and the
+        // maximum of the first keys does: the sum is taken without looking for a maximum, and only if
+        // it has left the range (or there is no reference yet) is the half tile reduced again.
+        auto sum_with = [&](float m_ref) {
+          float sum = 0.f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, acc[qh][r]);
-        // the reference moves only when a row's maximum grew by more than 2^8 (terms stay <= 256)
-        const float m_new = fmaxf(m[qh], tmax * c);
-        if (__any(m_new - m[qh] > 8.f)) {
-          z[qh] *= __builtin_amdgcn_exp2f(m[qh] - ((m_new == -INFINITY) ? 0.f : m_new));
+          for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[qh][r], c, -m_ref));
+          return sum;
+        };
+        float sum = sum_with(m[qh]);
+        if (__any(!(sum < 0x1p60f))) {  // also m = -inf (no key seen yet): the sum is then inf or nan
+          float tmax = -INFINITY;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, acc[qh][r]);
+          const float m_new = fmaxf(m[qh], tmax * c);
+          if (m_new != -INFINITY) z[qh] *= __builtin_amdgcn_exp2f(m[qh] - m_new);
           m[qh] = m_new;
+          sum = sum_with(m_new == -INFINITY ? 0.f : m_new);
         }
-        const float m_ref = (m[qh] == -INFINITY) ? 0.f : m[qh];
-        float sum = 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[qh][r], c, -m_ref));
         z[qh] += sum;
       }
-    }
-  }
-  if (do_means) {
-    __syncthreads();
-    if (pending >= 0 && tid < kHeadDim) {
-      const float(*ps)[kHeadDim] = ksum[pending & 1];
-      store_split(kblk + (size_t)kvh * means_tiles(sh.nb) * 2048, pending, tid,
-                  ((ps[0][tid] + ps[1][tid]) + (ps[2][tid] + ps[3][tid])) * (1.0f / (float)sh.b));
     }
   }
 #pragma unroll
@@ -338,17 +432,17 @@ __global__ __launch_bounds__(1024) void window_stats_reduce_kernel(const float2 
   }
 }
 
-// Lane shifts of a whole wavefront (DPP wave_shl:1 / wave_shr:1): lane l takes lane l+1 (l-1);
-// the lane without a source gets 0.
+// Lane shifts of a whole wavefront (DPP wave_shl:1 / wave_shr:1): lane l takes lane l+1, the last one 0.
 __device__ inline float wave_shl1(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x130, 0xF, 0xF, true));
 }
-__device__ inline float wave_shr1(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x138, 0xF, 0xF, true));
+// Lane l takes x of lane l - 1; lane 0 keeps `old`.
+__device__ inline float wave_shr1_into(float old, float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(x), 0x138, 0xF, 0xF, false));
 }
 
-// Weights of one 64-key tile (pass 2).  After the MFMAs lane l holds key 32kh + l%32 and
-// register r of acc[kh][qh] window row 32qh + 8(r/4) + 4(l/32) + r%4.  v_permlane32_swap of
+// Weights of one 64-key tile for 32 window rows (pass 2).  After the MFMAs lane l holds key 32kh + l%32
+// and register r of acc[kh] window row 32qh + 8(r/4) + 4(l/32) + r%4.  v_permlane32_swap of
 // the two key halves turns that into "register = one window row, lane = key 0..63": the row
 // constants are wave-uniform and the column sum stays in the lane.
 //
@@ -359,50 +453,76 @@ __device__ inline float wave_shr1(float x) {
 // there while shifting the other way, so that after the 64 rows of a tile done[l] is the finished
 // sum of offset (N - w - j0) + l.  Sums that straddle a chunk boundary are the only partial ones.
 template <bool TAIL>
-__device__ inline float scores_tile(const f32x16 (&acc)[2][2], const float (&bias)[kWin], float c,
-                                    int lim0, bool lane0, float &run, float &done) {
+__device__ inline float scores_rows(const f32x16 (&acc)[2], int qh, const float (&bias)[kWin], float c,
+                                    int lim0, float &run, float &done) {
   float colsum = 0.f;
+  // `done` trails `run` by one step: by then the previous `run` is dead, and its register can become the
+  // shifted `done` (lane 0, which the shift leaves alone, holds the finished sum) in one instruction
+  bool first = true;
 #pragma unroll
-  for (int qh = 1; qh >= 0; --qh)
+  for (int rq = 3; rq >= 0; --rq) {
+    float x[2][4];
 #pragma unroll
-    for (int rq = 3; rq >= 0; --rq) {
-      float x[2][4];
-#pragma unroll
-      for (int rm = 0; rm < 4; ++rm) {
-        const auto pr = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[0][qh][4 * rq + rm]),
-                                                         __float_as_uint(acc[1][qh][4 * rq + rm]), false, false);
-        x[0][rm] = __uint_as_float(pr[0]);
-        x[1][rm] = __uint_as_float(pr[1]);
-      }
-#pragma unroll
-      for (int u = 1; u >= 0; --u)
-#pragma unroll
-        for (int rm = 3; rm >= 0; --rm) {
-          const int i = 32 * qh + 8 * rq + 4 * u + rm;
-          float e = __builtin_amdgcn_exp2f(__builtin_fmaf(x[u][rm], c, -bias[i]));
-          if (TAIL) e = (lim0 + i >= 0) ? e : 0.f;  // key j0 + lane visible to row i iff j <= N-w+i
-          colsum += e;
-          run = wave_shl1(run) + e;
-          const float up = wave_shr1(done);  // a cross-lane move: never under a lane condition
-          done = lane0 ? run : up;
-        }
+    for (int rm = 0; rm < 4; ++rm) {
+      const auto pr = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[0][4 * rq + rm]),
+                                                       __float_as_uint(acc[1][4 * rq + rm]), false, false);
+      x[0][rm] = __uint_as_float(pr[0]);
+      x[1][rm] = __uint_as_float(pr[1]);
     }
+#pragma unroll
+    for (int u = 1; u >= 0; --u)
+#pragma unroll
+      for (int rm = 3; rm >= 0; --rm) {
+        const int i = 32 * qh + 8 * rq + 4 * u + rm;
+        float e = __builtin_amdgcn_exp2f(__builtin_fmaf(x[u][rm], c, -bias[i]));
+        if (TAIL) e = (lim0 + i >= 0) ? e : 0.f;  // key j0 + lane visible to row i iff j <= N-w+i
+        colsum += e;
+        const float next = wave_shl1(run) + e;
+        if (!first) done = wave_shr1_into(run, done);
+        first = false;
+        run = next;
+      }
+  }
+  done = wave_shr1_into(run, done);
   return colsum;
 }
 
-// pass 2: grid (nchunks, Hkv, ceil(g/4)), 256 threads.  Chunks are walked in the reverse order
-// of pass 1, so that the most recently streamed part of K is re-read first.
-__global__ __launch_bounds__(256) void window_scores_kernel(const uint16_t *__restrict__ Q,
-                                                            const uint16_t *__restrict__ K, Shape sh,
-                                                            float c, const float *__restrict__ bias_g,
-                                                            float *__restrict__ v_out,
-                                                            float *__restrict__ s_out) {
-  __shared__ __attribute__((aligned(16))) uint16_t Ks[kStages][64 * 128];
+// The row constants of a window from the per-chunk partials, one row per lane: max + log2(sum), in the
+// log2 domain, so that a window weight is exp2(logit * scale * log2e - bias).  Rows past the window
+// get +inf (weight 0).
+__device__ inline float window_bias(const float2 *__restrict__ part, int nchunks, int w, int lane) {
+  float M = -INFINITY, Z = 0.f;
+  for (int c0 = 0; c0 < nchunks; c0 += 16) {
+    float2 e[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k)  // past the end: the last chunk again, its sum dropped
+      e[k] = part[(size_t)min(c0 + k, nchunks - 1) * kWin + min(lane, w - 1)];
+    float Mn = M;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) Mn = fmaxf(Mn, e[k].x);
+    const float ref = Mn == -INFINITY ? 0.f : Mn;
+    Z *= __builtin_amdgcn_exp2f(M - ref);
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+      Z = __builtin_fmaf(c0 + k < nchunks ? e[k].y : 0.f, __builtin_amdgcn_exp2f(e[k].x - ref), Z);
+    M = Mn;
+  }
+  return lane < w ? M + __builtin_amdgcn_logf(Z) : INFINITY;  // v_log_f32 = log2
+}
+
+// pass 2, workgroup L of nchunks * Hkv * ceil(g/4), 256 threads.  Chunks are walked in the reverse order
+// of pass 1, so that the most recently streamed part of K is re-read first.  bias_g: the row constants
+// if a launch before has formed them, else nullptr.
+__device__ inline void window_scores(int L, uint16_t (*Ks)[64 * 128], const uint16_t *__restrict__ Q,
+                                     const uint16_t *__restrict__ K, const Shape &sh, float c,
+                                     const float2 *__restrict__ part, const float *__restrict__ bias_g,
+                                     float *__restrict__ v_out, float *__restrict__ s_out) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q = lane & 31, gg = lane >> 5;
-  const int chunk = sh.nchunks - 1 - (int)blockIdx.x, kvh = sh.Hkv - 1 - (int)blockIdx.y;
-  const int hsub = 4 * blockIdx.z + wv;
+  const int chunk = sh.nchunks - 1 - L % sh.nchunks, rest = L / sh.nchunks;
+  const int kvh = sh.Hkv - 1 - rest % sh.Hkv;
+  const int hsub = 4 * (rest / sh.Hkv) + wv;
   const bool head_ok = hsub < sh.g;
   const int hq = kvh * sh.g + (head_ok ? hsub : 0);
   const int jc0 = chunk * sh.chunk;
@@ -416,14 +536,17 @@ __global__ __launch_bounds__(256) void window_scores_kernel(const uint16_t *__re
 
   bf16x8 qf[2][8];
   load_qwin(Q, sh, hq, lane, qf);
+  const float row_bias = bias_g ? bias_g[(size_t)hq * kWin + lane]
+                                : window_bias(part + (size_t)hq * sh.nchunks * kWin, sh.nchunks, sh.w, lane);
   float bias[kWin];  // wave-uniform: lives in scalar registers
 #pragma unroll
   for (int i = 0; i < kWin; ++i)
-    bias[i] = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(bias_g[(size_t)hq * kWin + i])));
+    bias[i] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(row_bias), i));
 #pragma unroll
   for (int s2 = 1; s2 < kStages - 1; ++s2)
     if (s2 < nt) cp.issue(Kh + (size_t)s2 * 64 * sh.kv_rs, s2);
-  const unsigned kbase = (unsigned)(q * 256) | (unsigned)((q & 15) << 4);
+  KFrags kfr;
+  kfr.init(&Ks[0][0], lane);
   float *srow = s_out + (size_t)hq * sh.N;
   float run = 0.f, done = 0.f;
   float cv = c;  // in a vector register: an FMA takes only one scalar operand, and that is the row's bias
@@ -439,26 +562,22 @@ __global__ __launch_bounds__(256) void window_scores_kernel(const uint16_t *__re
     const uint16_t *Kt = Ks[cur];
     const int j0 = jc0 + 64 * t;
 
-    f32x16 acc[2][2];  // [key half][query half]
+    unsigned at[8];
 #pragma unroll
-    for (int kh = 0; kh < 2; ++kh) {
+    for (int ks = 0; ks < 8; ++ks) at[ks] = kfr.at[ks] + cur * (64 * 256);
+    // the upper 32 window rows first (the diagonal sums take the rows in descending order), by themselves:
+    // reading the K fragments twice costs less than the registers of all 64 rows, with which only two
+    // workgroups fit a compute unit
+    float colsum = 0.f;
 #pragma unroll
-      for (int qh = 0; qh < 2; ++qh)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[kh][qh][r] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        const bf16x8 kf = k_frag(Kt, kbase, gg, kh, ks);
-#pragma unroll
-        for (int qh = 0; qh < 2; ++qh)
-          acc[kh][qh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[qh][ks], kf, acc[kh][qh], 0, 0, 0);
-      }
+    for (int qh = 1; qh >= 0; --qh) {
+      f32x16 acc[2];  // [key half]
+      rows_tile(at, qf[qh], acc);
+      if (j0 + 63 > sh.N - sh.w)
+        colsum += scores_rows<true>(acc, qh, bias, cv, sh.N - sh.w - j0 - lane, run, done);
+      else
+        colsum += scores_rows<false>(acc, qh, bias, cv, 0, run, done);
     }
-    float colsum;
-    if (j0 + 63 > sh.N - sh.w)
-      colsum = scores_tile<true>(acc, bias, cv, sh.N - sh.w - j0 - lane, lane == 0, run, done);
-    else
-      colsum = scores_tile<false>(acc, bias, cv, 0, lane == 0, run, done);
     if (head_ok) {
       v_out[(size_t)hq * sh.N + j0 + lane] = colsum;
       // The first tile's sums lack the previous chunk's rows (all but lane 0): they are added to
@@ -481,61 +600,46 @@ __global__ __launch_bounds__(256) void window_scores_kernel(const uint16_t *__re
 
 // ------------------------------------------------------------------ block map
 // blk[h][R][C] = softmax over C <= R of scale * Qblk[R].Kblk[C]; entries C > R are 0.
-// One workgroup = 16 rows of one head.  The means arrive split into bf16 head + remainder (see
-// store_split), and v_mfma_f32_16x16x32_bf16 forms the 16x16 logit tiles from head x head and the
+// One workgroup = a strip of 16 rows of one head.  It first streams the strip's 16 b query rows (a row
+// block per wave at a time, its loads one batch of eight ahead of the sums) and keeps their means in
+// LDS.  The means are split into bf16 head + remainder (see store_split), and
+// v_mfma_f32_16x16x32_bf16 forms the 16x16 logit tiles from head x head and the
 // two cross products: fp32-grade logits (a bf16 product alone would break the 1e-3 tolerance of
 // blk) at a fifth of the cycles of the fp32 matrix instruction.  Lane l of a tile: column l%16,
-// rows 4(l/16) + r.  The column tiles of the strip go round-robin to the eight waves and stay in
+// rows 4(l/16) + r.  The column tiles of the strip go round-robin to the four waves and stay in
 // registers (MT tiles per wave) until the row maxima and sums are known, so blk is written exactly
-// once.  Eight waves (and few registers each) rather than four: the operand reads come from
-// another XCD's writes, and only occupancy hides them.
-// grid ceil(nb/16) * Hq, 512 threads; strips are taken longest first.
-constexpr int kMapWaves = 8;
-
+// once.  Strips are taken longest first.  Bound by the HBM stream of Q, which runs at 5 TB/s with the
+// workgroups of pass 2 beside it (278 us at 128K tokens and 32 heads).
 template <int MT>
-__global__ __launch_bounds__(64 * kMapWaves, (MT <= 8 ? 4 : 2)) void block_map_kernel(const float *__restrict__ qblk,
-                                                                   const float *__restrict__ kblk,
-                                                                   Shape sh, float c2,
-                                                                   float *__restrict__ blk,
-                                                                   const int32_t *__restrict__ only_bc) {
-  __shared__ float red[2][kMapWaves][16];
+__device__ inline void block_map_strip(int L, char *lds, const uint16_t *__restrict__ Q,
+                                       const float *__restrict__ kblk, const Shape &sh, float c2,
+                                       float *__restrict__ blk, const int32_t *__restrict__ only_bc) {
+  uint16_t *tile = (uint16_t *)lds;                            // 8 KB
+  float (*red)[kMapWaves][16] = (float (*)[kMapWaves][16])(lds + 8192);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, g = lane >> 4;
   const int nb = sh.nb;
-  // Consecutive workgroup ids land on consecutive XCDs.  While Hkv is a multiple of 8, KV head k
-  // is served by XCD k % 8 only, so that the L2 of an XCD holds the block means of one KV head at
-  // a time instead of all of them.
-  const int nstrips = (nb + 15) / 16;
-  const int L = blockIdx.x;
+  if (L >= (nb + 15) / 16 * sh.Hq) return;
   int strip, h;
-  if (sh.Hkv % 8 == 0) {
-    const int x = L & 7, s = L >> 3, hx = sh.Hq / 8;  // hx heads per XCD
-    const int hl = s % hx;
-    strip = nstrips - 1 - s / hx;
-    h = (x + 8 * (hl / sh.g)) * sh.g + hl % sh.g;
-  } else {
-    strip = nstrips - 1 - L % nstrips;
-    h = L / nstrips;
-  }
+  strip_of(L, sh, strip, h);
   if (only_bc && only_bc[h] != SA_BLOCK_CLUSTER) return;  // uniform over the workgroup, before any barrier
   const int R0 = 16 * strip;
   const int T = strip + 1;  // column tiles 0..strip hold every C <= R of this strip
+  // rows past nb are never formed; nothing that is kept depends on them
+  strip_means(Q + (size_t)h * sh.q_hs + (size_t)R0 * sh.b * sh.q_rs, sh, tile, wv, kMapWaves, min(16, nb - R0));
+  __syncthreads();
   // tile t of a means array: 8 KB = [part][st][lane][16 bytes]
-  const uint16_t *qsrc = (const uint16_t *)(qblk + (size_t)h * means_tiles(nb) * 2048) + 8 * lane;
   const uint16_t *ksrc = (const uint16_t *)(kblk + (size_t)(h / sh.g) * means_tiles(nb) * 2048) + 8 * lane;
 
   // operands of v_mfma_f32_16x16x32_bf16: lane (n = row of A / column of B, g) holds elements
   // 32 st + 8 g .. + 7 of its mean, st = 0..3: 16 bytes of heads and 16 bytes of remainders per step,
   // which is the order the means are stored in
   bf16x8 ah[4], al[4];
-  {
-    const uint16_t *ap = qsrc + (size_t)strip * 4096;
 #pragma unroll
-    for (int st = 0; st < 4; ++st) {
-      ah[st] = *(const bf16x8 *)(ap + 512 * st);
-      al[st] = *(const bf16x8 *)(ap + 2048 + 512 * st);
-    }
+  for (int st = 0; st < 4; ++st) {
+    ah[st] = *(const bf16x8 *)(tile + 512 * st + 8 * lane);
+    al[st] = *(const bf16x8 *)(tile + 2048 + 512 * st + 8 * lane);
   }
   f32x4 acc[MT];
   bf16x8 bh[4], bl[4];
@@ -647,91 +751,75 @@ __global__ __launch_bounds__(64 * kMapWaves, (MT <= 8 ? 4 : 2)) void block_map_k
   }
 }
 
-}  // namespace
-
-namespace {
-
-void launch_q_block_mean(const Shape &sh, const Workspace &ws, const uint16_t *Q, const int32_t *only_bc,
-                         hipStream_t sq) {
-  if (sh.b == 128)
-    q_block_mean_kernel<8><<<dim3(sh.nb, sh.Hq), 256, kQMeanLdsPad128, sq>>>(Q, sh, ws.qblk, only_bc);
-  else
-    q_block_mean_kernel<4><<<dim3(sh.nb, sh.Hq), 256, kQMeanLdsPad64, sq>>>(Q, sh, ws.qblk, only_bc);
+// ------------------------------------------------------------------ the two launches
+// The second launch in units of eight consecutive workgroups (one per XCD): window_units of them belong
+// to pass 2, spread evenly over the first `spread` units, the others to the block map.  True for a unit
+// of pass 2; k: its number among the units of its kind.
+__device__ inline bool window_unit(int u, int window_units, int spread, int &k) {
+  const int v = min(u, spread);
+  const int before = (int)((long long)v * window_units / spread);
+  const bool window = v < spread && (int)((long long)(v + 1) * window_units / spread) != before;
+  k = window ? before : u - before;
+  return window;
 }
 
-void launch_block_map(const Shape &sh, const Workspace &ws, float c, float *blk, const int32_t *only_bc,
-                      hipStream_t sq) {
-  const dim3 bgrid((sh.nb + 15) / 16 * sh.Hq);
-  const int tiles_per_wave = ((sh.nb + 15) / 16 + kMapWaves - 1) / kMapWaves;
-  if (tiles_per_wave <= 8)
-    block_map_kernel<8><<<bgrid, 64 * kMapWaves, 0, sq>>>(ws.qblk, ws.kblk, sh, c, blk, only_bc);
-  else if (tiles_per_wave <= 16)
-    block_map_kernel<16><<<bgrid, 64 * kMapWaves, 0, sq>>>(ws.qblk, ws.kblk, sh, c, blk, only_bc);
-  else
-    block_map_kernel<32><<<bgrid, 64 * kMapWaves, 0, sq>>>(ws.qblk, ws.kblk, sh, c, blk, only_bc);
+constexpr int kWindowLds = kStages * 64 * 128 * 2;
+
+// First: pass 1.
+__global__ __launch_bounds__(256, 3) void estimate_first_kernel(
+    const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, Shape sh, float c, float2 *__restrict__ part,
+    float *__restrict__ kblk, float *__restrict__ s_out) {
+  __shared__ __attribute__((aligned(16))) char lds[kWindowLds];
+  window_stats((int)blockIdx.x, (uint16_t (*)[64 * 128])lds, Q, K, sh, c, part, s_out, kblk);
 }
+
+// Second: pass 2, and the block map.
+template <int MT>
+__global__ __launch_bounds__(256, (MT <= 16 ? 3 : MT <= 32 ? 2 : 1)) void estimate_second_kernel(
+    const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, Shape sh, float c, const float2 *__restrict__ part,
+    const float *__restrict__ bias, const float *__restrict__ kblk, sa_scores out, int window_units, int spread,
+    const int32_t *__restrict__ only_bc) {
+  __shared__ __attribute__((aligned(16))) char lds[kWindowLds];
+  int k;
+  const bool window = window_unit((int)blockIdx.x >> 3, window_units, spread, k);
+  const int L = 8 * k + ((int)blockIdx.x & 7);
+  if (!window)
+    block_map_strip<MT>(L, lds, Q, kblk, sh, c, out.blk, only_bc);
+  else if (L < sh.nchunks * sh.Hkv * ((sh.g + 3) / 4))
+    window_scores(L, (uint16_t (*)[64 * 128])lds, Q, K, sh, c, part, bias, out.v, out.s);
+}
+
+// Chunks up to which every pass-2 workgroup forms its rows' constants itself; beyond, a launch does.
+constexpr int kBiasChunks = 128;
 
 }  // namespace
 
 hipError_t launch_estimate_part(const Shape &sh, const Workspace &ws, const uint16_t *Q, const uint16_t *K,
-                                sa_scores out, EstimatePart part, const int32_t *only_block_cluster,
+                                sa_scores out, EstimatePart what, const int32_t *only_block_cluster,
                                 hipStream_t st) {
   const float c = sh.scale * kLog2e;
-  float *bias = (float *)ws.stats;
-  if (part != EstimatePart::QChain) {
-    const dim3 wgrid(sh.nchunks, sh.Hkv, (sh.g + 3) / 4);
-    window_stats_kernel<<<wgrid, 256, 0, st>>>(Q, K, sh, c, ws.part, out.s, ws.kblk);
-    window_stats_reduce_kernel<<<dim3(sh.Hq, kWin / 16), 1024, 0, st>>>(ws.part, sh.nchunks, sh.w, bias);
-    window_scores_kernel<<<wgrid, 256, 0, st>>>(Q, K, sh, c, bias, out.v, out.s);
+  const int nstrips = (sh.nb + 15) / 16, windows = sh.nchunks * sh.Hkv * ((sh.g + 3) / 4);
+  float *bias = sh.nchunks > kBiasChunks ? (float *)ws.stats : nullptr;
+  if (what != EstimatePart::BlockMap) {
+    estimate_first_kernel<<<windows, 256, 0, st>>>(Q, K, sh, c, ws.part, ws.kblk, out.s);
+    if (bias) window_stats_reduce_kernel<<<dim3(sh.Hq, kWin / 16), 1024, 0, st>>>(ws.part, sh.nchunks, sh.w, bias);
   }
-  if (part != EstimatePart::KChain) {
-    launch_q_block_mean(sh, ws, Q, only_block_cluster, st);
-    launch_block_map(sh, ws, c, out.blk, only_block_cluster, st);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_estimate(const Shape &sh, const Workspace &ws, const uint16_t *Q,
-                           const uint16_t *K, sa_scores out, hipStream_t st, const Fork &fk,
-                           bool join_back) {
-  const float c = sh.scale * kLog2e;
-  float *bias = (float *)ws.stats;
-  // Two chains with complementary limits run side by side: the Q chain (block means of Q: HBM
-  // bandwidth; block map: latency of many small L2 reads) on the context's side stream, the K
-  // chain (both window passes: exp and vector ALU work on a quarter of the bytes) on the caller's
-  // stream.  The side stream forks from the caller's stream at entry and joins it at exit, so
-  // towards the caller the call behaves like a sequence of kernels on the given stream
-  // (join_back == false: the caller of this function goes on using both streams and joins them
-  // itself).
-  hipStream_t sq = st;
-  hipError_t e = hipSuccess;
-  bool forked = false;
-  if (fk.aux) {
-    if ((e = hipEventRecord(fk.fork, st)) != hipSuccess) return e;
-    if ((e = hipStreamWaitEvent(fk.aux, fk.fork, 0)) != hipSuccess) return e;
-    sq = fk.aux;
-    forked = true;
-  }
-  // From here on the side stream depends on the caller's stream: whatever fails below, it is joined
-  // back before the call returns, so that no later call (or an active capture) sees it dangling.
-  launch_q_block_mean(sh, ws, Q, nullptr, sq);
-  const dim3 wgrid(sh.nchunks, sh.Hkv, (sh.g + 3) / 4);
-  window_stats_kernel<<<wgrid, 256, 0, st>>>(Q, K, sh, c, ws.part, out.s, ws.kblk);
-  if (forked) {  // the block map needs the K block means of the stats pass
-    e = hipEventRecord(fk.mid, st);
-    if (e == hipSuccess) e = hipStreamWaitEvent(fk.aux, fk.mid, 0);
-  }
-  if (e == hipSuccess) {
-    launch_block_map(sh, ws, c, out.blk, nullptr, sq);
-    window_stats_reduce_kernel<<<dim3(sh.Hq, kWin / 16), 1024, 0, st>>>(ws.part, sh.nchunks, sh.w, bias);
-    window_scores_kernel<<<wgrid, 256, 0, st>>>(Q, K, sh, c, bias, out.v, out.s);
-  }
-  if (forked && (join_back || e != hipSuccess)) {
-    hipError_t j = hipEventRecord(fk.join, fk.aux);
-    if (j == hipSuccess) j = hipStreamWaitEvent(st, fk.join, 0);
-    if (e == hipSuccess) e = j;
-  }
-  if (e != hipSuccess) return e;
+  const int wu = what == EstimatePart::BlockMap ? 0 : (windows + 7) / 8;
+  const int units = wu + (what == EstimatePart::Windows ? 0 : (nstrips * sh.Hq + 7) / 8);
+  // 4/5: 386 us for the estimator at 128K tokens; all units 409 (pass 2 is left for the end), the first ones 408
+  // (it does not run beside the stream any more); 16K and 32K alike
+  int spread = units * 4 / 5;
+  if (spread < wu) spread = wu;
+  if (spread < 1) spread = 1;
+  const int tiles_per_wave = (nstrips + kMapWaves - 1) / kMapWaves;
+#define SA_SECOND(MT)                                                                                         \
+  estimate_second_kernel<MT><<<8 * units, 256, 0, st>>>(Q, K, sh, c, ws.part, bias, ws.kblk, out, wu, spread, \
+                                                        only_block_cluster)
+  if (tiles_per_wave <= 8) SA_SECOND(8);
+  else if (tiles_per_wave <= 16) SA_SECOND(16);
+  else if (tiles_per_wave <= 32) SA_SECOND(32);
+  else SA_SECOND(64);
+#undef SA_SECOND
   return hipGetLastError();
 }
 

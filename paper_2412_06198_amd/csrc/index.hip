@@ -1331,14 +1331,13 @@ hipError_t launch_build_index(const Shape &sh, const Workspace &ws, sa_scores in
   return hipGetLastError();
 }
 
-// The same work in parts, so that it can run beside the estimator: the selections on v and s as
-// soon as the window passes are done (they also write the patterns, for a caller that computes the
-// block map only where it is needed), the block-map selection as soon as the block map is (on
-// another stream), and the emission once both are.
+// The same work in parts, for a caller that computes the block map only where it is needed: the
+// selections on v and s, which write the patterns, then the selection on the block map and the
+// emission.
 hipError_t launch_index_stage(const Shape &sh, const Workspace &ws, sa_scores in, const Override &ov,
-                              sa_index out, IndexStage stage, hipStream_t st, bool lazy) {
-  IdxArgs a = index_args(sh, ws, in, ov, out, nullptr, lazy);
-  if (lazy) a.decided = out.pattern;
+                              sa_index out, IndexStage stage, hipStream_t st) {
+  IdxArgs a = index_args(sh, ws, in, ov, out, nullptr, true);
+  a.decided = out.pattern;
   switch (stage) {
     case IndexStage::Zero: launch_zero(a, st); break;
     case IndexStage::ColumnsDiagonals: launch_levels(a, true, false, st); break;

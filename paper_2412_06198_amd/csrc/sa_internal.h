@@ -29,14 +29,13 @@ struct Shape {
   int chunk, nchunks;             // keys per estimator workgroup (window passes), ceil(N / chunk)
   int n_cu;                       // compute units of the device the context was created on
   int64_t q_hs, q_rs, kv_hs, kv_rs;
-  int64_t o_hs, o_rs;             // output of the attention: as Q's, except inside the search
   float scale;
 };
 
 struct Workspace {
-  float *qblk, *kblk;             // [Hq][ceil(nb/16)] and [Hkv][ceil(nb/16)] tiles (8 KB) of block means
+  float *kblk;                    // [Hkv][ceil(nb/16)] tiles (8 KB) of K block means
   float2 *part;                   // [Hq][nchunks][64] partial (max, sum) of the window rows
-  float2 *stats;                  // [Hq][64] (max * scale*log2e, 1/sum)
+  float2 *stats;                  // [Hq][64] row constants, where a launch of their own forms them
   uint32_t *colbits;              // [Hq][N/32] membership bitmap of the selected columns
   int32_t *colprefix;             // [Hq][N/32] number of selected columns before each word of colbits
   float *dec_part;                // [Hq][splits][132] partial (max, sum, output) of the decode step
@@ -48,16 +47,11 @@ struct Workspace {
 
 size_t index_scratch_bytes(const Shape &sh);
 
-// Side stream of a context with the events that fork it from and join it back into the caller's
-// stream inside one call (the estimator runs its Q chain beside its K chain).  aux == nullptr:
-// everything is enqueued on the caller's stream.
-struct Fork { hipStream_t aux; hipEvent_t fork, mid, join; };
-
-// Parts of the index builder when it runs interleaved with the estimator.
+// Parts of the index builder when they run between the parts of the estimator.
 enum class IndexStage { Zero, ColumnsDiagonals, Blocks, Emit };
 
-// Which of the estimator's two chains a call enqueues.
-enum class EstimatePart { Both, KChain, QChain };
+// Which of the estimator's outputs a call computes: v and s (the window passes), blk, or all.
+enum class EstimatePart { All, Windows, BlockMap };
 
 }  // namespace sa
 
@@ -66,7 +60,6 @@ struct sa_ctx {
   sa_config cfg;
   sa::Shape sh;
   sa::Workspace ws;
-  sa::Fork fork;
   bool have_ws;
   size_t ws_bytes;
   size_t off[12];
@@ -77,26 +70,19 @@ namespace sa {
 
 // key blocks of a Triangular index
 long long triangular_count(int nb, int sink, int local);
-// sa_create, optionally without the estimator's side stream and its events
-sa_status create_context(const sa_config *cfg, sa_ctx **out, bool side_stream);
-
-hipError_t launch_estimate(const Shape &sh, const Workspace &ws, const uint16_t *Q,
-                           const uint16_t *K, sa_scores out, hipStream_t st, const Fork &fk,
-                           bool join_back = true);
-// One chain alone on st.  QChain needs the K block means that KChain leaves in the workspace;
+// All: windows and block map.  BlockMap needs the K block means that Windows leaves in the workspace;
 // only_block_cluster (device, [Hq] patterns, or nullptr = every head) restricts it to the heads
 // whose entry is SA_BLOCK_CLUSTER.
 hipError_t launch_estimate_part(const Shape &sh, const Workspace &ws, const uint16_t *Q, const uint16_t *K,
                                 sa_scores out, EstimatePart part, const int32_t *only_block_cluster,
                                 hipStream_t st);
-// budgets: device array of one entry per head, none above the shape's own, or nullptr = the shape's
 hipError_t launch_build_index(const Shape &sh, const Workspace &ws, sa_scores in,
                               const Override &ov, sa_index out, hipStream_t st,
                               const HeadBudget *budgets = nullptr);
-// lazy: the block-map part of the work is done only for the heads whose out.pattern (written by
-// the ColumnsDiagonals stage) is SA_BLOCK_CLUSTER.
+// The block-map part of the work is done only for the heads whose out.pattern (written by the
+// ColumnsDiagonals stage) is SA_BLOCK_CLUSTER.
 hipError_t launch_index_stage(const Shape &sh, const Workspace &ws, sa_scores in, const Override &ov,
-                              sa_index out, IndexStage stage, hipStream_t st, bool lazy = false);
+                              sa_index out, IndexStage stage, hipStream_t st);
 size_t decode_partial_bytes(const Shape &sh);
 // partials: decode_partial_bytes(sh) bytes of device memory (the context's workspace, or the static array)
 hipError_t launch_sparse_decode(const Shape &sh, float *partials, const uint16_t *q, const uint16_t *K,

@@ -26,19 +26,19 @@ constexpr size_t kBatchBytes = (size_t)2 << 30;  // scratch that a batch of head
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// partial[head][blockIdx.x] = sum over the block's rows of (A - B)^2, A and B [heads][N][128] bf16; fp64
-// accumulation, fixed order: bit-reproducible.  grid (blocks, heads)
+// partial[head][blockIdx.x] = sum over the block's rows of (A - B)^2, A and B [heads][N][128] bf16 with
+// Q's strides (elements); fp64 accumulation, fixed order: bit-reproducible.  grid (blocks, heads)
 __global__ __launch_bounds__(256) void sq_diff_kernel(const uint16_t *__restrict__ A,
-                                                      const uint16_t *__restrict__ B, int N,
-                                                      double *__restrict__ partial) {
+                                                      const uint16_t *__restrict__ B, int N, int64_t hs,
+                                                      int64_t rs, double *__restrict__ partial) {
   __shared__ double red[256];
   const int cc = threadIdx.x & 15, rg = threadIdx.x >> 4;
-  const size_t head = (size_t)blockIdx.y * N * sa::kHeadDim;
+  const size_t head = (size_t)blockIdx.y * hs;
   double acc = 0.0;
   // the rows of a block: kNormBlocks blocks' worth apart, whatever the grid (the sums of the blocks that
   // a short sequence leaves without rows are zero)
   for (int64_t i = (int64_t)blockIdx.x * 16 + rg; i < N; i += (int64_t)kNormBlocks * 16) {
-    const size_t o = head + (size_t)i * sa::kHeadDim + cc * 8;
+    const size_t o = head + (size_t)i * rs + cc * 8;
     const uint4 a = *(const uint4 *)(A + o), b = *(const uint4 *)(B + o);
     const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
@@ -191,14 +191,15 @@ sa_status plan_batch(const sa_ctx *ctx, int heads, Plan *z) {
   if (!c.q_head_stride) c.q_head_stride = ctx->sh.q_hs;
   if (!c.kv_head_stride) c.kv_head_stride = ctx->sh.kv_hs;
   sa_ctx *child = nullptr;
-  sa_status st = sa::create_context(&c, &child, false);  // host memory only: no stream, no events
+  sa_status st = sa_create(&c, &child);
   if (st != SA_OK) return st;
   size_t ws = 0, ix[7];
   st = sa_workspace_bytes(child, &ws);
   if (st == SA_OK) st = sa_index_bytes(child, ix);
   sa_destroy(child);
   if (st != SA_OK) return st;
-  const size_t o_bytes = (size_t)heads * N * sa::kHeadDim * 2;
+  // outputs have Q's strides
+  const size_t o_bytes = ((size_t)(heads - 1) * ctx->sh.q_hs + (size_t)(N - 1) * ctx->sh.q_rs + sa::kHeadDim) * 2;
   const size_t parts[12] = {ws, o_bytes, o_bytes, (size_t)heads * 4 * sizeof(sa::HeadBudget) + (size_t)heads * sizeof(Refine),
                             (size_t)heads * 3 * kNormBlocks * 8, ix[0], ix[1], ix[2], ix[3], ix[4], ix[5], ix[6]};
   size_t o = 0;
@@ -268,14 +269,12 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
   for (int i = 0; i < 7; ++i) *part[i] = (int32_t *)(base + z.off[5 + i]);
 
   sa_ctx *child = nullptr;
-  if ((st = sa::create_context(&z.cfg, &child, false)) != SA_OK) return failp(ctx, st, "search: batch rejected by sa_create");
+  if ((st = sa_create(&z.cfg, &child)) != SA_OK) return failp(ctx, st, "search: batch rejected by sa_create");
   st = sa_set_workspace(child, base + z.off[0], child->ws_bytes);
-  sa::Shape cs = child->sh;
+  const sa::Shape cs = child->sh;
   const sa::Workspace ws = child->ws;
   sa_destroy(child);
   if (st != SA_OK) return failp(ctx, st, "search: workspace");
-  cs.o_hs = (int64_t)N * sa::kHeadDim;  // outputs are compared here: contiguous whatever Q's layout
-  cs.o_rs = sa::kHeadDim;
 
   // pairs of an index made of whole blocks, the nb diagonal ones among them
   auto block_pairs = [&](int64_t blocks) { return (blocks - nb) * b * b + (int64_t)nb * b * (b + 1) / 2; };
@@ -334,7 +333,7 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
     if (he == hipSuccess && build(SA_TRIANGULAR, 0)) attend(o_dense);
     for (int p = 0; p < 3 && he == hipSuccess; ++p) {
       if (!build(p, 1 + p) || !attend(o_sparse)) break;
-      sq_diff_kernel<<<dim3(nblocks, B), 256, 0, stream>>>(o_sparse, o_dense, N, partial + (size_t)p * B * kNormBlocks);
+      sq_diff_kernel<<<dim3(nblocks, B), 256, 0, stream>>>(o_sparse, o_dense, N, sh.q_hs, sh.q_rs, partial + (size_t)p * B * kNormBlocks);
       ok(hipGetLastError());
     }
     std::vector<Refine> slash(B);
