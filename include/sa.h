@@ -202,7 +202,7 @@ sa_status sa_sparse_decode(sa_ctx *ctx, const void *q, const void *K, const void
  * sa_create accepts today fits; a larger one gets SA_ERR_UNSUPPORTED).  All calls on one GPU - from
  * any context or thread - share that array: calls that overlap in time on one GPU race, so keep
  * them on one stream or order them with events.  Nothing in the array needs clearing between calls
- * (every slot a call reads it has written first). */
+ * (what a call reads it has written first, and the arrival counters repair themselves). */
 sa_status sa_sparse_decode_static(sa_ctx *ctx, const void *q, const void *K, const void *V, sa_index idx,
                                   int64_t pos, void *o, void *hip_stream);
 
