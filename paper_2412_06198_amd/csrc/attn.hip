@@ -33,7 +33,7 @@ constexpr int BK = 64;            // keys per tile
 // head: what an XCD has in progress together (64 workgroups), so that the diagonals of its row blocks
 // read one stretch of keys per offset, not every second row block's of one twice as long (128K tokens,
 // 32 heads: 4.07 -> 3.98 ms).
-constexpr int kRun = 64;
+constexpr int kRunBits = 6, kRun = 1 << kRunBits;
 constexpr int NWORDS = kMaxSeq / BK / 32;
 
 struct AttnArgs {
@@ -49,15 +49,20 @@ struct AttnArgs {
   float c;  // softmax scale * log2(e)
   unsigned int *queue;           // [8] work-queue heads, zeroed by index_prepare_kernel
   int n_items;  // (head, row block) items in all
-  int xs;       // queues (XCDs) that share one KV head at a time: 1, 2, 4 or 8
-  int run;      // consecutive row blocks a queue takes in a row: kRun or 1
-  int per_q;    // tickets per queue and KV head, holes included
+  int share;    // log2 of the queues (XCDs) that share one KV head at a time (1, 2, 4 or 8), and from bit 4 on
+                // log2 of the consecutive row blocks a queue takes in a row (kRun or 1)
   int qcap;     // tickets per queue, holes of the id space included
   unsigned long long *counters;  // instrumentation only: {32x32 sub-tiles multiplied, kept (query,key) pairs}
   // Per KV head, written by index_prepare_kernel: [0] = number c of its query heads without
   // selected diagonals, [1..g] = the query heads of the group (0..g-1), those c first.
   int32_t *hperm;
 };
+
+// Tickets per queue and query head, holes included: whole runs of every queue that shares the KV head.
+__host__ __device__ inline int tickets_per_head(int nT, int share) {
+  const int bits = (share & 15) + (share >> 4);
+  return ((nT + (1 << bits) - 1) >> bits) << (share >> 4);
+}
 
 // Read-only words at a wave-uniform address: through the constant address space these become
 // scalar loads, which neither occupy the vector memory path nor count in vmcnt.
@@ -162,12 +167,12 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);  // wave-uniform for the compiler too
 
   // Persistent workgroups pull (head, row block) items from eight queues, one per XCD
-  // (consecutive workgroup ids land on consecutive XCDs).  xs queues share one KV head at a time
-  // and 8/xs KV heads are in progress together: with xs = 1 a KV head lives in a single L2, with
-  // larger xs fewer KV heads are live at once, so that the rows the diagonal phase fetches (no
-  // reuse inside an L2) come out of the memory-side cache instead of HBM.  Ticket k of queue qn:
-  // phase k / per_q selects the KV head, the rest walks the row blocks from the last (longest) one
-  // down, in runs of which the xs queues take one each in turn, back and forth: first for the query heads of the group that have no
+  // (consecutive workgroup ids land on consecutive XCDs).  1, 2, 4 or 8 queues share one KV head at a
+  // time: alone, a queue keeps its KV head in a single L2; with more of them fewer KV heads are live at
+  // once, so that the rows the diagonal phase fetches (no reuse inside an L2) come out of the
+  // memory-side cache instead of HBM.  Ticket k of queue qn: k / per_q selects the KV head, the rest
+  // walks the row blocks from the last (longest) one down, in runs of which the queues that share take
+  // one each in turn, back and forth: first for the query heads of the group that have no
   // selected diagonals, side by side per row block, then for each head with diagonals by itself
   // (the order index_prepare_kernel left in hperm).  A
   // workgroup whose own queue is empty takes from the others, then exits.  The ticket for the
@@ -208,8 +213,9 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
   int kvh, h, t128;
   {
     const int qn = id & 7, k = id >> 3;
-    const int nslots = 8 / p.xs, slot = qn / p.xs, sub = qn % p.xs;
-    const int per_q = p.per_q;
+    const int xb = p.share & 15, rb = p.share >> 4;
+    const int nslots = 8 >> xb, slot = qn >> xb, sub = qn & ((1 << xb) - 1);
+    const int per_q = tickets_per_head(p.nT, p.share) * p.g;
     const int r = k % per_q;
     kvh = k / per_q * nslots + slot;
     if (kvh >= p.Hkv) continue;  // a hole of the id space
@@ -226,8 +232,8 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
       const int r2 = r - c * rows_q;
       slot_h = c + r2 / rows_q; trow = r2 % rows_q;
     }
-    const int rn = trow / p.run;
-    const int tidx = (rn * p.xs + ((rn & 1) ? p.xs - 1 - sub : sub)) * p.run + trow % p.run;
+    const int rn = trow >> rb;
+    const int tidx = (((rn << xb) + ((rn & 1) ? (1 << xb) - 1 - sub : sub)) << rb) + (trow & ((1 << rb) - 1));
     if (tidx >= p.nT) continue;  // a hole of the id space
     h = kvh * p.g + min(max((int)uload(pm, 1 + slot_h), 0), p.g - 1);
     t128 = p.nT - 1 - tidx;
@@ -831,13 +837,12 @@ hipError_t launch_sparse_prefill(const Shape &sh, const Workspace &ws, const uin
   a.n_items = a.nT * sh.Hq;
   // KV heads in progress together: as many as there are queues, unless their K and V rows
   // (what the diagonal phase streams) exceed the 256 MiB memory-side cache
-  a.xs = 1;
-  while (a.xs < 8 && 8 / a.xs > sh.Hkv) a.xs *= 2;  // fewer than 8 KV heads: no idle queues
-  while (a.xs < 8 && (size_t)(8 / a.xs) * sh.N * kHeadDim * 2 * 2 > ((size_t)256 << 20)) a.xs *= 2;
+  int xb = 0;
+  while (xb < 3 && (8 >> xb) > sh.Hkv) ++xb;  // fewer than 8 KV heads: no idle queues
+  while (xb < 3 && (size_t)(8 >> xb) * sh.N * kHeadDim * 2 * 2 > ((size_t)256 << 20)) ++xb;
   // sequences of a few runs per queue would not share out evenly
-  a.run = a.xs > 1 && a.nT >= 4 * a.xs * kRun ? kRun : 1;
-  a.per_q = (a.nT + a.xs * a.run - 1) / (a.xs * a.run) * a.run * sh.g;
-  a.qcap = a.per_q * ((sh.Hkv + 8 / a.xs - 1) / (8 / a.xs));
+  a.share = xb | (xb > 0 && a.nT >= (4 << xb) * kRun ? kRunBits << 4 : 0);
+  a.qcap = tickets_per_head(a.nT, a.share) * sh.g * ((sh.Hkv + (8 >> xb) - 1) / (8 >> xb));
   const int grid = a.n_items < 2 * sh.n_cu ? a.n_items : 2 * sh.n_cu;  // two resident workgroups per CU
   if (counters)
     sparse_prefill_kernel<true><<<grid, 256, 0, st>>>(a);
