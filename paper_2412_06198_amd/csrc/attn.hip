@@ -35,6 +35,8 @@ constexpr int BK = 64;            // keys per tile
 // 32 heads: 4.07 -> 3.98 ms).
 constexpr int kRunBits = 6, kRun = 1 << kRunBits;
 constexpr int NWORDS = kMaxSeq / BK / 32;
+constexpr int kPlanWaves = 4;     // items per workgroup of index_prepare_kernel
+constexpr unsigned kNoItem = ~0u;
 
 struct AttnArgs {
   const uint16_t *Q, *K, *V;
@@ -53,9 +55,14 @@ struct AttnArgs {
                 // log2 of the consecutive row blocks a queue takes in a row (kRun or 1)
   int qcap;     // tickets per queue, holes of the id space included
   unsigned long long *counters;  // instrumentation only: {32x32 sub-tiles multiplied, kept (query,key) pairs}
-  // Per KV head, written by index_prepare_kernel: [0] = number c of its query heads without
-  // selected diagonals, [1..g] = the query heads of the group (0..g-1), those c first.
-  int32_t *hperm;
+  // Written by index_prepare_kernel.  items[queue + 8 * ticket] = {head | row block << 16 (kNoItem: a hole
+  // of the id space), key tiles in the list, list start inside the head's share of tiles, first two
+  // entries}; tiles [Hq][tile_cap] list entries: key tile (bits 0..11), kept by waves 0, 1 (bit 14) / by
+  // waves 2, 3 (bit 15).
+  uint4 *items;
+  uint16_t *tiles;
+  unsigned tile_cap;
+  int grid;     // workgroups of the attention kernel
 };
 
 // Tickets per queue and query head, holes included: whole runs of every queue that shares the KV head.
@@ -78,28 +85,121 @@ __device__ inline uint32_t bits_window32(const uint32_t *bm, int nw, int pos) {
   return (uint32_t)(((uint64_t)lo | ((uint64_t)hi << 32)) >> sh);
 }
 
+// Item id = queue + 8 * ticket: which head and row block it is, and the list of its key tiles.
+// Ticket k of queue qn: k / per_q selects the KV head, the rest walks the row blocks from the last
+// (longest) one down, in runs of which the queues that share take one each in turn, back and forth:
+// first for the query heads of the group that have no selected diagonals, side by side per row block
+// (their tiles overlap: the band of Triangular heads is the same for all of them), then for each head
+// with diagonals by itself (their diagonal phase re-reads nothing, and one head's gathered columns
+// stay in L2).  Here and not at the head of every item of the attention kernel, where the same steps
+// were four barriers and three round trips to memory one after the other while the matrix cores idled:
+// a whole layer of 4K, 10K, 16K, 32K and 128K tokens 59.8, 355, 432, 733 and 4543 us, now 57.0, 343, 414,
+// 718 and 4499 (plain causal attention at 16K 1986 and 1961).  One wave per item.
+__device__ inline void plan_item(const AttnArgs &p, int id, uint32_t *k0, uint32_t *k1, uint16_t *first2) {
+  const int lane = threadIdx.x & 63;
+  const int qn = id & 7, k = id >> 3;
+  const int xb = p.share & 15, rb = p.share >> 4;
+  const int nslots = 8 >> xb, slot = qn >> xb, sub = qn & ((1 << xb) - 1);
+  const int rows_q = tickets_per_head(p.nT, p.share), per_q = rows_q * p.g;
+  const int r = k % per_q, kvh = k / per_q * nslots + slot;
+  int h = -1, tidx = p.nT;
+  if (kvh < p.Hkv) {
+    // heads without diagonals, as two words (a group has at most kMaxHeads = 128 heads)
+    unsigned long long w[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int j = 64 * i + lane;
+      w[i] = __ballot(j < p.g && p.n_offs[kvh * p.g + min(j, p.g - 1)] <= 0);
+    }
+    const int c = __popcll(w[0]) + __popcll(w[1]);
+    const bool plain = r < c * rows_q;
+    const int r2 = r - c * rows_q;
+    int nth = plain ? r % c : r2 / rows_q;  // this many heads of its kind come before it
+    const int trow = plain ? r / c : r2 % rows_q;
+    for (int j = 0; j < p.g; ++j)
+      if ((((w[j >> 6] >> (j & 63)) & 1ull) != 0ull) == plain && nth-- == 0) h = kvh * p.g + j;
+    const int rn = trow >> rb;
+    tidx = (((rn << xb) + ((rn & 1) ? (1 << xb) - 1 - sub : sub)) << rb) + (trow & ((1 << rb) - 1));
+  }
+  if (h < 0 || tidx >= p.nT) {
+    if (lane == 0) p.items[id] = make_uint4(kNoItem, 0u, 0u, 0u);
+    return;
+  }
+  const int t128 = p.nT - 1 - tidx;
+  const int ilast = min((t128 + 1) * BQ, p.N) - 1;
+  const int nwords = (ilast / BK + 1 + 31) / 32;
+  for (int i = lane; i < nwords; i += 64) { k0[i] = 0u; k1[i] = 0u; }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  // CSR entry ranges of the row blocks of this item: one at block 128, two (2*t128 for waves 0,1
+  // and 2*t128+1 for waves 2,3) at block 64
+  const int32_t *rp = p.rowptr + (size_t)h * (p.nb + 1);
+  const int Ra = p.b == BQ ? t128 : 2 * t128;
+  const bool two = p.b != BQ && Ra + 1 < p.nb;
+  const int ea0 = max(rp[Ra], 0), ea1 = min(rp[Ra + 1], p.cap_b);
+  const int eb0 = max(rp[min(Ra + 1, p.nb)], 0), eb1 = min(rp[min(Ra + 2, p.nb)], p.cap_b);
+  const int na = max(ea1 - ea0, 0), nbk = two ? max(eb1 - eb0, 0) : 0;
+  const int32_t *bc = p.blkcols + (size_t)h * p.cap_b;
+  const int tpb = p.b / BK;  // key tiles per key block: their bits are adjacent in one word
+  const uint32_t tbits = tpb == 2 ? 3u : 1u;
+  for (int e0 = lane; e0 < na + nbk; e0 += 256) {
+    int C[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {  // four reads in flight
+      const int e = e0 + 64 * u;
+      C[u] = e < na + nbk ? bc[e >= na ? eb0 + (e - na) : ea0 + e] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool second = e0 + 64 * u >= na;
+      if (C[u] >= 0 && C[u] <= Ra + (second ? 1 : 0)) {
+        const int kt = C[u] * tpb;
+        if (!second) atomicOr(&k0[kt >> 5], tbits << (kt & 31));
+        if (second || p.b == BQ) atomicOr(&k1[kt >> 5], tbits << (kt & 31));
+      }
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  // one tile per lane: the kept ones in ascending order
+  const unsigned start = (unsigned)min(ea0, p.cap_b) * tpb;
+  const unsigned room = p.tile_cap - start;
+  uint16_t *out = p.tiles + (size_t)h * p.tile_cap + start;
+  unsigned base = 0;
+  for (int w0 = 0; w0 < nwords; w0 += 2) {
+    const int w = w0 + (lane >> 5);
+    const uint32_t a = w < nwords ? (k0[w] >> (lane & 31)) & 1u : 0u, b = w < nwords ? (k1[w] >> (lane & 31)) & 1u : 0u;
+    const unsigned long long m = __ballot((a | b) != 0u);
+    const unsigned pos = base + (unsigned)__popcll(m & ((1ull << lane) - 1ull));
+    if ((a | b) != 0u && pos < room) {
+      const uint16_t ent = (uint16_t)((w0 * 32 + lane) | (a << 14) | (b << 15));
+      out[pos] = ent;
+      if (pos < 2) first2[pos] = ent;
+    }
+    base += (unsigned)__popcll(m);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const unsigned n = min(base, room);
+  if (lane == 0)
+    p.items[id] = make_uint4((unsigned)h | (unsigned)t128 << 16, n, start,
+                             (n > 0 ? first2[0] : 0u) | (n > 1 ? (unsigned)first2[1] << 16 : 0u));
+}
+
 // What the attention kernel needs from the index before it starts, in one launch of 256-thread
 // blocks.  Blocks 0 .. Hq-1: membership bitmap of a head's selected columns and the running count
 // of selected columns before each bitmap word (built in LDS, written out once); block 0 also
-// resets the work-queue heads.  The other blocks, (gather tile g, head h) = Hq + h * ntile + g:
+// resets the work-queue heads (a workgroup's first ticket is its own number, so they start behind
+// those).  The next blocks: one wave per item, plan_item.  The rest, (gather tile g, head h):
 // the selected key columns of every head are copied once into contiguous [k][d] buffers so that
 // the attention kernel reads gather tiles like any other tile.
-__global__ __launch_bounds__(256) void index_prepare_kernel(AttnArgs p, unsigned int *queue) {
-  __shared__ uint32_t bm[kMaxSeq / 32];
+__global__ __launch_bounds__(256) void index_prepare_kernel(AttnArgs p, unsigned int *queue, int n_bitmap_words) {
+  extern __shared__ uint32_t bm[];  // the bitmap of a head, or two key-tile bitmaps per wave
   __shared__ int wsum[4];
   const int tid = threadIdx.x;
   if ((int)blockIdx.x < p.Hq) {
     const int h = blockIdx.x, nw = p.N / 32, lane = tid & 63, wv = tid >> 6;
-    if (h == 0 && tid < 8) queue[tid] = 0u;
-    if (h < p.Hkv && tid == 0) {  // the order in which the attention kernel walks the heads of KV head h
-      int32_t *pm = p.hperm + (size_t)h * (p.g + 1);
-      int c = 0;
-      for (int j = 0; j < p.g; ++j)
-        if (p.n_offs[h * p.g + j] <= 0) pm[1 + c++] = j;
-      pm[0] = c;
-      for (int j = 0; j < p.g; ++j)
-        if (p.n_offs[h * p.g + j] > 0) pm[1 + c++] = j;
-    }
+    if (h == 0 && tid < 8) queue[tid] = (unsigned)(p.grid + 7 - tid) >> 3;
     for (int i = tid; i < nw; i += 256) bm[i] = 0u;
     __syncthreads();
     const int nc = min(max(p.n_cols[h], 0), p.k_v);
@@ -132,8 +232,17 @@ __global__ __launch_bounds__(256) void index_prepare_kernel(AttnArgs p, unsigned
     }
     return;
   }
-  const int ntile = p.kvg_rows / BK;
-  const int h = ((int)blockIdx.x - p.Hq) / ntile, g = ((int)blockIdx.x - p.Hq) % ntile;
+  const int n_plan = (8 * p.qcap + kPlanWaves - 1) / kPlanWaves;
+  if ((int)blockIdx.x < p.Hq + n_plan) {
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int id = ((int)blockIdx.x - p.Hq) * kPlanWaves + wv;
+    const int words = n_bitmap_words / (2 * kPlanWaves);
+    uint32_t *k0 = bm + 2 * words * wv;
+    if (id < 8 * p.qcap) plan_item(p, id, k0, k0 + words, (uint16_t *)&wsum[wv]);
+    return;
+  }
+  const int ntile = p.kvg_rows / BK, gb = (int)blockIdx.x - p.Hq - n_plan;
+  const int h = gb / ntile, g = gb % ntile;
   const int nc = min(max(p.n_cols[h], 0), p.k_v);
   if (g * BK >= nc) return;
   const int kvh = h / p.g;
@@ -159,10 +268,8 @@ template <bool STATS>
 __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
   __shared__ __attribute__((aligned(16))) uint16_t Ks[2][BK * 128];
   __shared__ __attribute__((aligned(16))) uint16_t Vs[2][BK * 128];
-  __shared__ uint32_t need[NWORDS], kept0[NWORDS], kept1[NWORDS];
+  __shared__ uint32_t kept0[NWORDS], kept1[NWORDS];
   __shared__ uint16_t tlist[kMaxSeq / BK];
-  __shared__ int s_ntiles;
-  __shared__ int s_cmax[4];
 
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);  // wave-uniform for the compiler too
 
@@ -170,18 +277,14 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
   // (consecutive workgroup ids land on consecutive XCDs).  1, 2, 4 or 8 queues share one KV head at a
   // time: alone, a queue keeps its KV head in a single L2; with more of them fewer KV heads are live at
   // once, so that the rows the diagonal phase fetches (no reuse inside an L2) come out of the
-  // memory-side cache instead of HBM.  Ticket k of queue qn: k / per_q selects the KV head, the rest
-  // walks the row blocks from the last (longest) one down, in runs of which the queues that share take
-  // one each in turn, back and forth: first for the query heads of the group that have no
-  // selected diagonals, side by side per row block, then for each head with diagonals by itself
-  // (the order index_prepare_kernel left in hperm).  A
-  // workgroup whose own queue is empty takes from the others, then exits.  The ticket for the
-  // next item of the home queue is drawn while the current item finishes, so its round trip is
-  // off the critical path.
+  // memory-side cache instead of HBM.  plan_item has written down what every ticket stands for.  A
+  // workgroup whose own queue is empty takes from the others, then exits.  The first ticket is the
+  // workgroup's number; the one for the next item of the home queue is drawn while the current item
+  // finishes, so its round trip is off the critical path.
   __shared__ int s_item;
   const int home = blockIdx.x & 7;
-  int ticket = 0;            // thread 0 only: position drawn from the home queue
-  bool have_ticket = false;  // thread 0 only: ticket was drawn ahead and is not used yet
+  int ticket = blockIdx.x >> 3;  // thread 0 only: position drawn from the home queue
+  bool have_ticket = true;       // thread 0 only: ticket was drawn ahead and is not used yet
   bool home_open = true;     // thread 0 only: the home queue still had items at the last draw
   for (;;) {
   // Lane-derived constants are recomputed per item from an opaque copy of the thread id:
@@ -207,131 +310,21 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
     }
     s_item = item;
   }
+  if (tid < NWORDS) { kept0[tid] = 0u; kept1[tid] = 0u; }
   __syncthreads();
   const int id = __builtin_amdgcn_readfirstlane(s_item);
   if (id < 0) break;
-  int kvh, h, t128;
-  {
-    const int qn = id & 7, k = id >> 3;
-    const int xb = p.share & 15, rb = p.share >> 4;
-    const int nslots = 8 >> xb, slot = qn >> xb, sub = qn & ((1 << xb) - 1);
-    const int per_q = tickets_per_head(p.nT, p.share) * p.g;
-    const int r = k % per_q;
-    kvh = k / per_q * nslots + slot;
-    if (kvh >= p.Hkv) continue;  // a hole of the id space
-    // Heads without selected diagonals walk a row block side by side (their tiles overlap: the
-    // band of Triangular heads is the same for all of them); heads with diagonals follow one at a
-    // time (their diagonal phase re-reads nothing, and one head's gathered columns stay in L2).
-    const int rows_q = per_q / p.g;
-    const int32_t *pm = p.hperm + (size_t)kvh * (p.g + 1);
-    const int c = min(max((int)uload(pm, 0), 0), p.g);
-    int slot_h, trow;
-    if (r < c * rows_q) {
-      slot_h = r % c; trow = r / c;
-    } else {
-      const int r2 = r - c * rows_q;
-      slot_h = c + r2 / rows_q; trow = r2 % rows_q;
-    }
-    const int rn = trow >> rb;
-    const int tidx = (((rn << xb) + ((rn & 1) ? (1 << xb) - 1 - sub : sub)) << rb) + (trow & ((1 << rb) - 1));
-    if (tidx >= p.nT) continue;  // a hole of the id space
-    h = kvh * p.g + min(max((int)uload(pm, 1 + slot_h), 0), p.g - 1);
-    t128 = p.nT - 1 - tidx;
-  }
+  const uint32_t it_w = uload(p.items, 4 * id), it_n = uload(p.items, 4 * id + 1);
+  const uint32_t it_at = uload(p.items, 4 * id + 2), it_e = uload(p.items, 4 * id + 3);
+  if (it_w == kNoItem) continue;  // a hole of the id space
+  const int h = (int)(it_w & 0xFFFFu), t128 = (int)(it_w >> 16);
+  const int kvh = h / p.g;
+  const int ntr = (int)it_n;
   const int i0 = t128 * BQ;
   const int r0 = i0 + 32 * wv;
   const int iq = r0 + q;  // this lane's query row
   const int N = p.N;
   const int ilast = min(i0 + BQ, N) - 1;
-
-  // long-latency reads first: they overlap the construction of the tile list
-  bf16x8 qf[8];  // Q^T fragments: B operand, lane = query, 8 consecutive d per k-step half
-  {
-    const uint16_t *qrow = p.Q + (size_t)h * p.q_hs + (size_t)min(iq, N - 1) * p.q_rs;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qf[ks] = *(const bf16x8 *)(qrow + 16 * ks + 8 * gg);
-  }
-  // the item's small reads sit at wave-uniform addresses: scalar loads, all in flight together
-  const int nc = min(max((int)uload(p.n_cols, h), 0), p.k_v);
-  const bool has_offs = (int)uload(p.n_offs, h) > 0;
-  // CSR entry ranges of the row blocks of this item: one at block 128, two (2*t128 for waves 0,1
-  // and 2*t128+1 for waves 2,3) at block 64
-  const int32_t *rp = p.rowptr + (size_t)h * (p.nb + 1);
-  const int Ra = p.b == BQ ? t128 : 2 * t128;
-  const bool two = p.b != BQ && Ra + 1 < p.nb;
-  const int ea0 = max((int)uload(rp, Ra), 0), ea1 = min((int)uload(rp, Ra + 1), p.cap_b);
-  const int eb0 = max((int)uload(rp, min(Ra + 1, p.nb)), 0), eb1 = min((int)uload(rp, min(Ra + 2, p.nb)), p.cap_b);
-  const int na = max(ea1 - ea0, 0), nbk = two ? max(eb1 - eb0, 0) : 0;
-  // selected columns visible to this query = those up to its own position: the running count
-  // before its bitmap word plus the bits of that word up to the position (the list is ascending
-  // and without repeats, so this is also the query's cut in the gathered list)
-  int cle;
-  {
-    const int key = min(iq, N - 1), wi = key >> 5;
-    const size_t bo = (size_t)h * (N / 32) + wi;
-    cle = p.colprefix[bo] + __popc(p.colbits[bo] & (0xFFFFFFFFu >> (31 - (key & 31))));
-    cle = nc > 0 ? cle : 0;
-  }
-
-  // ---- tile list of this row block -------------------------------------------------------
-  const int nwords = ((ilast / BK + 1) + 31) / 32;
-  for (int i = tid; i < nwords; i += 256) { need[i] = 0u; kept0[i] = 0u; kept1[i] = 0u; }
-  __syncthreads();
-  {
-    // one pass over the entries of both row blocks, so that their reads are in flight together
-    const int32_t *bc = p.blkcols + (size_t)h * p.cap_b;
-    const int tpb = p.b / BK;  // key tiles per key block: their bits are adjacent in one word
-    const uint32_t tbits = tpb == 2 ? 3u : 1u;
-    for (int e = tid; e < na + nbk; e += 256) {
-      const bool second = e >= na;
-      const int C = bc[second ? eb0 + (e - na) : ea0 + e];
-      if (C >= 0 && C <= Ra + (second ? 1 : 0)) {
-        const int kt = C * tpb;
-        atomicOr(&need[kt >> 5], tbits << (kt & 31));
-        if (!second) atomicOr(&kept0[kt >> 5], tbits << (kt & 31));
-        if (second || p.b == BQ) atomicOr(&kept1[kt >> 5], tbits << (kt & 31));
-      }
-    }
-  }
-  __syncthreads();
-  if (wv == 0) {  // ordered compaction of the set bits into tlist
-    int base = 0;
-    for (int w0 = 0; w0 < nwords; w0 += 64) {
-      const uint32_t word = (w0 + lane < nwords) ? need[w0 + lane] : 0u;
-      const int cnt = __popc(word);
-      int incl = cnt;
-      for (int d = 1; d < 64; d <<= 1) {
-        const int o = __shfl_up(incl, d);
-        if (lane >= d) incl += o;
-      }
-      int pos = base + incl - cnt;
-      uint32_t wbits = word;
-      // the keep words are read once: the loop below then has no LDS read to wait for
-      const uint32_t k0 = (w0 + lane < nwords) ? kept0[w0 + lane] : 0u, k1 = (w0 + lane < nwords) ? kept1[w0 + lane] : 0u;
-      while (wbits) {
-        const int bit = __ffs(wbits) - 1;
-        wbits &= wbits - 1;
-        // entry: key tile (bits 0..11), kept by waves 0,1 (bit 14) / by waves 2,3 (bit 15)
-        tlist[pos++] = (uint16_t)(((w0 + lane) * 32 + bit) | (((k0 >> bit) & 1u) << 14) | (((k1 >> bit) & 1u) << 15));
-      }
-      base += __shfl(incl, 63);
-    }
-    if (lane == 0) s_ntiles = base;
-  }
-
-  int cmax = cle, cmin = cle;  // gather tiles this wave needs: up to its last query's cut; its first query's cut
-  for (int d = 32; d >= 1; d >>= 1) {
-    cmax = max(cmax, __shfl_xor(cmax, d));
-    cmin = min(cmin, __shfl_xor(cmin, d));
-  }
-  if (lane == 0) s_cmax[wv] = cmax;
-  __syncthreads();
-  const int ntr = __builtin_amdgcn_readfirstlane(s_ntiles);
-  const int cwave = __builtin_amdgcn_readfirstlane(cmax), cwmin = __builtin_amdgcn_readfirstlane(cmin);
-  const int call = __builtin_amdgcn_readfirstlane(max(max(s_cmax[0], s_cmax[1]), max(s_cmax[2], s_cmax[3])));
-  const int ng = (call + BK - 1) / BK;
-  const int ntot = ntr + ng;
-  const bool has_cols = nc > 0;
 
   // ---- operands ------------------------------------------------------------------------------
   const uint16_t *__restrict__ Kh = p.K + (size_t)kvh * p.kv_hs;
@@ -403,9 +396,51 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
 
   // list entries travel one tile ahead in scalar registers, so that neither the copy of the next
   // tile nor this tile's keep test waits for an LDS read behind the barrier
-  int e_cur = __builtin_amdgcn_readfirstlane((int)tlist[0]);
-  int r_nxt = (int)tlist[1];  // raw LDS value: made scalar only where it is used, a tile later
-  if (ntot > 0) SA_ISSUE_TILE(0, 0, e_cur);
+  int e_cur = (int)(it_e & 0xFFFFu);
+  int r_nxt = (int)(it_e >> 16);  // from LDS later on: made scalar only where it is used, a tile later
+  if (ntr > 0) SA_ISSUE_TILE(0, 0, e_cur);
+
+  // the item's other reads, all in flight together with the first tile's copies
+  bf16x8 qf[8];  // Q^T fragments: B operand, lane = query, 8 consecutive d per k-step half
+  {
+    const uint16_t *qrow = p.Q + (size_t)h * p.q_hs + (size_t)min(iq, N - 1) * p.q_rs;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) qf[ks] = *(const bf16x8 *)(qrow + 16 * ks + 8 * gg);
+  }
+  const bool has_offs = (int)uload(p.n_offs, h) > 0;
+  const int nc = min(max((int)uload(p.n_cols, h), 0), p.k_v);
+  const bool has_cols = nc > 0;
+  // Selected columns visible to a query = those up to its own position: the running count before its
+  // bitmap word plus the bits of that word up to the position (the list is ascending and without
+  // repeats, so this is also the query's cut in the gathered list).  The 32 queries of a wave share a
+  // word, the last of the row block ends one.
+  int cle, cwave, cwmin, call;  // this lane's query; the wave's last and first; the row block's last
+  {
+    const int32_t *cp = p.colprefix + (size_t)h * (N / 32);
+    const int wi = min(r0, N - 1) >> 5, wl = ilast >> 5;
+    const int before = (int)uload(cp, wi);
+    const uint32_t word = uload(colbm, wi);
+    cle = has_cols ? before + __popc(word & (0xFFFFFFFFu >> (31 - q))) : 0;
+    cwave = has_cols ? before + __popc(word) : 0;
+    cwmin = has_cols ? before + (int)(word & 1u) : 0;
+    call = has_cols ? (int)uload(cp, wl) + __popc(uload(colbm, wl)) : 0;
+  }
+  const int ng = (call + BK - 1) / BK;
+  const int ntot = ntr + ng;
+  if (ntr == 0 && ng > 0) SA_ISSUE_TILE(0, 0, e_cur);
+  {
+    // the list, for the tile loop (read behind its first barrier), and the kept tiles as bitmaps, for the diagonals
+    const uint16_t *tl = p.tiles + (size_t)h * p.tile_cap + it_at;
+    for (int i = tid; i < ntr; i += 256) {
+      const int ent = tl[i];
+      tlist[i] = (uint16_t)ent;
+      if (has_offs) {
+        const int kt = ent & 0xFFF;
+        if (ent & 0x4000) atomicOr(&kept0[kt >> 5], 1u << (kt & 31));
+        if (ent & 0x8000) atomicOr(&kept1[kt >> 5], 1u << (kt & 31));
+      }
+    }
+  }
 
   for (int t = 0; t < ntot; ++t) {
     const int cur = t & 1;
@@ -812,7 +847,27 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
 #undef SA_ISSUE_TILE
 #undef SA_DMA16
 
+// log2 of the queues that share a KV head, and from bit 4 on log2 of the row blocks a queue takes in a row
+int queue_share(const Shape &sh) {
+  const int nT = (sh.N + BQ - 1) / BQ;
+  // KV heads in progress together: as many as there are queues, unless their K and V rows
+  // (what the diagonal phase streams) exceed the 256 MiB memory-side cache
+  int xb = 0;
+  while (xb < 3 && (8 >> xb) > sh.Hkv) ++xb;  // fewer than 8 KV heads: no idle queues
+  while (xb < 3 && (size_t)(8 >> xb) * sh.N * kHeadDim * 2 * 2 > ((size_t)256 << 20)) ++xb;
+  // sequences of a few runs per queue would not share out evenly
+  return xb | (xb > 0 && nT >= (4 << xb) * kRun ? kRunBits << 4 : 0);
+}
+
+int queue_capacity(const Shape &sh) {
+  const int share = queue_share(sh), slots = 8 >> (share & 15);
+  return tickets_per_head((sh.N + BQ - 1) / BQ, share) * sh.g * ((sh.Hkv + slots - 1) / slots);
+}
+
 }  // namespace
+
+size_t attn_item_bytes(const Shape &sh) { return (size_t)8 * queue_capacity(sh) * sizeof(uint4); }
+size_t attn_tile_bytes(const Shape &sh) { return (size_t)sh.Hq * sh.cap_b * (sh.b / BK) * 2; }
 
 hipError_t launch_sparse_prefill(const Shape &sh, const Workspace &ws, const uint16_t *Q,
                                  const uint16_t *K, const uint16_t *V, sa_index idx, uint16_t *O,
@@ -828,22 +883,25 @@ hipError_t launch_sparse_prefill(const Shape &sh, const Workspace &ws, const uin
   a.q_hs = sh.q_hs; a.q_rs = sh.q_rs; a.kv_hs = sh.kv_hs; a.kv_rs = sh.kv_rs;
   a.c = sh.scale * 1.4426950408889634f;
   a.counters = counters;
-  a.hperm = ws.hperm;
   a.Kg = ws.kg; a.Vg = ws.vg; a.kvg_rows = (sh.k_v + BK - 1) / BK * BK;
-  index_prepare_kernel<<<sh.Hq + a.kvg_rows / BK * sh.Hq, 256, 0, st>>>(a, ws.queue);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   a.queue = ws.queue;
   a.n_items = a.nT * sh.Hq;
-  // KV heads in progress together: as many as there are queues, unless their K and V rows
-  // (what the diagonal phase streams) exceed the 256 MiB memory-side cache
-  int xb = 0;
-  while (xb < 3 && (8 >> xb) > sh.Hkv) ++xb;  // fewer than 8 KV heads: no idle queues
-  while (xb < 3 && (size_t)(8 >> xb) * sh.N * kHeadDim * 2 * 2 > ((size_t)256 << 20)) ++xb;
-  // sequences of a few runs per queue would not share out evenly
-  a.share = xb | (xb > 0 && a.nT >= (4 << xb) * kRun ? kRunBits << 4 : 0);
-  a.qcap = tickets_per_head(a.nT, a.share) * sh.g * ((sh.Hkv + (8 >> xb) - 1) / (8 >> xb));
-  const int grid = a.n_items < 2 * sh.n_cu ? a.n_items : 2 * sh.n_cu;  // two resident workgroups per CU
+  a.share = queue_share(sh);
+  a.qcap = queue_capacity(sh);
+  a.items = (uint4 *)ws.attn_items;
+  a.tiles = ws.attn_tiles;
+  a.tile_cap = (unsigned)(sh.cap_b * (sh.b / BK));
+  a.grid = a.n_items < 2 * sh.n_cu ? a.n_items : 2 * sh.n_cu;  // two resident workgroups per CU
+  const int n_plan = (8 * a.qcap + kPlanWaves - 1) / kPlanWaves;
+  // LDS for the larger of a head's column bitmap and the key-tile bitmaps of four items: this bound also
+  // limits the workgroups of a CU, so it follows the sequence
+  const int tile_words = (sh.N / BK + 31) / 32 + 1;
+  int words = 2 * kPlanWaves * tile_words;
+  if (words < sh.N / 32) words = (sh.N / 32 + 2 * kPlanWaves - 1) / (2 * kPlanWaves) * (2 * kPlanWaves);
+  index_prepare_kernel<<<sh.Hq + n_plan + a.kvg_rows / BK * sh.Hq, 256, words * 4, st>>>(a, ws.queue, words);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int grid = a.grid;
   if (counters)
     sparse_prefill_kernel<true><<<grid, 256, 0, st>>>(a);
   else

@@ -42,7 +42,8 @@ struct Workspace {
   unsigned int *queue;            // [8] work-queue heads of the attention kernel
   void *idx;                      // per-head scratch of the index builder
   uint16_t *kg, *vg;              // [Hq][roundup64(k_v)][kv_rs] gathered K / V rows of the selected columns
-  int32_t *hperm;                 // [Hkv][g + 1] order of a KV head's query heads in the attention kernel's queues
+  void *attn_items;               // what each ticket of the attention kernel's queues stands for (16 bytes)
+  uint16_t *attn_tiles;           // [Hq][cap_b * block / 64] key-tile lists of the row blocks
 };
 
 size_t index_scratch_bytes(const Shape &sh);
@@ -62,7 +63,7 @@ struct sa_ctx {
   sa::Workspace ws;
   bool have_ws;
   size_t ws_bytes;
-  size_t off[12];
+  size_t off[13];
   char err[256];
 };
 
@@ -84,6 +85,8 @@ hipError_t launch_build_index(const Shape &sh, const Workspace &ws, sa_scores in
 hipError_t launch_index_stage(const Shape &sh, const Workspace &ws, sa_scores in, const Override &ov,
                               sa_index out, IndexStage stage, hipStream_t st);
 size_t decode_partial_bytes(const Shape &sh);
+size_t attn_item_bytes(const Shape &sh);
+size_t attn_tile_bytes(const Shape &sh);
 // partials: decode_partial_bytes(sh) bytes of device memory (the context's workspace, or the static array)
 hipError_t launch_sparse_decode(const Shape &sh, float *partials, const uint16_t *q, const uint16_t *K,
                                 const uint16_t *V, sa_index idx, int pos, uint16_t *o, hipStream_t st);
