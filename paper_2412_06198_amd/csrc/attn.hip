@@ -161,13 +161,19 @@ __device__ inline void plan_item(const AttnArgs &p, int id, uint32_t *k0, uint32
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  // one tile per lane: the kept ones in ascending order
+  // One tile per lane, 64 at a time: the kept ones in ascending order.  Stretches that keep none are passed
+  // over by a mask of the others (a row of a long sequence has thousands of tiles and keeps some thirty:
+  // without it this launch took 46 us at 128K tokens and 32 heads, 34 with it).
   const unsigned start = (unsigned)min(ea0, p.cap_b) * tpb;
   const unsigned room = p.tile_cap - start;
   uint16_t *out = p.tiles + (size_t)h * p.tile_cap + start;
   unsigned base = 0;
-  for (int w0 = 0; w0 < nwords; w0 += 2) {
-    const int w = w0 + (lane >> 5);
+  static_assert(NWORDS <= 128, "one lane per pair of words");
+  uint32_t any = 0u;
+  if (2 * lane < nwords) any = k0[2 * lane] | k1[2 * lane];
+  if (2 * lane + 1 < nwords) any |= k0[2 * lane + 1] | k1[2 * lane + 1];
+  for (unsigned long long pairs = __ballot(any != 0u); pairs != 0ull; pairs &= pairs - 1ull) {
+    const int w0 = 2 * (__ffsll(pairs) - 1), w = w0 + (lane >> 5);
     const uint32_t a = w < nwords ? (k0[w] >> (lane & 31)) & 1u : 0u, b = w < nwords ? (k1[w] >> (lane & 31)) & 1u : 0u;
     const unsigned long long m = __ballot((a | b) != 0u);
     const unsigned pos = base + (unsigned)__popcll(m & ((1ull << lane) - 1ull));
