@@ -432,7 +432,7 @@ def run_sweep(steps):
             torch.cuda.synchronize()
             res[kind] = e0.elapsed_time(e1) / n
             if kind == "sparse":
-                # the same step recorded once into a HIP graph and replayed: what the ten small
+                # the same step recorded once into a HIP graph and replayed: what the small
                 # launches of the index builder cost on the host side at short sequences
                 res["sparse_graph"] = float("nan")
                 try:

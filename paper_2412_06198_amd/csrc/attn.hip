@@ -902,7 +902,7 @@ hipError_t launch_sparse_prefill(const Shape &sh, const Workspace &ws, const uin
   a.qcap = queue_capacity(sh);
   a.items = (uint4 *)ws.attn_items;
   a.tiles = ws.attn_tiles;
-  a.tile_cap = (unsigned)(sh.cap_b * (sh.b / BK));
+  a.tile_cap = (unsigned)sh.cap_b * (unsigned)(sh.b / BK);
   a.grid = a.n_items < 2 * sh.n_cu ? a.n_items : 2 * sh.n_cu;  // two resident workgroups per CU
   const int n_plan = (8 * a.qcap + kPlanWaves - 1) / kPlanWaves;
   // LDS for the larger of a head's column bitmap and the key-tile bitmaps of four items: this bound also
