@@ -201,8 +201,10 @@ sa_status sa_sparse_decode(sa_ctx *ctx, const void *q, const void *K, const void
  * times the split count the library picks must not exceed 512 partial results (every context
  * sa_create accepts today fits; a larger one gets SA_ERR_UNSUPPORTED).  All calls on one GPU - from
  * any context or thread - share that array: calls that overlap in time on one GPU race, so keep
- * them on one stream or order them with events.  Nothing in the array needs clearing between calls
- * (what a call reads it has written first, and the arrival counters repair themselves). */
+ * them on one stream or order them with events.  Nothing in the array needs clearing between calls,
+ * and calls that did overlap leave nothing behind that a later one could take for its own: a call reads
+ * only what it has written itself and counts arrivals under a number of its own (on a stream under
+ * capture: from counters that a launch of the recorded step clears). */
 sa_status sa_sparse_decode_static(sa_ctx *ctx, const void *q, const void *K, const void *V, sa_index idx,
                                   int64_t pos, void *o, void *hip_stream);
 

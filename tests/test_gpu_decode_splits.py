@@ -84,3 +84,43 @@ def test_decode_graph_replays():
             ses.decode(q, Kd, Vd, pos, o)
             torch.cuda.synchronize()
             assert torch.equal(o, w)
+
+
+def _decode_case(Hq, Hkv, N, b, extra, seed):
+    Q, K, V = gen.random_qkv(Hq, Hkv, N + extra, 128, seed=seed)
+    ses = sa.Session(Hq, Hkv, N, b, min(64, N), sink_blocks=1, local_blocks=1, k_vertical=200, k_slash=16,
+                     k_blocks=(N // b) * (N // b + 3) // 2, kv_head_stride=(N + extra) * 128)
+    ix = random_index(np.random.default_rng(seed), Hq, N, b, 200, 16, ses.cap_b)
+    upload_index(ses, ix)
+    return Q, K, V, ses, ix
+
+
+def _add_to_words(ws, k):
+    """Every 8-byte word of the workspace k higher: what a step that was cut short after k arrivals, or two steps
+    that overlapped on it, can leave in an arrival counter, wherever the counters are."""
+    off = (-ws.data_ptr()) % 8
+    ws[off: off + (ws.numel() - off) // 8 * 8].view(torch.int64).add_(k)
+
+
+@pytest.mark.parametrize("Hq,extra", [(4, 500), (1, 40)])
+def test_decode_after_a_leftover_arrival_count(Hq, extra):
+    # the next step gives the same bytes, eager and replayed, whatever count it finds
+    print(f"case decode leftover count Hq={Hq} extra={extra}", flush=True)
+    N = 1024
+    Q, K, V, ses, _ = _decode_case(Hq, 1, N, 64, extra, seed=Hq + extra)
+    Kd, Vd, pos = dev_bf16(K), dev_bf16(V), N + extra - 1
+    q, q2 = dev_bf16(Q[:, pos]), dev_bf16(Q[:, 0])
+    o, want = torch.empty_like(q), torch.empty_like(q)
+    ses.ws.zero_()
+    ses.decode(q, Kd, Vd, pos, want)
+    torch.cuda.synchronize()
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=side):
+        ses.decode(q, Kd, Vd, pos, o)
+    for k in list(range(1, 12)) + [63, 64, 255, 256, 65535, 65536, -1, -2]:
+        for step in (lambda: ses.decode(q, Kd, Vd, pos, o), graph.replay):
+            ses.decode(q2, Kd, Vd, pos, o)  # partials of another query, in case the step takes them for its own
+            _add_to_words(ses.ws, k)
+            step()
+            torch.cuda.synchronize()
+            assert torch.equal(o, want), k
