@@ -19,7 +19,7 @@
 namespace sa {
 namespace {
 
-constexpr int kPartStride = 132;  // floats per partial: max, sum, 2 unused, 128 outputs
+constexpr int kPartStride = 132;  // floats per partial: max, sum, 2 (first one: arrival counter, others: 0), 128 outputs
 
 // Partials of the variant that allocates nothing (sa_sparse_decode_static): room for the largest
 // head count x split count the launcher ever picks (Hq * splits <= 512), 270336 bytes on every GPU
@@ -29,7 +29,7 @@ constexpr int kStaticPartials = 512;
 static __device__ __align__(256) float scratch[kStaticPartials * kPartStride];
 constexpr int kMaxDevices = 64;
 
-// A head's arrival counter lives in the unused floats of its first partial: the step's token in the upper 48
+// A head's arrival counter lives in floats 2 and 3 of its first partial: the step's token in the upper 48
 // bits, in the lower 16 the number of workgroups that have arrived.  The memory may hold anything: what the
 // caller's workspace was used for before, or the count of a step that overlapped another one or never ended.
 // A step takes only its own token for a count: the first workgroup that finds another value there puts the
@@ -105,9 +105,12 @@ __device__ inline void merge(const float *src, int n, float *wgt, float *s_L, fl
     lk = get(src + (size_t)tid * kPartStride + 1);
   }
   float x[32];
+  // Places past the end weigh 0 and read the 0 that the last partial holds for them: anything else could be
+  // infinite.  (Masks on x after the reads cost 0.3 us.)
+  const int none = (n - 1) * kPartStride + 2;
 #pragma unroll
   for (int i = 0; i < 32; ++i) {
-    if (8 * (i / 8) * 2 < n) x[i] = get(src + (size_t)min(k0 + 2 * i, n - 1) * kPartStride + 4 + d);  // by eights
+    if (8 * (i / 8) * 2 < n) x[i] = get(src + (k0 + 2 * i < n ? (k0 + 2 * i) * kPartStride + 4 + d : none));  // by eights
     else x[i] = 0.f;
   }
   if (tid < 64) {
@@ -122,7 +125,8 @@ __device__ inline void merge(const float *src, int n, float *wgt, float *s_L, fl
   __syncthreads();
   float O = 0.f;
 #pragma unroll
-  for (int i = 0; i < 32; ++i) O = __builtin_fmaf(x[i], wgt[k0 + 2 * i], O);
+  for (int i = 0; i < 32; ++i)
+    O = __builtin_fmaf(x[i], wgt[k0 + 2 * i], O);
   if (k0) half[d] = O;
   __syncthreads();
   if (k0) return;
@@ -258,7 +262,12 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs p) {
   unpack8(qx, qv);
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-  auto attend = [&](const uint4 (&kr)[U], const uint4 (&vr)[U], int n) {
+  auto attend = [&](const uint4 (&kr)[U], uint4 (&vr)[U], int n) {
+    if (n < kStep) {  // the last step: a place without a key weighs 0, and 0 x inf is not 0
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (4 * u + slot >= n) vr[u] = make_uint4(0u, 0u, 0u, 0u);
+    }
     float s[U], m_new = m;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -330,7 +339,8 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs p) {
       p.o[(size_t)h * kHeadDim + tid] = __builtin_bit_cast(uint16_t, r);
     } else {
       float *dst = part + (size_t)sp * kPartStride;
-      if (tid == 0) { put(dst, M); put(dst + 1, lsum); }  // dst[2], dst[3] of the first one: the counter
+      if (tid == 0) { put(dst, M); put(dst + 1, lsum); }
+      if (tid == 1 && sp > 0) put(dst + 2, 0.f);  // see merge; dst[2], dst[3] of the first one: the counter
       put(dst + 4 + tid, O);
     }
   }
