@@ -157,6 +157,12 @@ __device__ inline KeyList key_list(const DecArgs &p, int h) {
   return k;
 }
 
+// What one lane has written to LDS before is read by the others of its wave after it, and the other way round.
+__device__ inline void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // grid (S, Hq), 256 threads.  Each wave walks a quarter of the workgroup's keys by itself: 64 lanes resolve 64
 // list places (which key, does it count here), the keys that count queue up in the wave's ring, and a step
 // reads the rows of 16 of them, slot s of 16 lanes every fourth one, lane ln elements 8 ln .. 8 ln + 7.
@@ -250,12 +256,14 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs p) {
   int cnt[2];
   auto fetch = [&](uint4 (&kr)[U], uint4 (&vr)[U], int &n) {
     n = min(put_at - get_at, kStep);
+    wave_lds_sync();
 #pragma unroll
     for (int u = 0; u < U; ++u) {  // a place without a key reads the last key again
       const int64_t row = ring[wave][(get_at + min(4 * u + slot, n - 1)) & (kRing - 1)];
       kr[u] = *(const uint4 *)(Kh + row);
       vr[u] = *(const uint4 *)(Vh + row);
     }
+    wave_lds_sync();
     get_at += n;
   };
   float qv[8], m = -INFINITY, l = 0.f, acc[8];
