@@ -15,7 +15,8 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
-#include <vector>
+#include <memory>
+#include <new>
 
 #include "sa_internal.h"
 
@@ -287,8 +288,13 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
   int rounds = 2;  // evaluations a bisection can take
   for (int64_t w = z.x_hi[1] - z.x_lo[1]; w > 1; w = (w + 1) / 2) ++rounds;
 
-  std::vector<char> head((size_t)B * (4 * sizeof(sa::HeadBudget) + sizeof(Refine)));
-  sa::HeadBudget *hb = (sa::HeadBudget *)head.data();
+  // host memory of the call: what goes to the device, what comes back
+  const size_t norms = (size_t)B * 3 * kNormBlocks, head_bytes = (size_t)B * (4 * sizeof(sa::HeadBudget) + sizeof(Refine));
+  const std::unique_ptr<sa::HeadBudget[]> head(new (std::nothrow) sa::HeadBudget[head_bytes / sizeof(sa::HeadBudget) + 1]);
+  const std::unique_ptr<double[]> hp(new (std::nothrow) double[norms]);
+  const std::unique_ptr<Refine[]> slash(new (std::nothrow) Refine[B]);
+  if (!head || !hp || !slash) return failp(ctx, SA_ERR_INVALID_ARG, "search: out of host memory");
+  sa::HeadBudget *hb = head.get();
   Refine *hr = (Refine *)(hb + (size_t)4 * B);
   for (int i = 0; i < B; ++i) {
     const sa::HeadBudget least = slash_budget(z.x_lo[1], N, nb);
@@ -298,8 +304,6 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
     hb[3 * B + i].k_b = (int32_t)clu.x;
     hr[i].start(z.x_lo[1], z.x_hi[1]);
   }
-  const size_t norms = (size_t)B * 3 * kNormBlocks;
-  std::vector<double> hp(norms);
   const int nblocks = (N + 15) / 16 < kNormBlocks ? (N + 15) / 16 : kNormBlocks;
 
   hipError_t he = hipSuccess;
@@ -320,7 +324,7 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
     auto attend = [&](uint16_t *O) {
       return ok(sa::launch_sparse_prefill(cs, ws, Qh, Kh, Vh, ix, O, nullptr, stream));
     };
-    ok(hipMemcpyAsync(budgets, head.data(), head.size(), hipMemcpyHostToDevice, stream));
+    ok(hipMemcpyAsync(budgets, hb, head_bytes, hipMemcpyHostToDevice, stream));
     // RefineSearchSpace of the Interval-Slash candidate, all heads a step per round (a head that is done
     // repeats its last index)
     for (int r = 0; r < rounds && he == hipSuccess; ++r) {
@@ -336,9 +340,8 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
       sq_diff_kernel<<<dim3(nblocks, B), 256, 0, stream>>>(o_sparse, o_dense, N, sh.q_hs, sh.q_rs, partial + (size_t)p * B * kNormBlocks);
       ok(hipGetLastError());
     }
-    std::vector<Refine> slash(B);
-    ok(hipMemcpyAsync(slash.data(), state, (size_t)B * sizeof(Refine), hipMemcpyDeviceToHost, stream));
-    ok(hipMemcpyAsync(hp.data(), partial, norms * 8, hipMemcpyDeviceToHost, stream));
+    ok(hipMemcpyAsync(slash.get(), state, (size_t)B * sizeof(Refine), hipMemcpyDeviceToHost, stream));
+    ok(hipMemcpyAsync(hp.get(), partial, norms * 8, hipMemcpyDeviceToHost, stream));
     // also after an error: nothing of this call is in flight when it returns
     const hipError_t last = hipStreamSynchronize(stream);
     if (!ok(last)) break;
