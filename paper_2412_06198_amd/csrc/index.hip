@@ -14,7 +14,8 @@
 //   refine  a second pass that splits a bin in 1024, only for selections whose boundary bin holds
 //           more keys than a list can take (it returns at once otherwise, which is the rule);
 //   count   a pass that counts, per wave, the keys above the boundary bin and appends the few
-//           inside it to a list, from which the exact threshold follows;
+//           inside it to a list, from which the exact threshold follows (or, where long runs of equal
+//           scores leave more of them than a list takes, counts them per wave);
 //   emit    a pass that writes the selected entries in index order (wave ballots), so the result
 //           is sorted without any sort; only the pattern's own arrays are read.
 // Small steps between the passes (finding a bin, resolving a list, prefixes, the pattern decision)
@@ -55,7 +56,10 @@ constexpr int kBinShift = 17;      // key bits below a bin: 6 mantissa bits coun
 // Bin 0 takes everything up to 2^-25 (2^-19), the last bin everything from 2^7 (2^13) on: window
 // sums stay below 64 and block weights below 1, or below the row length where they are scaled by it.
 constexpr int kBase = ((127 + 7) << 6) - kBins, kBaseRowNorm = ((127 + 13) << 6) - kBins;
-constexpr int kListVs = 4096, kListBlk = 16384;  // boundary keys a list takes
+constexpr int kListVs = 4096, kListBlk = 16384;  // boundary keys that are listed without splitting their bin first
+// Keys of a range that does not fit its list are counted one by one, per wave part, while there are no more
+// different ones than this: what the refine pass leaves of a bin.
+constexpr int kDense = 1 << (kBinShift - 10);
 
 typedef unsigned long long u64;
 typedef unsigned u32x4a __attribute__((ext_vector_type(4), aligned(4)));
@@ -68,6 +72,7 @@ struct IdxScratch {
   unsigned nlist[NSEL];                   // boundary keys appended so far
   unsigned ticket[3][3];                  // per launch (hist, refine, count) and array
   unsigned ticket_vs;                     // v and s resolved
+  unsigned dense_max[NSEL], dense_inv[NSEL];  // of a range with more keys than a list takes: largest key, largest ~key
   // everything above is zeroed at the start of a call
   alignas(16) u64 psum[2];                // sums of the probe best of v and s
   unsigned lo[NSEL], last[NSEL];          // key range that holds the k-th key of a selection ...
@@ -91,6 +96,7 @@ struct IdxArgs {
   Override ov;
   sa_index out;
   int Pv, Pb;                      // workgroups per head for v (and for s), and for the block map
+  int refine_vs, refine_blk;       // likewise, in the refine launch
   int vpart, bpart;                // entries of v and s, and of the block map (row-major, upper half included) per wave
   int first;                       // array v of a launch starts at workgroup -first (see Role)
   int decide_here;                 // 1: the launches before the emission write the patterns, 0: it decides by itself
@@ -224,7 +230,7 @@ struct Four {
 // multiplication; all values are >= +0, so the products order like their bit patterns too).
 // part: wave-uniform.
 template <class Fn>
-__device__ inline void visit(const IdxArgs &a, int arr, const unsigned *src, int part, Fn fn) {
+__device__ __forceinline__ void visit(const IdxArgs &a, int arr, const unsigned *src, int part, Fn fn) {
   const int lane = threadIdx.x & 63, nb = a.sh.nb;
   const unsigned total = arr == 2 ? (unsigned)nb * (unsigned)nb : (unsigned)a.sh.N;
   const unsigned len = (unsigned)(arr == 2 ? a.bpart : a.vpart);
@@ -359,7 +365,7 @@ __device__ inline void block_exclusive_scan2(unsigned &a, unsigned &b, unsigned 
 struct Pick { unsigned bin, rank, count; };
 
 template <int NT, int NB, int COPIES>
-__device__ inline void block_find_kth(const unsigned *hist, int ns, unsigned k0, unsigned k1, Pick *pick, unsigned *wsum) {
+__device__ __forceinline__ void block_find_kth(const unsigned *hist, int ns, unsigned k0, unsigned k1, Pick *pick, unsigned *wsum) {
   constexpr int PER = NB / NT;  // thread t owns PER bins, the first threads the top ones
   const int top = NB - 1 - (int)threadIdx.x * PER;
   unsigned c[PER], tot = 0, unused = 0;
@@ -677,8 +683,38 @@ __global__ __launch_bounds__(BT) void idx_hist_kernel(IdxArgs a) {
   }
 }
 
+// Counts the keys of `bits` (bit j: entry j of the lane) by their offset from lo, shifted: hist[(key - lo) >> shift].
+// For ranges that hold runs of equal keys: a wave that meets a single value adds once, a lane likewise; additions
+// of a wave to one counter take their turns otherwise, 64 of them for each entry of a lane.
+__device__ inline void count_keys(const Four &f, unsigned bits, unsigned lo, int shift, unsigned *hist) {
+  const u64 any = __ballot(bits != 0u);
+  if (any == 0ull) return;
+  unsigned d[4], mine = 0u;
+  bool same = true;
+#pragma unroll
+  for (int j = 3; j >= 0; --j) {
+    d[j] = (f.k[j] - lo) >> shift;
+    if ((bits >> j) & 1u) mine = d[j];
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) same = same && (!((bits >> j) & 1u) || d[j] == mine);
+  const unsigned first = (unsigned)__builtin_amdgcn_readlane((int)mine, __builtin_ctzll(any));
+  if (__all(bits == 0u || (same && mine == first))) {
+    unsigned n = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) n += __popcll(__ballot((bits >> j) & 1u));
+    if ((threadIdx.x & 63) == 0) atomicAdd(&hist[first], n);
+  } else if (same) {
+    if (bits) atomicAdd(&hist[mine], (unsigned)__popc(bits));
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if ((bits >> j) & 1u) atomicAdd(&hist[d[j]], 1u);
+  }
+}
+
 // ---- pass 2, where it is needed: a boundary bin with more keys than its list takes is split --------
-// grid (kRefineVs + kRefineVs + kRefineBlk, Hq): few workgroups, since most have nothing to do
+// grid (refine_vs + refine_vs + refine_blk, Hq): few workgroups, since most have nothing to do (see index_args)
 constexpr int kRefineVs = 4, kRefineBlk = 24;
 
 __global__ __launch_bounds__(BT) void idx_refine_kernel(IdxArgs a) {
@@ -687,22 +723,22 @@ __global__ __launch_bounds__(BT) void idx_refine_kernel(IdxArgs a) {
   __shared__ unsigned wsum[2 * WPB];
   const int h = blockIdx.y, tid = threadIdx.x;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  int x = (int)blockIdx.x, arr = 2, nwg = kRefineBlk;
+  int x = (int)blockIdx.x, arr = 2, nwg = a.refine_blk;
   if (a.first == 0) {
-    if (x < 2 * kRefineVs) { arr = x / kRefineVs; x %= kRefineVs; nwg = kRefineVs; }
-    else x -= 2 * kRefineVs;
+    if (x < 2 * a.refine_vs) { arr = x >= a.refine_vs; x -= arr ? a.refine_vs : 0; nwg = a.refine_vs; }
+    else x -= 2 * a.refine_vs;
   }
   if (!head_wants(a, h, arr == 2)) return;
   IdxScratch *G = a.scratch + h;
   const int ns = n_sel(arr);
-  const unsigned cap = arr == 2 ? (unsigned)a.cap_blk : (unsigned)a.cap_vs;
+  const unsigned most = arr == 2 ? kListBlk : kListVs;
   unsigned lo[2], last[2];
   int shift[2];
   bool want[2];
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     const int q = sel_of(arr, k < ns ? k : 0);
-    want[k] = k < ns && G->pop[q] > cap;
+    want[k] = k < ns && G->pop[q] > most;
     lo[k] = G->lo[q]; last[k] = G->last[q];
     shift[k] = digit_shift(last[k] - lo[k]);
   }
@@ -714,10 +750,13 @@ __global__ __launch_bounds__(BT) void idx_refine_kernel(IdxArgs a) {
     visit(a, arr, array_of(a, arr, h), part, [&](const Four &f) {
 #pragma unroll
       for (int k = 0; k < 2; ++k)
+        if (want[k]) {
+          unsigned bits = 0u;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (want[k] && ((f.ok >> j) & 1u) && f.k[j] >= lo[k] && f.k[j] <= last[k])
-            atomicAdd(&hist[k][(f.k[j] - lo[k]) >> shift[k]], 1u);
+          for (int j = 0; j < 4; ++j)
+            if (((f.ok >> j) & 1u) && f.k[j] >= lo[k] && f.k[j] <= last[k]) bits |= 1u << j;
+          count_keys(f, bits, lo[k], shift[k], hist[k]);
+        }
     });
   __syncthreads();
 #pragma unroll
@@ -746,8 +785,8 @@ __global__ __launch_bounds__(BT) void idx_refine_kernel(IdxArgs a) {
 
 // ---- pass 3: counts, thresholds, pattern ---------------------------------------------------------
 __global__ __launch_bounds__(BT) void idx_count_kernel(IdxArgs a) {
-  __shared__ u64 list[2][kList];   // the workgroup's boundary keys; later the head's
-  __shared__ unsigned n_list[2], s_base[2];
+  __shared__ __attribute__((aligned(16))) u64 list[2][kList];  // the workgroup's boundary keys; later the head's
+  __shared__ unsigned n_list[2], s_base[2], s_ext[2][2];
   __shared__ u64 red[WPB];
   __shared__ unsigned hist[2][kSubWords];
   __shared__ Pick pick[2];
@@ -764,18 +803,43 @@ __global__ __launch_bounds__(BT) void idx_count_kernel(IdxArgs a) {
   const unsigned *src = array_of(a, arr, h);
   auto list_of = [&](int k) { return arr == 2 ? a.list_blk + (size_t)h * cap : a.list_vs + ((size_t)h * 4 + arr + 2 * k) * cap; };
   if (tid < 2) n_list[tid] = 0u;
+  if (tid < 4) (&s_ext[0][0])[tid] = 0u;
   Ranges r;
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     const int q = sel_of(arr, k < ns ? k : 0);
     r.lo[k] = G->lo[q]; r.last[k] = G->last[q]; r.rank[k] = G->rem[q]; r.n[k] = G->pop[q];
   }
+  // A range with more keys than its list takes holds stretches of equal scores, or nearly equal ones.  Its keys
+  // are counted instead: each of them per wave part where the range has no more than kDense (what is left of a bin
+  // after the refine pass), else all together with their smallest and largest.  32 heads, 128K tokens, the index
+  // alone (scores without ties 108 us): v and s constant 192 us, block map constant 173, 99 of 100 blocks 0 185.
+  // (One workgroup per array that walks it for them takes 1.73, 3.15 and 5.97 ms.)
+  const bool dense[2] = {r.n[0] > cap, ns > 1 && r.n[1] > cap}, any_dense = dense[0] || dense[1];
+  typedef unsigned __attribute__((may_alias)) word;
+  word *counts[2] = {(word *)list[0], (word *)list[1]};  // [2][WPB][kDense], where the list would be
+  static_assert(2 * WPB * kDense * sizeof(unsigned) <= sizeof(list[0]), "counts in place of a list");
+  if (any_dense)
+    for (int i = tid; i < (int)(sizeof(list) / 16); i += BT) ((uint4 *)&list[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
 
   const int part = ro.p * WPB + wv;
   {
     const unsigned lom = km ? r.lo[1] : r.lo[0], lastm = km ? r.last[1] : r.last[0];
-    const bool fitm = (km ? r.n[1] : r.n[0]) <= cap, fitp = arr < 2 && r.n[0] <= cap;  // no list where it would not hold them all
+    // of a dense range; a wide one: number of keys, largest key and largest ~key, a counter of each lane's own
+    auto count = [&](int k, const Four &f, unsigned bits) {
+      const unsigned lo = k ? r.lo[1] : r.lo[0], last = k ? r.last[1] : r.last[0];
+      word *c = (k ? counts[1] : counts[0]) + wv * kDense;
+      if (last - lo < kDense) {
+        count_keys(f, bits, lo, 0, c);
+      } else {
+        word *up = c + WPB * kDense + lane, *down = up + 64;
+        c[lane] += (unsigned)__popc(bits);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if ((bits >> j) & 1u) { *up = max((unsigned)*up, f.k[j]); *down = max((unsigned)*down, ~f.k[j]); }
+      }
+    };
     unsigned gt = 0;
     u64 ts = 0;
     visit(a, arr, src, part, [&](const Four &f) {
@@ -791,8 +855,10 @@ __global__ __launch_bounds__(BT) void idx_count_kernel(IdxArgs a) {
           else inp |= 1u << j;
         }
       }
-      inm = fitm ? inm : 0u;
-      inp = fitp ? inp : 0u;
+      if (any_dense) {
+        if (dense[km]) { count(km, f, inm); inm = 0u; }
+        if (arr < 2 && dense[0]) { count(0, f, inp); inp = 0u; }
+      }
       unsigned k0 = f.k[0], k1 = f.k[1], k2 = f.k[2], k3 = f.k[3];
       while (inm | inp) {
 #pragma unroll 1
@@ -828,6 +894,27 @@ __global__ __launch_bounds__(BT) void idx_count_kernel(IdxArgs a) {
     u64 *to = list_of(k);
     for (unsigned i = tid; i < n; i += BT) agent_store(&to[b + i], list[k][i]);
   }
+  if (any_dense) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      if (dense[k]) {  // 16 bits each: a part has 32768 entries at most
+        const word *c = counts[k] + wv * kDense, *ext = c + WPB * kDense;
+        unsigned *to = (unsigned *)list_of(k) + part * (kDense / 2);
+        if (r.last[k] - r.lo[k] < kDense) {
+          agent_store(to + lane, c[2 * lane] | c[2 * lane + 1] << 16);
+        } else {
+          const unsigned n = wave_inclusive_sum(c[lane]);
+          agent_store(to + 63 - lane, lane == 63 ? n : 0u);  // the last lane has the sum, word 0 takes it
+          if (ext[lane]) atomicMax(&s_ext[k][0], ext[lane]);
+          if (ext[64 + lane]) atomicMax(&s_ext[k][1], ext[64 + lane]);
+        }
+      }
+    __syncthreads();
+    if (tid < 4 && s_ext[tid >> 1][tid & 1])
+      atomicMax((tid & 1 ? G->dense_inv : G->dense_max) + sel_of(arr, tid >> 1), s_ext[tid >> 1][tid & 1]);
+  }
+  static_assert(kDense == 128, "two counts per lane");
+  static_assert((long long)kMaxNb * kMaxNb / kMaxBlkParts < 65536, "counts of 16 bits");
   if (!arrives_last(&G->ticket[2][arr], ro.n)) return;
 
   // ---- one workgroup: the exact threshold of every selection on this array.  All reads that pass the
@@ -838,24 +925,67 @@ __global__ __launch_bounds__(BT) void idx_count_kernel(IdxArgs a) {
   for (int j = 0; j < 2; ++j)
     own[j] = 2 * tid + j < nparts ? agent_load(arr == 2 ? &G->bgt[2 * tid + j] : &G->wgt[arr][2 * tid + j]) : 0u;
   u64 ts = tid == 0 && arr < 2 ? agent_load(&G->topsum[arr]) : 0ull;
-  const bool listed = r.n[0] <= cap && r.n[1] <= cap;
-  const unsigned n0 = r.n[0], n1 = r.n[1];
-  if (listed)
-    for (int k = 0; k < ns; ++k)
-      for (unsigned i = tid; i < min(k ? n1 : n0, (unsigned)kList); i += BT) list[k][i] = agent_load(&list_of(k)[i]);
+  unsigned m[2] = {dense[0] ? 0u : r.n[0], ns > 1 && !dense[1] ? r.n[1] : 0u};  // on the lists
+  for (int k = 0; k < ns; ++k)
+    for (unsigned i = tid; i < min(m[k], (unsigned)kList); i += BT) list[k][i] = agent_load(&list_of(k)[i]);
   for (int i = tid; i < nparts; i += BT) { pgt[i] = 0u; peq[i] = 0u; }
   if (tid < 2) n_list[tid] = 0u;
   if (ns == 1) r.lo[1] = r.last[1] = r.n[1] = 0u;
   __syncthreads();
-  if (!listed) {
-    // Even the refined range of a selection did not fit its list: whole stretches of equal scores.
+  bool counted = true;  // every dense range has kDense different keys at most, or a single one
+  if (any_dense) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      if (dense[k] && r.last[k] - r.lo[k] >= kDense) {
+        const unsigned key = agent_load(&G->dense_max[sel_of(arr, k)]);
+        counted = counted && key == ~agent_load(&G->dense_inv[sel_of(arr, k)]);
+      }
+  }
+  if (any_dense && !counted) {
+    // A wide range of different keys, more than a list takes: below the lowest bin (or above the highest) only.
     const unsigned top[2] = {r.last[0], r.last[1]};
     narrow<BT>(a, arr, src, nparts, ns, hist, pick, wsum, r);
     collect<BT>(a, arr, src, nparts, ns, r, top, list, n_list, pgt, peq, ts);
+    m[0] = n_list[0]; m[1] = n_list[1];
+  } else if (any_dense) {
+#pragma unroll 1
+    for (int k = 0; k < ns; ++k) {
+      if (!(k ? dense[1] : dense[0])) continue;
+      const unsigned *c = (const unsigned *)list_of(k) + lane;
+      unsigned lo = k ? r.lo[1] : r.lo[0];
+      if ((k ? r.last[1] : r.last[0]) - lo >= kDense) lo = agent_load(&G->dense_max[sel_of(arr, k)]);
+      for (int i = tid; i < kSubWords; i += BT) hist[k][i] = 0u;
+      __syncthreads();
+      unsigned n0 = 0, n1 = 0;
+#pragma unroll 8
+      for (int pt = wv; pt < nparts; pt += WPB) {
+        const unsigned x = agent_load(c + pt * (kDense / 2));
+        n0 += x & 0xFFFFu; n1 += x >> 16;
+      }
+      atomicAdd(&hist[k][2 * lane], n0);
+      atomicAdd(&hist[k][2 * lane + 1], n1);
+      __syncthreads();
+      block_find_kth<BT, kSubBins, 1>(hist[k], 1, k ? r.rank[1] : r.rank[0], 0u, &pick[k], wsum);
+      const unsigned d = pick[k].bin;
+      if (k == km) {
+#pragma unroll 4
+        for (int pt = wv; pt < nparts; pt += WPB) {
+          const unsigned x = agent_load(c + pt * (kDense / 2));
+          const unsigned lo16 = x & 0xFFFFu, hi16 = x >> 16;
+          const unsigned g = wave_inclusive_sum((2 * lane > (int)d ? lo16 : 0u) + (2 * lane + 1 > (int)d ? hi16 : 0u));
+          if (lane == 63) pgt[pt] = g;
+          if (lane == (int)(d >> 1)) peq[pt] = d & 1u ? hi16 : lo16;
+        }
+      } else if (tid > (int)d && tid < kDense) {
+        ts += (u64)hist[k][tid] * fx30(lo + (unsigned)tid);
+      }
+      if (k) { r.lo[1] = r.last[1] = lo + d; r.rank[1] = pick[1].rank; }
+      else { r.lo[0] = r.last[0] = lo + d; r.rank[0] = pick[0].rank; }
+    }
+    __syncthreads();
   }
-  const unsigned m0 = listed ? n0 : n_list[0], m1 = listed ? n1 : n_list[1];
   auto each = [&](int k, auto fn) {
-    for (unsigned i = tid; i < (k ? m1 : m0); i += BT) {
+    for (unsigned i = tid; i < (k ? m[1] : m[0]); i += BT) {
       const u64 it = i < kList ? list[k][i] : agent_load(&list_of(k)[i]);
       fn((unsigned)(it >> 32), (int)(unsigned)it);
     }
@@ -1197,10 +1327,17 @@ __global__ __launch_bounds__(BT) void idx_diag_rows_kernel(IdxArgs a) {
   }
 }
 
-int list_cap_vs(const Shape &sh) { return sh.N < kListVs ? sh.N : kListVs; }
+// Boundary keys a list takes (8 bytes each).  The same memory holds the counts of a range whose keys are counted
+// instead, kDense of 2 bytes per wave part; and a 128th of a large map, so that a range of many different keys fits
+// where it holds no more (an eighth of an octave below the lowest bin does, unless the map is nearly flat there).
+int list_cap_vs(const Shape &sh) {
+  const int counts = (sh.N + WPB * kVsUnits * kUnit - 1) / (WPB * kVsUnits * kUnit) * WPB * (kDense * 2 / 8);
+  return sh.N < kListVs ? sh.N : counts > kListVs ? counts : kListVs;
+}
+static_assert(kMaxBlkParts * (kDense * 2 / 8) <= kListBlk, "counts of all wave parts");
 int list_cap_blk(const Shape &sh) {
   const long long all = (long long)sh.nb * (sh.nb - 1) / 2 + 1;
-  return all < kListBlk ? (int)all : kListBlk;
+  return all < kListBlk ? (int)all : all / 128 > kListBlk ? (int)(all / 128) : kListBlk;
 }
 size_t round16(size_t x) { return (x + 15) & ~(size_t)15; }
 
@@ -1246,6 +1383,9 @@ IdxArgs index_args(const Shape &sh, const Workspace &ws, sa_scores in, const Ove
   a.Pb = (int)(((units + per - 1) / per + WPB - 1) / WPB);
   // under the per-row rule a wave of the emission takes whole rows
   if (sh.row_select) a.Pb = (sh.nb + WPB - 1) / WPB < 128 ? (sh.nb + WPB - 1) / WPB : 128;
+  // 1024 workgroups for up to 32 heads: where the launch has something to do, one or two heads need the chip too
+  a.refine_vs = min(a.Pv, max(kRefineVs, 32 * kRefineVs / sh.Hq));
+  a.refine_blk = min(a.Pb, max(kRefineBlk, 32 * kRefineBlk / sh.Hq));
   a.first = 0;
   a.decide_here = lazy || !one_launch(sh);
   a.nb_magic = ((1ull << 40) + sh.nb - 1) / sh.nb;
@@ -1300,7 +1440,7 @@ void launch_levels(IdxArgs a, bool vs, bool blk, hipStream_t st) {
   a.first = vs ? 0 : 2 * a.Pv;
   const dim3 grid((vs ? 2 * a.Pv : 0) + (blk ? a.Pb : 0), a.sh.Hq);
   idx_hist_kernel<<<grid, BT, 0, st>>>(a);
-  idx_refine_kernel<<<dim3((vs ? 2 * kRefineVs : 0) + (blk ? kRefineBlk : 0), a.sh.Hq), BT, 0, st>>>(a);
+  idx_refine_kernel<<<dim3((vs ? 2 * a.refine_vs : 0) + (blk ? a.refine_blk : 0), a.sh.Hq), BT, 0, st>>>(a);
   idx_count_kernel<<<grid, BT, 0, st>>>(a);
 }
 
