@@ -471,6 +471,36 @@ __device__ inline void narrow_step(int ns, unsigned (*hist)[kSubWords], Pick *pi
     }
 }
 
+// Counts the keys of `bits` (bit j: entry j of the lane) by their offset from lo, shifted: hist[(key - lo) >> shift].
+// For ranges that hold runs of equal keys: a wave that meets a single value adds once, a lane likewise; additions
+// of a wave to one counter take their turns otherwise, 64 of them for each entry of a lane.
+__device__ inline void count_keys(const Four &f, unsigned bits, unsigned lo, int shift, unsigned *hist) {
+  const u64 any = __ballot(bits != 0u);
+  if (any == 0ull) return;
+  unsigned d[4], mine = 0u;
+  bool same = true;
+#pragma unroll
+  for (int j = 3; j >= 0; --j) {
+    d[j] = (f.k[j] - lo) >> shift;
+    if ((bits >> j) & 1u) mine = d[j];
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) same = same && (!((bits >> j) & 1u) || d[j] == mine);
+  const unsigned first = (unsigned)__builtin_amdgcn_readlane((int)mine, __builtin_ctzll(any));
+  if (__all(bits == 0u || (same && mine == first))) {
+    unsigned n = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) n += __popcll(__ballot((bits >> j) & 1u));
+    if ((threadIdx.x & 63) == 0) atomicAdd(&hist[first], n);
+  } else if (same) {
+    if (bits) atomicAdd(&hist[mine], (unsigned)__popc(bits));
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if ((bits >> j) & 1u) atomicAdd(&hist[d[j]], 1u);
+  }
+}
+
 // One workgroup narrows the ranges by walks over the whole array until at most kList keys are left or
 // a single one, ...
 template <int NT>
@@ -487,11 +517,11 @@ __device__ inline void narrow(const IdxArgs &a, int arr, const unsigned *src, in
 #pragma unroll
         for (int k = 0; k < 2; ++k)
           if (want[k]) {
-            const int shift = digit_shift(r.last[k] - r.lo[k]);
+            unsigned bits = 0u;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              if (((f.ok >> j) & 1u) && f.k[j] >= r.lo[k] && f.k[j] <= r.last[k])
-                atomicAdd(&hist[k][(f.k[j] - r.lo[k]) >> shift], 1u);
+              if (((f.ok >> j) & 1u) && f.k[j] >= r.lo[k] && f.k[j] <= r.last[k]) bits |= 1u << j;
+            count_keys(f, bits, r.lo[k], digit_shift(r.last[k] - r.lo[k]), hist[k]);
           }
       });
     narrow_step<NT>(ns, hist, pick, wsum, want, r);
@@ -680,36 +710,6 @@ __global__ __launch_bounds__(BT) void idx_hist_kernel(IdxArgs a) {
     bin_range(pick[tid].bin, first_bin(a, ro.arr), G->lo[q], G->last[q]);
     G->rem[q] = pick[tid].rank;
     G->pop[q] = pick[tid].count;
-  }
-}
-
-// Counts the keys of `bits` (bit j: entry j of the lane) by their offset from lo, shifted: hist[(key - lo) >> shift].
-// For ranges that hold runs of equal keys: a wave that meets a single value adds once, a lane likewise; additions
-// of a wave to one counter take their turns otherwise, 64 of them for each entry of a lane.
-__device__ inline void count_keys(const Four &f, unsigned bits, unsigned lo, int shift, unsigned *hist) {
-  const u64 any = __ballot(bits != 0u);
-  if (any == 0ull) return;
-  unsigned d[4], mine = 0u;
-  bool same = true;
-#pragma unroll
-  for (int j = 3; j >= 0; --j) {
-    d[j] = (f.k[j] - lo) >> shift;
-    if ((bits >> j) & 1u) mine = d[j];
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) same = same && (!((bits >> j) & 1u) || d[j] == mine);
-  const unsigned first = (unsigned)__builtin_amdgcn_readlane((int)mine, __builtin_ctzll(any));
-  if (__all(bits == 0u || (same && mine == first))) {
-    unsigned n = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) n += __popcll(__ballot((bits >> j) & 1u));
-    if ((threadIdx.x & 63) == 0) atomicAdd(&hist[first], n);
-  } else if (same) {
-    if (bits) atomicAdd(&hist[mine], (unsigned)__popc(bits));
-  } else {
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if ((bits >> j) & 1u) atomicAdd(&hist[d[j]], 1u);
   }
 }
 
