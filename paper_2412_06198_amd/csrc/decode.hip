@@ -9,8 +9,9 @@
 // memory round trips (list lengths, list, rows, partial (max, sum, output) triple, arrival counter, all
 // triples of the head) and what a single wave issues in between: the workgroup that arrives last merges
 // instead of a second launch, and a list place is resolved by one lane, not by the 16 that read its row.
-// 8 heads, 4096-token prompt: 10.1 -> 7.1 us (an empty launch is 2.2); 32 heads, 128K-token prompt, 53 MB
-// of rows: 16.2 -> 10.5 us.
+// 8 heads, 4096-token prompt: 10.9 -> 6.8 us (an empty launch is 2.2); 32 heads, 128K-token prompt, 29 MB
+// of rows out of the memory-side cache: 16.3 -> 10.9 us, and 26.7 -> 15.0 (the kernels alone) where K and V
+// have been pushed out of it, as they are where a step reads other layers in between.
 #include <atomic>
 #include <mutex>
 
@@ -91,7 +92,8 @@ __device__ inline float sum16(float x) {
 }
 
 // Partial results cross workgroups inside the launch by agent-scope accesses, which pass the L2 caches
-// by: nothing has to be written back or invalidated on the way (fences at that scope cost 40 us here).
+// by: nothing has to be written back or invalidated on the way (fences at that scope cost 40 us here).  They
+// are ordered before the arrival by vmcnt(0) and the workgroup's barrier, see the top of index.hip.
 __device__ inline void put(float *p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline float get(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 

@@ -16,8 +16,8 @@
 //    writes its causal row softmax once.
 // The first launch is pass 1; the second holds the workgroups of pass 2 (bound by exp and vector
 // ALU) spread among those of the block map (bound by the HBM stream of Q), which needs the K means of
-// pass 1.  One stream, no events: with five launches on two streams 4 heads of 4096 tokens took 59 us,
-// now 18; 32 heads at 10K, 16K and 32K tokens 62, 74 and 122, now 54, 63 and 113; at 128K both take 390.
+// pass 1.  One stream, no events: with five launches on two streams 4 heads of 4096 tokens took 55 us,
+// now 18; 32 heads at 10K, 16K, 32K, 64K and 128K tokens 59, 78, 122, 189 and 394, now 55, 65, 114, 183 and 364.
 #include "sa_internal.h"
 
 namespace sa {
@@ -612,7 +612,7 @@ __device__ inline void window_scores(int L, uint16_t (*Ks)[64 * 128], const uint
 // rows 4(l/16) + r.  The column tiles of the strip go round-robin to the four waves and stay in
 // registers (MT tiles per wave) until the row maxima and sums are known, so blk is written exactly
 // once.  Strips are taken longest first.  Bound by the HBM stream of Q, which runs at 5 TB/s with the
-// workgroups of pass 2 beside it (278 us at 128K tokens and 32 heads).
+// workgroups of pass 2 beside it (281 us at 128K tokens and 32 heads).
 template <int MT>
 __device__ inline void block_map_strip(int L, char *lds, const uint16_t *__restrict__ Q,
                                        const float *__restrict__ kblk, const Shape &sh, float c2,
@@ -676,7 +676,7 @@ __device__ inline void block_map_strip(int L, char *lds, const uint16_t *__restr
       for (int r = 0; r < 4; ++r) acc[k][r] = -INFINITY;
     }
   }
-  // row maxima: over this lane's tiles, the 16 lanes of a group, the eight waves
+  // row maxima: over this lane's tiles, the 16 lanes of a group, the four waves
   float mx[4], sm[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -809,8 +809,8 @@ hipError_t launch_estimate_part(const Shape &sh, const Workspace &ws, const uint
   }
   const int wu = what == EstimatePart::BlockMap ? 0 : (windows + 7) / 8;
   const int units = wu + (what == EstimatePart::Windows ? 0 : (nstrips * sh.Hq + 7) / 8);
-  // 4/5: 386 us for the estimator at 128K tokens; all units 409 (pass 2 is left for the end), the first ones 408
-  // (it does not run beside the stream any more); 16K and 32K alike
+  // 4/5: 364 us for the estimator at 128K tokens, 114 at 32K; all units 388 and 119 (pass 2 is left for the end), the
+  // first ones 388 and 121 (it does not run beside the stream any more); 65, 65 and 62 at 16K
   int spread = units * 4 / 5;
   if (spread < wu) spread = wu;
   if (spread < 1) spread = 1;

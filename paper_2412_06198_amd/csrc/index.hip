@@ -22,11 +22,14 @@
 // are done by the workgroup of a head and array that arrives last, not by launches of their own:
 // an integer ticket says who that is, nobody waits.  What it reads from the others travels in
 // atomic operations and agent-scope loads and stores (which pass the L2 caches by), each completed
-// before the ticket is drawn, so that no cache has to be written back or invalidated on the way.
+// before the ticket is drawn (vmcnt(0) in every wave, then the workgroup's barrier), so that no cache has to
+// be written back or invalidated on the way.  The order rests on gfx950 there: a memory operation that
+// the counter reports as done has been performed at its scope.  The language promises nothing of the kind
+// for relaxed atomics, and the fences that would cost an L2 write-back per workgroup.
 // Every launch costs 3 to 8 us whatever it does, and a pass over the scores of 32 heads 10 to 40 us.
 // Short prompts take two launches, see idx_select_kernel.  With ten launches and five passes before,
-// 32 heads took 85 us at 16K tokens, 105 at 32K, 113 at 64K and 170 at 128K; now 41, 54, 59 and 103
-// (4 heads at 4K: 70 and 14).
+// 32 heads took 83 us at 10K tokens, 86 at 16K, 105 at 32K, 113 at 64K and 175 at 128K; now 30, 40, 55, 60 and
+// 103 (4 heads at 4K: 66 and 14).
 //
 // With the per-row block rule (every row block of a Block-Cluster head keeps the
 // same fraction of its causal blocks) the fifth selection is switched off and
