@@ -33,11 +33,12 @@ constexpr int kMaxDevices = 64;
 // A head's arrival counter lives in floats 2 and 3 of its first partial: the step's token in the upper 48
 // bits, in the lower 16 the number of workgroups that have arrived.  The memory may hold anything: what the
 // caller's workspace was used for before, or the count of a step that overlapped another one or never ended.
-// A step takes only its own token for a count: the first workgroup that finds another value there puts the
-// token with a count of 0, and nothing is read from what was left.  Each launch has a token of its own, so
-// that no clearing launch is needed; a recorded one repeats its token with every replay, so there the counters
-// are cleared by a launch before it (8 heads, 4096 tokens: 8.4 us a recorded step instead of 6.6; a count that
-// the last one to arrive put back to 0 cost 0.1 us less, and what an overlapping step left there stayed for good).
+// A step takes only its own token for a count: a head's first workgroup puts the token there while its rows are
+// on their way, one that arrives before that does it itself, and nothing is read from what was left.  Each
+// launch has a token of its own, so that no clearing launch is needed; a recorded one repeats its token with
+// every replay, so there the counters are cleared by a launch before it (8 heads, 4096 tokens: 8.4 us a
+// recorded step instead of 6.6; a count that the last one to arrive put back to 0 cost 0.1 us less, and what an
+// overlapping step left there stayed for good).
 constexpr int kCountBits = 16;
 
 struct DecArgs {
@@ -184,9 +185,10 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs p) {
   if (sp >= L.n) return;
   float *part = p.part + (size_t)h * p.S * kPartStride;
   uint64_t *arrived = (uint64_t *)(part + 2);
-  const bool counts = tid == kThreads - 1;  // in the wave with the fewest keys: 0.07 us less than in the first one
+  // the thread that counts the arrival, in the wave with the fewest keys (0.07 us less than in the first one)
+  const bool counts = tid == kThreads - 1, claims = counts && sp == 0;
   uint64_t seen = 0;
-  if (counts) seen = __hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (claims) seen = __hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int32_t *bc = p.blkcols + (size_t)h * p.cap_b + L.e0;
   const int32_t *colp = p.cols + (size_t)h * p.k_v;
   const int32_t *offp = p.offs + (size_t)h * p.k_s;
@@ -246,13 +248,6 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs p) {
     }
     return put_at > get_at;
   };
-  // The token into the counter, once a workgroup of this step has not been here yet: on its way while the rows are.
-  auto claim = [&] {
-    if (__hip_atomic_compare_exchange_strong(arrived, &seen, p.token, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT))
-      seen = p.token;
-  };
-  if (counts && (seen ^ p.token) >> kCountBits) claim();
   const int slot = lane >> 4;
   uint4 kx[2][U], vx[2][U];
   int cnt[2];
@@ -307,6 +302,10 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs p) {
   // the rows of a step are read while the step before is computed
   if (resolve()) {
     fetch(kx[0], vx[0], cnt[0]);
+    // the token into the counter, unless a workgroup of this step has been there
+    if (claims && (seen ^ p.token) >> kCountBits)
+      (void)__hip_atomic_compare_exchange_strong(arrived, &seen, p.token, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
     for (;;) {
       const bool more = resolve();
       if (more) fetch(kx[1], vx[1], cnt[1]);
@@ -360,8 +359,17 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs p) {
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this thread's partials have been performed
   __syncthreads();
   if (counts) {
-    while ((seen ^ p.token) >> kCountBits) claim();  // only where other steps use the counter at the same time
-    const uint64_t before = __hip_atomic_fetch_add(arrived, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint64_t before = __hip_atomic_fetch_add(arrived, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while ((before ^ p.token) >> kCountBits) {  // added to a value that is not this step's: nobody has been here yet
+      uint64_t cur = before + 1;                // ends: an exchange only fails where a workgroup has changed the counter
+      if (__hip_atomic_compare_exchange_strong(arrived, &cur, p.token + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT))
+        before = p.token;  // this one put the token there, and itself
+      else if ((cur ^ p.token) >> kCountBits)
+        before = cur - 1;
+      else
+        before = __hip_atomic_fetch_add(arrived, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     s_last = before == p.token + (uint64_t)(L.n - 1);
   }
   __syncthreads();
