@@ -37,6 +37,9 @@ constexpr int kRunBits = 6, kRun = 1 << kRunBits;
 constexpr int NWORDS = kMaxSeq / BK / 32;
 constexpr int kPlanWaves = 4;     // items per workgroup of index_prepare_kernel
 constexpr unsigned kNoItem = ~0u;
+// Diagonals whose scores are taken before their products with V: as many as leave two workgroups a compute
+// unit's LDS.
+constexpr int kDiagBatch = 28;
 
 struct AttnArgs {
   const uint16_t *Q, *K, *V;
@@ -75,15 +78,6 @@ __host__ __device__ inline int tickets_per_head(int nT, int share) {
 // scalar loads, which neither occupy the vector memory path nor count in vmcnt.
 typedef const uint32_t __attribute__((address_space(4))) *const_u32p;
 __device__ inline uint32_t uload(const void *p, int idx) { return ((const_u32p)(uintptr_t)p)[idx]; }
-
-// 32 bits of a bitmap starting at bit `pos` (may be negative or run past the end); pos wave-uniform.
-__device__ inline uint32_t bits_window32(const uint32_t *bm, int nw, int pos) {
-  const int wi = pos >> 5, sh = pos & 31;  // arithmetic shift: floor for negatives
-  uint32_t lo = uload(bm, min(max(wi, 0), nw - 1)), hi = uload(bm, min(max(wi + 1, 0), nw - 1));
-  lo = (wi >= 0 && wi < nw) ? lo : 0u;
-  hi = (wi + 1 >= 0 && wi + 1 < nw) ? hi : 0u;
-  return (uint32_t)(((uint64_t)lo | ((uint64_t)hi << 32)) >> sh);
-}
 
 // Item id = queue + 8 * ticket: which head and row block it is, and the list of its key tiles.
 // Ticket k of queue qn: k / per_q selects the KV head, the rest walks the row blocks from the last
@@ -284,7 +278,10 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
   __shared__ __attribute__((aligned(16))) uint16_t Ks[2][BK * 128];
   __shared__ __attribute__((aligned(16))) uint16_t Vs[2][BK * 128];
   __shared__ uint32_t kept0[NWORDS], kept1[NWORDS];
-  __shared__ uint16_t tlist[kMaxSeq / BK];
+  // the item's list of key tiles; later the scores of a batch of diagonals, [offset][query]
+  __shared__ __attribute__((aligned(16))) float dscore[kDiagBatch * BQ];
+  static_assert(sizeof(dscore) >= kMaxSeq / BK * 2, "holds the list");
+  uint16_t *const tlist = (uint16_t *)dscore;
 
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);  // wave-uniform for the compiler too
 
@@ -653,38 +650,31 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
 
   // ---- selected diagonals: one 32-key tile per (wave, offset), no workgroup barriers -----------
   // For offset o the 32 queries of this wave need the 32 keys r0-o .. r0-o+31, and in
-  // S^T = K Q^T (32 keys x 32 queries) the wanted entries are the main diagonal.  K and V are
-  // copied by the LDS DMA into a wave-private K tile and V tile (8 KB each, swizzled like the
-  // shared tiles) and read from there like any tile.  An entry is dropped when its key block is
-  // kept by the CSR or its key is a selected column: those tiles already counted it.
-  // Nothing here is reused, so the phase lives on the memory path: the next offset's K is
-  // requested as soon as S^T has read this offset's K tile, its V as soon as the PV product has
-  // read this offset's V tile, so each copy has half an offset to land.
+  // S^T = K Q^T (32 keys x 32 queries) the wanted entries are the main diagonal.  K and V tiles are
+  // copied by the LDS DMA into two wave-private 8 KB buffers in turn (swizzled like the shared tiles)
+  // and read from there like any tile, the copies of one running while the one before is multiplied.
+  // An entry is dropped when its key block is kept by the CSR or its key is a selected column: those
+  // tiles already counted it.
+  // The phase waits for its rows: copies of such tiles run at 33 TB/s out of an L2 on this chip and at 8 TB/s out
+  // of the memory-side cache, and little of what a row block reads is in its XCD's L2 (nearby row blocks reach
+  // the same keys at another offset and another time).  So the chain between two copies is kept short: which
+  // queries take an entry is worked out for 64 offsets at once, one per lane, and the scores of a batch of offsets
+  // are taken from K before their products with V, so that the row maximum is exchanged and compared once a
+  // batch and either copy has a whole step of the other buffer to land.  Against K and V of one offset after the
+  // other, the bitmaps read at each: 32 heads, 128K tokens 1025 -> 995 us of diagonals, 32K 98 -> 93, a layer of
+  // 16K 430 -> 421, 4K 55.8 -> 54.9.
   __builtin_amdgcn_s_setprio(0);
   if (tid == 0 && ticket < p.qcap) ticket = (int)atomicAdd(&p.queue[home], 1u);  // used at the next item
-  if (has_offs) __syncthreads();  // all waves are done with the shared tiles: reuse them as private V tiles
+  if (has_offs) __syncthreads();  // all waves are done with the shared tiles and the list: reuse them
   if (has_offs && r0 < N) {
     const int32_t *__restrict__ offp = p.offs + (size_t)h * p.k_s;
     const int no = min(max(p.n_offs[h], 0), p.k_s);
-    const int rmax = min(r0 + 31, N - 1);
     int dl = lane;
     asm volatile("" : "+v"(dl));  // this phase's lane constants are born here, not before the tile loop
     const int q = dl & 31, gg = dl >> 5, lane = dl;
-    int nd = 0;  // offsets are ascending: the usable ones (0 <= o <= last row of the wave) come first
-    for (int base = 0; base < no; base += 64) {
-      const int i = base + lane;
-      const int ov = i < no ? offp[i] : -1;
-      const unsigned long long bad = ~__ballot(i < no && ov >= 0 && ov <= rmax);
-      const int run = bad ? __ffsll(bad) - 1 : 64;
-      nd += run;
-      if (run < 64) break;
-    }
-    nd = __builtin_amdgcn_readfirstlane(nd);
-    // one 8 KB K tile and one 8 KB V tile per wave: waves 0, 1 in the V buffers, waves 2, 3 in the K buffers
-    uint16_t *Kw = (wv < 2 ? &Vs[0][0] : &Ks[0][0]) + (wv & 1) * (2 * 32 * 128);
-    uint16_t *Vw = Kw + 32 * 128;
-    const unsigned ldsKw = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)Kw;
-    const unsigned ldsVw = ldsKw + 32 * 256;
+    // two 8 KB tiles per wave: waves 0, 1 in the V buffers, waves 2, 3 in the K buffers
+    uint16_t *const tile0 = (wv < 2 ? &Vs[0][0] : &Ks[0][0]) + (wv & 1) * (2 * 32 * 128);
+    const unsigned ldsT = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)tile0;
     const int rstar = 4 * (q >> 3) + (q & 3);        // register of S^T that holds key_local == q
     const bool holder = gg == ((q >> 2) & 1);        // ... in this half of the lane pair
     const int vrow = lane >> 4;                      // copies: one instruction moves rows 4n + vrow
@@ -693,124 +683,161 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
     const unsigned kchunk = (unsigned)(((lane & 15) ^ vrow) << 4);
     const unsigned krow = (unsigned)(vrow * (int)p.kv_rs * 2);
     const uint32_t *kw = wv < 2 ? kept0 : kept1;
-    uint32_t cw = 0u;
-    // The copies of one offset: 32 K rows and 32 V rows, both global -> LDS.  (K used to be read
-    // straight into the operand registers, one row per lane: every quarter-wave of such a read
-    // touches 16 different cache lines, and the L1's tag lookups, 512 per wave and offset, were what
-    // this phase waited for.)
-#define SA_DIAG_COPY(src, o, fastv, chunkv, swzn, ldsb)                                           \
+    float *const dsc = dscore + 32 * wv + q;
+#define SA_DIAG_COPY(src, jb_, swzc, swzn, ldsb)                                                 \
   {                                                                                              \
-    const int jb_ = r0 - (o);                                                                    \
-    if (jb_ >= 0 && jb_ + 31 < N) {                                                              \
-      const uint16_t *b_ = (src) + (size_t)jb_ * p.kv_rs;                                        \
+    if ((jb_) >= 0) {                                                                            \
+      const uint16_t *b_ = (src) + (size_t)(jb_) * p.kv_rs;                                      \
       _Pragma("unroll") for (int n_ = 0; n_ < 8; ++n_)                                           \
-        SA_DMA16(b_ + (size_t)(4 * n_) * p.kv_rs, (fastv) + ((chunkv) ^ (unsigned)(swzn)), (ldsb) + n_ * 1024); \
-    } else { /* rows outside the sequence: clamped copies, masked out by the validity test */    \
+        SA_DMA16(b_ + (size_t)(4 * n_) * p.kv_rs, krow + ((swzc) ^ (unsigned)(swzn)), (ldsb) + n_ * 1024); \
+    } else { /* rows before the sequence: clamped copies, masked out by the validity test */     \
       _Pragma("unroll") for (int n_ = 0; n_ < 8; ++n_) {                                         \
-        const int rb_ = min(max(jb_ + 4 * n_, 0), N - 1);                                        \
-        const int dr_ = min(max(jb_ + 4 * n_ + vrow, 0), N - 1) - rb_; /* >= 0 */                \
+        const int rb_ = max((jb_) + 4 * n_, 0);                                                  \
+        const int dr_ = max((jb_) + 4 * n_ + vrow, 0) - rb_; /* >= 0 */                          \
         SA_DMA16((src) + (size_t)rb_ * p.kv_rs,                                                  \
-                 (unsigned)(dr_ * (int)p.kv_rs * 2) + ((chunkv) ^ (unsigned)(swzn)), (ldsb) + n_ * 1024); \
+                 (unsigned)(dr_ * (int)p.kv_rs * 2) + ((swzc) ^ (unsigned)(swzn)), (ldsb) + n_ * 1024); \
       }                                                                                          \
     }                                                                                            \
   }
-#define SA_DIAG_ISSUE_K(o)                                                                       \
-  {                                                                                              \
-    if (has_cols) cw = bits_window32(colbm, N / 32, r0 - (o));                                   \
-    SA_DIAG_COPY(Kh, o, krow, kchunk, ((4 * n_) & 15) << 4, ldsKw)                               \
-  }
-#define SA_DIAG_ISSUE_V(o) SA_DIAG_COPY(Vh, o, (unsigned)(vrow * (int)p.kv_rs * 2), vchunk, 0, ldsVw)
-    // An offset whose (at most two) key tiles are both kept by the CSR contributes nothing here -
-    // every one of its entries was counted by those tiles - so it is skipped before any copy is
-    // issued.  The test is wave-uniform; `e` walks the offsets that are left.
-    auto dead = [&](int o_) {
-      const int jb_ = r0 - o_;
-      const int kta_ = max(jb_, 0) >> 6, ktb_ = max(jb_ + 31, 0) >> 6;
-      return (((kw[kta_ >> 5] >> (kta_ & 31)) & (kw[ktb_ >> 5] >> (ktb_ & 31))) & 1u) != 0u;
-    };
-    auto next_live = [&](int e_) {
-      while (e_ < nd && __builtin_amdgcn_readfirstlane((int)dead((int)uload(offp, e_)))) ++e_;
-      return e_;
-    };
-    int e = next_live(0);
-    if (e < nd) {
-      const int o0 = (int)uload(offp, e);
-      SA_DIAG_ISSUE_K(o0);
-      SA_DIAG_ISSUE_V(o0);
-    }
-    while (e < nd) {
-      const int o = (int)uload(offp, e);
-      const int e_nxt = next_live(e + 1);
-      const int onext = (int)uload(offp, min(e_nxt, nd - 1));
-      const int jb = r0 - o;
-      f32x16 sd;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sd[r] = 0.f;
-      // K of this offset has landed once only the 8 copies of its V, issued after it, are outstanding
-      __builtin_amdgcn_s_waitcnt(0x0F78);  // vmcnt(8)
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks)
-        sd = __builtin_amdgcn_mfma_f32_32x32x16_bf16(SA_KFRAG(Kw, 0, ks), qf[ks], sd, 0, 0, 0);
-      float sv = sd[0];
-#pragma unroll
-      for (int r = 1; r < 16; ++r) sv = (r == rstar) ? sd[r] : sv;
-      const bool cbit = (cw >> q) & 1u;
-      // the K tile has been read into the matrix pipe: the next offset's K may land
-      if (e_nxt < nd) SA_DIAG_ISSUE_K(onext);
-      // validity of (query iq, key iq - o)
-      const int j = iq - o;
-      bool valid = holder && j >= 0 && iq < N;
-      {
-        const int kta = max(jb, 0) >> 6, ktb = max(jb + 31, 0) >> 6;  // the (at most two) key tiles touched
-        const bool ba = (kw[kta >> 5] >> (kta & 31)) & 1u, bb = (kw[ktb >> 5] >> (ktb & 31)) & 1u;
-        if (((max(j, 0) >> 6) == kta) ? ba : bb) valid = false;
-        if (has_cols && cbit) valid = false;
-      }
-      if constexpr (STATS) {
-        st_kept += valid ? 1u : 0u;
-        st_tiles += 1u;
-      }
-      float sm = valid ? sv : -INFINITY;
-      sm = max_pair(sm);  // both lanes of the pair know the row's score
-      const float m_new = fmaxf(m_run, sm * p.c);
-      if (__any(m_new - m_run > 8.f)) {
-        const float alpha = __builtin_amdgcn_exp2f(m_run - ((m_new == -INFINITY) ? 0.f : m_new));
-        m_run = m_new;
-        l_run *= alpha;
-#pragma unroll
-        for (int db = 0; db < 4; ++db)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
-      }
-      const float m_ref = (m_run == -INFINITY) ? 0.f : m_run;
-      const float pv = valid ? __builtin_amdgcn_exp2f(__builtin_fmaf(sv, p.c, -m_ref)) : 0.f;
-      const __bf16 pvb = (__bf16)pv, zb = (__bf16)0.f;
-      l_run += (float)pvb;  // the weight as the matrix pipe sees it (see the tile loop's normaliser)
-      // V of this offset has landed once only the 8 copies of the next K, issued after it, are
-      // outstanding
-      if (e_nxt < nd) __builtin_amdgcn_s_waitcnt(0x0F78);  // vmcnt(8)
-      else __builtin_amdgcn_s_waitcnt(0x0F70);                       // vmcnt(0)
-      // P^T is diagonal: slot e2 of k-step u is register 8u+e2
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        bf16x8 pb;
-#pragma unroll
-        for (int e2 = 0; e2 < 8; ++e2) pb[e2] = (8 * u + e2 == rstar) ? pvb : zb;
-#pragma unroll
-        for (int db = 0; db < 4; ++db) {
-          const s16x4 lo = SA_VTR(Vw, db, 16 * u);
-          const s16x4 hi = SA_VTR(Vw, db, 16 * u + 8);
-          const s16x8 av = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-          oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), pb,
-                                                             oacc[db], 0, 0, 0);
+    for (int base = 0; base < no; base += 64) {
+      // One offset per lane: which of the wave's queries (bit q) take its entry.  Offsets are ascending:
+      // the usable ones (0 <= o <= last row of the wave) come first.
+      const int ov = base + lane < no ? offp[base + lane] : -1;
+      const unsigned long long bad = ~__ballot(ov >= 0 && ov <= r0 + 31);
+      const int run = bad ? __ffsll(bad) - 1 : 64;
+      uint32_t take = 0u;
+      if (lane < run) {
+        const int jb = r0 - ov;
+        const int kta = max(jb, 0) >> 6, ktb = (jb + 31) >> 6;  // the (at most two) key tiles touched
+        const int cut = 64 * (kta + 1) - jb;                    // queries below it take a key of the first
+        const uint32_t first = cut >= 32 ? ~0u : (1u << cut) - 1u;
+        take = jb >= 0 ? ~0u : ~0u << -jb;
+        if ((kw[kta >> 5] >> (kta & 31)) & 1u) take &= ~first;
+        if ((kw[ktb >> 5] >> (ktb & 31)) & 1u) take &= kta == ktb ? 0u : first;
+        if (has_cols) {
+          const int wi = jb >> 5;
+          const uint32_t lo = wi >= 0 ? colbm[wi] : 0u, hi = (jb & 31) ? colbm[wi + 1] : 0u;
+          take &= ~(uint32_t)(((uint64_t)lo | ((uint64_t)hi << 32)) >> (jb & 31));
         }
       }
-      // the V tile has been read: the next offset's V may land
-      if (e_nxt < nd) SA_DIAG_ISSUE_V(onext);
-      e = e_nxt;
+      // An offset that no query takes is passed over.  The others in even batches; of the batch whose
+      // copies are issued: its offsets (i_all), those still to be issued in this pass (i_left), which pass.
+      unsigned long long rest = __ballot(take != 0u);
+      const int n_live = __popcll(rest), n_batch = (n_live + kDiagBatch - 1) / kDiagBatch;
+      const int per_batch = n_batch ? (n_live + n_batch - 1) / n_batch : 0;
+      auto next_batch = [&]() {
+        const bool mine = (rest >> lane) & 1ull;
+        const unsigned long long b = __ballot(mine && __popcll(rest & ((1ull << lane) - 1ull)) < per_batch);
+        rest &= ~b;
+        return b;
+      };
+      unsigned long long i_all = next_batch(), i_left = i_all;
+      bool i_v = false;
+      int n_out = 0, ibuf = 0, cbuf = 0;  // tiles in flight; buffers of the next copy and of the next product
+      auto issue = [&]() {
+        if (i_left == 0ull) {
+          if (!i_v) {
+            i_v = true;
+          } else {
+            i_all = next_batch();
+            i_v = false;
+          }
+          i_left = i_all;
+          if (i_left == 0ull) return;
+        }
+        const int jb = r0 - __builtin_amdgcn_readlane(ov, __ffsll(i_left) - 1);
+        i_left &= i_left - 1ull;
+        const unsigned ldsb = ldsT + ibuf * (32 * 256);
+        if (i_v) SA_DIAG_COPY(Vh, jb, vchunk, 0, ldsb)
+        else SA_DIAG_COPY(Kh, jb, kchunk, ((4 * n_) & 15) << 4, ldsb)
+        ibuf ^= 1;
+        ++n_out;
+      };
+      auto landed = [&]() {  // the oldest tile in flight has arrived
+        if (n_out > 1) __builtin_amdgcn_s_waitcnt(0x0F78);  // vmcnt(8)
+        else __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0)
+        asm volatile("" ::: "memory");
+        --n_out;
+      };
+      if (i_all != 0ull) {
+        issue();
+        issue();
+      }
+      while (n_out > 0) {
+        const unsigned long long batch = i_all;  // copies run two tiles ahead, never past the batch after this one
+        float smax = -INFINITY;
+        int slot = 0;
+        for (unsigned long long left = batch; left != 0ull; left &= left - 1ull, ++slot) {
+          const uint32_t tk = (uint32_t)__builtin_amdgcn_readlane((int)take, __ffsll(left) - 1);
+          landed();
+          const uint16_t *Kw = tile0 + cbuf * (32 * 128);
+          bf16x8 kf[8];
+#pragma unroll
+          for (int ks = 0; ks < 8; ++ks) kf[ks] = SA_KFRAG(Kw, 0, ks);
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the tile is in registers: its buffer is free
+          __builtin_amdgcn_sched_barrier(0);
+          cbuf ^= 1;
+          issue();
+          f32x16 sd;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sd[r] = 0.f;
+#pragma unroll
+          for (int ks = 0; ks < 8; ++ks)
+            sd = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], sd, 0, 0, 0);
+          float sv = sd[0];
+#pragma unroll
+          for (int r = 1; r < 16; ++r) sv = (r == rstar) ? sd[r] : sv;
+          const float sm = max_pair(holder && ((tk >> q) & 1u) ? sv : -INFINITY);  // both lanes of the pair know it
+          smax = fmaxf(smax, sm);
+          dsc[slot * BQ] = sm;
+          if constexpr (STATS) {
+            st_kept += holder && ((tk >> q) & 1u) ? 1u : 0u;
+            st_tiles += 1u;
+          }
+        }
+        const float m_new = fmaxf(m_run, smax * p.c);
+        if (__any(m_new - m_run > 8.f)) {
+          const float alpha = __builtin_amdgcn_exp2f(m_run - ((m_new == -INFINITY) ? 0.f : m_new));
+          m_run = m_new;
+          l_run *= alpha;
+#pragma unroll
+          for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
+        }
+        const float m_ref = (m_run == -INFINITY) ? 0.f : m_run;
+        slot = 0;
+        for (unsigned long long left = batch; left != 0ull; left &= left - 1ull, ++slot) {
+          const uint32_t tk = (uint32_t)__builtin_amdgcn_readlane((int)take, __ffsll(left) - 1);
+          const float sv = dsc[slot * BQ];
+          const float pv = holder && ((tk >> q) & 1u) ? __builtin_amdgcn_exp2f(__builtin_fmaf(sv, p.c, -m_ref)) : 0.f;
+          const __bf16 pvb = (__bf16)pv, zb = (__bf16)0.f;
+          l_run += (float)pvb;  // the weight as the matrix pipe sees it (see the tile loop's normaliser)
+          landed();
+          const uint16_t *Vw = tile0 + cbuf * (32 * 128);
+          s16x4 vf[16];
+#pragma unroll
+          for (int i = 0; i < 16; ++i) vf[i] = SA_VTR(Vw, (i >> 1) & 3, 16 * (i >> 3) + 8 * (i & 1));
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          __builtin_amdgcn_sched_barrier(0);
+          cbuf ^= 1;
+          issue();
+          // P^T is diagonal: slot e2 of k-step u is register 8u+e2
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            bf16x8 pb;
+#pragma unroll
+            for (int e2 = 0; e2 < 8; ++e2) pb[e2] = (8 * u + e2 == rstar) ? pvb : zb;
+#pragma unroll
+            for (int db = 0; db < 4; ++db) {
+              const s16x8 av = __builtin_shufflevector(vf[8 * u + 2 * db], vf[8 * u + 2 * db + 1], 0, 1, 2, 3, 4, 5, 6, 7);
+              oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), pb,
+                                                                 oacc[db], 0, 0, 0);
+            }
+          }
+        }
+      }
     }
-#undef SA_DIAG_ISSUE_K
-#undef SA_DIAG_ISSUE_V
 #undef SA_DIAG_COPY
   }
 
