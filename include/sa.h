@@ -223,7 +223,7 @@ sa_status sa_sparse_decode_static(sa_ctx *ctx, const void *q, const void *K, con
  * Q, K, V, scores: device, as for the other calls (scores from sa_estimate_patterns).  scratch:
  * DEVICE, 256-byte aligned, sa_search_scratch_bytes bytes, owned by the caller.  out_host: HOST
  * array of n_q_heads results, candidates in pattern-id order.  The call runs the index builder and
- * the attention kernel of this library on batches of heads (as many as 2 GiB of scratch hold, one at
+ * the attention kernel of this library on batches of heads (as many as 2 GiB of scratch hold, at most 32, one at
  * least), waits for the stream after each batch (do not capture it in a graph) and returns when all
  * results are in out_host.  ctx's own workspace is not used. */
 typedef struct {

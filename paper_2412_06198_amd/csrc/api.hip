@@ -101,7 +101,7 @@ sa_status sa_create(const sa_config *cfg, sa_ctx **out) {
   if (!c) return SA_ERR_INVALID_ARG;
   c->cfg = *cfg;
   sa::Shape &s = c->sh;
-  s.Hq = cfg->n_q_heads; s.Hkv = cfg->n_kv_heads; s.g = s.Hq / s.Hkv;
+  s.Hq = cfg->n_q_heads; s.Hkv = cfg->n_kv_heads; s.g = s.gq = s.Hq / s.Hkv;
   s.N = cfg->seq_len; s.b = cfg->block; s.nb = nb; s.w = cfg->last_q;
   s.k_v = cfg->k_vertical; s.k_s = cfg->k_slash; s.k_b = cfg->k_blocks;
   s.sink = cfg->sink_blocks; s.local = cfg->local_blocks;
@@ -127,6 +127,8 @@ sa_status sa_create(const sa_config *cfg, sa_ctx **out) {
   s.cap_b = (int)cap;
   s.q_rs = cfg->q_row_stride ? cfg->q_row_stride : sa::kHeadDim;
   s.q_hs = cfg->q_head_stride ? cfg->q_head_stride : (int64_t)s.N * s.q_rs;
+  s.o_rs = s.q_rs;
+  s.o_hs = s.q_hs;
   s.kv_rs = cfg->kv_row_stride ? cfg->kv_row_stride : sa::kHeadDim;
   s.kv_hs = cfg->kv_head_stride ? cfg->kv_head_stride : (int64_t)s.N * s.kv_rs;
   if (s.q_rs % 8 || s.kv_rs % 8 || s.q_hs % 8 || s.kv_hs % 8 || s.q_rs < sa::kHeadDim ||

@@ -49,8 +49,8 @@ struct AttnArgs {
   const int32_t *colprefix;  // [Hq][N/32] selected columns before each word of colbits
   uint16_t *Kg, *Vg;  // [Hq][kvg_rows][kv_rs] selected key columns, gathered once per call
   int kvg_rows;
-  int Hq, Hkv, g, N, b, nb, nT, k_v, k_s, cap_b;
-  int64_t q_hs, q_rs, kv_hs, kv_rs;
+  int Hq, Hkv, g, gq, N, b, nb, nT, k_v, k_s, cap_b;
+  int64_t q_hs, q_rs, kv_hs, kv_rs, o_hs, o_rs;
   float c;  // softmax scale * log2(e)
   unsigned int *queue;           // [8] work-queue heads, zeroed by index_prepare_kernel
   int n_items;  // (head, row block) items in all
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
   // the item's other reads, all in flight together with the first tile's copies
   bf16x8 qf[8];  // Q^T fragments: B operand, lane = query, 8 consecutive d per k-step half
   {
-    const uint16_t *qrow = p.Q + (size_t)h * p.q_hs + (size_t)min(iq, N - 1) * p.q_rs;
+    const uint16_t *qrow = p.Q + (size_t)query_head(h, p.g, p.gq) * p.q_hs + (size_t)min(iq, N - 1) * p.q_rs;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) qf[ks] = *(const bf16x8 *)(qrow + 16 * ks + 8 * gg);
   }
@@ -875,7 +875,7 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
       const int r = 4 * n + rr;
       const uint4 v = *(const uint4 *)(ow + r * 256 + (pc << 4));
       if (r0 + r < N)
-        *(uint4 *)(p.O + (size_t)h * p.q_hs + (size_t)(r0 + r) * p.q_rs + ((pc ^ (r & 15)) << 3)) = v;
+        *(uint4 *)(p.O + (size_t)h * p.o_hs + (size_t)(r0 + r) * p.o_rs + ((pc ^ (r & 15)) << 3)) = v;
     }
   }
   }  // work-queue loop
@@ -916,10 +916,11 @@ hipError_t launch_sparse_prefill(const Shape &sh, const Workspace &ws, const uin
   a.n_cols = idx.n_cols; a.cols = idx.cols; a.n_offs = idx.n_offs; a.offs = idx.offs;
   a.rowptr = idx.rowptr; a.blkcols = idx.blkcols;
   a.colbits = ws.colbits; a.colprefix = ws.colprefix;
-  a.Hq = sh.Hq; a.Hkv = sh.Hkv; a.g = sh.g; a.N = sh.N; a.b = sh.b; a.nb = sh.nb;
+  a.Hq = sh.Hq; a.Hkv = sh.Hkv; a.g = sh.g; a.gq = sh.gq; a.N = sh.N; a.b = sh.b; a.nb = sh.nb;
   a.nT = (sh.N + BQ - 1) / BQ;
   a.k_v = sh.k_v; a.k_s = sh.k_s; a.cap_b = sh.cap_b;
   a.q_hs = sh.q_hs; a.q_rs = sh.q_rs; a.kv_hs = sh.kv_hs; a.kv_rs = sh.kv_rs;
+  a.o_hs = sh.o_hs; a.o_rs = sh.o_rs;
   a.c = sh.scale * 1.4426950408889634f;
   a.counters = counters;
   a.Kg = ws.kg; a.Vg = ws.vg; a.kvg_rows = (sh.k_v + BK - 1) / BK * BK;

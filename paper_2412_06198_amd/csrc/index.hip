@@ -410,7 +410,8 @@ constexpr int kList = 512;        // boundary keys of a selection that a workgro
 
 __device__ inline int first_bin(const IdxArgs &a, int arr) { return arr == 2 && a.sh.row_norm ? kBaseRowNorm : kBase; }
 __device__ inline const unsigned *array_of(const IdxArgs &a, int arr, int h) {
-  return arr == 2 ? a.blk + (size_t)h * a.sh.nb * a.sh.nb : (arr ? a.s : a.v) + (size_t)h * a.sh.N;
+  const size_t q = (size_t)query_head(h, a.sh.g, a.sh.gq);
+  return arr == 2 ? a.blk + q * a.sh.nb * a.sh.nb : (arr ? a.s : a.v) + q * a.sh.N;
 }
 
 // One wave part into the level-1 histogram; of v also the fixed-point sums over all keys and over
@@ -1187,7 +1188,7 @@ __global__ __launch_bounds__(BT) void idx_emit_kernel(IdxArgs a) {
   // block CSR
   int32_t *rp = a.out.rowptr + (size_t)h * (nb + 1);
   int32_t *bc = a.out.blkcols + (size_t)h * sh.cap_b;
-  const unsigned *hb = a.blk + (size_t)h * nb * nb;
+  const unsigned *hb = array_of(a, 2, h);
   int total;
   if (pat == SA_BLOCK_CLUSTER && T > 0) {
     // every workgroup finds its rows' pointers for itself: thread t sums the shares of RP rows

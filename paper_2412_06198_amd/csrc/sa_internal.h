@@ -20,6 +20,8 @@ struct HeadBudget { int32_t k_v, k_s, k_b, local; };
 // Everything the kernels need, resolved from sa_config at sa_create time.
 struct Shape {
   int Hq, Hkv, g, N, b, nb, w;
+  int gq;                         // query heads of a KV head in Q and the scores: g, or a part of it where every one
+                                  // of them is taken with several indices (head h is then query head h % gq of its group)
   int k_v, k_s, k_b, cap_b, sink, local;
   int probe_v, probe_s, lift_num, lift_den;
   int row_select;                 // Block-Cluster heads: 1 = every row keeps its own share of k_b
@@ -29,6 +31,7 @@ struct Shape {
   int chunk, nchunks;             // keys per estimator workgroup (window passes), ceil(N / chunk)
   int n_cu;                       // compute units of the device the context was created on
   int64_t q_hs, q_rs, kv_hs, kv_rs;
+  int64_t o_hs, o_rs;             // of the attention output: Q's
   float scale;
 };
 
@@ -45,6 +48,9 @@ struct Workspace {
   void *attn_items;               // what each ticket of the attention kernel's queues stands for (16 bytes)
   uint16_t *attn_tiles;           // [Hq][cap_b * block / 64] key-tile lists of the row blocks
 };
+
+// Head of Q and of the scores that head h stands for.
+__host__ __device__ inline int query_head(int h, int g, int gq) { return g == gq ? h : h / g * gq + h % gq; }
 
 size_t index_scratch_bytes(const Shape &sh);
 

@@ -6,12 +6,15 @@
 //   Evaluate Patterns - the head's dense causal output against the sparse output of every
 //     refined candidate, Frobenius norm of the difference, smallest wins (ties: lowest id).
 // All heads of a batch go through every step together, with budgets of their own each, and the host
-// waits once per batch.  The pairs of a Triangular or Block-Cluster candidate follow from its number
-// of blocks alone; those of an Interval-Slash candidate are counted from the selected columns and
-// offsets (slash_step_kernel), which also takes the head's next bisection step, so a probe is an
-// index build and one small kernel, and no attention runs before the sizes are known.  (With one
-// head at a time, an attention call per probe to count its pairs and a wait after each, 8 heads of
-// 4096 tokens took 35 ms; this takes 0.67.)
+// waits once per batch.  A head is taken with several indices at a time: index and attention launches see
+// kSets times as many heads as the batch has (Shape::gq), so that the dense reference and the three candidates are
+// one index build and one attention launch, and a step of the refinement evaluates three sizes, the one that the
+// bisection asks for and the two it can ask for next.  The pairs of a Triangular or Block-Cluster candidate follow from
+// its number of blocks alone; those of an Interval-Slash candidate are counted from the selected columns and
+// offsets (slash_step_kernel), which also takes the head's next steps, and no attention runs before the sizes are
+// known.  (With one head at a time, an attention call per probe to count its pairs and a wait after each, 8 heads
+// of 4096 tokens took 35 ms; with one index at a time, 13 index builds and four attention launches as long as
+// their longest row block each, 661 us; now 382.)
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -23,23 +26,31 @@
 namespace {
 
 constexpr int kNormBlocks = 1024;
+constexpr int kSets = 4;    // indices of a head in the last launches: dense, then the candidates
+constexpr int kProbes = 3;  // indices of a head in a refinement step
 constexpr size_t kBatchBytes = (size_t)2 << 30;  // scratch that a batch of heads may take (one head always may)
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// partial[head][blockIdx.x] = sum over the block's rows of (A - B)^2, A and B [heads][N][128] bf16 with
-// Q's strides (elements); fp64 accumulation, fixed order: bit-reproducible.  grid (blocks, heads)
-__global__ __launch_bounds__(256) void sq_diff_kernel(const uint16_t *__restrict__ A,
-                                                      const uint16_t *__restrict__ B, int N, int64_t hs,
-                                                      int64_t rs, double *__restrict__ partial) {
+// Virtual head of index `set` of head i, gb heads per KV head: a KV head's heads with their first index, with their
+// second, ...
+__host__ __device__ inline int virtual_head(int i, int set, int gb, int sets) { return (i / gb * sets + set) * gb + i % gb; }
+
+// partial[set - 1][head][block] = sum over the block's rows of (output with index set - output with index 0)^2,
+// O [virtual heads][N][128] bf16; fp64 accumulation, fixed order: bit-reproducible.
+// grid (blocks, heads, kSets - 1)
+__global__ __launch_bounds__(256) void sq_diff_kernel(const uint16_t *__restrict__ O, int gb, int N,
+                                                      double *__restrict__ partial) {
+  const size_t hs = (size_t)N * sa::kHeadDim;
   __shared__ double red[256];
   const int cc = threadIdx.x & 15, rg = threadIdx.x >> 4;
-  const size_t head = (size_t)blockIdx.y * hs;
+  const uint16_t *A = O + (size_t)virtual_head(blockIdx.y, blockIdx.z + 1, gb, kSets) * hs;
+  const uint16_t *B = O + (size_t)virtual_head(blockIdx.y, 0, gb, kSets) * hs;
   double acc = 0.0;
   // the rows of a block: kNormBlocks blocks' worth apart, whatever the grid (the sums of the blocks that
   // a short sequence leaves without rows are zero)
   for (int64_t i = (int64_t)blockIdx.x * 16 + rg; i < N; i += (int64_t)kNormBlocks * 16) {
-    const size_t o = head + (size_t)i * rs + cc * 8;
+    const size_t o = (size_t)i * sa::kHeadDim + cc * 8;
     const uint4 a = *(const uint4 *)(A + o), b = *(const uint4 *)(B + o);
     const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
@@ -55,7 +66,7 @@ __global__ __launch_bounds__(256) void sq_diff_kernel(const uint16_t *__restrict
     if ((int)threadIdx.x < d) red[threadIdx.x] += red[threadIdx.x + d];
     __syncthreads();
   }
-  if (threadIdx.x == 0) partial[(size_t)blockIdx.y * kNormBlocks + blockIdx.x] = red[0];
+  if (threadIdx.x == 0) partial[((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = red[0];
 }
 
 // RefineSearchSpace of one candidate, a step per evaluated size: the smallest size, the largest, then
@@ -64,10 +75,21 @@ struct Refine {
   int64_t lo, hi, p_lo, p_hi;  // sizes around the target and their pairs
   int64_t x, px;               // size to evaluate next, or (done) the answer and its pairs
   int32_t stage, done;
+  uint32_t arrived, unused;    // probes of this step whose pairs are counted
+  int64_t pairs[kProbes];
   __host__ __device__ void start(int64_t x_lo, int64_t x_hi) {
     lo = x = x_lo; hi = x_hi;
     p_lo = p_hi = px = 0;
     stage = done = 0;
+    arrived = unused = 0;
+    for (int i = 0; i < kProbes; ++i) pairs[i] = 0;
+  }
+  // Sizes of a step's probes: x, and what can follow it (x again where nothing can).
+  __host__ __device__ int64_t probe(int i) const {
+    if (i == 0 || done) return x;
+    if (stage == 0) return i == 1 ? hi : hi - lo > 1 ? (lo + hi) / 2 : x;
+    const int64_t l = i == 1 ? lo : x, h = i == 1 ? x : hi;
+    return h - l > 1 ? (l + h) / 2 : x;
   }
   __host__ __device__ void step(int64_t pairs, int64_t target, int64_t eps) {
     if (done) return;
@@ -104,44 +126,58 @@ __host__ __device__ inline sa::HeadBudget slash_budget(int64_t x, int N, int nb)
   return b;
 }
 
-// One workgroup per head: the kept pairs of the head's Interval-Slash index (its diagonal blocks, the
-// selected columns, the selected diagonals; each pair once), then the next step of its refinement.
+// One workgroup per virtual head of a refinement step: the kept pairs of its Interval-Slash index (its diagonal blocks,
+// the selected columns, the selected diagonals; each pair once).  The workgroup that counts a head's last
+// probe takes the steps of its bisection that the probes answer.
 //   diagonal blocks: nb b (b + 1) / 2
 //   column c: the queries behind its key block
 //   offset o: the pairs (i, i - o) in different blocks, less those whose key is a selected column,
 //     i.e. the columns c < N - o with c % b >= b - o
-__global__ __launch_bounds__(256) void slash_step_kernel(const int32_t *cols, const int32_t *offs, int k_v,
-                                                         int k_s, int N, int b, Refine *state,
-                                                         sa::HeadBudget *budget, int64_t target, int64_t eps) {
+constexpr int kStepThreads = 512, kStepCols = 8192;  // columns that are searched in LDS
+
+__global__ __launch_bounds__(kStepThreads) void slash_step_kernel(const int32_t *cols, const int32_t *offs, int k_v, int k_s,
+                                                                  int N, int b, int gb, Refine *state, sa::HeadBudget *probes,
+                                                                  sa::HeadBudget *last, int64_t target, int64_t eps) {
   __shared__ int by_pos[128];            // columns outside the last key block by their position in the block
   __shared__ int from[129];              // ... at position p or behind
-  __shared__ long long red[256];
-  const int h = blockIdx.x, tid = threadIdx.x, nb = N / b;
-  if (state[h].done) return;
-  const int nc = min(budget[h].k_v, N), no = min(budget[h].k_s, N);
+  __shared__ long long red[kStepThreads / 64];
+  __shared__ int32_t c_lds[kStepCols];
+  const int i0 = blockIdx.x, pr = blockIdx.y, h = virtual_head(i0, pr, gb, kProbes), tid = threadIdx.x, nb = N / b;
+  Refine *st = state + i0;
+  if (st->done) return;
+  const int nc = min(probes[h].k_v, N), no = min(probes[h].k_s, N);
   const int32_t *c = cols + (size_t)h * k_v, *o = offs + (size_t)h * k_s;
+  const bool in_lds = nc <= kStepCols;
   if (tid < b) by_pos[tid] = 0;
   __syncthreads();
   long long sum = 0;
-  for (int i = tid; i < nc; i += 256) {
+  for (int i = tid; i < nc; i += kStepThreads) {
     const int key = c[i], blk = key / b;
+    if (in_lds) c_lds[i] = key;
     sum += N - (blk + 1) * b;
     if (blk < nb - 1) atomicAdd(&by_pos[key - blk * b], 1);
   }
   __syncthreads();
-  if (tid <= b) {
-    int n = 0;
-    for (int p = tid; p < b; ++p) n += by_pos[p];
-    from[tid] = n;
+  if (tid < 64) {  // b is 64 or 128: a wave sums from the end, b / 64 positions per lane
+    const int per = b >> 6, p0 = b - per * (tid + 1);
+    const int x0 = by_pos[p0], x1 = per > 1 ? by_pos[p0 + 1] : 0;
+    int incl = x0 + x1;
+    for (int d = 1; d < 64; d <<= 1) {
+      const int y = __shfl_up(incl, d);
+      if (tid >= d) incl += y;
+    }
+    from[p0] = incl;
+    if (per > 1) from[p0 + 1] = incl - x0;
+    if (tid == 0) from[b] = 0;
   }
   __syncthreads();
-  for (int i = tid; i < no; i += 256) {
+  for (int i = tid; i < no; i += kStepThreads) {
     const int off = o[i];
     if (off >= b) {
       int lo = 0, hi = nc;  // the first column that is not below N - off
       while (lo < hi) {
         const int m = (lo + hi) >> 1;
-        if (c[m] < N - off) lo = m + 1;
+        if ((in_lds ? c_lds[m] : c[m]) < N - off) lo = m + 1;
         else hi = m;
       }
       sum += N - off - lo;
@@ -149,26 +185,42 @@ __global__ __launch_bounds__(256) void slash_step_kernel(const int32_t *cols, co
       sum += (long long)(N - off) - (long long)nb * (b - off) - from[b - off];
     }
   }
-  red[tid] = sum;
+  for (int d = 32; d >= 1; d >>= 1) sum += __shfl_down(sum, d);
+  if ((tid & 63) == 0) red[tid >> 6] = sum;
   __syncthreads();
-  for (int d = 128; d >= 1; d >>= 1) {
-    if (tid < d) red[tid] += red[tid + d];
-    __syncthreads();
+  if (tid != 0) return;
+  for (int i = 1; i < kStepThreads / 64; ++i) sum += red[i];
+  // Agent-scope accesses, the pairs performed (vmcnt(0)) before the arrival is counted: the last one reads them all.
+  __hip_atomic_store(&st->pairs[pr], (int64_t)(sum + (long long)nb * b * (b + 1) / 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+  asm volatile("" ::: "memory");
+  if (atomicAdd(&st->arrived, 1u) != kProbes - 1) return;
+  Refine r = *st;
+  int64_t size[kProbes], pairs[kProbes];
+#pragma unroll
+  for (int i = 0; i < kProbes; ++i) {
+    size[i] = r.probe(i);
+    pairs[i] = __hip_atomic_load(&st->pairs[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (tid == 0) {
-    Refine r = state[h];
-    r.step(red[0] + (long long)nb * b * (b + 1) / 2, target, eps);
-    state[h] = r;
-    budget[h] = slash_budget(r.x, N, nb);
+  for (bool known = true; known && !r.done;) {
+    known = false;
+    for (int i = 0; i < kProbes && !known; ++i)
+      if (size[i] == r.x) { r.step(pairs[i], target, eps); known = true; }
   }
+  r.arrived = 0;
+  *st = r;
+#pragma unroll
+  for (int i = 0; i < kProbes; ++i) probes[virtual_head(i0, i, gb, kProbes)] = slash_budget(r.probe(i), N, nb);
+  last[virtual_head(i0, 1 + SA_INTERVAL_SLASH, gb, kSets)] = slash_budget(r.x, N, nb);
 }
 
 // Heads that go through the search together, and the scratch they take.
 struct Plan {
   int heads, kv_heads;  // query heads of a batch (whole KV groups, or a part of one), their KV heads
-  sa_config cfg;        // of a batch: budgets as large as any candidate's
+  sa_config cfg;        // of a batch's virtual heads: budgets as large as any candidate's
   int64_t x_lo[3], x_hi[3];
-  size_t off[12], total;
+  size_t off[11], total;
 };
 
 sa_status plan_batch(const sa_ctx *ctx, int heads, Plan *z) {
@@ -182,7 +234,7 @@ sa_status plan_batch(const sa_ctx *ctx, int heads, Plan *z) {
   if (z->x_hi[2] > 0x7FFFFFFFll) return SA_ERR_UNSUPPORTED;
   sa_config &c = z->cfg;
   c = p;
-  c.n_q_heads = heads; c.n_kv_heads = z->kv_heads;
+  c.n_q_heads = kSets * heads; c.n_kv_heads = z->kv_heads;
   const sa::HeadBudget most = slash_budget(z->x_hi[1], N, nb);
   c.k_vertical = most.k_v; c.k_slash = most.k_s;
   c.local_blocks = nb; c.k_blocks = (int32_t)z->x_hi[2];
@@ -199,12 +251,11 @@ sa_status plan_batch(const sa_ctx *ctx, int heads, Plan *z) {
   if (st == SA_OK) st = sa_index_bytes(child, ix);
   sa_destroy(child);
   if (st != SA_OK) return st;
-  // outputs have Q's strides
-  const size_t o_bytes = ((size_t)(heads - 1) * ctx->sh.q_hs + (size_t)(N - 1) * ctx->sh.q_rs + sa::kHeadDim) * 2;
-  const size_t parts[12] = {ws, o_bytes, o_bytes, (size_t)heads * 4 * sizeof(sa::HeadBudget) + (size_t)heads * sizeof(Refine),
-                            (size_t)heads * 3 * kNormBlocks * 8, ix[0], ix[1], ix[2], ix[3], ix[4], ix[5], ix[6]};
+  const size_t o_bytes = (size_t)kSets * heads * N * sa::kHeadDim * 2;
+  const size_t parts[11] = {ws, o_bytes, (size_t)heads * (kSets + kProbes) * sizeof(sa::HeadBudget),
+                            (size_t)heads * (sizeof(Refine) + 3 * kNormBlocks * 8), ix[0], ix[1], ix[2], ix[3], ix[4], ix[5], ix[6]};
   size_t o = 0;
-  for (int i = 0; i < 12; ++i) { z->off[i] = o; o += align256(parts[i]); }
+  for (int i = 0; i < 11; ++i) { z->off[i] = o; o += align256(parts[i]); }
   z->total = o;
   return SA_OK;
 }
@@ -214,12 +265,12 @@ sa_status plan(const sa_ctx *ctx, Plan *z) {
   const int g = ctx->sh.g;
   sa_status st = SA_OK;
   for (int kv = ctx->sh.Hkv; kv >= 1; --kv) {
-    if (ctx->sh.Hkv % kv) continue;
+    if (ctx->sh.Hkv % kv || kSets * kv * g > sa::kMaxHeads) continue;
     if ((st = plan_batch(ctx, kv * g, z)) != SA_OK) return st;
     if (z->total <= kBatchBytes) return SA_OK;
   }
   for (int n = g - 1; n >= 1; --n) {
-    if (g % n) continue;
+    if (g % n || kSets * n > sa::kMaxHeads) continue;
     if ((st = plan_batch(ctx, n, z)) != SA_OK) return st;
     if (z->total <= kBatchBytes) return SA_OK;
   }
@@ -261,18 +312,25 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
   const sa::Shape &sh = ctx->sh;
   const int N = sh.N, nb = sh.nb, b = sh.b, B = z.heads;
   char *base = (char *)scratch;
-  uint16_t *o_dense = (uint16_t *)(base + z.off[1]), *o_sparse = (uint16_t *)(base + z.off[2]);
-  sa::HeadBudget *budgets = (sa::HeadBudget *)(base + z.off[3]);  // dense, then the three candidates
-  Refine *state = (Refine *)(budgets + (size_t)4 * B);
-  double *partial = (double *)(base + z.off[4]);
+  const int gb = B / z.kv_heads;  // heads of a KV head in the batch
+  uint16_t *outputs = (uint16_t *)(base + z.off[1]);
+  sa::HeadBudget *budgets = (sa::HeadBudget *)(base + z.off[2]);  // of the virtual heads: dense and candidates, probes
+  sa::HeadBudget *probes = budgets + (size_t)kSets * B;
+  Refine *state = (Refine *)(base + z.off[3]);  // and the sums behind it: the results
+  double *partial = (double *)(state + B);
   sa_index ix;
   int32_t **part[7] = {&ix.pattern, &ix.n_cols, &ix.cols, &ix.n_offs, &ix.offs, &ix.rowptr, &ix.blkcols};
-  for (int i = 0; i < 7; ++i) *part[i] = (int32_t *)(base + z.off[5 + i]);
+  for (int i = 0; i < 7; ++i) *part[i] = (int32_t *)(base + z.off[4 + i]);
 
   sa_ctx *child = nullptr;
   if ((st = sa_create(&z.cfg, &child)) != SA_OK) return failp(ctx, st, "search: batch rejected by sa_create");
   st = sa_set_workspace(child, base + z.off[0], child->ws_bytes);
-  const sa::Shape cs = child->sh;
+  sa::Shape cs = child->sh;
+  cs.gq = gb;
+  cs.o_rs = sa::kHeadDim;
+  cs.o_hs = (int64_t)N * sa::kHeadDim;
+  sa::Shape ps = cs;  // of a refinement step
+  ps.Hq = kProbes * B; ps.g = kProbes * gb;
   const sa::Workspace ws = child->ws;
   sa_destroy(child);
   if (st != SA_OK) return failp(ctx, st, "search: workspace");
@@ -285,27 +343,31 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
   while (!tri.done) tri.step(block_pairs(sa::triangular_count(nb, sh.sink, (int)tri.x)), target_pairs, eps_pairs);
   clu.start(z.x_lo[2], z.x_hi[2]);
   while (!clu.done) clu.step(block_pairs(clu.x), target_pairs, eps_pairs);
-  int rounds = 2;  // evaluations a bisection can take
-  for (int64_t w = z.x_hi[1] - z.x_lo[1]; w > 1; w = (w + 1) / 2) ++rounds;
+  // A bisection evaluates the ends and a size per halving; the first step takes both ends and the middle, every
+  // other one two sizes in a row.
+  int halvings = 0;
+  for (int64_t w = z.x_hi[1] - z.x_lo[1]; w > 1; w = (w + 1) / 2) ++halvings;
+  const int rounds = 1 + halvings / 2;
 
   // host memory of the call: what goes to the device, what comes back
-  const size_t norms = (size_t)B * 3 * kNormBlocks, head_bytes = (size_t)B * (4 * sizeof(sa::HeadBudget) + sizeof(Refine));
-  const std::unique_ptr<sa::HeadBudget[]> head(new (std::nothrow) sa::HeadBudget[head_bytes / sizeof(sa::HeadBudget) + 1]);
-  const std::unique_ptr<double[]> hp(new (std::nothrow) double[norms]);
-  const std::unique_ptr<Refine[]> slash(new (std::nothrow) Refine[B]);
-  if (!head || !hp || !slash) return failp(ctx, SA_ERR_INVALID_ARG, "search: out of host memory");
-  sa::HeadBudget *hb = head.get();
-  Refine *hr = (Refine *)(hb + (size_t)4 * B);
-  for (int i = 0; i < B; ++i) {
-    const sa::HeadBudget least = slash_budget(z.x_lo[1], N, nb);
-    hb[i] = hb[B + i] = hb[2 * B + i] = hb[3 * B + i] = least;
-    hb[i].local = nb;
-    hb[B + i].local = (int32_t)tri.x;
-    hb[3 * B + i].k_b = (int32_t)clu.x;
-    hr[i].start(z.x_lo[1], z.x_hi[1]);
-  }
   const int nblocks = (N + 15) / 16 < kNormBlocks ? (N + 15) / 16 : kNormBlocks;
-
+  const size_t norms = (size_t)B * 3 * nblocks, n_budgets = (size_t)B * (kSets + kProbes);
+  static_assert(sizeof(Refine) % sizeof(double) == 0, "the sums follow the states");
+  const std::unique_ptr<sa::HeadBudget[]> head(new (std::nothrow) sa::HeadBudget[n_budgets]);
+  const std::unique_ptr<Refine[]> begin(new (std::nothrow) Refine[B]);
+  const std::unique_ptr<double[]> back(new (std::nothrow) double[B * (sizeof(Refine) / sizeof(double)) + norms]);
+  if (!head || !begin || !back) return failp(ctx, SA_ERR_INVALID_ARG, "search: out of host memory");
+  sa::HeadBudget *hb = head.get();
+  Refine *hr = begin.get();
+  const double *hp = back.get() + B * (sizeof(Refine) / sizeof(double));
+  for (int i = 0; i < B; ++i) {
+    hr[i].start(z.x_lo[1], z.x_hi[1]);
+    for (int p = 0; p < kProbes; ++p) hb[kSets * B + virtual_head(i, p, gb, kProbes)] = slash_budget(hr[i].probe(p), N, nb);
+    for (int k = 0; k < kSets; ++k) hb[virtual_head(i, k, gb, kSets)] = slash_budget(z.x_lo[1], N, nb);
+    hb[virtual_head(i, 0, gb, kSets)].local = nb;
+    hb[virtual_head(i, 1 + SA_TRIANGULAR, gb, kSets)].local = (int32_t)tri.x;
+    hb[virtual_head(i, 1 + SA_BLOCK_CLUSTER, gb, kSets)].k_b = (int32_t)clu.x;
+  }
   hipError_t he = hipSuccess;
   auto ok = [&](hipError_t e) {
     if (e != hipSuccess && he == hipSuccess) he = e;
@@ -316,41 +378,39 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
     const uint16_t *Kh = (const uint16_t *)K + (size_t)(h0 / sh.g) * sh.kv_hs;
     const uint16_t *Vh = (const uint16_t *)V + (size_t)(h0 / sh.g) * sh.kv_hs;
     const sa_scores sc{scores.v + (size_t)h0 * N, scores.s + (size_t)h0 * N, scores.blk + (size_t)h0 * nb * nb};
-    auto build = [&](int pattern, int which) {  // every head's index of one pattern from budget row `which`
-      sa::Override ov;
-      for (int h = 0; h < sa::kMaxHeads; ++h) ov.pat[h] = (int8_t)pattern;
-      return ok(sa::launch_build_index(cs, ws, sc, ov, ix, stream, budgets + (size_t)which * B));
-    };
-    auto attend = [&](uint16_t *O) {
-      return ok(sa::launch_sparse_prefill(cs, ws, Qh, Kh, Vh, ix, O, nullptr, stream));
-    };
-    ok(hipMemcpyAsync(budgets, hb, head_bytes, hipMemcpyHostToDevice, stream));
+    ok(hipMemcpyAsync(budgets, hb, n_budgets * sizeof(sa::HeadBudget), hipMemcpyHostToDevice, stream));
+    ok(hipMemcpyAsync(state, hr, (size_t)B * sizeof(Refine), hipMemcpyHostToDevice, stream));
     // RefineSearchSpace of the Interval-Slash candidate, all heads a step per round (a head that is done
     // repeats its last index)
+    sa::Override ov;
+    for (int h = 0; h < sa::kMaxHeads; ++h) ov.pat[h] = SA_INTERVAL_SLASH;
     for (int r = 0; r < rounds && he == hipSuccess; ++r) {
-      if (!build(SA_INTERVAL_SLASH, 2)) break;
-      slash_step_kernel<<<B, 256, 0, stream>>>(ix.cols, ix.offs, cs.k_v, cs.k_s, N, b, state, budgets + 2 * (size_t)B,
-                                               target_pairs, eps_pairs);
+      if (!ok(sa::launch_build_index(ps, ws, sc, ov, ix, stream, probes))) break;
+      slash_step_kernel<<<dim3(B, kProbes), kStepThreads, 0, stream>>>(ix.cols, ix.offs, cs.k_v, cs.k_s, N, b, gb, state, probes,
+                                                                       budgets, target_pairs, eps_pairs);
       ok(hipGetLastError());
     }
-    // dense reference: the band as wide as the sequence; then every refined candidate against it
-    if (he == hipSuccess && build(SA_TRIANGULAR, 0)) attend(o_dense);
-    for (int p = 0; p < 3 && he == hipSuccess; ++p) {
-      if (!build(p, 1 + p) || !attend(o_sparse)) break;
-      sq_diff_kernel<<<dim3(nblocks, B), 256, 0, stream>>>(o_sparse, o_dense, N, sh.q_hs, sh.q_rs, partial + (size_t)p * B * kNormBlocks);
+    // dense reference (the band as wide as the sequence) and every refined candidate, and the candidates against it
+    for (int i = 0; i < B; ++i)
+      for (int k = 0; k < kSets; ++k)
+        ov.pat[virtual_head(i, k, gb, kSets)] = (int8_t)(k == 0 ? SA_TRIANGULAR : k - 1);
+    if (he == hipSuccess && ok(sa::launch_build_index(cs, ws, sc, ov, ix, stream, budgets)) &&
+        ok(sa::launch_sparse_prefill(cs, ws, Qh, Kh, Vh, ix, outputs, nullptr, stream))) {
+      sq_diff_kernel<<<dim3(nblocks, B, kSets - 1), 256, 0, stream>>>(outputs, gb, N, partial);
       ok(hipGetLastError());
     }
-    ok(hipMemcpyAsync(slash.get(), state, (size_t)B * sizeof(Refine), hipMemcpyDeviceToHost, stream));
-    ok(hipMemcpyAsync(hp.get(), partial, norms * 8, hipMemcpyDeviceToHost, stream));
+    ok(hipMemcpyAsync(back.get(), state, (size_t)B * sizeof(Refine) + norms * 8, hipMemcpyDeviceToHost, stream));
     // also after an error: nothing of this call is in flight when it returns
     const hipError_t last = hipStreamSynchronize(stream);
     if (!ok(last)) break;
     for (int i = 0; i < B; ++i) {
       sa_search_head &r = out_host[h0 + i];
-      const Refine *c[3] = {&tri, &slash[i], &clu};
+      Refine slash;
+      memcpy(&slash, back.get() + i * (sizeof(Refine) / sizeof(double)), sizeof(Refine));
+      const Refine *c[3] = {&tri, &slash, &clu};
       for (int p = 0; p < 3; ++p) {
         double sum = 0.0;
-        for (int k = 0; k < nblocks; ++k) sum += hp[((size_t)p * B + i) * kNormBlocks + k];
+        for (int k = 0; k < nblocks; ++k) sum += hp[((size_t)p * B + i) * nblocks + k];
         r.param[p] = (int32_t)c[p]->x;
         r.pairs[p] = c[p]->px;
         r.err[p] = std::sqrt(sum);
