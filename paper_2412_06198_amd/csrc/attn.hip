@@ -37,6 +37,7 @@ constexpr int kRunBits = 6, kRun = 1 << kRunBits;
 constexpr int NWORDS = kMaxSeq / BK / 32;
 constexpr int kPlanWaves = 4;     // items per workgroup of index_prepare_kernel
 constexpr unsigned kNoItem = ~0u;
+static_assert(kMaxHeads == 128 && kMaxSeq / BQ <= 2048, "an item's heads and row block fill a word");
 // Diagonals whose scores are taken before their products with V: as many as leave two workgroups a compute
 // unit's LDS.
 constexpr int kDiagBatch = 28;
@@ -57,11 +58,12 @@ struct AttnArgs {
   int share;    // log2 of the queues (XCDs) that share one KV head at a time (1, 2, 4 or 8), and from bit 4 on
                 // log2 of the consecutive row blocks a queue takes in a row (kRun or 1)
   int qcap;     // tickets per queue, holes of the id space included
+  int side_by_side;  // also the heads with diagonals take a row block together, see plan_item
   unsigned long long *counters;  // instrumentation only: {32x32 sub-tiles multiplied, kept (query,key) pairs}
-  // Written by index_prepare_kernel.  items[queue + 8 * ticket] = {head | row block << 16 (kNoItem: a hole
-  // of the id space), key tiles in the list, list start inside the head's share of tiles, first two
-  // entries}; tiles [Hq][tile_cap] list entries: key tile (bits 0..11), kept by waves 0, 1 (bit 14) / by
-  // waves 2, 3 (bit 15).
+  // Written by index_prepare_kernel.  items[queue + 8 * ticket] = {head | its query head << 7 | its KV head << 14 |
+  // row block << 21, key tiles in the list (kNoItem: a hole of the id space), list start inside the head's share
+  // of tiles, first two entries}; tiles [Hq][tile_cap] list entries: key tile (bits 0..11), kept by waves 0, 1
+  // (bit 14) / by waves 2, 3 (bit 15).
   uint4 *items;
   uint16_t *tiles;
   unsigned tile_cap;
@@ -85,7 +87,10 @@ __device__ inline uint32_t uload(const void *p, int idx) { return ((const_u32p)(
 // first for the query heads of the group that have no selected diagonals, side by side per row block
 // (their tiles overlap: the band of Triangular heads is the same for all of them), then for each head
 // with diagonals by itself (their diagonal phase re-reads nothing, and one head's gathered columns
-// stay in L2).  Here and not at the head of every item of the attention kernel, where the same steps
+// stay in L2).  With up to four items per workgroup (side_by_side) it is the order of lengths that counts, and
+// the heads with diagonals take a row block side by side too: 8 heads of one KV head, all with diagonals, 42 -> 34 us at
+// 8K tokens, 81 -> 71 at 16K, 146 -> 145 at 32K (four items each), 32 heads at 8K 99 -> 97; with five and more it
+// costs: 10K 177 -> 182, 32 heads at 32K 529 -> 536.  Here and not at the head of every item of the attention kernel, where the same steps
 // were four barriers and three round trips to memory one after the other while the matrix cores idled:
 // a whole layer of 4K, 10K, 16K, 32K and 128K tokens 59.8, 355, 432, 733 and 4543 us, now 57.0, 343, 414,
 // 718 and 4499 (plain causal attention at 16K 1986 and 1961).  One wave per item.
@@ -108,15 +113,17 @@ __device__ inline void plan_item(const AttnArgs &p, int id, uint32_t *k0, uint32
     const int c = __popcll(w[0]) + __popcll(w[1]);
     const bool plain = r < c * rows_q;
     const int r2 = r - c * rows_q;
-    int nth = plain ? r % c : r2 / rows_q;  // this many heads of its kind come before it
-    const int trow = plain ? r / c : r2 % rows_q;
+    const int side = plain ? c : p.side_by_side ? p.g - c : 0;  // heads that take a row block together
+    const int rk = plain ? r : r2;
+    int nth = side ? rk % side : rk / rows_q;  // this many heads of its kind come before it
+    const int trow = side ? rk / side : rk % rows_q;
     for (int j = 0; j < p.g; ++j)
       if ((((w[j >> 6] >> (j & 63)) & 1ull) != 0ull) == plain && nth-- == 0) h = kvh * p.g + j;
     const int rn = trow >> rb;
     tidx = (((rn << xb) + ((rn & 1) ? (1 << xb) - 1 - sub : sub)) << rb) + (trow & ((1 << rb) - 1));
   }
   if (h < 0 || tidx >= p.nT) {
-    if (lane == 0) p.items[id] = make_uint4(kNoItem, 0u, 0u, 0u);
+    if (lane == 0) p.items[id] = make_uint4(0u, kNoItem, 0u, 0u);
     return;
   }
   const int t128 = p.nT - 1 - tidx;
@@ -182,7 +189,7 @@ __device__ inline void plan_item(const AttnArgs &p, int id, uint32_t *k0, uint32
   __builtin_amdgcn_wave_barrier();
   const unsigned n = min(base, room);
   if (lane == 0)
-    p.items[id] = make_uint4((unsigned)h | (unsigned)t128 << 16, n, start,
+    p.items[id] = make_uint4((unsigned)h | (unsigned)query_head(h, p.g, p.gq) << 7 | (unsigned)kvh << 14 | (unsigned)t128 << 21, n, start,
                              (n > 0 ? first2[0] : 0u) | (n > 1 ? (unsigned)first2[1] << 16 : 0u));
 }
 
@@ -329,12 +336,11 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
   if (id < 0) break;
   const uint32_t it_w = uload(p.items, 4 * id), it_n = uload(p.items, 4 * id + 1);
   const uint32_t it_at = uload(p.items, 4 * id + 2), it_e = uload(p.items, 4 * id + 3);
-  if (it_w == kNoItem) {  // a hole of the id space
+  if (it_n == kNoItem) {  // a hole of the id space
     if (tid == 0 && ticket < p.qcap) ticket = (int)atomicAdd(&p.queue[home], 1u);
     continue;
   }
-  const int h = (int)(it_w & 0xFFFFu), t128 = (int)(it_w >> 16);
-  const int kvh = h / p.g;
+  const int h = (int)(it_w & 127u), qh = (int)(it_w >> 7 & 127u), kvh = (int)(it_w >> 14 & 127u), t128 = (int)(it_w >> 21);
   const int ntr = (int)it_n;
   const int i0 = t128 * BQ;
   const int r0 = i0 + 32 * wv;
@@ -419,7 +425,7 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
   // the item's other reads, all in flight together with the first tile's copies
   bf16x8 qf[8];  // Q^T fragments: B operand, lane = query, 8 consecutive d per k-step half
   {
-    const uint16_t *qrow = p.Q + (size_t)query_head(h, p.g, p.gq) * p.q_hs + (size_t)min(iq, N - 1) * p.q_rs;
+    const uint16_t *qrow = p.Q + (size_t)qh * p.q_hs + (size_t)min(iq, N - 1) * p.q_rs;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) qf[ks] = *(const bf16x8 *)(qrow + 16 * ks + 8 * gg);
   }
@@ -928,6 +934,7 @@ hipError_t launch_sparse_prefill(const Shape &sh, const Workspace &ws, const uin
   a.n_items = a.nT * sh.Hq;
   a.share = queue_share(sh);
   a.qcap = queue_capacity(sh);
+  a.side_by_side = a.n_items <= 8 * sh.n_cu;
   a.items = (uint4 *)ws.attn_items;
   a.tiles = ws.attn_tiles;
   a.tile_cap = (unsigned)sh.cap_b * (unsigned)(sh.b / BK);
