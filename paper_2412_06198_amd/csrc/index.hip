@@ -34,7 +34,7 @@
 // With the per-row block rule (every row block of a Block-Cluster head keeps the
 // same fraction of its causal blocks) the fifth selection is switched off and
 // the emission selects inside each row instead: one wave per row, keys in
-// registers, the threshold found bit by bit.
+// registers, the threshold found by halving the range of the row's keys.
 //
 // With block-granular diagonals two launches after the emission turn the selected
 // offsets of the Interval-Slash heads into rows of the block CSR (bitmap per row,
@@ -329,6 +329,17 @@ __device__ inline unsigned wave_inclusive_sum(unsigned x) {
   x += lane_move<0x143, 0xC>(x);  // row_bcast:31 into rows 2 and 3
   return x;
 }
+// The largest (smallest) of the wave's values.
+__device__ inline unsigned wave_max(unsigned x) {
+  x = max(x, lane_move<0x111, 0xF>(x));
+  x = max(x, lane_move<0x112, 0xF>(x));
+  x = max(x, lane_move<0x114, 0xF>(x));
+  x = max(x, lane_move<0x118, 0xF>(x));
+  x = max(x, lane_move<0x142, 0xA>(x));
+  x = max(x, lane_move<0x143, 0xC>(x));
+  return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
+}
+__device__ inline unsigned wave_min(unsigned x) { return ~wave_max(~x); }
 template <int CTRL, int ROWS>
 __device__ inline u64 lane_move64(u64 x) {
   return (u64)lane_move<CTRL, ROWS>((unsigned)x) | ((u64)lane_move<CTRL, ROWS>((unsigned)(x >> 32)) << 32);
@@ -1102,45 +1113,99 @@ __device__ inline void emit_group(const Four &f, unsigned thr, unsigned need,
   erun += etot;
 }
 
+// Keys raised by one: 0 stands for no key.
+__device__ inline unsigned raised(unsigned key) { return max(key, key + 1u); }  // (the largest word stays: no score)
+
 // Per-row block rule, one wave per row: out[0..kr) = the kr candidates C < R with the largest keys
-// (ties to the lower C) in ascending order, out[kr] = R (the forced diagonal block).  Lane l holds
-// the keys of the candidates l, l + 64, ... in registers (T of them, R <= 64 T); slots past the
-// row hold key 0, which no counting step below can reach.
-template <int T>
+// (ties to the lower C) in ascending order, out[kr] = R (the forced diagonal block).  Lane l holds four neighbours of
+// every 256 keys in registers (U times, R <= 256 U), raised by one: slots past the row hold 0.
+// What bounds it is its own instructions: a step of the search compares, counts and adds per 64 keys.  With 32
+// steps, one per bit, and a key per lane and load the index of 32 heads took 28.8 us at 161 blocks, 61 at 512, 89 at
+// 1024 and 695 at 2048; like this 25.4, 48, 57 and 126.
+template <int U>
 __device__ inline void emit_row_select(const unsigned *row, int R, int kr, int32_t *out) {
   const int lane = threadIdx.x & 63;
   if (kr > 0) {
-    unsigned key[T];
+    u32x4a x[U];
 #pragma unroll
-    for (int t = 0; t < T; ++t) key[t] = (64 * t + lane < R) ? row[64 * t + lane] : 0u;
-    auto count_ge = [&](unsigned c) {  // c >= 1
-      unsigned n = 0;
+    for (int u = 0; u < U; ++u) {
+      x[u] = u32x4a{0u, 0u, 0u, 0u};
+      const int i = kUnit * u + 4 * lane;
+      if (i + 3 < R) {
+        x[u] = *(const u32x4a *)(row + i);
+      } else if (i < R) {  // nothing is read behind the row: the last one ends the map
+        x[u].x = row[i];
+        if (i + 1 < R) x[u].y = row[i + 1];
+        if (i + 2 < R) x[u].z = row[i + 2];
+      }
+    }
+    unsigned most = 0u, least = 0xFFFFFFFFu;
 #pragma unroll
-      for (int t = 0; t < T; ++t)
-        if (64 * t < R) n += __popcll(__ballot(key[t] >= c));
+    for (int u = 0; u < U; ++u) {
+      const int i = kUnit * u + 4 * lane;
+      if (kUnit * u >= R) continue;
+      x[u] = u32x4a{i < R ? raised(x[u].x) : 0u, i + 1 < R ? raised(x[u].y) : 0u, i + 2 < R ? raised(x[u].z) : 0u,
+                    i + 3 < R ? raised(x[u].w) : 0u};
+      most = max(most, max(max(x[u].x, x[u].y), max(x[u].z, x[u].w)));
+      least = min(least, min(min(x[u].x - 1u, x[u].y - 1u), min(x[u].z - 1u, x[u].w - 1u)));
+    }
+    auto reach = [&](unsigned c) {  // keys >= c, c >= 1
+      int n = 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (kUnit * u < R)
+          n += __popcll(__ballot(x[u].x >= c)) + __popcll(__ballot(x[u].y >= c)) + __popcll(__ballot(x[u].z >= c)) +
+               __popcll(__ballot(x[u].w >= c));
       return n;
     };
-    // the kr-th largest key: the largest t with at least kr keys >= t, found bit by bit
-    unsigned thr = 0u;
-    for (int bit = 31; bit >= 0; --bit) {
-      const unsigned c = thr | (1u << bit);
-      if (count_ge(c) >= (unsigned)kr) thr = c;
-    }
-    const unsigned gt = thr == 0xFFFFFFFFu ? 0u : count_ge(thr + 1u);
-    const unsigned need = (unsigned)kr - gt;  // ties at the threshold, taken in index order
-    const u64 below = (1ull << lane) - 1ull;
-    unsigned grun = 0, erun = 0;
-#pragma unroll
-    for (int t = 0; t < T; ++t)
-      if (64 * t < R) {
-        const bool ok = 64 * t + lane < R;
-        const bool isgt = ok && key[t] > thr, iseq = ok && key[t] == thr;
-        const u64 bg = __ballot(isgt), be = __ballot(iseq);
-        const unsigned gb = grun + __popcll(bg & below), eb = erun + __popcll(be & below);
-        if (isgt || (iseq && eb < need)) out[gb + min(eb, need)] = 64 * t + lane;
-        grun += __popcll(bg);
-        erun += __popcll(be);
+    // The kr-th largest key, between the smallest and the largest, in halves.  The search is over as soon as kr keys
+    // reach the middle: after 12 of up to 31 steps in a row of 1000 softmax weights, the gaps between which are
+    // wide against their last bits.
+    unsigned lo = wave_min(least) + 1u, hi = wave_max(most), need = 0xFFFFFFFFu;  // need: ties taken, in index order
+    while (kr < R) {
+      if (lo == hi) {
+        need = (unsigned)kr - (hi == 0xFFFFFFFFu ? 0u : (unsigned)reach(hi + 1u));
+        break;
       }
+      const unsigned c = lo + (hi - lo + 1u) / 2u;
+      const int n = reach(c);
+      if (n >= kr) lo = c;
+      else hi = c - 1u;
+      if (n == kr) break;
+    }
+    unsigned run = 0u, erun = 0u;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (kUnit * u >= R) continue;
+      const unsigned y[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+      u64 in[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) in[j] = __ballot(y[j] >= lo);
+      if (need != 0xFFFFFFFFu) {
+        u64 eq[4];
+        unsigned before = erun;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          eq[j] = __ballot(y[j] == lo);
+          before += __builtin_amdgcn_mbcnt_hi((unsigned)(eq[j] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)eq[j], 0u));
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          in[j] &= ~__ballot(y[j] == lo && before >= need);
+          before += (unsigned)((eq[j] >> lane) & 1ull);
+          erun += (unsigned)__popcll(eq[j]);
+        }
+      }
+      unsigned pos = run;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        pos = __builtin_amdgcn_mbcnt_hi((unsigned)(in[j] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)in[j], pos));
+        run += (unsigned)__popcll(in[j]);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if ((in[j] >> lane) & 1ull) out[pos++] = kUnit * u + 4 * lane + j;
+    }
   }
   if (lane == 0) out[kr] = R;
 }
@@ -1213,7 +1278,7 @@ __global__ __launch_bounds__(BT) void idx_emit_kernel(IdxArgs a) {
     for (int R = part; R < nb; R += nparts) {
       const int at = __builtin_amdgcn_readfirstlane(s_at[R]), end = __builtin_amdgcn_readfirstlane(s_at[R + 1]);
       if (lane == 0) rp[R] = at;
-      emit_row_select<T == 0 ? 1 : T>(hb + (size_t)R * nb, R, end - at - 1, bc + at);
+      emit_row_select<T == 0 ? 1 : T / 4>(hb + (size_t)R * nb, R, end - at - 1, bc + at);
     }
     total = s_at[nb];
   } else if (pat == SA_BLOCK_CLUSTER) {
