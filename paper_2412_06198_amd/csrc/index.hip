@@ -8,7 +8,8 @@
 //
 // Five selections run side by side for every head, so that nothing waits on the
 // pattern decision: the probe_v / probe_s best of v and s (pattern rule), the
-// k_v best columns, the k_s best diagonals, the k_b - nb best blocks.  Five launches:
+// k_v best columns, the k_s best diagonals, the k_b - nb best blocks.  Where workgroups can hold the arrays in
+// segments and what those select (see idx_top_kernel and held_arrays), two launches; else five:
 //   zero    clears the head's counters;
 //   hist    one pass over the scores: 2048 logarithmic bins (64 per octave);
 //   refine  a second pass that splits a bin in 1024, only for selections whose boundary bin holds
@@ -26,10 +27,9 @@
 // be written back or invalidated on the way.  The order rests on gfx950 there: a memory operation that
 // the counter reports as done has been performed at its scope.  The language promises nothing of the kind
 // for relaxed atomics, and the fences that would cost an L2 write-back per workgroup.
-// Every launch costs 3 to 8 us whatever it does, and a pass over the scores of 32 heads 10 to 40 us.
-// Short prompts take two launches, see idx_select_kernel.  With ten launches and five passes before,
-// 32 heads took 83 us at 10K tokens, 86 at 16K, 105 at 32K, 113 at 64K and 175 at 128K; now 30, 40, 55, 60 and
-// 103 (4 heads at 4K: 66 and 14).
+// Every launch costs 3 to 8 us whatever it does, and a pass over the scores of 32 heads 10 to 40 us.  Five
+// launches take 30 us at 10K tokens, 40 at 16K, 55 at 32K, 60 at 64K and 103 at 128K; two, where they are taken,
+// 21, 30, 54, 46 and none (4 heads at 4K: 14).
 //
 // With the per-row block rule (every row block of a Block-Cluster head keeps the
 // same fraction of its causal blocks) the fifth selection is switched off and
@@ -39,6 +39,7 @@
 // With block-granular diagonals two launches after the emission turn the selected
 // offsets of the Interval-Slash heads into rows of the block CSR (bitmap per row,
 // count and prefix, ordered write).
+#include <algorithm>
 #include <cstddef>
 
 #include "sa_internal.h"
@@ -49,7 +50,7 @@ namespace {
 constexpr int BT = 256;            // threads per workgroup
 constexpr int WPB = BT / 64;       // waves per workgroup
 constexpr int kUnit = 256;         // keys a wave takes with one load: 16 bytes per lane
-constexpr int kVsUnits = 4;        // units of v or s per wave (one where a workgroup walks a whole array)
+constexpr int kVsUnits = 4;        // units of v or s per wave
 constexpr int kMaxVsParts = kMaxSeq / (kVsUnits * kUnit);
 constexpr int kMaxBlkParts = 512;  // waves that share the block map of a head
 constexpr int kMaxNb = kMaxSeq / 64;
@@ -63,6 +64,7 @@ constexpr int kListVs = 4096, kListBlk = 16384;  // boundary keys that are liste
 // Keys of a range that does not fit its list are counted one by one, per wave part, while there are no more
 // different ones than this: what the refine pass leaves of a bin.
 constexpr int kDense = 1 << (kBinShift - 10);
+constexpr int kMaxSegs = 8, kMaxMapSegs = 16;  // of arrays that workgroups hold
 
 typedef unsigned long long u64;
 typedef unsigned u32x4a __attribute__((ext_vector_type(4), aligned(4)));
@@ -74,10 +76,13 @@ struct IdxScratch {
   u64 vtot, ct, topsum[2];
   unsigned nlist[NSEL];                   // boundary keys appended so far
   unsigned ticket[3][3];                  // per launch (hist, refine, count) and array
-  unsigned ticket_vs;                     // v and s resolved
+  unsigned ticket_vs;                     // v and s resolved (where their launch writes the patterns)
   unsigned dense_max[NSEL], dense_inv[NSEL];  // of a range with more keys than a list takes: largest key, largest ~key
   // everything above is zeroed at the start of a call
   alignas(16) u64 psum[2];                // sums of the probe best of v and s
+  // arrays that workgroups hold whole or in segments: sums of v per segment, best keys per segment of v and s
+  u64 seg_vtot[kMaxSegs], seg_ct[kMaxSegs];
+  unsigned seg_best[2][64], seg_thr[3][kMaxMapSegs];
   unsigned lo[NSEL], last[NSEL];          // key range that holds the k-th key of a selection ...
   unsigned rem[NSEL], pop[NSEL];          // ... its rank inside, and the keys in the range
   unsigned thr[NSEL], need[NSEL];
@@ -114,6 +119,11 @@ struct IdxArgs {
   // is then done for the Block-Cluster heads only (the block map of the others was never computed).
   const int32_t *decided;
   const HeadBudget *hb;            // not null: budgets per head instead of the configuration's
+  // Arrays that workgroups hold (see idx_top_kernel): segments of v (and of s) and of the block map's lower triangle,
+  // keys of a segment; the best of a segment, indices ([Hq][2][segments][cap], [Hq][segments][cap]) and, where
+  // there are several segments, keys in the same order.
+  int held, seg_vs, seg_blk, per_vs, per_blk, cap_top_vs, cap_top_blk;
+  unsigned *top_vs, *top_blk, *top_vs_key, *top_blk_key;
 };
 
 // What crosses workgroups inside a launch: agent-scope accesses, see the top of the file.
@@ -185,13 +195,12 @@ __device__ inline u64 fx30(unsigned bits) {
   return big ? u << 8 : u;
 }
 
-// Pattern of head h by the integer lift tests, from the sums of the hist launch (vtot, ct) and the
+// Pattern of a head by the integer lift tests, from the sums of v (all, and in the Triangular region) and the
 // sums sv, ss of the probe best of v and s.
-__device__ inline int decide_pattern(const IdxArgs &a, const IdxScratch *G, u64 sv, u64 ss) {
+__device__ inline int decide_pattern(const IdxArgs &a, u64 vtot, u64 ct, u64 sv, u64 ss) {
   const Shape &sh = a.sh;
   typedef unsigned __int128 u128;
-  const u64 vtot = agent_load(&G->vtot);
-  if ((u128)sh.lift_den * agent_load(&G->ct) * a.E >= (u128)sh.lift_num * vtot * a.ET) return SA_TRIANGULAR;
+  if ((u128)sh.lift_den * ct * a.E >= (u128)sh.lift_num * vtot * a.ET) return SA_TRIANGULAR;
   if ((u128)sh.lift_den * (sv + ss) * a.E >=
       (u128)sh.lift_num * vtot * (u64)(sh.probe_v + sh.probe_s) * (u64)sh.w)
     return SA_INTERVAL_SLASH;
@@ -676,7 +685,7 @@ __device__ inline void finish_vs(const IdxArgs &a, IdxScratch *G, int arr, int h
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
   asm volatile("" ::: "memory");
   if (atomicAdd(&G->ticket_vs, 1u) == 1u && a.ov.pat[h] < 0)
-    a.out.pattern[h] = decide_pattern(a, G, agent_load(&G->psum[0]), agent_load(&G->psum[1]));
+    a.out.pattern[h] = decide_pattern(a, agent_load(&G->vtot), agent_load(&G->ct), agent_load(&G->psum[0]), agent_load(&G->psum[1]));
 }
 
 // ---- pass 1: histograms ------------------------------------------------------------------------
@@ -1011,77 +1020,6 @@ __global__ __launch_bounds__(BT) void idx_count_kernel(IdxArgs a) {
   finish_vs(a, G, arr, h);
 }
 
-// ---- passes 1 to 3 of short prompts in one launch ------------------------------------------------
-// grid (arrays, Hq), 1024 threads: one workgroup walks a whole array, two or three times out of L2,
-// and needs nothing from the others: no counters to clear, no tickets, no merging.  Taken while the
-// walks are short against the launches and round trips they replace (see one_launch).
-constexpr int ST = 1024, SW = ST / 64;
-
-__global__ __launch_bounds__(ST) void idx_select_kernel(IdxArgs a, int first_array) {
-  __shared__ __attribute__((aligned(16))) union {
-    unsigned l1[kL1Words];
-    unsigned sub[2][kSubWords];
-  } hist;
-  __shared__ u64 list[2][kList];
-  __shared__ unsigned n_list[2];
-  __shared__ Pick pick[2];
-  __shared__ unsigned pgt[kMaxBlkParts], peq[kMaxBlkParts];
-  __shared__ unsigned wsum[2 * SW];
-  __shared__ u64 red[2][SW];
-  const int arr = first_array + (int)blockIdx.x, h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (arr == 0 && tid == 0 && a.ov.pat[h] >= 0) a.out.pattern[h] = a.ov.pat[h];
-  if (!head_wants(a, h, arr == 2)) return;
-  IdxScratch *G = a.scratch + h;
-  const int ns = n_sel(arr), nparts = (arr == 2 ? a.Pb : a.Pv) * WPB;
-  const unsigned *src = array_of(a, arr, h);
-  for (int i = tid; i < kL1Words / 4; i += ST) ((uint4 *)hist.l1)[i] = make_uint4(0u, 0u, 0u, 0u);
-  if (tid < 2) n_list[tid] = 0u;
-  __syncthreads();
-  u64 vt = 0, ct = 0;
-  for (int pt = wv; pt < nparts; pt += SW) hist_part(a, arr, src, pt, hist.l1, vt, ct);
-  if (arr == 0) {
-    vt = wave_sum63(vt);
-    ct = wave_sum63(ct);
-    if (lane == 63) { red[0][wv] = vt; red[1][wv] = ct; }
-  }
-  __syncthreads();
-  u64 sum_v = 0, sum_c = 0;  // thread 0, array v
-  if (arr == 0 && tid == 0)
-    for (int w = 0; w < SW; ++w) { sum_v += red[0][w]; sum_c += red[1][w]; }
-  block_find_kth<ST, kBins, kCopies>(hist.l1, ns, (unsigned)ksel(a, h, sel_of(arr, 0)),
-                                     (unsigned)ksel(a, h, sel_of(arr, ns - 1)), pick, wsum);
-  Ranges r;
-  unsigned top[2];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    r.lo[k] = r.last[k] = r.rank[k] = r.n[k] = 0u;
-    top[k] = 0xFFFFFFFFu;
-    if (k < ns) {
-      bin_range(pick[k].bin, first_bin(a, arr), r.lo[k], r.last[k]);
-      r.rank[k] = pick[k].rank; r.n[k] = pick[k].count;
-    }
-  }
-  u64 ts = 0;
-  narrow<ST>(a, arr, src, nparts, ns, hist.sub, pick, wsum, r);
-  collect<ST>(a, arr, src, nparts, ns, r, top, list, n_list, pgt, peq, ts);
-  auto each = [&](int k, auto fn) {
-    for (unsigned i = tid; i < n_list[k]; i += ST) {
-      const u64 it = list[k][i];
-      fn((unsigned)(it >> 32), (int)(unsigned)it);
-    }
-  };
-  const unsigned own[2] = {0u, 0u};
-  const u64 sum = finish_array<ST>(a, G, arr, nparts, ns, list, each, hist.sub, pick, r, own, pgt, peq, wsum, red[0], ts);
-  if (arr == 2 || tid != 0) return;
-  if (arr == 0) {
-    agent_store(&G->vtot, sum_v);
-    agent_store(&G->ct, sum_c);
-  }
-  agent_store(&G->psum[arr], sum);
-  if (a.decide_here) finish_vs(a, G, arr, h);
-}
-
 // ---- pass 4: emission ------------------------------------------------------------------------------
 // One 256-key group of a wave: an element is selected if its key is above the threshold, or equal to
 // it and among the first `need` such elements in index order.  visit(j, pos, sel) receives every
@@ -1210,6 +1148,54 @@ __device__ inline void emit_row_select(const unsigned *row, int R, int kr, int32
   if (lane == 0) out[kr] = R;
 }
 
+// Block CSR of a Block-Cluster head under the per-row rule, by workgroups of 64 NW threads: a wave takes whole rows
+// (part of nparts).  Every workgroup finds its rows' pointers for itself: thread t sums the shares of `per` rows.
+template <int T, int NW>
+__device__ inline int emit_rows(const IdxArgs &a, const unsigned *hb, int part, int nparts, int32_t *rp, int32_t *bc,
+                                int *s_at, unsigned *wsum) {
+  const int tid = threadIdx.x, lane = tid & 63, nb = a.sh.nb;
+  const int per = (nb + 64 * NW - 1) / (64 * NW);
+  unsigned sum = 0, unused = 0;
+  for (int j = 0; j < per; ++j)
+    if (per * tid + j < nb) sum += (unsigned)row_share(a, per * tid + j);
+  unsigned run = sum;
+  block_exclusive_scan2<NW>(run, unused, wsum);
+  for (int j = 0; j < per; ++j) {
+    const int R = per * tid + j;
+    if (R < nb) {
+      s_at[R] = (int)run;
+      run += (unsigned)row_share(a, R);
+      if (R == nb - 1) s_at[nb] = (int)run;
+    }
+  }
+  __syncthreads();
+  for (int R = part; R < nb; R += nparts) {
+    const int at = __builtin_amdgcn_readfirstlane(s_at[R]), end = __builtin_amdgcn_readfirstlane(s_at[R + 1]);
+    if (lane == 0) rp[R] = at;
+    emit_row_select<T / 4>(hb + (size_t)R * nb, R, end - at - 1, bc + at);
+  }
+  return s_at[nb];
+}
+
+// Block CSR of a Triangular head (a wave takes whole rows) or an Interval-Slash head: the blocks of all rows.
+__device__ inline int emit_fixed(const IdxArgs &a, int h, int pat, int part, int nparts, int gtid, int gthreads,
+                                 int32_t *rp, int32_t *bc) {
+  const Shape &sh = a.sh;
+  const int lane = threadIdx.x & 63, nb = sh.nb;
+  if (pat == SA_TRIANGULAR) {
+    const int local = head_budget(a, h).local;
+    for (int R = part; R < nb; R += nparts) {
+      const int at = tri_prefix(sh.sink, local, R);
+      const int bs = max(R - local + 1, 0), ns = min(sh.sink, bs), n = ns + R - bs + 1;
+      if (lane == 0) rp[R] = at;
+      for (int i = lane; i < n; i += 64) bc[at + i] = i < ns ? i : bs + i - ns;
+    }
+    return tri_prefix(sh.sink, local, nb);
+  }
+  for (int R = gtid; R < nb; R += gthreads) { rp[R] = R; bc[R] = R; }
+  return nb;
+}
+
 // grid as in the passes above.  T: 64-key slices of a row under the per-row rule (nb <= 64 T), 0 for
 // the rules with one selection per head.
 template <int T>
@@ -1217,12 +1203,12 @@ __global__ __launch_bounds__(BT) void idx_emit_kernel(IdxArgs a) {
   __shared__ unsigned s_wsum[2 * WPB];
   const Shape &sh = a.sh;
   const Role ro = role_of(a);
-  const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int h = blockIdx.y, tid = threadIdx.x;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int N = sh.N, nb = sh.nb;
+  const int nb = sh.nb;
   IdxScratch *G = a.scratch + h;
   int pat = a.ov.pat[h];
-  if (pat < 0) pat = a.decide_here ? a.out.pattern[h] : decide_pattern(a, G, G->psum[0], G->psum[1]);
+  if (pat < 0) pat = a.out.pattern[h];
   pat = __builtin_amdgcn_readfirstlane(pat);
   const int part = ro.p * WPB + wv, nparts = ro.n * WPB;
   const int gtid = ro.p * BT + tid, gthreads = ro.n * BT;
@@ -1245,7 +1231,6 @@ __global__ __launch_bounds__(BT) void idx_emit_kernel(IdxArgs a) {
     for (int i = shown + gtid; i < width; i += gthreads) idx[i] = -1;
     if (gtid == 0) {
       (ro.arr ? a.out.n_offs : a.out.n_cols)[h] = shown;
-      if (ro.arr == 0 && !a.decide_here) a.out.pattern[h] = pat;
       if (aside) G->ticket_rows = 0u;
     }
     return;
@@ -1256,31 +1241,8 @@ __global__ __launch_bounds__(BT) void idx_emit_kernel(IdxArgs a) {
   const unsigned *hb = array_of(a, 2, h);
   int total;
   if (pat == SA_BLOCK_CLUSTER && T > 0) {
-    // every workgroup finds its rows' pointers for itself: thread t sums the shares of RP rows
     __shared__ int s_at[kMaxNb + 1];
-    constexpr int RP = kMaxNb / BT;
-    const int per = (nb + BT - 1) / BT;  // <= RP
-    unsigned sum = 0, unused = 0;
-    for (int j = 0; j < per; ++j)
-      if (per * tid + j < nb) sum += (unsigned)row_share(a, per * tid + j);
-    unsigned run = sum;
-    static_assert(RP * BT == kMaxNb, "rows per thread");
-    block_exclusive_scan2<WPB>(run, unused, s_wsum);
-    for (int j = 0; j < per; ++j) {
-      const int R = per * tid + j;
-      if (R < nb) {
-        s_at[R] = (int)run;
-        run += (unsigned)row_share(a, R);
-        if (R == nb - 1) s_at[nb] = (int)run;
-      }
-    }
-    __syncthreads();
-    for (int R = part; R < nb; R += nparts) {
-      const int at = __builtin_amdgcn_readfirstlane(s_at[R]), end = __builtin_amdgcn_readfirstlane(s_at[R + 1]);
-      if (lane == 0) rp[R] = at;
-      emit_row_select<T == 0 ? 1 : T / 4>(hb + (size_t)R * nb, R, end - at - 1, bc + at);
-    }
-    total = s_at[nb];
+    total = emit_rows<T == 0 ? 4 : T, WPB>(a, hb, part, nparts, rp, bc, s_at, s_wsum);
   } else if (pat == SA_BLOCK_CLUSTER) {
     const int k = ksel(a, h, 4);
     // no block below the diagonal is selected: no key is above this threshold, and no tie is taken
@@ -1296,18 +1258,742 @@ __global__ __launch_bounds__(BT) void idx_emit_kernel(IdxArgs a) {
       });
     });
     total = k + nb;
-  } else if (pat == SA_TRIANGULAR) {
-    const int local = head_budget(a, h).local;
-    for (int R = part; R < nb; R += nparts) {
-      const int at = tri_prefix(sh.sink, local, R);
-      const int bs = max(R - local + 1, 0), ns = min(sh.sink, bs), n = ns + R - bs + 1;
-      if (lane == 0) rp[R] = at;
-      for (int i = lane; i < n; i += 64) bc[at + i] = i < ns ? i : bs + i - ns;
-    }
-    total = tri_prefix(sh.sink, local, nb);
   } else {
-    for (int R = gtid; R < nb; R += gthreads) { rp[R] = R; bc[R] = R; }
-    total = nb;
+    total = emit_fixed(a, h, pat, part, nparts, gtid, gthreads, rp, bc);
+  }
+  if (gtid == 0) rp[nb] = total;
+  for (int i = total + gtid; i < sh.cap_b; i += gthreads) bc[i] = -1;
+}
+
+// ---- arrays that workgroups hold --------------------------------------------------------------------
+// Two launches instead of the five above: idx_top_kernel, in which a workgroup reads a segment of an array once, into
+// registers, and finds the best k of its keys, and idx_place_kernel, which decides the pattern, takes the best
+// of the segments' best where an array has several, and writes the index.  Nothing is merged between workgroups
+// of a launch, so there are no counters to clear and no tickets.  Taken where the segments' best fit a
+// workgroup again (see held_arrays).
+// What such a workgroup waits for is its own instructions: one on each of 32768 keys takes a compute unit
+// 0.25 us.  So few are spent on all keys: of the four keys of a lane the largest goes into a histogram while they
+// arrive; the k-th of those is a bound that k keys reach; the keys that reach it, a tenth more than k as a rule,
+// go to a list in LDS, in order, and everything else is done on that list.  (With all keys in LDS and the
+// walks over them 37 us a launch of 32 heads at 64K tokens, with 64 keys a step in registers 46, 27 like this.)
+constexpr int ST = 1024, SW = ST / 64;
+constexpr int kHeldUnits = 8;                          // units of a wave at most
+constexpr int kSeg = SW * kHeldUnits * kUnit;          // keys of a workgroup
+constexpr int kCap = 16384;                            // keys of its list
+constexpr int kDirect = SW * kUnit;                    // keys that go to the list all
+constexpr int kFew = 256;                              // keys that are ranked one against the other
+constexpr int kWide = 8;                               // copies of a bin in the histogram of all keys
+
+struct TopShared {
+  __attribute__((aligned(16))) unsigned hist[kL1Words];
+  u64 red[2][SW];
+  unsigned few[2][kFew], n_few[2], above[2][kFew], equal[2][kFew];
+  Pick pick[2];
+  unsigned wsum[2 * SW], wgt[SW], weq[SW];
+};
+template <int CAP>
+struct List {
+  __attribute__((aligned(16))) unsigned key[CAP];
+  uint16_t at[CAP];  // place in the segment
+};
+
+// Keys of a wave, four per lane and unit in index order, raised by one: 0 stands for no key.
+template <int UNITS>
+struct Held { u32x4a k[UNITS]; int units; };
+// Units per wave and the first key of a wave for n keys.
+__device__ inline int wave_units(int n) { return (n + SW * kUnit - 1) / (SW * kUnit); }
+
+__device__ inline int bin_of(unsigned key, int base) { return min(max((int)(key >> kBinShift) - base, 0), kBins - 1); }
+__device__ inline void zero_hist(TopShared &s) {
+  for (int i = threadIdx.x; i < kL1Words / 4; i += ST) ((uint4 *)s.hist)[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// Walk of a list of n keys, one per thread and step; fn is called by whole waves.
+template <int CAP, class Fn>
+__device__ __forceinline__ void list_visit(const List<CAP> &l, int n, Fn fn) {
+#pragma unroll 1
+  for (int i = threadIdx.x; i < ((n + 63) & ~63); i += ST) fn(i, i < n ? l.key[i] : 0u);
+}
+
+// Keys into a histogram of `bins`, in which a wave that meets one bin adds once: equal scores come in runs.
+__device__ inline void count_key(bool mine, unsigned bin, unsigned *hist, int copies) {
+  const u64 in = __ballot(mine);
+  if (in == 0ull) return;
+  const int first = __builtin_ctzll(in);
+  if ((__ballot(bin == (unsigned)__builtin_amdgcn_readlane((int)bin, first)) & in) == in) {
+    if ((int)(threadIdx.x & 63) == first) atomicAdd(&hist[bin * copies], (unsigned)__popcll(in));
+  } else if (mine) {
+    atomicAdd(&hist[bin * copies + (threadIdx.x & (copies - 1))], 1u);
+  }
+}
+
+// The list of the keys that reach a bound which at least the larger k (>= 1) of the workgroup's n keys reach, or, where
+// too many are equal, of exactly the k best; returns its length.  known: such a bound, or 0.  alike: the keys of a lane
+// are much alike (neighbours in a row of the block map), so that the largest of them says little.  hist is zero and
+// left zero.  r: the ranges that hold the k-th keys, where all keys were counted (else left alone).
+template <int UNITS, int CAP>
+__device__ __forceinline__ int held_list(const Held<UNITS> &x, int n, const int (&ks)[2], unsigned known, bool alike, int base,
+                                         TopShared &s, List<CAP> &l, Ranges &r) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), k = max(ks[0], ks[1]);
+  // Keys of a unit into the histogram; all of them, or the largest of every four.
+  auto count = [&](const u32x4a &y, bool all, unsigned *hist, int copies) {
+    const unsigned m = max(max(y.x, y.y), max(y.z, y.w));
+    if (m == 0u) return;
+    const int b3 = bin_of(m, base), copy = lane & (copies - 1);
+    if (!all) {
+      atomicAdd(&hist[b3 * copies + copy], 1u);
+      return;
+    }
+    const unsigned f = min(min(y.x, y.y), min(y.z, y.w));
+    if (f != 0u && bin_of(f, base) == b3) {  // the four share their bin
+      atomicAdd(&hist[b3 * copies + copy], 4u);
+    } else {
+      atomicAdd(&hist[bin_of(y.x, base) * copies + copy], 1u);
+      if (y.y) atomicAdd(&hist[bin_of(y.y, base) * copies + copy], 1u);
+      if (y.z) atomicAdd(&hist[bin_of(y.z, base) * copies + copy], 1u);
+      if (y.w) atomicAdd(&hist[bin_of(y.w, base) * copies + copy], 1u);
+    }
+  };
+  auto ranges = [&]() {  // of the k-th keys, from the bins picked
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (ks[q] > 0) {
+        bin_range(s.pick[q].bin, base, r.lo[q], r.last[q]);
+        r.lo[q] = max(r.lo[q], 1u);
+        r.rank[q] = s.pick[q].rank; r.n[q] = s.pick[q].count;
+      }
+  };
+  if (UNITS == 1 || n <= kDirect) {
+    if (x.units > 0) {
+      const int i = wv * kUnit + 4 * lane;
+      if (i < n) *(u32x4a *)(l.key + i) = x.k[0];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) l.at[i + j] = (uint16_t)(i + j);
+      if (k < n) count(x.k[0], true, s.hist, kCopies);
+    }
+    __syncthreads();
+    if (k < n) {
+      block_find_kth<ST, kBins, kCopies>(s.hist, 2, (unsigned)max(ks[0], 0), (unsigned)max(ks[1], 0), s.pick, s.wsum);
+      ranges();
+    }
+    return n;
+  }
+  if constexpr (UNITS > 1) {
+    unsigned floor = known ? known : 1u;
+    auto reach = [&]() {  // keys that reach the bound, in the waves up to each
+      int c = 0;
+  #pragma unroll
+      for (int u = 0; u < UNITS; ++u)
+        if (u < x.units)
+          c += __popcll(__ballot(x.k[u].x >= floor)) + __popcll(__ballot(x.k[u].y >= floor)) +
+               __popcll(__ballot(x.k[u].z >= floor)) + __popcll(__ballot(x.k[u].w >= floor));
+      __syncthreads();
+      if (lane == 0) s.wgt[wv] = (unsigned)c;
+      __syncthreads();
+      return wave_inclusive_sum(lane < SW ? s.wgt[lane] : 0u);
+    };
+    unsigned sums = 0u;
+    int total = CAP + 1;
+    if (known) {
+      sums = reach();
+      total = (int)__builtin_amdgcn_readlane(sums, SW - 1);
+    }
+    if (!known || total > 2 * k) {
+      if (k < n) {
+        // Keys that are alike: in the list's memory, with many copies of a bin (the weights of a map's row fall into a few
+        // bins, and additions of a wave to one counter take their turns).
+        const bool all = alike || 8 * k > n || n <= 2 * SW * kUnit;
+        unsigned *hist = alike ? l.key : s.hist;
+        static_assert(kBins * kWide <= CAP, "the histogram fits the list");
+        if (alike) {
+          for (int i = tid; i < kBins * kWide / 4; i += ST) ((uint4 *)hist)[i] = make_uint4(0u, 0u, 0u, 0u);
+          __syncthreads();
+        }
+        const int copies = alike ? kWide : kCopies;
+  #pragma unroll
+        for (int u = 0; u < UNITS; ++u)
+          if (u < x.units) count(x.k[u], all, hist, copies);
+        __syncthreads();
+        unsigned last;
+        if (all) {
+          if (alike) block_find_kth<ST, kBins, kWide>(hist, 2, (unsigned)max(ks[0], 0), (unsigned)max(ks[1], 0), s.pick, s.wsum);
+          else block_find_kth<ST, kBins, kCopies>(hist, 2, (unsigned)max(ks[0], 0), (unsigned)max(ks[1], 0), s.pick, s.wsum);
+          ranges();
+          floor = ks[0] > 0 ? r.lo[0] : r.lo[1];
+          if (ks[1] > 0) floor = min(floor, r.lo[1]);
+        } else {
+          block_find_kth<ST, kBins, kCopies>(hist, 1, (unsigned)k, 0u, s.pick, s.wsum);
+          bin_range(s.pick[0].bin, base, floor, last);
+          floor = max(floor, 1u);
+        }
+        if (!alike) zero_hist(s);
+      }
+      sums = reach();
+      total = (int)__builtin_amdgcn_readlane(sums, SW - 1);
+    }
+    unsigned need = 0u;  // not 0: of the keys equal to the bound only the first ones
+    if (total > CAP) {
+      r.n[0] = r.n[1] = 0u;
+      // Runs of nearly equal scores: the range of the k-th key, ten bits at a time.
+      unsigned lo = floor, last = 0xFFFFFFFFu, rank = (unsigned)k;
+      do {
+        const int shift = digit_shift(last - lo);
+  #pragma unroll
+        for (int u = 0; u < UNITS; ++u)
+          if (u < x.units) {
+            const unsigned y[4] = {x.k[u].x, x.k[u].y, x.k[u].z, x.k[u].w};
+  #pragma unroll 1
+            for (int j = 0; j < 4; ++j) {
+              const unsigned key = j == 0 ? y[0] : j == 1 ? y[1] : j == 2 ? y[2] : y[3];
+              count_key(key >= lo && key <= last, (key - lo) >> shift, s.hist, 1);
+            }
+          }
+        __syncthreads();
+        block_find_kth<ST, kSubBins, 1>(s.hist, 1, rank, 0u, s.pick, s.wsum);
+        lo += s.pick[0].bin << shift;
+        last = min(last, lo + ((1u << shift) - 1u));
+        rank = s.pick[0].rank;
+        total = k - (int)rank + (int)s.pick[0].count;
+        for (int i = tid; i < kSubBins; i += ST) s.hist[i] = 0u;
+        __syncthreads();
+      } while (total > CAP && lo != last);
+      floor = lo;
+      if (total > CAP) need = rank;
+      sums = reach();
+      total = need ? k : (int)__builtin_amdgcn_readlane(sums, SW - 1);
+    }
+    unsigned run = wv ? __builtin_amdgcn_readlane(sums, wv - 1) : 0u, erun = 0u;
+    if (need) {  // keys above the bound and equal to it, before this wave
+      int e = 0;
+  #pragma unroll
+      for (int u = 0; u < UNITS; ++u)
+        if (u < x.units)
+          e += __popcll(__ballot(x.k[u].x == floor)) + __popcll(__ballot(x.k[u].y == floor)) +
+               __popcll(__ballot(x.k[u].z == floor)) + __popcll(__ballot(x.k[u].w == floor));
+      if (lane == 0) s.weq[wv] = (unsigned)e;
+      __syncthreads();
+      const unsigned es = wave_inclusive_sum(lane < SW ? s.weq[lane] : 0u);
+      erun = wv ? __builtin_amdgcn_readlane(es, wv - 1) : 0u;
+      run = run - erun + min(erun, need);
+    }
+    const int at0 = wv * wave_units(n) * kUnit + 4 * lane;
+  #pragma unroll
+    for (int u = 0; u < UNITS; ++u)
+      if (u < x.units) {
+        const unsigned y[4] = {x.k[u].x, x.k[u].y, x.k[u].z, x.k[u].w};
+        u64 in[4];
+  #pragma unroll
+        for (int j = 0; j < 4; ++j) in[j] = __ballot(y[j] >= floor);
+        if (need) {  // uniform: cut the ties, in index order
+          u64 eq[4];
+          unsigned before = erun;
+  #pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            eq[j] = __ballot(y[j] == floor);
+            before += __builtin_amdgcn_mbcnt_hi((unsigned)(eq[j] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)eq[j], 0u));
+          }
+  #pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            in[j] &= ~__ballot(y[j] == floor && before >= need);
+            before += (unsigned)((eq[j] >> lane) & 1ull);
+            erun += (unsigned)__popcll(eq[j]);
+          }
+        }
+        if ((in[0] | in[1] | in[2] | in[3]) == 0ull) continue;
+        unsigned pos = run;
+  #pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          pos = __builtin_amdgcn_mbcnt_hi((unsigned)(in[j] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)in[j], pos));
+          run += (unsigned)__popcll(in[j]);
+        }
+  #pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if ((in[j] >> lane) & 1ull) {
+            l.key[pos] = y[j];
+            l.at[pos] = (uint16_t)(at0 + kUnit * u + j);
+            ++pos;
+          }
+      }
+    __syncthreads();
+    return total;
+  }
+}
+
+// The k-th largest of a list's n keys for two values of k, and how many of the keys equal to it are among the k.  A key
+// is among the k best if it lies above thr, or is one of the first `need` that equal it.  k <= 0: none is; k >= n: all
+// are.  hist is zero.  r.n[q] != 0: the range that holds the k[q]-th key is known.
+struct Top { unsigned thr[2], need[2]; };
+template <int CAP>
+__device__ __forceinline__ Top list_top(const List<CAP> &l, int n, const int (&k)[2], int base, TopShared &s, Ranges &r) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  Top t;
+  bool open[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    open[q] = k[q] > 0 && k[q] < n;
+    t.thr[q] = k[q] > 0 ? 0u : 0xFFFFFFFFu;
+    t.need[q] = 0u;
+  }
+  if (!open[0] && !open[1]) return t;
+  if (tid < 2) s.n_few[tid] = 0u;
+  if (tid < 2 * kFew) { (&s.above[0][0])[tid] = 0u; (&s.equal[0][0])[tid] = 0u; }
+  if ((open[0] && r.n[0] == 0u) || (open[1] && r.n[1] == 0u)) {
+    list_visit(l, n, [&](int, unsigned key) { count_key(key != 0u, (unsigned)bin_of(key, base), s.hist, kCopies); });
+    __syncthreads();
+    block_find_kth<ST, kBins, kCopies>(s.hist, 2, open[0] ? (unsigned)k[0] : 0u, open[1] ? (unsigned)k[1] : 0u, s.pick, s.wsum);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (open[q]) {
+        bin_range(s.pick[q].bin, base, r.lo[q], r.last[q]);
+        r.lo[q] = max(r.lo[q], 1u);
+        r.rank[q] = s.pick[q].rank; r.n[q] = s.pick[q].count;
+      }
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+    if (!open[q]) r.lo[q] = r.last[q] = r.n[q] = 0u;
+  __syncthreads();
+  while (r.open(0, kFew) || r.open(1, kFew)) {  // too many to rank them: ten bits at a time
+    const bool want[2] = {r.open(0, kFew), r.open(1, kFew)};
+    unsigned (*sub)[kSubWords] = (unsigned (*)[kSubWords])s.hist;
+    __syncthreads();
+    for (int i = tid; i < 2 * kSubWords; i += ST) s.hist[i] = 0u;
+    __syncthreads();
+    list_visit(l, n, [&](int, unsigned key) {
+#pragma unroll 1
+      for (int q = 0; q < 2; ++q) {
+        const unsigned lo = q ? r.lo[1] : r.lo[0], last = q ? r.last[1] : r.last[0];
+        if (q ? want[1] : want[0]) count_key(key >= lo && key <= last, (key - lo) >> digit_shift(last - lo), s.hist + q * kSubWords, 1);
+      }
+    });
+    narrow_step<ST>(2, sub, s.pick, s.wsum, want, r);
+  }
+  const bool few[2] = {r.lo[0] != r.last[0], r.lo[1] != r.last[1]};
+  if (few[0] || few[1]) {
+    list_visit(l, n, [&](int, unsigned key) {
+      if (few[0] && key - r.lo[0] <= r.last[0] - r.lo[0]) s.few[0][atomicAdd(&s.n_few[0], 1u)] = key;
+      if (few[1] && key - r.lo[1] <= r.last[1] - r.lo[1]) s.few[1][atomicAdd(&s.n_few[1], 1u)] = key;
+    });
+    __syncthreads();
+    // every key against every other: a thread takes a key and a part of those it is compared with
+#pragma unroll 1
+    for (int q = 0; q < 2; ++q) {
+      const int m = (int)(q ? r.n[1] : r.n[0]);
+      if (!(q ? few[1] : few[0])) continue;
+      const int own = tid & (kFew - 1), parts = ST / kFew;
+      if (own < m) {
+        const unsigned key = s.few[q][own];
+        unsigned g = 0, e = 0;
+        for (int i = tid / kFew; i < m; i += parts) {
+          const unsigned o = s.few[q][i];
+          g += o > key;
+          e += o == key;
+        }
+        atomicAdd(&s.above[q][own], g);
+        atomicAdd(&s.equal[q][own], e);
+      }
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int q = 0; q < 2; ++q) {
+      const unsigned rank = q ? r.rank[1] : r.rank[0];
+      if ((q ? few[1] : few[0]) && tid < (int)(q ? r.n[1] : r.n[0])) {
+        const unsigned g = s.above[q][tid], e = s.equal[q][tid];
+        if (g < rank && rank <= g + e) s.pick[q] = {s.few[q][tid], rank - g, e};  // equal keys write the same
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (few[q]) { r.lo[q] = s.pick[q].bin; r.rank[q] = s.pick[q].rank; }
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+    if (open[q]) { t.thr[q] = r.lo[q]; t.need[q] = r.rank[q]; }
+  return t;
+}
+
+// every(key): all keys.  place(key, value(entry of the list), position): the selected keys in order.  A wave takes a
+// stretch of the list, four times 64 keys at a time, whose values are read together.
+template <int CAP, class Every, class Value, class Place>
+__device__ __forceinline__ void list_place(const List<CAP> &l, int n, unsigned thr, unsigned need, TopShared &s, Every every, Value value,
+                                           Place place) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int len = (n + 64 * SW - 1) / (64 * SW) * 64, begin = wv * len, end = min(begin + len, n);
+  int g = 0, e = 0;
+#pragma unroll 1
+  for (int i = begin + lane; i - lane < end; i += 64) {
+    const unsigned key = i < end ? l.key[i] : 0u;
+    every(key);
+    g += __popcll(__ballot(key > thr));
+    e += __popcll(__ballot(key == thr && key != 0u));
+  }
+  if (lane == 0) { s.wgt[wv] = (unsigned)g; s.weq[wv] = (unsigned)e; }
+  __syncthreads();
+  const unsigned gs = wave_inclusive_sum(lane < SW ? s.wgt[lane] : 0u), es = wave_inclusive_sum(lane < SW ? s.weq[lane] : 0u);
+  unsigned erun = wv ? __builtin_amdgcn_readlane(es, wv - 1) : 0u;
+  unsigned run = (wv ? __builtin_amdgcn_readlane(gs, wv - 1) : 0u) + min(erun, need);
+#pragma unroll 1
+  for (int i0 = begin + lane; i0 - lane < end; i0 += 256) {
+    unsigned val[4], key[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int i = i0 + 64 * j;
+      key[j] = i < end ? l.key[i] : 0u;
+      val[j] = i < end ? value(i) : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool tie = key[j] == thr && key[j] != 0u;
+      const u64 eq = __ballot(tie);
+      const unsigned before = erun + __builtin_amdgcn_mbcnt_hi((unsigned)(eq >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)eq, 0u));
+      const u64 sel = __ballot(key[j] > thr || (tie && before < need));
+      erun += (unsigned)__popcll(eq);
+      if ((sel >> lane) & 1ull)
+        place(key[j], val[j], (int)__builtin_amdgcn_mbcnt_hi((unsigned)(sel >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)sel, run)));
+      run += (unsigned)__popcll(sel);
+    }
+  }
+}
+
+// Row and column of candidate i of the block map's lower triangle, row by row: i = R (R - 1) / 2 + C, C < R.
+__device__ inline void map_entry(unsigned i, int &R, int &C) {
+  int r = (int)((1.f + sqrtf(8.f * (float)i + 1.f)) * 0.5f);  // i < 2^23: off by one at most
+  if ((unsigned)r * (unsigned)(r - 1) / 2 > i) --r;
+  if ((unsigned)r * (unsigned)(r + 1) / 2 <= i) ++r;
+  R = r;
+  C = (int)(i - (unsigned)r * (unsigned)(r - 1) / 2);
+}
+
+__device__ inline int held_total(const IdxArgs &a, int arr) { return arr == 2 ? a.sh.nb * (a.sh.nb - 1) / 2 : a.sh.N; }
+// The best of an array's segments, one segment after the other: indices, or keys (key = true).
+__device__ inline unsigned *top_of(const IdxArgs &a, int h, int arr, bool key) {
+  unsigned *p = arr == 2 ? (key ? a.top_blk_key : a.top_blk) : (key ? a.top_vs_key : a.top_vs);
+  return arr == 2 ? p + (size_t)h * a.seg_blk * a.cap_top_blk : p + ((size_t)h * 2 + arr) * a.seg_vs * a.cap_top_vs;
+}
+
+// Sum of the best of v or s over its segments; whole wave, the result in every lane.  BEFORE: the segments' results
+// are those of a launch before, not of this one.
+template <bool BEFORE, class X>
+__device__ inline X result_load(const X *p) { return BEFORE ? *p : agent_load(p); }
+template <bool BEFORE>
+__device__ inline u64 held_best_sum(const IdxArgs &a, const IdxScratch *G, int arr) {
+  if (a.seg_vs == 1) return result_load<BEFORE>(&G->psum[arr]);
+  const int lane = threadIdx.x & 63, n = a.seg_vs * a.ksel[arr];
+  const unsigned key = lane < n ? result_load<BEFORE>(&G->seg_best[arr][lane]) : 0u;
+  int before = 0;  // keys of higher rank, the lower lane of equal ones first
+  for (int i = 0; i < n; ++i) {
+    const unsigned o = __builtin_amdgcn_readlane(key, i);
+    before += o > key || (o == key && i < lane);
+  }
+  const u64 sum = wave_sum63(before < a.ksel[arr] ? fx30(key) : 0ull);
+  return (u64)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)sum, 63) |
+         (u64)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(sum >> 32), 63) << 32;
+}
+template <bool BEFORE>
+__device__ inline int held_pattern(const IdxArgs &a, const IdxScratch *G) {
+  u64 vt = 0, ct = 0;
+  for (int i = 0; i < a.seg_vs; ++i) { vt += result_load<BEFORE>(&G->seg_vtot[i]); ct += result_load<BEFORE>(&G->seg_ct[i]); }
+  return decide_pattern(a, vt, ct, held_best_sum<BEFORE>(a, G, 0), held_best_sum<BEFORE>(a, G, 1));
+}
+
+// grid (segments of v, of s and of the block map, from segment `first` on, Hq).
+template <int UNITS>
+__global__ __launch_bounds__(ST) void idx_top_kernel(IdxArgs a, int first) {
+  __shared__ TopShared s;
+  __shared__ List<(UNITS == 1 ? kDirect : kCap)> l;
+  const int x0 = (int)blockIdx.x + first, h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int arr = x0 < a.seg_vs ? 0 : x0 < 2 * a.seg_vs ? 1 : 2, seg = x0 - arr * a.seg_vs;
+  const Shape &sh = a.sh;
+  if (arr == 0 && seg == 0 && tid == 0 && a.ov.pat[h] >= 0) a.out.pattern[h] = a.ov.pat[h];
+  if (!head_wants(a, h, arr == 2)) return;
+  IdxScratch *G = a.scratch + h;
+  const unsigned *src = array_of(a, arr, h);
+  const int ns = n_sel(arr), nsegs = arr == 2 ? a.seg_blk : a.seg_vs, per = arr == 2 ? a.per_blk : a.per_vs;
+  const int start = seg * per, n = min(held_total(a, arr) - start, per);
+  const int units = wave_units(n), w0 = wv * units * kUnit;
+  Held<UNITS> x;
+  x.units = max(0, min(units, (n - w0 + kUnit - 1) / kUnit));
+  // every key is on its way before the first is looked at
+  if (arr < 2) {
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+      x.k[u] = u32x4a{0u, 0u, 0u, 0u};
+      const int i = w0 + kUnit * u + 4 * lane;
+      if (u < x.units && i < n) x.k[u] = *(const u32x4a *)(src + start + i);  // n is a multiple of 4
+    }
+  } else {
+    int R, C;
+    map_entry((unsigned)min(start + w0 + 4 * lane, held_total(a, 2) - 1), R, C);
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+      x.k[u] = u32x4a{0u, 0u, 0u, 0u};
+      const int i = w0 + kUnit * u + 4 * lane;
+      if (u >= x.units) continue;
+      if (u > 0) {  // kUnit candidates on
+        C += kUnit;
+        while (__any(C >= R)) {
+          const bool next = C >= R;
+          C -= next ? R : 0;
+          R += next ? 1 : 0;
+        }
+      }
+      if (i < n) {
+        const unsigned *p = src + (size_t)R * sh.nb + C;
+        if (C + 3 < R && i + 3 < n) {
+          x.k[u] = *(const u32x4a *)p;
+        } else if (R >= 4) {  // the end of a row and the start of the next
+          const int wrap = R - C, skip = sh.nb - R;
+          unsigned y[4] = {*p, 0u, 0u, 0u};
+#pragma unroll
+          for (int j = 1; j < 4; ++j)
+            if (i + j < n) y[j] = p[j + (j >= wrap ? skip : 0)];
+          x.k[u] = u32x4a{y[0], y[1], y[2], y[3]};
+        } else {
+          unsigned y[4] = {0u, 0u, 0u, 0u};
+          int r = R, c = C;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            if (i + j < n) y[j] = src[(size_t)r * sh.nb + c];
+            if (++c == r) { ++r; c = 0; }
+          }
+          x.k[u] = u32x4a{y[0], y[1], y[2], y[3]};
+        }
+      }
+    }
+  }
+  zero_hist(s);
+  __syncthreads();
+  u64 vt = 0, ct = 0;
+  {
+    const int sbnd = (int)min((long long)sh.sink * sh.b, (long long)sh.N), lb0 = max((sh.nb - sh.local) * sh.b, sbnd);
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u)
+      if (u < x.units) {
+        const int i = w0 + kUnit * u + 4 * lane;
+        unsigned y[4] = {x.k[u].x, x.k[u].y, x.k[u].z, x.k[u].w};
+        if (arr == 2 && sh.row_norm) {
+          int R, C;
+          map_entry((unsigned)(start + i), R, C);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            y[j] = __float_as_uint(__uint_as_float(y[j]) * (float)(R + 1));
+            if (++C == R) { ++R; C = 0; }
+          }
+        }
+        if (arr == 0) {
+          u64 z = 0;
+          if (__any(max(max(y[0], y[1]), max(y[2], y[3])) >= 0x40800000u)) {  // 4 and more: beyond 32 bits
+#pragma unroll
+            for (int j = 0; j < 4; ++j) z += fx30(y[j]);
+          } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) z += (u64)(unsigned)(__uint_as_float(y[j]) * 1073741824.f);
+          }
+          vt += z;  // nothing where there is no key
+          const int c = start + i;  // the boundaries are multiples of a block
+          if (c < sbnd || c >= lb0) ct += z;
+        }
+        x.k[u] = u32x4a{i < n ? raised(y[0]) : 0u, i + 1 < n ? raised(y[1]) : 0u, i + 2 < n ? raised(y[2]) : 0u, i + 3 < n ? raised(y[3]) : 0u};
+      }
+  }
+  if (arr == 0) {
+    vt = wave_sum63(vt);
+    ct = wave_sum63(ct);
+    if (lane == 63) { s.red[0][wv] = vt; s.red[1][wv] = ct; }
+  }
+  const int k[2] = {min(ksel(a, h, sel_of(arr, 0)), n), ns > 1 ? min(ksel(a, h, sel_of(arr, 1)), n) : 0};
+  const int base = first_bin(a, arr), most = max(k[0], k[1]);
+  if (most <= 0) return;  // the block map's selection only, and then nobody else waits
+  Ranges r;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) r.lo[q] = r.last[q] = r.n[q] = r.rank[q] = 0u;
+  const int m = held_list(x, n, k, 0u, arr == 2, base, s, l, r);
+  if (arr == 0 && tid < 2) {  // behind a barrier of the list
+    u64 t = 0;
+    for (int w = 0; w < SW; ++w) t += s.red[tid][w];
+    agent_store(tid ? &G->seg_ct[seg] : &G->seg_vtot[seg], t);
+  }
+  const Top t = list_top(l, m, k, base, s, r);
+  u64 ts = 0;  // of the probe: the keys above its threshold
+  const unsigned thr_p = t.thr[0], ties = arr < 2 && k[0] < m ? thr_p - 1u : 0u;
+  if (arr < 2) {
+    __syncthreads();
+    if (nsegs > 1) {  // its keys, for the sum over all segments
+      unsigned *to = G->seg_best[arr] + seg * a.ksel[arr];
+      if (tid == 0) s.n_few[0] = 0u;
+      __syncthreads();
+      list_visit(l, m, [&](int, unsigned key) {
+        if (key > thr_p) agent_store(&to[atomicAdd(&s.n_few[0], 1u)], key - 1u);
+      });
+      __syncthreads();
+      // the ties, and nothing behind the end of a short segment
+      if (tid >= (int)s.n_few[0] && tid < a.ksel[arr]) agent_store(&to[tid], tid < k[0] ? ties : 0u);
+    }
+  }
+  const int km = ns > 1 ? k[1] : k[0];
+  const unsigned thr = km <= 0 ? ~0u : ns > 1 ? t.thr[1] : t.thr[0], need = km <= 0 ? 0u : ns > 1 ? t.need[1] : t.need[0];
+  {
+    const size_t at = (size_t)seg * min(ksel(a, h, sel_of(arr, ns - 1)), per);  // of every segment before: k, or all its keys
+    unsigned *to = top_of(a, h, arr, false) + at, *to_key = nsegs > 1 ? top_of(a, h, arr, true) + at : nullptr;
+    if (nsegs > 1 && km > 0 && tid == 0) G->seg_thr[arr][seg] = max(thr, 1u);
+    list_place(l, m, thr, need, s,
+               [&](unsigned key) {
+                 if (arr < 2 && nsegs == 1 && key > thr_p) ts += fx30(key - 1u);
+               },
+               [&](int i) { return (unsigned)(start + l.at[i]); },
+               [&](unsigned key, unsigned idx, int pos) {
+                 to[pos] = idx;
+                 if (to_key) to_key[pos] = key;
+               });
+  }
+  if (arr < 2 && nsegs == 1) {
+    ts = wave_sum63(ts);
+    if (lane == 63) s.red[1][wv] = ts;
+    __syncthreads();
+    if (tid == 0) {
+      u64 sum = (u64)t.need[0] * fx30(ties);
+      for (int w = 0; w < SW; ++w) sum += s.red[1][w];
+      agent_store(&G->psum[arr], sum);
+    }
+  }
+  if (arr == 2 || !a.decide_here) return;
+  // the block map waits for the patterns: the workgroup of v and s that arrives last decides
+  if (!arrives_last(&G->ticket_vs, 2 * a.seg_vs)) return;
+  if (a.ov.pat[h] < 0 && wv == 0) {
+    const int pat = held_pattern<false>(a, G);
+    if (lane == 0) a.out.pattern[h] = pat;
+  }
+}
+
+// grid (2 + workgroups of the block CSR, Hq): columns, diagonals, block CSR.  ROWS as T in idx_emit_kernel; SEGS: an array
+// has several segments.
+template <int ROWS, bool SEGS>
+__global__ __launch_bounds__(ST) void idx_place_kernel(IdxArgs a) {
+  __shared__ TopShared s;
+  __shared__ int s_pat, s_at[kMaxNb + 1];
+  __shared__ __attribute__((aligned(16))) char s_list[SEGS ? sizeof(List<kCap>) : 16];
+  const Shape &sh = a.sh;
+  const int h = blockIdx.y, tid = threadIdx.x, arr = min((int)blockIdx.x, 2), nb = sh.nb;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  IdxScratch *G = a.scratch + h;
+  const int nsegs = arr == 2 ? a.seg_blk : a.seg_vs, kq = ksel(a, h, arr == 2 ? 4 : arr + 2);
+  // The segments' best one after the other (of a segment kq, or all its keys), on their way while the pattern is decided.
+  Held<SEGS ? kHeldUnits : 1> x;
+  int n = 0;
+  if constexpr (SEGS) if (nsegs > 1 && !(arr == 2 && ROWS > 0)) {
+    const unsigned *from_key = top_of(a, h, arr, true);
+    const int per = arr == 2 ? a.per_blk : a.per_vs;
+    n = (nsegs - 1) * min(kq, per) + min(kq, held_total(a, arr) - (nsegs - 1) * per);
+    const int lane = tid & 63, units = wave_units(n), w0 = wv * units * kUnit;
+    x.units = max(0, min(units, (n - w0 + kUnit - 1) / kUnit));
+#pragma unroll
+    for (int u = 0; u < kHeldUnits; ++u) {
+      x.k[u] = u32x4a{0u, 0u, 0u, 0u};
+      const int i = w0 + kUnit * u + 4 * lane;
+      if (u < x.units && i < n)  // up to three words behind the end: there is room (see index_scratch_bytes)
+        x.k[u] = *(const u32x4a *)(from_key + i);
+    }
+  }
+  int pat = a.ov.pat[h];
+  if (pat < 0) {
+    if (wv == 0) {
+      const int p = a.decide_here ? a.out.pattern[h] : held_pattern<true>(a, G);
+      if (tid == 0) {
+        s_pat = p;
+        if (arr == 0) a.out.pattern[h] = p;
+      }
+    }
+    __syncthreads();
+    pat = s_pat;
+  }
+  pat = __builtin_amdgcn_readfirstlane(pat);
+  const bool wanted = pat == (arr == 2 ? SA_BLOCK_CLUSTER : SA_INTERVAL_SLASH) && !(arr == 2 && ROWS > 0);
+  const int k = wanted ? kq : 0;
+
+  // put(index, position) for the selected entries
+  auto selected = [&](auto put) {
+    const unsigned *from = top_of(a, h, arr, false);
+    if (!SEGS || nsegs <= 1) {
+      for (int i = tid; i < k; i += ST) put(from[i], i);
+      return;
+    }
+    if constexpr (SEGS) {
+      if (k <= 0) return;
+      List<kCap> &l = *(List<kCap> *)&s_list;
+      const int lane = tid & 63, w0 = wv * wave_units(n) * kUnit;
+#pragma unroll
+      for (int u = 0; u < kHeldUnits; ++u) {
+        const int i = w0 + kUnit * u + 4 * lane;
+        x.k[u].y = i + 1 < n ? x.k[u].y : 0u;
+        x.k[u].z = i + 2 < n ? x.k[u].z : 0u;
+        x.k[u].w = i + 3 < n ? x.k[u].w : 0u;
+      }
+      zero_hist(s);
+      __syncthreads();
+      const int kk[2] = {k, 0}, base = first_bin(a, arr);
+      Ranges r;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) r.lo[q] = r.last[q] = r.n[q] = r.rank[q] = 0u;
+      unsigned floor = 1u;  // k keys of one segment reach its threshold
+      for (int i = 0; i < nsegs; ++i) floor = max(floor, G->seg_thr[arr][i]);
+      const int m = held_list(x, n, kk, floor, true, base, s, l, r);
+      const Top t = list_top(l, m, kk, base, s, r);
+      __syncthreads();
+      list_place(l, m, t.thr[0], t.need[0], s, [](unsigned) {}, [&](int i) { return from[l.at[i]]; }, [&](unsigned, unsigned idx, int pos) { put(idx, pos); });
+    }
+  };
+
+  if (arr < 2) {
+    const int width = arr ? sh.k_s : sh.k_v;
+    int32_t *idx = (arr ? a.out.offs : a.out.cols) + (size_t)h * width;
+    const bool aside = arr == 1 && sh.diag_blocks;  // the offsets become blocks: the list stays empty
+    int32_t *dst = aside ? a.doffs + (size_t)h * width : idx;
+    selected([&](unsigned i, int pos) { dst[pos] = (int)i; });
+    const int shown = aside ? 0 : k;
+    for (int i = shown + tid; i < width; i += ST) idx[i] = -1;
+    if (tid == 0) {
+      (arr ? a.out.n_offs : a.out.n_cols)[h] = shown;
+      if (aside) G->ticket_rows = 0u;
+    }
+    return;
+  }
+  const int wg = (int)blockIdx.x - 2, nwg = (int)gridDim.x - 2;
+  const int part = wg * SW + wv, nparts = nwg * SW, gtid = wg * ST + tid, gthreads = nwg * ST;
+  int32_t *rp = a.out.rowptr + (size_t)h * (nb + 1);
+  int32_t *bc = a.out.blkcols + (size_t)h * sh.cap_b;
+  int total;
+  if (pat == SA_BLOCK_CLUSTER && ROWS > 0) {
+    total = emit_rows<ROWS == 0 ? 4 : ROWS, SW>(a, array_of(a, 2, h), part, nparts, rp, bc, s_at, s.wsum);
+  } else if (pat == SA_BLOCK_CLUSTER) {  // one workgroup
+    for (int i = tid; i < nb; i += ST) s_at[i] = 0;
+    __syncthreads();
+    // an entry of row R lands after the R diagonal blocks of the rows above
+    selected([&](unsigned i, int pos) {
+      int R, C;
+      map_entry(i, R, C);
+      bc[pos + R] = C;
+      atomicAdd(&s_at[R], 1);
+    });
+    __syncthreads();
+    const int per = (nb + ST - 1) / ST;
+    unsigned sum = 0, unused = 0;
+    for (int j = 0; j < per; ++j)
+      if (per * tid + j < nb) sum += (unsigned)s_at[per * tid + j];
+    unsigned run = sum;
+    block_exclusive_scan2<SW>(run, unused, s.wsum);
+    for (int j = 0; j < per; ++j) {
+      const int R = per * tid + j;
+      if (R < nb) {
+        rp[R] = (int)run + R;
+        run += (unsigned)s_at[R];
+        bc[run + R] = R;
+      }
+    }
+    total = k + nb;
+  } else {
+    total = emit_fixed(a, h, pat, part, nparts, gtid, gthreads, rp, bc);
   }
   if (gtid == 0) rp[nb] = total;
   for (int i = total + gtid; i < sh.cap_b; i += gthreads) bc[i] = -1;
@@ -1410,23 +2096,51 @@ int list_cap_blk(const Shape &sh) {
 }
 size_t round16(size_t x) { return (x + 15) & ~(size_t)15; }
 
+// What idx_top_kernel leaves of every array.
+struct HeldPlan { bool held; int seg_vs, seg_blk, per_vs, per_blk, cap_vs, cap_blk; };
+
+// Arrays that workgroups hold: where a segment's best fit its list, and the best of all segments of an array, which a
+// workgroup of the second launch takes again, are no more than it holds (and the best of all segments by the
+// pattern rule no more than a wave).  Two launches against five, 32 heads: 17.7 us and 22 at 8K tokens, 30 and 40 at 16K,
+// 54.2 and 54.6 at 32K with 7400 blocks selected below the diagonal, 34 and 53 with 2100, 46 and 60 at 64K.  A list
+// of more than 8192 blocks loses: 38.6 and 39.3 with 9400 at 16K tokens, 43.4 and 40.4 with 12600, 47 and 41 with 15300,
+// 42.5 and 36.8 with 8 heads.
+HeldPlan held_arrays(const Shape &sh) {
+  HeldPlan p;
+  const long long ncand = sh.row_select ? 0 : (long long)sh.nb * (sh.nb - 1) / 2;
+  auto split = [](long long n, int &segs, int &per) {  // even segments, in units
+    segs = (int)((n + kSeg - 1) / kSeg);
+    per = segs ? (int)(((n + segs - 1) / segs + kUnit - 1) / kUnit * kUnit) : 0;
+  };
+  split(sh.N, p.seg_vs, p.per_vs);
+  split(ncand, p.seg_blk, p.per_blk);
+  // the best k of a segment, or all its keys
+  auto best = [](long long k, long long n, int per) { return (int)std::min<long long>(k < 1 ? 1 : k, std::min<long long>(n, per)); };
+  const int kv = std::max(std::max(sh.k_v, sh.k_s), std::max(sh.probe_v, sh.probe_s));
+  p.cap_vs = best(kv, sh.N, p.per_vs);
+  p.cap_blk = ncand ? best((long long)sh.k_b - sh.nb, ncand, p.per_blk) : 0;
+  p.held = p.cap_vs <= kCap && p.cap_blk <= kCap / 2 &&
+           (p.seg_vs == 1 || (p.seg_vs <= kMaxSegs && (long long)p.seg_vs * p.cap_vs <= kSeg &&
+                              (long long)p.seg_vs * std::max(sh.probe_v, sh.probe_s) <= 64)) &&
+           (p.seg_blk <= 1 || (p.seg_blk <= kMaxMapSegs && (long long)p.seg_blk * p.cap_blk <= kSeg));
+  return p;
+}
+
+// Words of idx_top_kernel's results: indices, and keys where there are several segments.
+size_t top_words_vs(const Shape &sh, const HeldPlan &p) { return (size_t)sh.Hq * 2 * p.seg_vs * p.cap_vs; }
+size_t top_words_blk(const Shape &sh, const HeldPlan &p) { return (size_t)sh.Hq * p.seg_blk * p.cap_blk; }
+
 }  // namespace
 
 size_t index_scratch_bytes(const Shape &sh) {
   const size_t H = (size_t)sh.Hq;
-  return H * sizeof(IdxScratch) + H * 4 * list_cap_vs(sh) * 8 + H * list_cap_blk(sh) * 8 +
-         (sh.diag_blocks ? round16(H * (size_t)sh.k_s * 4) : 0);
+  const HeldPlan p = held_arrays(sh);
+  const size_t keys = p.held ? ((p.seg_vs > 1 ? 2 : 1) * top_words_vs(sh, p) + (p.seg_blk > 1 ? 2 : 1) * top_words_blk(sh, p)) * 4
+                             : H * 4 * list_cap_vs(sh) * 8 + H * list_cap_blk(sh) * 8;
+  return H * sizeof(IdxScratch) + round16(keys) + 16 + (sh.diag_blocks ? round16(H * (size_t)sh.k_s * 4) : 0);
 }
 
 namespace {
-
-// Prompts whose arrays one workgroup walks faster than several merge: see idx_select_kernel.  Measured
-// with 32 heads, one launch against four: 4096 keys and a 64 x 64 map 10 us against 29; a 256 x 256
-// map 37 against 27 (one compute unit then spends 13 us per walk), so the line lies between.
-constexpr int kSelectMaxKeys = 32768, kSelectMaxEntries = 32768;
-bool one_launch(const Shape &sh) {
-  return sh.N <= kSelectMaxKeys && (sh.row_select || sh.nb * sh.nb <= kSelectMaxEntries);
-}
 
 IdxArgs index_args(const Shape &sh, const Workspace &ws, sa_scores in, const Override &ov, sa_index out,
                    const HeadBudget *hb, bool lazy) {
@@ -1437,17 +2151,28 @@ IdxArgs index_args(const Shape &sh, const Workspace &ws, sa_scores in, const Ove
   a.list_vs = (u64 *)(a.scratch + sh.Hq);
   a.list_blk = a.list_vs + (size_t)sh.Hq * 4 * a.cap_vs;
   a.doffs = (int32_t *)(a.list_blk + (size_t)sh.Hq * a.cap_blk);
+  const HeldPlan held = held_arrays(sh);
+  a.held = held.held;
+  a.seg_vs = held.seg_vs; a.seg_blk = held.seg_blk; a.per_vs = held.per_vs; a.per_blk = held.per_blk;
+  a.cap_top_vs = held.cap_vs; a.cap_top_blk = held.cap_blk;
+  a.top_vs = a.top_vs_key = a.top_blk = a.top_blk_key = nullptr;
+  if (held.held) {
+    const size_t nv = top_words_vs(sh, held), nk = top_words_blk(sh, held);
+    a.top_vs = (unsigned *)(a.scratch + sh.Hq);
+    a.top_vs_key = a.top_vs + nv;
+    a.top_blk = a.top_vs + (held.seg_vs > 1 ? 2 : 1) * nv;
+    a.top_blk_key = a.top_blk + nk;
+    a.doffs = (int32_t *)((char *)a.top_vs + round16(((held.seg_vs > 1 ? 2 : 1) * nv + (held.seg_blk > 1 ? 2 : 1) * nk) * 4));
+  }
   a.sh = sh; a.ov = ov; a.out = out;
   // A wave takes 1024 keys of v or s; of the block map it takes 1024 entries or a 512th of the map,
   // whichever is more (a 256th at 128K tokens: 119 us for the index, a 512th 103; more, shorter waves
-  // hide more latency until merging their histograms takes over).  Where a workgroup walks a whole
-  // array, parts are single units: its waves share the work evenly from 4096 keys on.
-  const bool whole = one_launch(sh);
-  a.vpart = (whole ? 1 : kVsUnits) * kUnit;
+  // hide more latency until merging their histograms takes over).
+  a.vpart = kVsUnits * kUnit;
   a.Pv = (sh.N + WPB * a.vpart - 1) / (WPB * a.vpart);
   const long long entries = (long long)sh.nb * sh.nb, units = (entries + kUnit - 1) / kUnit;
-  long long per = whole ? 1 : (units + kMaxBlkParts - 1) / kMaxBlkParts;
-  if (!whole && per < 4) per = 4;
+  long long per = (units + kMaxBlkParts - 1) / kMaxBlkParts;
+  if (per < 4) per = 4;
   a.bpart = (int)per * kUnit;
   a.Pb = (int)(((units + per - 1) / per + WPB - 1) / WPB);
   // under the per-row rule a wave of the emission takes whole rows
@@ -1456,7 +2181,7 @@ IdxArgs index_args(const Shape &sh, const Workspace &ws, sa_scores in, const Ove
   a.refine_vs = min(a.Pv, max(kRefineVs, 32 * kRefineVs / sh.Hq));
   a.refine_blk = min(a.Pb, max(kRefineBlk, 32 * kRefineBlk / sh.Hq));
   a.first = 0;
-  a.decide_here = lazy || !one_launch(sh);
+  a.decide_here = lazy || !held.held;
   a.nb_magic = ((1ull << 40) + sh.nb - 1) / sh.nb;
   a.wrap_magic = ((1u << 20) + sh.nb - 1) / sh.nb;
   const u64 all = (u64)sh.nb * (sh.nb + 1) / 2;
@@ -1502,8 +2227,13 @@ void launch_zero(const IdxArgs &a, hipStream_t st) {
 void launch_levels(IdxArgs a, bool vs, bool blk, hipStream_t st) {
   if (a.sh.row_select || (a.ksel[4] <= 0 && !a.hb)) blk = false;
   if (!vs && !blk) return;
-  if (one_launch(a.sh)) {
-    idx_select_kernel<<<dim3((vs ? 2 : 0) + (blk ? 1 : 0), a.sh.Hq), ST, 0, st>>>(a, vs ? 0 : 2);
+  if (a.held) {
+    const dim3 grid((vs ? 2 * a.seg_vs : 0) + (blk ? a.seg_blk : 0), a.sh.Hq);
+    const int first = vs ? 0 : 2 * a.seg_vs;
+    // a unit per wave and nothing to bound: a third of the code, which every call of a prompt's layers fetches anew
+    // (4 heads at 4K tokens, in a layer: 1.2 us less)
+    if (max(a.per_vs, a.per_blk) <= kDirect) idx_top_kernel<1><<<grid, ST, 0, st>>>(a, first);
+    else idx_top_kernel<kHeldUnits><<<grid, ST, 0, st>>>(a, first);
     return;
   }
   a.first = vs ? 0 : 2 * a.Pv;
@@ -1514,8 +2244,25 @@ void launch_levels(IdxArgs a, bool vs, bool blk, hipStream_t st) {
 }
 
 void launch_finish(const IdxArgs &a, hipStream_t st) {
-  const dim3 grid(2 * a.Pv + a.Pb, a.sh.Hq);
-  if (!a.sh.row_select) idx_emit_kernel<0><<<grid, BT, 0, st>>>(a);
+  const dim3 grid(2 * a.Pv + a.Pb, a.sh.Hq), place(2 + (a.sh.row_select ? (a.sh.nb + SW - 1) / SW : 1), a.sh.Hq);
+  const bool one = a.seg_vs == 1 && a.seg_blk <= 1;
+  if (a.held && !a.sh.row_select) {
+    if (one) idx_place_kernel<0, false><<<place, ST, 0, st>>>(a);
+    else idx_place_kernel<0, true><<<place, ST, 0, st>>>(a);
+  } else if (a.held && one) {
+    static_assert(kSeg / 64 <= 1024, "rows of a map beside arrays of one segment");
+    if (a.sh.nb <= 256) idx_place_kernel<4, false><<<place, ST, 0, st>>>(a);
+    else idx_place_kernel<16, false><<<place, ST, 0, st>>>(a);
+  } else if (a.held) {
+    // the rows by themselves, in workgroups without a list's memory
+    idx_place_kernel<0, true><<<dim3(2, a.sh.Hq), ST, 0, st>>>(a);
+    IdxArgs b = a;
+    b.first = 2 * a.Pv;
+    const dim3 rows(a.Pb, a.sh.Hq);
+    if (a.sh.nb <= 1024) idx_emit_kernel<16><<<rows, BT, 0, st>>>(b);
+    else idx_emit_kernel<kMaxNb / 64><<<rows, BT, 0, st>>>(b);
+  }
+  else if (!a.sh.row_select) idx_emit_kernel<0><<<grid, BT, 0, st>>>(a);
   else if (a.sh.nb <= 256) idx_emit_kernel<4><<<grid, BT, 0, st>>>(a);
   else if (a.sh.nb <= 1024) idx_emit_kernel<16><<<grid, BT, 0, st>>>(a);
   else idx_emit_kernel<kMaxNb / 64><<<grid, BT, 0, st>>>(a);
