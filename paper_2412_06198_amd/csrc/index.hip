@@ -29,7 +29,7 @@
 // for relaxed atomics, and the fences that would cost an L2 write-back per workgroup.
 // Every launch costs 3 to 8 us whatever it does, and a pass over the scores of 32 heads 10 to 40 us.  Five
 // launches take 30 us at 10K tokens, 40 at 16K, 55 at 32K, 60 at 64K and 103 at 128K; two, where they are taken,
-// 21, 30, 54, 46 and none (4 heads at 4K: 14).
+// 21, 30, 44, 41 and none (4 heads at 4K: 14).
 //
 // With the per-row block rule (every row block of a Block-Cluster head keeps the
 // same fraction of its causal blocks) the fifth selection is switched off and
@@ -122,7 +122,7 @@ struct IdxArgs {
   // Arrays that workgroups hold (see idx_top_kernel): segments of v (and of s) and of the block map's lower triangle,
   // keys of a segment; the best of a segment, indices ([Hq][2][segments][cap], [Hq][segments][cap]) and, where
   // there are several segments, keys in the same order.
-  int held, seg_vs, seg_blk, per_vs, per_blk, cap_top_vs, cap_top_blk;
+  int held, seg_vs, seg_blk, per_vs, per_blk, cap_top_vs, cap_top_blk, place_vs;
   unsigned *top_vs, *top_blk, *top_vs_key, *top_blk_key;
 };
 
@@ -466,10 +466,11 @@ __device__ inline void hist_part(const IdxArgs &a, int arr, const unsigned *src,
   });
 }
 
-// The range of keys that bin `bin` of the level-1 histogram stands for.
+// The range of keys that bin `bin` of the level-1 histogram stands for (of one that is 2^FINE times as fine).
+template <int FINE = 0>
 __device__ inline void bin_range(unsigned bin, int base, unsigned &lo, unsigned &last) {
-  lo = bin == 0 ? 0u : (bin + base) << kBinShift;
-  last = bin == kBins - 1 ? 0xFFFFFFFFu : ((bin + 1 + base) << kBinShift) - 1u;
+  lo = bin == 0 ? 0u : (bin + (base << FINE)) << (kBinShift - FINE);
+  last = bin == (kBins << FINE) - 1 ? 0xFFFFFFFFu : ((bin + 1 + (base << FINE)) << (kBinShift - FINE)) - 1u;
 }
 
 // The selections of one array on their way to a threshold: the k-th key lies in lo .. last, has rank
@@ -1061,7 +1062,7 @@ __device__ inline unsigned raised(unsigned key) { return max(key, key + 1u); }  
 // steps, one per bit, and a key per lane and load the index of 32 heads took 28.8 us at 161 blocks, 61 at 512, 89 at
 // 1024 and 695 at 2048; like this 25.4, 48, 57 and 126.
 template <int U>
-__device__ inline void emit_row_select(const unsigned *row, int R, int kr, int32_t *out) {
+__device__ __forceinline__ void emit_row_select(const unsigned *row, int R, int kr, int32_t *out) {
   const int lane = threadIdx.x & 63;
   if (kr > 0) {
     u32x4a x[U];
@@ -1151,7 +1152,7 @@ __device__ inline void emit_row_select(const unsigned *row, int R, int kr, int32
 // Block CSR of a Block-Cluster head under the per-row rule, by workgroups of 64 NW threads: a wave takes whole rows
 // (part of nparts).  Every workgroup finds its rows' pointers for itself: thread t sums the shares of `per` rows.
 template <int T, int NW>
-__device__ inline int emit_rows(const IdxArgs &a, const unsigned *hb, int part, int nparts, int32_t *rp, int32_t *bc,
+__device__ __forceinline__ int emit_rows(const IdxArgs &a, const unsigned *hb, int part, int nparts, int32_t *rp, int32_t *bc,
                                 int *s_at, unsigned *wsum) {
   const int tid = threadIdx.x, lane = tid & 63, nb = a.sh.nb;
   const int per = (nb + 64 * NW - 1) / (64 * NW);
@@ -1272,22 +1273,22 @@ __global__ __launch_bounds__(BT) void idx_emit_kernel(IdxArgs a) {
 // of a launch, so there are no counters to clear and no tickets.  Taken where the segments' best fit a
 // workgroup again (see held_arrays).
 // What such a workgroup waits for is its own instructions: one on each of 32768 keys takes a compute unit
-// 0.25 us.  So few are spent on all keys: of the four keys of a lane the largest goes into a histogram while they
-// arrive; the k-th of those is a bound that k keys reach; the keys that reach it, a tenth more than k as a rule,
-// go to a list in LDS, in order, and everything else is done on that list.  (With all keys in LDS and the
-// walks over them 37 us a launch of 32 heads at 64K tokens, with 64 keys a step in registers 46, 27 like this.)
+// 0.25 us.  So few are spent on all keys: of the four keys of a lane the largest goes into a histogram
+// (all four where they are alike); the k-th of those is a bound that k keys reach; the keys that reach it, a
+// tenth more than k as a rule, go to a list in LDS, in order, and everything else is done on that list.  (With all
+// keys in LDS and the walks over them 37 us a launch of 32 heads at 64K tokens, with 64 keys a step in
+// registers 46, 25 like this.)
 constexpr int ST = 1024, SW = ST / 64;
 constexpr int kHeldUnits = 8;                          // units of a wave at most
 constexpr int kSeg = SW * kHeldUnits * kUnit;          // keys of a workgroup
 constexpr int kCap = 16384;                            // keys of its list
 constexpr int kDirect = SW * kUnit;                    // keys that go to the list all
-constexpr int kFew = 256;                              // keys that are ranked one against the other
-constexpr int kWide = 8;                               // copies of a bin in the histogram of all keys
+constexpr int kFew = 64;                               // keys that a wave ranks one against the other
 
 struct TopShared {
   __attribute__((aligned(16))) unsigned hist[kL1Words];
   u64 red[2][SW];
-  unsigned few[2][kFew], n_few[2], above[2][kFew], equal[2][kFew];
+  unsigned few[2][kFew], n_few[2];
   Pick pick[2];
   unsigned wsum[2 * SW], wgt[SW], weq[SW];
 };
@@ -1304,6 +1305,12 @@ struct Held { u32x4a k[UNITS]; int units; };
 __device__ inline int wave_units(int n) { return (n + SW * kUnit - 1) / (SW * kUnit); }
 
 __device__ inline int bin_of(unsigned key, int base) { return min(max((int)(key >> kBinShift) - base, 0), kBins - 1); }
+// Of keys that are alike: four bins in the place of one, so that fewer additions meet in one (those of a wave to one
+// counter take their turns) and fewer keys share that of the k-th.
+constexpr int kFine = 2, kFineBins = kBins << kFine;
+__device__ inline int fine_bin_of(unsigned key, int base) {
+  return min(max((int)(key >> (kBinShift - kFine)) - (base << kFine), 0), kFineBins - 1);
+}
 __device__ inline void zero_hist(TopShared &s) {
   for (int i = threadIdx.x; i < kL1Words / 4; i += ST) ((uint4 *)s.hist)[i] = make_uint4(0u, 0u, 0u, 0u);
 }
@@ -1328,11 +1335,11 @@ __device__ inline void count_key(bool mine, unsigned bin, unsigned *hist, int co
 }
 
 // The list of the keys that reach a bound which at least the larger k (>= 1) of the workgroup's n keys reach, or, where
-// too many are equal, of exactly the k best; returns its length.  known: such a bound, or 0.  alike: the keys of a lane
-// are much alike (neighbours in a row of the block map), so that the largest of them says little.  hist is zero and
-// left zero.  r: the ranges that hold the k-th keys, where all keys were counted (else left alone).
+// too many are equal, of exactly the k best; returns its length.  alike: the keys of a lane
+// are much alike (neighbours in a row of the block map), so that the largest of them says little.  hist is zero.
+// r: the ranges that hold the k-th keys, where all keys were counted (else left alone).
 template <int UNITS, int CAP>
-__device__ __forceinline__ int held_list(const Held<UNITS> &x, int n, const int (&ks)[2], unsigned known, bool alike, int base,
+__device__ __forceinline__ int held_list(const Held<UNITS> &x, int n, const int (&ks)[2], bool alike, int base,
                                          TopShared &s, List<CAP> &l, Ranges &r) {
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), k = max(ks[0], ks[1]);
   // Keys of a unit into the histogram; all of them, or the largest of every four.
@@ -1354,11 +1361,12 @@ __device__ __forceinline__ int held_list(const Held<UNITS> &x, int n, const int 
       if (y.w) atomicAdd(&hist[bin_of(y.w, base) * copies + copy], 1u);
     }
   };
-  auto ranges = [&]() {  // of the k-th keys, from the bins picked
+  auto ranges = [&](bool fine) {  // of the k-th keys, from the bins picked
 #pragma unroll
     for (int q = 0; q < 2; ++q)
       if (ks[q] > 0) {
-        bin_range(s.pick[q].bin, base, r.lo[q], r.last[q]);
+        if (fine) bin_range<kFine>(s.pick[q].bin, base, r.lo[q], r.last[q]);
+        else bin_range(s.pick[q].bin, base, r.lo[q], r.last[q]);
         r.lo[q] = max(r.lo[q], 1u);
         r.rank[q] = s.pick[q].rank; r.n[q] = s.pick[q].count;
       }
@@ -1374,15 +1382,15 @@ __device__ __forceinline__ int held_list(const Held<UNITS> &x, int n, const int 
     __syncthreads();
     if (k < n) {
       block_find_kth<ST, kBins, kCopies>(s.hist, 2, (unsigned)max(ks[0], 0), (unsigned)max(ks[1], 0), s.pick, s.wsum);
-      ranges();
+      ranges(false);
     }
     return n;
   }
   if constexpr (UNITS > 1) {
-    unsigned floor = known ? known : 1u;
+    unsigned floor = 1u;
     auto reach = [&]() {  // keys that reach the bound, in the waves up to each
       int c = 0;
-  #pragma unroll
+#pragma unroll
       for (int u = 0; u < UNITS; ++u)
         if (u < x.units)
           c += __popcll(__ballot(x.k[u].x >= floor)) + __popcll(__ballot(x.k[u].y >= floor)) +
@@ -1392,45 +1400,43 @@ __device__ __forceinline__ int held_list(const Held<UNITS> &x, int n, const int 
       __syncthreads();
       return wave_inclusive_sum(lane < SW ? s.wgt[lane] : 0u);
     };
-    unsigned sums = 0u;
-    int total = CAP + 1;
-    if (known) {
-      sums = reach();
-      total = (int)__builtin_amdgcn_readlane(sums, SW - 1);
-    }
-    if (!known || total > 2 * k) {
-      if (k < n) {
-        // Keys that are alike: in the list's memory, with many copies of a bin (the weights of a map's row fall into a few
-        // bins, and additions of a wave to one counter take their turns).
-        const bool all = alike || 8 * k > n || n <= 2 * SW * kUnit;
-        unsigned *hist = alike ? l.key : s.hist;
-        static_assert(kBins * kWide <= CAP, "the histogram fits the list");
-        if (alike) {
-          for (int i = tid; i < kBins * kWide / 4; i += ST) ((uint4 *)hist)[i] = make_uint4(0u, 0u, 0u, 0u);
-          __syncthreads();
-        }
-        const int copies = alike ? kWide : kCopies;
-  #pragma unroll
-        for (int u = 0; u < UNITS; ++u)
-          if (u < x.units) count(x.k[u], all, hist, copies);
+    if (k < n) {
+      const bool all = alike || 8 * k > n || n <= 2 * SW * kUnit;
+      if (alike) {  // in the list's memory
+        static_assert(kFineBins * kCopies <= CAP, "the histogram fits the list");
+        for (int i = tid; i < kFineBins * kCopies / 4; i += ST) ((uint4 *)l.key)[i] = make_uint4(0u, 0u, 0u, 0u);
         __syncthreads();
-        unsigned last;
-        if (all) {
-          if (alike) block_find_kth<ST, kBins, kWide>(hist, 2, (unsigned)max(ks[0], 0), (unsigned)max(ks[1], 0), s.pick, s.wsum);
-          else block_find_kth<ST, kBins, kCopies>(hist, 2, (unsigned)max(ks[0], 0), (unsigned)max(ks[1], 0), s.pick, s.wsum);
-          ranges();
-          floor = ks[0] > 0 ? r.lo[0] : r.lo[1];
-          if (ks[1] > 0) floor = min(floor, r.lo[1]);
-        } else {
-          block_find_kth<ST, kBins, kCopies>(hist, 1, (unsigned)k, 0u, s.pick, s.wsum);
-          bin_range(s.pick[0].bin, base, floor, last);
-          floor = max(floor, 1u);
-        }
-        if (!alike) zero_hist(s);
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u)
+          if (u < x.units) {
+            const unsigned y[4] = {x.k[u].x, x.k[u].y, x.k[u].z, x.k[u].w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (y[j]) atomicAdd(&l.key[fine_bin_of(y[j], base) * kCopies + (lane & (kCopies - 1))], 1u);
+          }
+        __syncthreads();
+        block_find_kth<ST, kFineBins, kCopies>(l.key, 2, (unsigned)max(ks[0], 0), (unsigned)max(ks[1], 0), s.pick, s.wsum);
+      } else {
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u)
+          if (u < x.units) count(x.k[u], all, s.hist, kCopies);
+        __syncthreads();
+        if (all) block_find_kth<ST, kBins, kCopies>(s.hist, 2, (unsigned)max(ks[0], 0), (unsigned)max(ks[1], 0), s.pick, s.wsum);
+        else block_find_kth<ST, kBins, kCopies>(s.hist, 1, (unsigned)k, 0u, s.pick, s.wsum);
+        zero_hist(s);
       }
-      sums = reach();
-      total = (int)__builtin_amdgcn_readlane(sums, SW - 1);
+      if (all) {
+        ranges(alike);
+        floor = ks[0] > 0 ? r.lo[0] : r.lo[1];
+        if (ks[1] > 0) floor = min(floor, r.lo[1]);
+      } else {
+        unsigned last;
+        bin_range(s.pick[0].bin, base, floor, last);
+        floor = max(floor, 1u);
+      }
     }
+    unsigned sums = reach();
+    int total = (int)__builtin_amdgcn_readlane(sums, SW - 1);
     unsigned need = 0u;  // not 0: of the keys equal to the bound only the first ones
     if (total > CAP) {
       r.n[0] = r.n[1] = 0u;
@@ -1465,7 +1471,7 @@ __device__ __forceinline__ int held_list(const Held<UNITS> &x, int n, const int 
     unsigned run = wv ? __builtin_amdgcn_readlane(sums, wv - 1) : 0u, erun = 0u;
     if (need) {  // keys above the bound and equal to it, before this wave
       int e = 0;
-  #pragma unroll
+#pragma unroll
       for (int u = 0; u < UNITS; ++u)
         if (u < x.units)
           e += __popcll(__ballot(x.k[u].x == floor)) + __popcll(__ballot(x.k[u].y == floor)) +
@@ -1519,6 +1525,19 @@ __device__ __forceinline__ int held_list(const Held<UNITS> &x, int n, const int 
   }
 }
 
+// Of n <= kFew keys the one of rank `rank` from the top, its rank among its equals, and those: a wave, each lane counts the
+// keys above its own.
+__device__ inline void few_rank(TopShared &s, int q, unsigned n, unsigned rank) {
+  const unsigned lane = threadIdx.x & 63, key = lane < n ? s.few[q][lane] : 0u;
+  unsigned g = 0u, e = 0u;
+  for (unsigned i = 0; i < n; ++i) {
+    const unsigned o = (unsigned)__builtin_amdgcn_readlane((int)key, (int)i);
+    g += o > key;
+    e += o == key;
+  }
+  if (lane < n && g < rank && rank <= g + e) s.pick[q] = {key, rank - g, e};  // equal keys write the same
+}
+
 // The k-th largest of a list's n keys for two values of k, and how many of the keys equal to it are among the k.  A key
 // is among the k best if it lies above thr, or is one of the first `need` that equal it.  k <= 0: none is; k >= n: all
 // are.  hist is zero.  r.n[q] != 0: the range that holds the k[q]-th key is known.
@@ -1536,7 +1555,6 @@ __device__ __forceinline__ Top list_top(const List<CAP> &l, int n, const int (&k
   }
   if (!open[0] && !open[1]) return t;
   if (tid < 2) s.n_few[tid] = 0u;
-  if (tid < 2 * kFew) { (&s.above[0][0])[tid] = 0u; (&s.equal[0][0])[tid] = 0u; }
   if ((open[0] && r.n[0] == 0u) || (open[1] && r.n[1] == 0u)) {
     list_visit(l, n, [&](int, unsigned key) { count_key(key != 0u, (unsigned)bin_of(key, base), s.hist, kCopies); });
     __syncthreads();
@@ -1575,33 +1593,8 @@ __device__ __forceinline__ Top list_top(const List<CAP> &l, int n, const int (&k
       if (few[1] && key - r.lo[1] <= r.last[1] - r.lo[1]) s.few[1][atomicAdd(&s.n_few[1], 1u)] = key;
     });
     __syncthreads();
-    // every key against every other: a thread takes a key and a part of those it is compared with
-#pragma unroll 1
-    for (int q = 0; q < 2; ++q) {
-      const int m = (int)(q ? r.n[1] : r.n[0]);
-      if (!(q ? few[1] : few[0])) continue;
-      const int own = tid & (kFew - 1), parts = ST / kFew;
-      if (own < m) {
-        const unsigned key = s.few[q][own];
-        unsigned g = 0, e = 0;
-        for (int i = tid / kFew; i < m; i += parts) {
-          const unsigned o = s.few[q][i];
-          g += o > key;
-          e += o == key;
-        }
-        atomicAdd(&s.above[q][own], g);
-        atomicAdd(&s.equal[q][own], e);
-      }
-    }
-    __syncthreads();
-#pragma unroll 1
-    for (int q = 0; q < 2; ++q) {
-      const unsigned rank = q ? r.rank[1] : r.rank[0];
-      if ((q ? few[1] : few[0]) && tid < (int)(q ? r.n[1] : r.n[0])) {
-        const unsigned g = s.above[q][tid], e = s.equal[q][tid];
-        if (g < rank && rank <= g + e) s.pick[q] = {s.few[q][tid], rank - g, e};  // equal keys write the same
-      }
-    }
+    if (wv == 0 && few[0]) few_rank(s, 0, r.n[0], r.rank[0]);
+    if (wv == 1 && few[1]) few_rank(s, 1, r.n[1], r.rank[1]);
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < 2; ++q)
@@ -1724,8 +1717,10 @@ __global__ __launch_bounds__(ST) void idx_top_kernel(IdxArgs a, int first) {
       if (u < x.units && i < n) x.k[u] = *(const u32x4a *)(src + start + i);  // n is a multiple of 4
     }
   } else {
+    // Four candidates of a lane lie in one row, or in the end of one and the start of the next: `skip` entries further on.
     int R, C;
     map_entry((unsigned)min(start + w0 + 4 * lane, held_total(a, 2) - 1), R, C);
+    unsigned at = (unsigned)R * sh.nb + C;
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) {
       x.k[u] = u32x4a{0u, 0u, 0u, 0u};
@@ -1733,33 +1728,34 @@ __global__ __launch_bounds__(ST) void idx_top_kernel(IdxArgs a, int first) {
       if (u >= x.units) continue;
       if (u > 0) {  // kUnit candidates on
         C += kUnit;
+        at += kUnit;
         while (__any(C >= R)) {
           const bool next = C >= R;
           C -= next ? R : 0;
+          at += next ? sh.nb - R : 0;
           R += next ? 1 : 0;
         }
       }
-      if (i < n) {
-        const unsigned *p = src + (size_t)R * sh.nb + C;
-        if (C + 3 < R && i + 3 < n) {
-          x.k[u] = *(const u32x4a *)p;
-        } else if (R >= 4) {  // the end of a row and the start of the next
-          const int wrap = R - C, skip = sh.nb - R;
-          unsigned y[4] = {*p, 0u, 0u, 0u};
-#pragma unroll
-          for (int j = 1; j < 4; ++j)
-            if (i + j < n) y[j] = p[j + (j >= wrap ? skip : 0)];
-          x.k[u] = u32x4a{y[0], y[1], y[2], y[3]};
+      if (i + 3 < n && R >= 4) {
+        const int wrap = R - C, skip = sh.nb - R;
+        const unsigned *q = src + at;
+        if (wrap >= 4) {
+          x.k[u] = *(const u32x4a *)q;
         } else {
-          unsigned y[4] = {0u, 0u, 0u, 0u};
-          int r = R, c = C;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            if (i + j < n) y[j] = src[(size_t)r * sh.nb + c];
-            if (++c == r) { ++r; c = 0; }
-          }
-          x.k[u] = u32x4a{y[0], y[1], y[2], y[3]};
+          x.k[u].x = q[0];
+          x.k[u].y = q[1 + (wrap > 1 ? 0 : skip)];
+          x.k[u].z = q[2 + (wrap > 2 ? 0 : skip)];
+          x.k[u].w = q[3 + skip];
         }
+      } else if (i < n) {  // the first rows, and the end of the segment
+        unsigned y[4] = {0u, 0u, 0u, 0u};
+        int r = R, c = C;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (i + j < n) y[j] = src[(size_t)r * sh.nb + c];
+          if (++c == r) { ++r; c = 0; }
+        }
+        x.k[u] = u32x4a{y[0], y[1], y[2], y[3]};
       }
     }
   }
@@ -1809,7 +1805,7 @@ __global__ __launch_bounds__(ST) void idx_top_kernel(IdxArgs a, int first) {
   Ranges r;
 #pragma unroll
   for (int q = 0; q < 2; ++q) r.lo[q] = r.last[q] = r.n[q] = r.rank[q] = 0u;
-  const int m = held_list(x, n, k, 0u, arr == 2, base, s, l, r);
+  const int m = held_list(x, n, k, arr == 2, base, s, l, r);
   if (arr == 0 && tid < 2) {  // behind a barrier of the list
     u64 t = 0;
     for (int w = 0; w < SW; ++w) t += s.red[tid][w];
@@ -1867,34 +1863,106 @@ __global__ __launch_bounds__(ST) void idx_top_kernel(IdxArgs a, int first) {
   }
 }
 
-// grid (2 + workgroups of the block CSR, Hq): columns, diagonals, block CSR.  ROWS as T in idx_emit_kernel; SEGS: an array
-// has several segments.
+constexpr int kSlice = 4 * ST;    // selected entries' candidates that a workgroup of the second launch writes
+constexpr int kMapCopies = 4;     // copies of a bin in its histogram
+
+// The k best of an array's segments' best, of which every thread holds four neighbours per slice: threshold, and how many
+// of the keys equal to it are among them (all: 0).  floor: a bound that k keys reach.  hist and n_few are zero.
+// The range of the k-th key is cut into 2048, and on into 1024, until a wave can compare the keys in it.
+__device__ __forceinline__ void best_of_segments(const Held<kHeldUnits> &x, unsigned k, unsigned floor, unsigned *hist,
+                                                 TopShared &s, unsigned &thr, unsigned &need) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  unsigned most = 0u;
+#pragma unroll
+  for (int u = 0; u < kHeldUnits; ++u)
+    if (u < x.units) most = max(max(most, max(x.k[u].x, x.k[u].y)), max(x.k[u].z, x.k[u].w));
+  most = wave_max(most);
+  if (lane == 0) s.wgt[wv] = most;
+  __syncthreads();
+  unsigned lo = floor, last = wave_max(lane < SW ? s.wgt[lane] : 0u), rank = k, n;
+  {
+    const unsigned bits = 32 - __clz((int)(last - lo));  // __clz(0) = 32
+    const int shift = bits > 11 ? (int)bits - 11 : 0;
+#pragma unroll
+    for (int u = 0; u < kHeldUnits; ++u)
+      if (u < x.units) {
+        const unsigned y[4] = {x.k[u].x, x.k[u].y, x.k[u].z, x.k[u].w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (y[j] >= lo) atomicAdd(&hist[((y[j] - lo) >> shift) * kMapCopies + (lane & (kMapCopies - 1))], 1u);
+      }
+    __syncthreads();
+    block_find_kth<ST, kBins, kMapCopies>(hist, 1, rank, 0u, s.pick, s.wsum);
+    lo += s.pick[0].bin << shift;
+    last = min(last, lo + ((1u << shift) - 1u));
+    rank = s.pick[0].rank;
+    n = s.pick[0].count;
+  }
+  while (n > (unsigned)kFew && lo != last) {
+    const int shift = digit_shift(last - lo);
+    __syncthreads();
+    for (int i = threadIdx.x; i < kSubBins; i += ST) hist[i] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kHeldUnits; ++u)
+      if (u < x.units) {
+        const unsigned y[4] = {x.k[u].x, x.k[u].y, x.k[u].z, x.k[u].w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) count_key(y[j] >= lo && y[j] <= last, (y[j] - lo) >> shift, hist, 1);
+      }
+    __syncthreads();
+    block_find_kth<ST, kSubBins, 1>(hist, 1, rank, 0u, s.pick, s.wsum);
+    lo += s.pick[0].bin << shift;
+    last = min(last, lo + ((1u << shift) - 1u));
+    rank = s.pick[0].rank;
+    n = s.pick[0].count;
+  }
+  if (lo != last) {
+#pragma unroll
+    for (int u = 0; u < kHeldUnits; ++u)
+      if (u < x.units) {
+        const unsigned y[4] = {x.k[u].x, x.k[u].y, x.k[u].z, x.k[u].w};
+        if (min(min(y[0] - lo, y[1] - lo), min(y[2] - lo, y[3] - lo)) > last - lo) continue;  // as a rule
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (y[j] - lo <= last - lo) s.few[0][atomicAdd(&s.n_few[0], 1u)] = y[j];
+      }
+    __syncthreads();
+    if (wv == 0) few_rank(s, 0, n, rank);
+    __syncthreads();
+    lo = s.pick[0].bin; rank = s.pick[0].rank; n = s.pick[0].count;
+  }
+  thr = lo;
+  need = rank < n ? rank : 0u;
+}
+
+// grid (slices of the columns, of the diagonals, workgroups of the block CSR, Hq).  ROWS as T in idx_emit_kernel; SEGS: an
+// array has several segments, the best of whose best every workgroup finds for itself; then it writes the selected entries of
+// its slice.  What bounds it is the instructions that a workgroup spends on all segments' best, some 12 on each, and before
+// them the time until the pattern is known and the keys are there (5 of 18 us).  With one workgroup per array and head,
+// which made a list of the keys that reach the bound, 32 heads at 32K tokens (29500 best of four segments) took 28 us,
+// like this 18; at 64K (19000 of four) 21 and 15.
 template <int ROWS, bool SEGS>
 __global__ __launch_bounds__(ST) void idx_place_kernel(IdxArgs a) {
   __shared__ TopShared s;
-  __shared__ int s_pat, s_at[kMaxNb + 1];
-  __shared__ __attribute__((aligned(16))) char s_list[SEGS ? sizeof(List<kCap>) : 16];
+  __shared__ int s_pat, s_at[ROWS > 0 ? kMaxNb + 1 : 1];
+  __shared__ __attribute__((aligned(16))) unsigned s_hist[SEGS ? kBins * kMapCopies : 4];
+  __shared__ uint16_t s_row[ROWS > 0 ? 1 : kSlice];  // rows of the selected entries of the slice
   const Shape &sh = a.sh;
-  const int h = blockIdx.y, tid = threadIdx.x, arr = min((int)blockIdx.x, 2), nb = sh.nb;
+  const int x0 = (int)blockIdx.x, h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, nb = sh.nb;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int place_vs = SEGS ? a.place_vs : 1;
+  const int arr = x0 < place_vs ? 0 : x0 < 2 * place_vs ? 1 : 2, wg = x0 - arr * place_vs;
+  const int nwg = arr == 2 ? (int)gridDim.x - 2 * place_vs : place_vs;
+  const bool rows = arr == 2 && ROWS > 0;
   IdxScratch *G = a.scratch + h;
   const int nsegs = arr == 2 ? a.seg_blk : a.seg_vs, kq = ksel(a, h, arr == 2 ? 4 : arr + 2);
-  // The segments' best one after the other (of a segment kq, or all its keys), on their way while the pattern is decided.
-  Held<SEGS ? kHeldUnits : 1> x;
-  int n = 0;
-  if constexpr (SEGS) if (nsegs > 1 && !(arr == 2 && ROWS > 0)) {
-    const unsigned *from_key = top_of(a, h, arr, true);
+  const unsigned *from = top_of(a, h, arr, false);
+  const int i0 = wg * kSlice + (SEGS ? 4 * tid : tid);  // the first of this thread's four entries of the slice
+  int n = kq;
+  if (SEGS && nsegs > 1) {  // the segments' best one after the other: of a segment kq, or all its keys
     const int per = arr == 2 ? a.per_blk : a.per_vs;
     n = (nsegs - 1) * min(kq, per) + min(kq, held_total(a, arr) - (nsegs - 1) * per);
-    const int lane = tid & 63, units = wave_units(n), w0 = wv * units * kUnit;
-    x.units = max(0, min(units, (n - w0 + kUnit - 1) / kUnit));
-#pragma unroll
-    for (int u = 0; u < kHeldUnits; ++u) {
-      x.k[u] = u32x4a{0u, 0u, 0u, 0u};
-      const int i = w0 + kUnit * u + 4 * lane;
-      if (u < x.units && i < n)  // up to three words behind the end: there is room (see index_scratch_bytes)
-        x.k[u] = *(const u32x4a *)(from_key + i);
-    }
   }
   int pat = a.ov.pat[h];
   if (pat < 0) {
@@ -1902,95 +1970,175 @@ __global__ __launch_bounds__(ST) void idx_place_kernel(IdxArgs a) {
       const int p = a.decide_here ? a.out.pattern[h] : held_pattern<true>(a, G);
       if (tid == 0) {
         s_pat = p;
-        if (arr == 0) a.out.pattern[h] = p;
+        if (x0 == 0) a.out.pattern[h] = p;
       }
     }
     __syncthreads();
     pat = s_pat;
   }
   pat = __builtin_amdgcn_readfirstlane(pat);
-  const bool wanted = pat == (arr == 2 ? SA_BLOCK_CLUSTER : SA_INTERVAL_SLASH) && !(arr == 2 && ROWS > 0);
+  const bool wanted = pat == (arr == 2 ? SA_BLOCK_CLUSTER : SA_INTERVAL_SLASH) && !rows;
   const int k = wanted ? kq : 0;
-
-  // put(index, position) for the selected entries
-  auto selected = [&](auto put) {
-    const unsigned *from = top_of(a, h, arr, false);
-    if (!SEGS || nsegs <= 1) {
-      for (int i = tid; i < k; i += ST) put(from[i], i);
-      return;
-    }
-    if constexpr (SEGS) {
-      if (k <= 0) return;
-      List<kCap> &l = *(List<kCap> *)&s_list;
-      const int lane = tid & 63, w0 = wv * wave_units(n) * kUnit;
+  Held<SEGS ? kHeldUnits : 1> x;
+  unsigned floor = 1u;            // k keys of one segment reach its threshold
+  unsigned begin = 0u, end = 0u;  // the first candidates of this slice and of the next
+  if (wanted && arr == 2) {
+    if (wg > 0 && wg * kSlice < n) begin = from[wg * kSlice];
+    if ((wg + 1) * kSlice < n) end = from[(wg + 1) * kSlice];
+  }
+  // Up to three words behind the end are read: there is room (see index_scratch_bytes).
+  unsigned own[4] = {0u, 0u, 0u, 0u};
+  if (!SEGS && arr == 2) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (i0 + ST * j < k) own[j] = from[i0 + ST * j];
+  } else if (SEGS && k > 0 && i0 < n) {
+    const u32x4a y = *(const u32x4a *)(from + i0);
+    own[0] = y.x; own[1] = y.y; own[2] = y.z; own[3] = y.w;
+  }
+  if constexpr (SEGS)
+    if (k > 0 && nsegs > 1) {  // only now: all heads' keys to all their workgroups are more than the pattern takes to decide
+      const unsigned *from_key = top_of(a, h, arr, true);
+      x.units = (n + kSlice - 1) / kSlice;
 #pragma unroll
       for (int u = 0; u < kHeldUnits; ++u) {
-        const int i = w0 + kUnit * u + 4 * lane;
+        x.k[u] = u32x4a{0u, 0u, 0u, 0u};
+        const int i = kSlice * u + 4 * tid;
+        if (i < n) x.k[u] = *(const u32x4a *)(from_key + i);
+      }
+      for (int i = 0; i < nsegs; ++i) floor = max(floor, G->seg_thr[arr][i]);
+      for (int i = tid; i < kBins * kMapCopies / 4; i += ST) ((uint4 *)s_hist)[i] = make_uint4(0u, 0u, 0u, 0u);
+      if (tid == 0) s.n_few[0] = 0u;
+    }
+
+  // This thread's entries: places in the index (-1: not selected); of the slice: selected entries before it and in it.
+  int pos[4] = {-1, -1, -1, -1}, before = 0, count = 0;
+  if (k > 0 && (!SEGS || nsegs <= 1)) {
+    count = max(0, min(k - wg * kSlice, kSlice));
+    before = min(wg * kSlice, k);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int i = i0 + (SEGS ? j : ST * j);
+      pos[j] = i < k ? i : -1;
+    }
+  }
+  if constexpr (SEGS)
+    if (k > 0 && nsegs > 1) {
+#pragma unroll
+      for (int u = 0; u < kHeldUnits; ++u) {
+        const int i = kSlice * u + 4 * tid;
         x.k[u].y = i + 1 < n ? x.k[u].y : 0u;
         x.k[u].z = i + 2 < n ? x.k[u].z : 0u;
         x.k[u].w = i + 3 < n ? x.k[u].w : 0u;
       }
-      zero_hist(s);
       __syncthreads();
-      const int kk[2] = {k, 0}, base = first_bin(a, arr);
-      Ranges r;
+      unsigned thr, need;
+      best_of_segments(x, (unsigned)k, floor, s_hist, s, thr, need);
+      // In the order of the index: slice by slice, wave by wave.  Above the threshold (or, where all ties are taken, from it
+      // on) and equal to it, in the slices before and in this one.
+      const unsigned below = need ? thr : thr - 1u;
+      int gt = 0, eq = 0, gt_own = 0, eq_own = 0;
+      unsigned in = 0u, tie = 0u;
 #pragma unroll
-      for (int q = 0; q < 2; ++q) r.lo[q] = r.last[q] = r.n[q] = r.rank[q] = 0u;
-      unsigned floor = 1u;  // k keys of one segment reach its threshold
-      for (int i = 0; i < nsegs; ++i) floor = max(floor, G->seg_thr[arr][i]);
-      const int m = held_list(x, n, kk, floor, true, base, s, l, r);
-      const Top t = list_top(l, m, kk, base, s, r);
+      for (int u = 0; u < kHeldUnits; ++u)
+        if (u < x.units && u <= wg) {
+          const unsigned y[4] = {x.k[u].x, x.k[u].y, x.k[u].z, x.k[u].w};
+          int g = 0, e = 0;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            g += __popcll(__ballot(y[j] > below));
+            if (need) e += __popcll(__ballot(y[j] == thr));
+          }
+          if (u < wg) {
+            gt += g; eq += e;
+          } else {
+            gt_own = g; eq_own = e;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              in |= (unsigned)(y[j] > below) << j;
+              tie |= (unsigned)(need && y[j] == thr) << j;
+            }
+          }
+        }
+      if (lane == 0) { s.wgt[wv] = (unsigned)(gt + (gt_own << 16)); s.weq[wv] = (unsigned)(eq + (eq_own << 16)); }
       __syncthreads();
-      list_place(l, m, t.thr[0], t.need[0], s, [](unsigned) {}, [&](int i) { return from[l.at[i]]; }, [&](unsigned, unsigned idx, int pos) { put(idx, pos); });
+      const unsigned sg = lane < SW ? s.wgt[lane] : 0u, se = lane < SW ? s.weq[lane] : 0u;
+      const unsigned g0 = wave_inclusive_sum(sg & 0xFFFFu), g1 = wave_inclusive_sum(sg >> 16);
+      const unsigned e0 = wave_inclusive_sum(se & 0xFFFFu), e1 = wave_inclusive_sum(se >> 16);
+      const unsigned ties0 = __builtin_amdgcn_readlane(e0, SW - 1), ties1 = ties0 + __builtin_amdgcn_readlane(e1, SW - 1);
+      before = (int)(__builtin_amdgcn_readlane(g0, SW - 1) + min(ties0, need));
+      count = (int)(__builtin_amdgcn_readlane(g0, SW - 1) + __builtin_amdgcn_readlane(g1, SW - 1) + min(ties1, need)) - before;
+      unsigned gr = __builtin_amdgcn_readlane(g0, SW - 1) + (wv ? __builtin_amdgcn_readlane(g1, wv - 1) : 0u);
+      unsigned er = ties0 + (wv ? __builtin_amdgcn_readlane(e1, wv - 1) : 0u);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const u64 bg = __ballot((in >> j) & 1u), be = __ballot((tie >> j) & 1u);
+        gr = __builtin_amdgcn_mbcnt_hi((unsigned)(bg >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bg, gr));
+        er = __builtin_amdgcn_mbcnt_hi((unsigned)(be >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)be, er));
+      }
+      int at = (int)(gr + min(er, need));
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (((in >> j) & 1u) || (((tie >> j) & 1u) && er++ < need)) pos[j] = at++;
     }
-  };
 
   if (arr < 2) {
     const int width = arr ? sh.k_s : sh.k_v;
     int32_t *idx = (arr ? a.out.offs : a.out.cols) + (size_t)h * width;
     const bool aside = arr == 1 && sh.diag_blocks;  // the offsets become blocks: the list stays empty
     int32_t *dst = aside ? a.doffs + (size_t)h * width : idx;
-    selected([&](unsigned i, int pos) { dst[pos] = (int)i; });
+    if constexpr (SEGS) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (pos[j] >= 0) dst[pos[j]] = (int)own[j];
+    } else {
+      for (int i = tid; i < k; i += ST) dst[i] = (int)from[i];
+    }
     const int shown = aside ? 0 : k;
-    for (int i = shown + tid; i < width; i += ST) idx[i] = -1;
-    if (tid == 0) {
+    for (int i = shown + wg * ST + tid; i < width; i += nwg * ST) idx[i] = -1;
+    if (wg == 0 && tid == 0) {
       (arr ? a.out.n_offs : a.out.n_cols)[h] = shown;
       if (aside) G->ticket_rows = 0u;
     }
     return;
   }
-  const int wg = (int)blockIdx.x - 2, nwg = (int)gridDim.x - 2;
   const int part = wg * SW + wv, nparts = nwg * SW, gtid = wg * ST + tid, gthreads = nwg * ST;
   int32_t *rp = a.out.rowptr + (size_t)h * (nb + 1);
   int32_t *bc = a.out.blkcols + (size_t)h * sh.cap_b;
   int total;
   if (pat == SA_BLOCK_CLUSTER && ROWS > 0) {
     total = emit_rows<ROWS == 0 ? 4 : ROWS, SW>(a, array_of(a, 2, h), part, nparts, rp, bc, s_at, s.wsum);
-  } else if (pat == SA_BLOCK_CLUSTER) {  // one workgroup
-    for (int i = tid; i < nb; i += ST) s_at[i] = 0;
-    __syncthreads();
+  } else if (pat == SA_BLOCK_CLUSTER) {
     // an entry of row R lands after the R diagonal blocks of the rows above
-    selected([&](unsigned i, int pos) {
-      int R, C;
-      map_entry(i, R, C);
-      bc[pos + R] = C;
-      atomicAdd(&s_at[R], 1);
-    });
-    __syncthreads();
-    const int per = (nb + ST - 1) / ST;
-    unsigned sum = 0, unused = 0;
-    for (int j = 0; j < per; ++j)
-      if (per * tid + j < nb) sum += (unsigned)s_at[per * tid + j];
-    unsigned run = sum;
-    block_exclusive_scan2<SW>(run, unused, s.wsum);
-    for (int j = 0; j < per; ++j) {
-      const int R = per * tid + j;
-      if (R < nb) {
-        rp[R] = (int)run + R;
-        run += (unsigned)s_at[R];
-        bc[run + R] = R;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (pos[j] >= 0) {
+        int R, C;
+        map_entry(own[j], R, C);
+        bc[pos[j] + R] = C;
+        s_row[pos[j] - before] = (uint16_t)R;
       }
+    __syncthreads();
+    // The rows behind that of the slice's first candidate, up to that of the next slice's first: no entry of another slice
+    // decides where they start.
+    int r0 = 0, r1 = nb, C;
+    if (wg > 0) {
+      if (wg * kSlice < n) map_entry(begin, r0, C);
+      else r0 = nb;
     }
+    if ((wg + 1) * kSlice < n) map_entry(end, r1, C);
+    for (int r = r0 + 1 + tid; r <= r1; r += ST) {
+      int lo = 0, hi = count;  // the first entry of the slice in row r or behind
+      while (lo < hi) {
+        const int m = (lo + hi) / 2;
+        if ((int)s_row[m] < r) lo = m + 1;
+        else hi = m;
+      }
+      const int at = before + lo + r;
+      if (r < nb) rp[r] = at;
+      bc[at - 1] = r - 1;
+    }
+    if (gtid == 0) rp[0] = 0;
     total = k + nb;
   } else {
     total = emit_fixed(a, h, pat, part, nparts, gtid, gthreads, rp, bc);
@@ -2101,8 +2249,8 @@ struct HeldPlan { bool held; int seg_vs, seg_blk, per_vs, per_blk, cap_vs, cap_b
 
 // Arrays that workgroups hold: where a segment's best fit its list, and the best of all segments of an array, which a
 // workgroup of the second launch takes again, are no more than it holds (and the best of all segments by the
-// pattern rule no more than a wave).  Two launches against five, 32 heads: 17.7 us and 22 at 8K tokens, 30 and 40 at 16K,
-// 54.2 and 54.6 at 32K with 7400 blocks selected below the diagonal, 34 and 53 with 2100, 46 and 60 at 64K.  A list
+// pattern rule no more than a wave).  Two launches against five, 32 heads: 18 us and 22 at 8K tokens, 30 and 40 at 16K,
+// 44 and 55 at 32K with 7400 blocks selected below the diagonal, 32 and 53 with 2100, 41 and 60 at 64K.  A list
 // of more than 8192 blocks loses: 38.6 and 39.3 with 9400 at 16K tokens, 43.4 and 40.4 with 12600, 47 and 41 with 15300,
 // 42.5 and 36.8 with 8 heads.
 HeldPlan held_arrays(const Shape &sh) {
@@ -2155,6 +2303,7 @@ IdxArgs index_args(const Shape &sh, const Workspace &ws, sa_scores in, const Ove
   a.held = held.held;
   a.seg_vs = held.seg_vs; a.seg_blk = held.seg_blk; a.per_vs = held.per_vs; a.per_blk = held.per_blk;
   a.cap_top_vs = held.cap_vs; a.cap_top_blk = held.cap_blk;
+  a.place_vs = (held.seg_vs * held.cap_vs + kSlice - 1) / kSlice;
   a.top_vs = a.top_vs_key = a.top_blk = a.top_blk_key = nullptr;
   if (held.held) {
     const size_t nv = top_words_vs(sh, held), nk = top_words_blk(sh, held);
@@ -2244,8 +2393,10 @@ void launch_levels(IdxArgs a, bool vs, bool blk, hipStream_t st) {
 }
 
 void launch_finish(const IdxArgs &a, hipStream_t st) {
-  const dim3 grid(2 * a.Pv + a.Pb, a.sh.Hq), place(2 + (a.sh.row_select ? (a.sh.nb + SW - 1) / SW : 1), a.sh.Hq);
+  const dim3 grid(2 * a.Pv + a.Pb, a.sh.Hq);
   const bool one = a.seg_vs == 1 && a.seg_blk <= 1;
+  const int place_blk = a.sh.row_select ? (a.sh.nb + SW - 1) / SW : max(1, (a.seg_blk * a.cap_top_blk + kSlice - 1) / kSlice);
+  const dim3 place(2 * (one ? 1 : a.place_vs) + place_blk, a.sh.Hq);
   if (a.held && !a.sh.row_select) {
     if (one) idx_place_kernel<0, false><<<place, ST, 0, st>>>(a);
     else idx_place_kernel<0, true><<<place, ST, 0, st>>>(a);
@@ -2255,7 +2406,7 @@ void launch_finish(const IdxArgs &a, hipStream_t st) {
     else idx_place_kernel<16, false><<<place, ST, 0, st>>>(a);
   } else if (a.held) {
     // the rows by themselves, in workgroups without a list's memory
-    idx_place_kernel<0, true><<<dim3(2, a.sh.Hq), ST, 0, st>>>(a);
+    idx_place_kernel<0, true><<<dim3(2 * a.place_vs, a.sh.Hq), ST, 0, st>>>(a);
     IdxArgs b = a;
     b.first = 2 * a.Pv;
     const dim3 rows(a.Pb, a.sh.Hq);
