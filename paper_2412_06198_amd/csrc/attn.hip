@@ -280,17 +280,22 @@ __device__ inline float max_pair(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-template <bool STATS>
-__global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
-  __shared__ __attribute__((aligned(16))) uint16_t Ks[2][BK * 128];
-  __shared__ __attribute__((aligned(16))) uint16_t Vs[2][BK * 128];
+// G groups of four waves share an item: group j takes every G-th tile and diagonal from the j-th on, with buffers of
+// its own, and the groups' sums are merged at the end.  With G = 1 two workgroups live on a compute unit, with G = 2
+// one: see split_items for where that pays.
+template <bool STATS, int G>
+__global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) {
+  __shared__ __attribute__((aligned(16))) uint16_t Ks[G][2][BK * 128];
+  __shared__ __attribute__((aligned(16))) uint16_t Vs[G][2][BK * 128];
   __shared__ uint32_t kept0[NWORDS], kept1[NWORDS];
   // the item's list of key tiles; later the scores of a batch of diagonals, [offset][query]
-  __shared__ __attribute__((aligned(16))) float dscore[kDiagBatch * BQ];
-  static_assert(sizeof(dscore) >= kMaxSeq / BK * 2, "holds the list");
-  uint16_t *const tlist = (uint16_t *)dscore;
+  __shared__ __attribute__((aligned(16))) float dscore[G][kDiagBatch * BQ];
+  static_assert(sizeof(dscore[0]) >= kMaxSeq / BK * 2, "holds the list");
+  uint16_t *const tlist = (uint16_t *)dscore[0];
 
-  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);  // wave-uniform for the compiler too
+  // wave-uniform for the compiler too; the wave inside its group
+  const int grp = G == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) - 4 * grp;
 
   // Persistent workgroups pull (head, row block) items from eight queues, one per XCD
   // (consecutive workgroup ids land on consecutive XCDs).  1, 2, 4 or 8 queues share one KV head at a
@@ -306,11 +311,12 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
   for (;;) {
   // Lane-derived constants are recomputed per item from an opaque copy of the thread id:
   // hoisted out of this loop they would stay live across every phase and spill.
-  int tid = threadIdx.x;
+  int tid = threadIdx.x;  // inside its group
   asm volatile("" : "+v"(tid));
+  if (G > 1) tid &= 255;
   const int lane = tid & 63, q = lane & 31, gg = lane >> 5;
   __syncthreads();  // previous item fully retired: LDS work lists and tiles may be reused
-  if (wv == 0) {
+  if (wv == 0 && grp == 0) {
     const int drawn = __builtin_amdgcn_readfirstlane(ticket);
     int item = drawn < p.qcap ? home + 8 * drawn : -1;
     if (item < 0) {
@@ -337,7 +343,7 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
   const uint32_t it_w = uload(p.items, 4 * id), it_n = uload(p.items, 4 * id + 1);
   const uint32_t it_at = uload(p.items, 4 * id + 2), it_e = uload(p.items, 4 * id + 3);
   if (it_n == kNoItem) {  // a hole of the id space
-    if (tid == 0 && ticket < p.qcap) ticket = (int)atomicAdd(&p.queue[home], 1u);
+    if (tid == 0 && grp == 0 && ticket < p.qcap) ticket = (int)atomicAdd(&p.queue[home], 1u);
     continue;
   }
   const int h = (int)(it_w & 127u), qh = (int)(it_w >> 7 & 127u), kvh = (int)(it_w >> 14 & 127u), t128 = (int)(it_w >> 21);
@@ -372,8 +378,8 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
   const int rl = 4 * wv + (lane >> 4);  // (row & 15) of the rows this lane moves; (row & 3) = lane >> 4
   const unsigned dmaK = (unsigned)(rl * (int)p.kv_rs * 2 + (((lane & 15) ^ rl) << 4));
   const unsigned dmaV = (unsigned)(rl * (int)p.kv_rs * 2 + (((lane & 15) ^ ((lane >> 4) << 2)) << 4));
-  const unsigned ldsK0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)&Ks[0][0] + 4 * wv * 256;
-  const unsigned ldsV0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)&Vs[0][0] + 4 * wv * 256;
+  const unsigned ldsK0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)&Ks[grp][0][0] + 4 * wv * 256;
+  const unsigned ldsV0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)&Vs[grp][0][0] + 4 * wv * 256;
   const size_t row16 = 16 * (size_t)p.kv_rs;  // elements between the rows of consecutive instructions
 #define SA_DMA16(gptr, voff, ldsb)                                                                    \
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(gptr), \
@@ -418,9 +424,9 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
 
   // list entries travel one tile ahead in scalar registers, so that neither the copy of the next
   // tile nor this tile's keep test waits for an LDS read behind the barrier
-  int e_cur = (int)(it_e & 0xFFFFu);
+  int e_cur = (int)((grp ? it_e >> 16 : it_e) & 0xFFFFu);
   int r_nxt = (int)(it_e >> 16);  // from LDS later on: made scalar only where it is used, a tile later
-  if (ntr > 0) SA_ISSUE_TILE(0, 0, e_cur);
+  if (grp < ntr) SA_ISSUE_TILE(grp, 0, e_cur);
 
   // the item's other reads, all in flight together with the first tile's copies
   bf16x8 qf[8];  // Q^T fragments: B operand, lane = query, 8 consecutive d per k-step half
@@ -449,11 +455,12 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
   }
   const int ng = (call + BK - 1) / BK;
   const int ntot = ntr + ng;
-  if (ntr == 0 && ng > 0) SA_ISSUE_TILE(0, 0, e_cur);
+  if (grp >= ntr && grp < ntot) SA_ISSUE_TILE(grp, 0, e_cur);
   {
     // the list, for the tile loop (read behind its first barrier), and the kept tiles as bitmaps, for the diagonals
     const uint16_t *tl = p.tiles + (size_t)h * p.tile_cap + it_at;
-    for (int i = tid; i < ntr; i += 256) {
+    if (G > 1) r_nxt = G + grp < ntr ? tl[G + grp] : 0;
+    for (int i = tid + 256 * grp; i < ntr; i += 256 * G) {
       const int ent = tl[i];
       tlist[i] = (uint16_t)ent;
       if (has_offs) {
@@ -464,17 +471,18 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
     }
   }
 
-  for (int t = 0; t < ntot; ++t) {
-    const int cur = t & 1;
+  const int n_step = (ntot + G - 1) / G;
+  for (int step = 0; step < n_step; ++step) {
+    const int t = G * step + grp, cur = step & 1;
     // this wave's share of tile t has landed (nothing else is in flight); after the barrier the
     // whole tile is in LDS[cur] and every wave has finished reading LDS[cur^1] (tile t-1)
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     __syncthreads();
     const int e_nxt = __builtin_amdgcn_readfirstlane(r_nxt);
-    if (t + 1 < ntot) SA_ISSUE_TILE(t + 1, cur ^ 1, e_nxt);
+    if (t + G < ntot) SA_ISSUE_TILE(t + G, cur ^ 1, e_nxt);
     const int e_this = e_cur;
     e_cur = e_nxt;
-    r_nxt = (int)tlist[min(t + 2, kMaxSeq / BK - 1)];
+    r_nxt = (int)tlist[min(t + 2 * G, kMaxSeq / BK - 1)];
 
     // ---- what this wave keeps of the tile: a 64-bit mask per lane over the key slots ---------
     // slot c (0..59 used) stands for key_local = c + 4*gg; see the accumulator layout below.
@@ -516,7 +524,7 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
     }
 
     // ---- S^T = K Q^T : lane = query (q), accumulator r of half hf <-> key 32hf + 8(r/4) + 4gg + r%4
-    const uint16_t *Kt = Ks[cur];
+    const uint16_t *Kt = Ks[grp][cur];
     f32x16 sacc[2];
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf)
@@ -605,7 +613,7 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
     // (2 passes each) replace eight additions on the vector ALU.
     const s16x4 ones4 = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
     // ---- O^T += V^T P^T : k-slot (gg,e) of step (hf,u) <-> key 32hf + 16u + 8(e/4) + 4gg + e%4 ----
-    const uint16_t *Vt = Vs[cur];
+    const uint16_t *Vt = Vs[grp][cur];
     {
       // 16 V^T fragments (4 key steps x 4 d blocks), each two transposing reads; same ring of four
       s16x4 vlo[4], vhi[4];
@@ -670,7 +678,7 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
   // other, the bitmaps read at each: 32 heads, 128K tokens 1025 -> 995 us of diagonals, 32K 98 -> 93, a layer of
   // 16K 430 -> 421, 4K 55.8 -> 54.9.
   __builtin_amdgcn_s_setprio(0);
-  if (tid == 0 && ticket < p.qcap) ticket = (int)atomicAdd(&p.queue[home], 1u);  // used at the next item
+  if (tid == 0 && grp == 0 && ticket < p.qcap) ticket = (int)atomicAdd(&p.queue[home], 1u);  // used at the next item
   if (has_offs) __syncthreads();  // all waves are done with the shared tiles and the list: reuse them
   if (has_offs && r0 < N) {
     const int32_t *__restrict__ offp = p.offs + (size_t)h * p.k_s;
@@ -679,7 +687,7 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
     asm volatile("" : "+v"(dl));  // this phase's lane constants are born here, not before the tile loop
     const int q = dl & 31, gg = dl >> 5, lane = dl;
     // two 8 KB tiles per wave: waves 0, 1 in the V buffers, waves 2, 3 in the K buffers
-    uint16_t *const tile0 = (wv < 2 ? &Vs[0][0] : &Ks[0][0]) + (wv & 1) * (2 * 32 * 128);
+    uint16_t *const tile0 = (wv < 2 ? &Vs[grp][0][0] : &Ks[grp][0][0]) + (wv & 1) * (2 * 32 * 128);
     const unsigned ldsT = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)tile0;
     const int rstar = 4 * (q >> 3) + (q & 3);        // register of S^T that holds key_local == q
     const bool holder = gg == ((q >> 2) & 1);        // ... in this half of the lane pair
@@ -689,7 +697,7 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
     const unsigned kchunk = (unsigned)(((lane & 15) ^ vrow) << 4);
     const unsigned krow = (unsigned)(vrow * (int)p.kv_rs * 2);
     const uint32_t *kw = wv < 2 ? kept0 : kept1;
-    float *const dsc = dscore + 32 * wv + q;
+    float *const dsc = dscore[grp] + 32 * wv + q;
 #define SA_DIAG_COPY(src, jb_, swzc, swzn, ldsb)                                                 \
   {                                                                                              \
     if ((jb_) >= 0) {                                                                            \
@@ -729,6 +737,7 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
       // An offset that no query takes is passed over.  The others in even batches; of the batch whose
       // copies are issued: its offsets (i_all), those still to be issued in this pass (i_left), which pass.
       unsigned long long rest = __ballot(take != 0u);
+      if (G > 1) rest = __ballot(((rest >> lane) & 1ull) && __popcll(rest & ((1ull << lane) - 1ull)) % G == grp);
       const int n_live = __popcll(rest), n_batch = (n_live + kDiagBatch - 1) / kDiagBatch;
       const int per_batch = n_batch ? (n_live + n_batch - 1) / n_batch : 0;
       auto next_batch = [&]() {
@@ -859,11 +868,35 @@ __global__ __launch_bounds__(256, 2) void sparse_prefill_kernel(AttnArgs p) {
   // A lane holds 16 separate 8-byte pieces of its row.  They go through an 8 KB LDS tile of the
   // wave's own (swizzled like a K tile) and leave as whole 256-byte rows, 16 bytes per lane: 64
   // cache lines per wave instead of 1024 partial writes.
+  if constexpr (G == 2) {
+    // The second group hands its sums to the first: 16 KB a wave through its own tiles.
+    f32x4 *const xo = (f32x4 *)((wv < 2 ? &Vs[1][0][0] : &Ks[1][0][0]) + (wv & 1) * (64 * 128)) + lane;
+    float *const xml = dscore[1] + tid;
+    __syncthreads();
+    if (grp == 1) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        xo[64 * i] = f32x4{oacc[i >> 2][4 * (i & 3)], oacc[i >> 2][4 * (i & 3) + 1], oacc[i >> 2][4 * (i & 3) + 2], oacc[i >> 2][4 * (i & 3) + 3]};
+      xml[0] = m_run;
+      xml[256] = l_run;
+    }
+    __syncthreads();
+    if (grp == 1) continue;
+    const float m1 = xml[0], l1 = xml[256], m = fmaxf(m_run, m1), m_ref = m == -INFINITY ? 0.f : m;
+    const float a0 = __builtin_amdgcn_exp2f(m_run - m_ref), a1 = __builtin_amdgcn_exp2f(m1 - m_ref);
+    l_run = l_run * a0 + l1 * a1;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const f32x4 o = xo[64 * i];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) oacc[i >> 2][4 * (i & 3) + e] = oacc[i >> 2][4 * (i & 3) + e] * a0 + o[e] * a1;
+    }
+  }
   const float ltot = l_run + __shfl_xor(l_run, 32);
   const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
-  if (!has_offs) __syncthreads();  // the shared tiles are free (with diagonals, that barrier has been passed)
+  if (G == 1 && !has_offs) __syncthreads();  // the shared tiles are free (else such a barrier has been passed)
   {
-    char *ow = (char *)((wv < 2 ? &Vs[0][0] : &Ks[0][0]) + (wv & 1) * (2 * 32 * 128));
+    char *ow = (char *)((wv < 2 ? &Vs[0][0][0] : &Ks[0][0][0]) + (wv & 1) * (2 * 32 * 128));
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -904,6 +937,20 @@ int queue_share(const Shape &sh) {
   return xb | (xb > 0 && nT >= (4 << xb) * kRun ? kRunBits << 4 : 0);
 }
 
+// Whether two groups of waves share an item.  A launch is at least as long as its longest item, whose tiles follow each
+// other at 1.4 us with a compute unit to itself; with two groups, two tiles take 1.9.  Where the items
+// are no more than the compute units, it is faster for every kind of head: layers of 4 to 8 heads at 1K to
+// 4K tokens 19.7 -> 18.8 us, 28.9 -> 25.3, 45.2 -> 36.9, 56 -> 45 at 8K, slash heads only 22.9 -> 22.9 to 57 -> 47.
+// With up to twice as many it depends on how unlike the items are, since two workgroups would share the unit anyway:
+// where the band of Triangular heads covers the sequence (plain causal attention) 2K to 16K tokens 56 -> 50, 97 -> 81,
+// 180 -> 141, 352 -> 263 us (at 2.25 items per unit 81 -> 90); slash heads 34 -> 41, a mix 62 -> 46, which
+// cannot be told apart here.  Heads taken with several indices (the offline search) stay whole: their results must not
+// depend on how many heads are taken together.
+bool split_items(const Shape &sh) {
+  const int n_items = (sh.N + BQ - 1) / BQ * sh.Hq;
+  return sh.gq == sh.g && n_items <= (sh.local >= sh.nb ? 2 : 1) * sh.n_cu;
+}
+
 int queue_capacity(const Shape &sh) {
   const int share = queue_share(sh), slots = 8 >> (share & 15);
   return tickets_per_head((sh.N + BQ - 1) / BQ, share) * sh.g * ((sh.Hkv + slots - 1) / slots);
@@ -938,7 +985,9 @@ hipError_t launch_sparse_prefill(const Shape &sh, const Workspace &ws, const uin
   a.items = (uint4 *)ws.attn_items;
   a.tiles = ws.attn_tiles;
   a.tile_cap = (unsigned)sh.cap_b * (unsigned)(sh.b / BK);
-  a.grid = a.n_items < 2 * sh.n_cu ? a.n_items : 2 * sh.n_cu;  // two resident workgroups per CU
+  const bool split = split_items(sh);
+  const int resident = (split ? 1 : 2) * sh.n_cu;  // workgroups
+  a.grid = a.n_items < resident ? a.n_items : resident;
   const int n_plan = (8 * a.qcap + kPlanWaves - 1) / kPlanWaves;
   // LDS for the larger of a head's column bitmap and the key-tile bitmaps of four items: this bound also
   // limits the workgroups of a CU, so it follows the sequence
@@ -949,10 +998,14 @@ hipError_t launch_sparse_prefill(const Shape &sh, const Workspace &ws, const uin
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int grid = a.grid;
-  if (counters)
-    sparse_prefill_kernel<true><<<grid, 256, 0, st>>>(a);
+  if (counters && split)
+    sparse_prefill_kernel<true, 2><<<grid, 512, 0, st>>>(a);
+  else if (counters)
+    sparse_prefill_kernel<true, 1><<<grid, 256, 0, st>>>(a);
+  else if (split)
+    sparse_prefill_kernel<false, 2><<<grid, 512, 0, st>>>(a);
   else
-    sparse_prefill_kernel<false><<<grid, 256, 0, st>>>(a);
+    sparse_prefill_kernel<false, 1><<<grid, 256, 0, st>>>(a);
   return hipGetLastError();
 }
 
