@@ -257,6 +257,13 @@ __device__ inline void rows_tile(const unsigned (&at)[8], const bf16x8 (&qf)[8],
   __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
 }
 
+// The head of a workgroup's four that wave wv takes.  Where there are fewer (g < 4, or the last ones of a group), the waves
+// without one only copy; workgroups that share a compute unit (256 apart) leave others without, since the wave's
+// number decides on its SIMD.  With those waves repeating the first head's work, 8 heads without groups took 215 us at 128K
+// tokens, 71.6 at 32K and 45.7 at 16K, like this 184, 69.2 and 42.6; 4 heads 122.6, 51.4 and (4K) 18.1, now 115.3,
+// 49.2 and 18.1.
+__device__ inline int head_wave(int L, int wv) { return (wv + (L >> 8)) & 3; }
+
 // pass 1, workgroup L of nchunks * Hkv * ceil(g/4), 256 threads.
 __device__ inline void window_stats(int L, uint16_t (*Ks)[64 * 128], const uint16_t *__restrict__ Q,
                                     const uint16_t *__restrict__ K, const Shape &sh, float c,
@@ -266,7 +273,7 @@ __device__ inline void window_stats(int L, uint16_t (*Ks)[64 * 128], const uint1
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q = lane & 31, gg = lane >> 5;
   const int chunk = L % sh.nchunks, kvh = L / sh.nchunks % sh.Hkv, z0 = L / (sh.nchunks * sh.Hkv);
-  const int hsub = 4 * z0 + wv;
+  const int hsub = 4 * z0 + head_wave(L, wv);
   const bool head_ok = hsub < sh.g;
   const int hq = kvh * sh.g + (head_ok ? hsub : 0);
   const int jc0 = chunk * sh.chunk;
@@ -339,6 +346,7 @@ __device__ inline void window_stats(int L, uint16_t (*Ks)[64 * 128], const uint1
       }
     }
 
+    if (!head_ok) continue;
     // One 32-key half of the tile at a time: its scores are reduced to (max, sum) before the next
     // half is multiplied, so only 32 accumulator registers are live (three waves per SIMD fit).
     // lane = query 32qh+q ; acc[qh][r] <-> key j0 + 32kh + 8(r/4) + 4gg + r%4
@@ -525,7 +533,7 @@ __device__ inline void window_scores(int L, uint16_t (*Ks)[64 * 128], const uint
   const int q = lane & 31, gg = lane >> 5;
   const int chunk = sh.nchunks - 1 - L % sh.nchunks, rest = L / sh.nchunks;
   const int kvh = sh.Hkv - 1 - rest % sh.Hkv;
-  const int hsub = 4 * (rest / sh.Hkv) + wv;
+  const int hsub = 4 * (rest / sh.Hkv) + head_wave(L, wv);
   const bool head_ok = hsub < sh.g;
   const int hq = kvh * sh.g + (head_ok ? hsub : 0);
   const int jc0 = chunk * sh.chunk;
@@ -562,7 +570,7 @@ __device__ inline void window_scores(int L, uint16_t (*Ks)[64 * 128], const uint
     __syncthreads();
     if (t + kStages - 1 < nt)
       cp.issue(Kh + (size_t)(t + kStages - 1) * 64 * sh.kv_rs, (t + kStages - 1) % kStages);
-    const uint16_t *Kt = Ks[cur];
+    if (!head_ok) continue;
     const int j0 = jc0 + 64 * t;
 
     unsigned at[8];
@@ -581,7 +589,7 @@ __device__ inline void window_scores(int L, uint16_t (*Ks)[64 * 128], const uint
       else
         colsum += scores_rows<false>(acc, qh, bias, cv, 0, run, done);
     }
-    if (head_ok) {
+    {
       v_out[(size_t)hq * sh.N + j0 + lane] = colsum;
       // The first tile's sums lack the previous chunk's rows (all but lane 0): they are added to
       // the zeroed slot, as is that chunk's remainder below.  Every offset so receives at most
