@@ -323,21 +323,6 @@ __device__ __forceinline__ void visit(const IdxArgs &a, int arr, const unsigned 
   }
 }
 
-// Prefix sums and sums over a wave on the data-parallel lane moves (row shifts inside 16 lanes, then
-// two broadcasts): a shuffle through LDS per step is a round trip of some 60 cycles.
-template <int CTRL, int ROWS>
-__device__ inline unsigned lane_move(unsigned x) {
-  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
-}
-__device__ inline unsigned wave_inclusive_sum(unsigned x) {
-  x += lane_move<0x111, 0xF>(x);  // row_shr:1
-  x += lane_move<0x112, 0xF>(x);  // row_shr:2
-  x += lane_move<0x114, 0xF>(x);  // row_shr:4
-  x += lane_move<0x118, 0xF>(x);  // row_shr:8
-  x += lane_move<0x142, 0xA>(x);  // row_bcast:15 into rows 1 and 3
-  x += lane_move<0x143, 0xC>(x);  // row_bcast:31 into rows 2 and 3
-  return x;
-}
 // The largest (smallest) of the wave's values.
 __device__ inline unsigned wave_max(unsigned x) {
   x = max(x, lane_move<0x111, 0xF>(x));
@@ -349,21 +334,6 @@ __device__ inline unsigned wave_max(unsigned x) {
   return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
 }
 __device__ inline unsigned wave_min(unsigned x) { return ~wave_max(~x); }
-template <int CTRL, int ROWS>
-__device__ inline u64 lane_move64(u64 x) {
-  return (u64)lane_move<CTRL, ROWS>((unsigned)x) | ((u64)lane_move<CTRL, ROWS>((unsigned)(x >> 32)) << 32);
-}
-// The sum over the wave, in lane 63.
-__device__ inline u64 wave_sum63(u64 x) {
-  x += lane_move64<0x111, 0xF>(x);
-  x += lane_move64<0x112, 0xF>(x);
-  x += lane_move64<0x114, 0xF>(x);
-  x += lane_move64<0x118, 0xF>(x);
-  x += lane_move64<0x142, 0xA>(x);
-  x += lane_move64<0x143, 0xC>(x);
-  return x;
-}
-
 // Exclusive prefixes of two values per thread over the 64 * NW threads of a workgroup: lane moves inside
 // the waves, the wave totals through LDS (wsum: 2 * NW words).  Called by all threads.
 template <int NW>

@@ -17,6 +17,36 @@ struct Override { int8_t pat[kMaxHeads]; };
 // Budgets of one head, for index builds whose heads differ in them (device arrays of these).
 struct HeadBudget { int32_t k_v, k_s, k_b, local; };
 
+// Prefix sums and sums over a wave on the data-parallel lane moves (row shifts inside 16 lanes, then
+// two broadcasts): a shuffle through LDS per step is a round trip of some 60 cycles.
+template <int CTRL, int ROWS>
+__device__ inline unsigned lane_move(unsigned x) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
+}
+__device__ inline unsigned wave_inclusive_sum(unsigned x) {
+  x += lane_move<0x111, 0xF>(x);  // row_shr:1
+  x += lane_move<0x112, 0xF>(x);  // row_shr:2
+  x += lane_move<0x114, 0xF>(x);  // row_shr:4
+  x += lane_move<0x118, 0xF>(x);  // row_shr:8
+  x += lane_move<0x142, 0xA>(x);  // row_bcast:15 into rows 1 and 3
+  x += lane_move<0x143, 0xC>(x);  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+template <int CTRL, int ROWS>
+__device__ inline unsigned long long lane_move64(unsigned long long x) {
+  return (unsigned long long)lane_move<CTRL, ROWS>((unsigned)x) | ((unsigned long long)lane_move<CTRL, ROWS>((unsigned)(x >> 32)) << 32);
+}
+// The sum over the wave, in lane 63.
+__device__ inline unsigned long long wave_sum63(unsigned long long x) {
+  x += lane_move64<0x111, 0xF>(x);
+  x += lane_move64<0x112, 0xF>(x);
+  x += lane_move64<0x114, 0xF>(x);
+  x += lane_move64<0x118, 0xF>(x);
+  x += lane_move64<0x142, 0xA>(x);
+  x += lane_move64<0x143, 0xC>(x);
+  return x;
+}
+
 // Everything the kernels need, resolved from sa_config at sa_create time.
 struct Shape {
   int Hq, Hkv, g, N, b, nb, w;

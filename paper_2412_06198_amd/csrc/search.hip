@@ -8,13 +8,15 @@
 // All heads of a batch go through every step together, with budgets of their own each, and the host
 // waits once per batch.  A head is taken with several indices at a time: index and attention launches see
 // kSets times as many heads as the batch has (Shape::gq), so that the dense reference and the three candidates are
-// one index build and one attention launch, and a step of the refinement evaluates three sizes, the one that the
-// bisection asks for and the two it can ask for next.  The pairs of a Triangular or Block-Cluster candidate follow from
+// one index build and one attention launch.  The pairs of a Triangular or Block-Cluster candidate follow from
 // its number of blocks alone; those of an Interval-Slash candidate are counted from the selected columns and
-// offsets (slash_step_kernel), which also takes the head's next steps, and no attention runs before the sizes are
-// known.  (With one head at a time, an attention call per probe to count its pairs and a wait after each, 8 heads
-// of 4096 tokens took 35 ms; with one index at a time, 13 index builds and four attention launches as long as
-// their longest row block each, 661 us; now 382.)
+// offsets, and no attention runs before the sizes are known.  A head of a short sequence goes through its whole refinement
+// in one workgroup (slash_refine_kernel).  Of a longer one a step evaluates three sizes with an index build, the one
+// that the bisection asks for and the two it can ask for next, and slash_step_kernel counts their pairs and
+// takes the head's next steps.
+// (With one head at a time, an attention call per probe to count its pairs and a wait after each, 8 heads of 4096
+// tokens took 35 ms; with one index at a time, 13 index builds and four attention launches as long as their longest
+// row block each, 661 us; with index builds for every step of the refinement 333, now 273.)
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -215,6 +217,154 @@ __global__ __launch_bounds__(kStepThreads) void slash_step_kernel(const int32_t 
   last[virtual_head(i0, 1 + SA_INTERVAL_SLASH, gb, kSets)] = slash_budget(r.x, N, nb);
 }
 
+// RefineSearchSpace of the Interval-Slash candidate of short sequences, a workgroup per head.  The selections of all
+// sizes are prefixes of one ranking, so columns and offsets are ranked once and a size is evaluated from the ranks: its
+// columns as a bitmap, with the counts before each word, answer how many of them lie below N - o.
+// The ranking is a bitonic sort in LDS, by half of the waves for each array, four strides a pass in registers
+// (one at a time it is bound by LDS).  A key is a score and its index in the mantissa of a double
+// between 1 and 2, so that a comparison is v_max_f64 and v_min_f64, and a change of sign turns the order.
+// What bounds it is one compute unit: 28 us of 45 at 4096 are the sorts, 1.9 each evaluation.  Four steps of
+// an index build and a count each took 108 (a whole search of 1, 4, 8 and 24 heads of 4096 tokens 249, 289, 333
+// and 515 us, now 190, 224, 273 and 447; 8 heads of 8192 tokens 629 and 556, of 1024 172 and 130).  As far as both
+// arrays fit LDS; beyond, the attention is what a search waits for.
+constexpr int kRankThreads = 1024, kRankHalf = kRankThreads / 2, kRankMaxSeq = 8192;
+constexpr unsigned long long kRankOne = 0x3FF0000000000000ull, kRankSign = 1ull << 63;
+__device__ inline unsigned long long rank_key(uint32_t score, int i) {
+  return kRankOne | (unsigned long long)score << 13 | (unsigned)(kRankMaxSeq - 1 - i);
+}
+__device__ inline int rank_index(unsigned long long key) { return kRankMaxSeq - 1 - (int)(key & (kRankMaxSeq - 1)); }
+
+// Where key i of a sort sits: keys 8, 64 or 1 apart, which the lanes of a wave take, spread over the banks.
+__device__ inline int rank_slot(int i) { return i ^ (i >> 3 & 31); }
+
+__device__ __forceinline__ void rank_pair(double &larger, double &smaller) {
+  double hi, lo;
+  asm("v_max_f64 %0, %1, %2" : "=v"(hi) : "v"(larger), "v"(smaller));
+  asm("v_min_f64 %0, %1, %2" : "=v"(lo) : "v"(larger), "v"(smaller));
+  larger = hi;
+  smaller = lo;
+}
+
+// S strides of a bitonic merge of k keys, j and below, largest first: 2^S keys per thread and chunk.  FIRST: all merges
+// of up to 2^S neighbours.
+template <int S, bool FIRST = false>
+__device__ __forceinline__ void rank_pass(unsigned long long *key, int P, int k, int j, int ht) {
+  const int jl = j >> (S - 1);
+  __syncthreads();
+  for (int t = ht; t < P >> S; t += kRankHalf) {
+    const int at = (t & ~(jl - 1)) << S | (t & (jl - 1));
+    const unsigned long long turn = (at & k) ? kRankSign : 0ull;
+    double e[1 << S];
+    int slot[1 << S];
+#pragma unroll
+    for (int i = 0; i < 1 << S; ++i) slot[i] = rank_slot(at + i * jl);
+#pragma unroll
+    for (int i = 0; i < 1 << S; ++i) e[i] = __longlong_as_double((long long)(key[slot[i]] ^ turn));
+    if (FIRST) {
+#pragma unroll
+      for (int m = 1; m < S; ++m)
+#pragma unroll
+        for (int s = m - 1; s >= 0; --s)
+#pragma unroll
+          for (int i = 0; i < 1 << S; ++i)
+            if (!((i >> s) & 1)) {
+              if ((i >> m) & 1) rank_pair(e[i | 1 << s], e[i]);
+              else rank_pair(e[i], e[i | 1 << s]);
+            }
+    }
+#pragma unroll
+    for (int s = S - 1; s >= 0; --s)
+#pragma unroll
+      for (int i = 0; i < 1 << S; ++i)
+        if (!((i >> s) & 1)) rank_pair(e[i], e[i | 1 << s]);
+#pragma unroll
+    for (int i = 0; i < 1 << S; ++i) key[slot[i]] = (unsigned long long)__double_as_longlong(e[i]) ^ turn;
+  }
+}
+
+__global__ __launch_bounds__(kRankThreads) void slash_refine_kernel(const uint32_t *v, const uint32_t *s, int N, int b, int gb,
+                                                                    int64_t x_lo, int64_t x_hi, Refine *state, sa::HeadBudget *last,
+                                                                    int64_t target, int64_t eps) {
+  typedef unsigned long long u64;
+  __shared__ u64 key[2][kRankMaxSeq];
+  __shared__ uint16_t group[kRankMaxSeq];         // a column's rank / 32
+  __shared__ uint16_t offset[kRankMaxSeq / 32];   // offsets by rank
+  __shared__ u64 word[kRankMaxSeq / 64];          // the columns of a size ...
+  __shared__ int before[kRankMaxSeq / 64];        // ... and how many lie before each word
+  __shared__ int by_pos[2][128], from[129];       // as in slash_step_kernel, of this size and of the next
+  __shared__ long long red[2][kRankThreads / 64];
+  const int i0 = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nb = N / b, bl = b == 64 ? 6 : 7, half = tid / kRankHalf, ht = tid % kRankHalf;
+  int P = 64;
+  while (P < N) P *= 2;
+  const uint32_t *src = (half ? s : v) + (size_t)i0 * N;
+  for (int i = ht; i < P; i += kRankHalf) key[half][rank_slot(i)] = i < N ? rank_key(src[i], i) : kRankOne;  // fillers last
+  rank_pass<4, true>(key[half], P, 16, 8, ht);
+  for (int k = 32; k <= P; k *= 2) {
+    int j = k / 2;
+    const int steps = 31 - __clz(k);
+    if (steps % 4 == 1) { rank_pass<1>(key[half], P, k, j, ht); j >>= 1; }
+    if (steps % 4 == 2) { rank_pass<2>(key[half], P, k, j, ht); j >>= 2; }
+    if (steps % 4 == 3) { rank_pass<3>(key[half], P, k, j, ht); j >>= 3; }
+    for (; j > 0; j >>= 4) rank_pass<4>(key[half], P, k, j, ht);
+  }
+  __syncthreads();
+  for (int i = tid; i < N; i += kRankThreads) group[rank_index(key[0][rank_slot(i)])] = (uint16_t)(i >> 5);
+  for (int i = tid; i < N / 32; i += kRankThreads) offset[i] = (uint16_t)rank_index(key[1][rank_slot(i)]);
+
+  Refine r;
+  r.start(x_lo, x_hi);
+  if (tid < 256) by_pos[tid >> 7][tid & 127] = 0;
+  __syncthreads();
+  for (int cur = 0; !r.done; cur ^= 1) {
+    const int x = (int)r.x;  // so many offsets, and the columns of the first x groups
+    long long sum = 0;
+    for (int c = tid; c < N; c += kRankThreads) {  // whole waves: N is a multiple of 64
+      const bool in = (int)group[c] < x;
+      const u64 m = __ballot(in);
+      if (lane == 0) word[c >> 6] = m;
+      if (in) {
+        const int blk = c >> bl;
+        sum += N - ((blk + 1) << bl);
+        if (blk < nb - 1) atomicAdd(&by_pos[cur][c - (blk << bl)], 1);
+      }
+    }
+    __syncthreads();
+    if (wv == 0) {  // two words per lane
+      const int w = 2 * lane, nw = N >> 6;
+      const int n0 = w < nw ? __popcll(word[w]) : 0, n1 = w + 1 < nw ? __popcll(word[w + 1]) : 0;
+      const int incl = (int)sa::wave_inclusive_sum((unsigned)(n0 + n1));
+      if (w < nw) before[w] = incl - n0 - n1;
+      if (w + 1 < nw) before[w + 1] = incl - n1;
+    } else if (wv == 1) {  // sums from the end, b / 64 positions per lane
+      const int per = b >> 6, p0 = b - per * (lane + 1);
+      const int n0 = by_pos[cur][p0], n1 = per > 1 ? by_pos[cur][p0 + 1] : 0;
+      const int incl = (int)sa::wave_inclusive_sum((unsigned)(n0 + n1));
+      from[p0] = incl;
+      if (per > 1) from[p0 + 1] = incl - n0;
+      if (lane == 0) from[b] = 0;
+    } else if (wv < 4) {
+      by_pos[cur ^ 1][64 * (wv - 2) + lane] = 0;
+    }
+    __syncthreads();
+    if (tid < x) {
+      const int off = offset[tid], m = N - off;  // its keys lie below m
+      if (off >= b) sum += m - before[m >> 6] - __popcll(word[m >> 6] & ((1ull << (m & 63)) - 1ull));
+      else sum += (long long)m - (long long)nb * (b - off) - from[b - off];
+    }
+    sum = (long long)sa::wave_sum63((u64)sum);
+    if (lane == 63) red[cur][wv] = sum;
+    __syncthreads();
+    long long pairs = (long long)nb * b * (b + 1) / 2;
+#pragma unroll
+    for (int i = 0; i < kRankThreads / 64; ++i) pairs += red[cur][i];
+    r.step(pairs, target, eps);  // every thread the same
+  }
+  if (tid != 0) return;
+  state[i0] = r;
+  last[virtual_head(i0, 1 + SA_INTERVAL_SLASH, gb, kSets)] = slash_budget(r.x, N, nb);
+}
+
 // Heads that go through the search together, and the scratch they take.
 struct Plan {
   int heads, kv_heads;  // query heads of a batch (whole KV groups, or a part of one), their KV heads
@@ -348,6 +498,7 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
   int halvings = 0;
   for (int64_t w = z.x_hi[1] - z.x_lo[1]; w > 1; w = (w + 1) / 2) ++halvings;
   const int rounds = 1 + halvings / 2;
+  const bool ranked = N <= kRankMaxSeq;  // all steps in one launch
 
   // host memory of the call: what goes to the device, what comes back
   const int nblocks = (N + 15) / 16 < kNormBlocks ? (N + 15) / 16 : kNormBlocks;
@@ -379,12 +530,17 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
     const uint16_t *Vh = (const uint16_t *)V + (size_t)(h0 / sh.g) * sh.kv_hs;
     const sa_scores sc{scores.v + (size_t)h0 * N, scores.s + (size_t)h0 * N, scores.blk + (size_t)h0 * nb * nb};
     ok(hipMemcpyAsync(budgets, hb, n_budgets * sizeof(sa::HeadBudget), hipMemcpyHostToDevice, stream));
-    ok(hipMemcpyAsync(state, hr, (size_t)B * sizeof(Refine), hipMemcpyHostToDevice, stream));
+    if (!ranked) ok(hipMemcpyAsync(state, hr, (size_t)B * sizeof(Refine), hipMemcpyHostToDevice, stream));
     // RefineSearchSpace of the Interval-Slash candidate, all heads a step per round (a head that is done
     // repeats its last index)
     sa::Override ov;
     for (int h = 0; h < sa::kMaxHeads; ++h) ov.pat[h] = SA_INTERVAL_SLASH;
-    for (int r = 0; r < rounds && he == hipSuccess; ++r) {
+    if (ranked && he == hipSuccess) {
+      slash_refine_kernel<<<B, kRankThreads, 0, stream>>>((const uint32_t *)sc.v, (const uint32_t *)sc.s, N, b, gb, z.x_lo[1], z.x_hi[1],
+                                                          state, budgets, target_pairs, eps_pairs);
+      ok(hipGetLastError());
+    }
+    for (int r = 0; !ranked && r < rounds && he == hipSuccess; ++r) {
       if (!ok(sa::launch_build_index(ps, ws, sc, ov, ix, stream, probes))) break;
       slash_step_kernel<<<dim3(B, kProbes), kStepThreads, 0, stream>>>(ix.cols, ix.offs, cs.k_v, cs.k_s, N, b, gb, state, probes,
                                                                        budgets, target_pairs, eps_pairs);
