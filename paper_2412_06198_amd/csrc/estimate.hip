@@ -611,7 +611,8 @@ __device__ inline void window_scores(int L, uint16_t (*Ks)[64 * 128], const uint
 
 // ------------------------------------------------------------------ block map
 // blk[h][R][C] = softmax over C <= R of scale * Qblk[R].Kblk[C]; entries C > R are 0.
-// One workgroup = a strip of 16 rows of one head.  It first streams the strip's 16 b query rows (a row
+// One workgroup = a strip of 16 rows of one head, or rows_wg = 8 or 4 of them where the strips are few: the other rows
+// of its matrix tiles are then left alone.  It first streams its rows_wg b query rows (a row
 // block per wave at a time, its loads one batch of eight ahead of the sums) and keeps their means in
 // LDS.  The means are split into bf16 head + remainder (see store_split), and
 // v_mfma_f32_16x16x32_bf16 forms the 16x16 logit tiles from head x head and the
@@ -622,7 +623,7 @@ __device__ inline void window_scores(int L, uint16_t (*Ks)[64 * 128], const uint
 // once.  Strips are taken longest first.  Bound by the HBM stream of Q, which runs at 5 TB/s with the
 // workgroups of pass 2 beside it (281 us at 128K tokens and 32 heads).
 template <int MT>
-__device__ inline void block_map_strip(int L, char *lds, const uint16_t *__restrict__ Q,
+__device__ inline void block_map_strip(int L, int rows_wg, char *lds, const uint16_t *__restrict__ Q,
                                        const float *__restrict__ kblk, const Shape &sh, float c2,
                                        float *__restrict__ blk, const int32_t *__restrict__ only_bc) {
   uint16_t *tile = (uint16_t *)lds;                            // 8 KB
@@ -631,14 +632,18 @@ __device__ inline void block_map_strip(int L, char *lds, const uint16_t *__restr
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, g = lane >> 4;
   const int nb = sh.nb;
-  if (L >= (nb + 15) / 16 * sh.Hq) return;
+  const int nst = (nb + 15) / 16 * sh.Hq;
+  if (L * rows_wg >= 16 * nst) return;
+  int sub = 0;
+  while (L - sub * nst >= nst) ++sub;
   int strip, h;
-  strip_of(L, sh, strip, h);
+  strip_of(L - sub * nst, sh, strip, h);
   if (only_bc && only_bc[h] != SA_BLOCK_CLUSTER) return;  // uniform over the workgroup, before any barrier
-  const int R0 = 16 * strip;
+  const int R0 = 16 * strip + sub * rows_wg, rows = min(rows_wg, nb - R0);
+  if (rows <= 0) return;
   const int T = strip + 1;  // column tiles 0..strip hold every C <= R of this strip
-  // rows past nb are never formed; nothing that is kept depends on them
-  strip_means(Q + (size_t)h * sh.q_hs + (size_t)R0 * sh.b * sh.q_rs, sh, tile, wv, kMapWaves, min(16, nb - R0));
+  // other rows of the matrix tile are never formed; nothing that is kept depends on them
+  strip_means(Q + (size_t)h * sh.q_hs + (size_t)R0 * sh.b * sh.q_rs, sh, tile, wv, kMapWaves, rows);
   __syncthreads();
   // tile t of a means array: 8 KB = [part][st][lane][16 bytes]
   const uint16_t *ksrc = (const uint16_t *)(kblk + (size_t)(h / sh.g) * means_tiles(nb) * 2048) + 8 * lane;
@@ -740,23 +745,22 @@ __device__ inline void block_map_strip(int L, char *lds, const uint16_t *__restr
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int R = R0 + 4 * g + r;
-        if (R < nb && C < nb) dst[(size_t)R * nb + C] = acc[k][r] * sm[r];
+        if (4 * g + r < rows && C < nb) dst[(size_t)R * nb + C] = acc[k][r] * sm[r];
       }
     }
   }
   // zeros right of the strip's last tile (16 bytes per lane where the rows allow it)
   const int c0 = 16 * T;
   if ((nb & 3) == 0) {
-    const int n4 = (nb - c0) >> 2, rows = min(16, nb - R0);
+    const int n4 = (nb - c0) >> 2;
     const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int i = tid; i < rows * n4; i += 64 * kMapWaves) {
       const int r = i / n4, c4 = i - r * n4;
       *(float4 *)(dst + (size_t)(R0 + r) * nb + c0 + 4 * c4) = z4;
     }
   } else {
-    for (int r = 0; r < 16; ++r) {
+    for (int r = 0; r < rows; ++r) {
       const int R = R0 + r;
-      if (R >= nb) break;
       for (int C = c0 + tid; C < nb; C += 64 * kMapWaves) dst[(size_t)R * nb + C] = 0.f;
     }
   }
@@ -789,13 +793,13 @@ template <int MT>
 __global__ __launch_bounds__(256, (MT <= 16 ? 3 : MT <= 32 ? 2 : 1)) void estimate_second_kernel(
     const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, Shape sh, float c, const float2 *__restrict__ part,
     const float *__restrict__ bias, const float *__restrict__ kblk, sa_scores out, int window_units, int spread,
-    const int32_t *__restrict__ only_bc) {
+    int rows_wg, const int32_t *__restrict__ only_bc) {
   __shared__ __attribute__((aligned(16))) char lds[kWindowLds];
   int k;
   const bool window = window_unit((int)blockIdx.x >> 3, window_units, spread, k);
   const int L = 8 * k + ((int)blockIdx.x & 7);
   if (!window)
-    block_map_strip<MT>(L, lds, Q, kblk, sh, c, out.blk, only_bc);
+    block_map_strip<MT>(L, rows_wg, lds, Q, kblk, sh, c, out.blk, only_bc);
   else if (L < sh.nchunks * sh.Hkv * ((sh.g + 3) / 4))
     window_scores(L, (uint16_t (*)[64 * 128])lds, Q, K, sh, c, part, bias, out.v, out.s);
 }
@@ -816,7 +820,14 @@ hipError_t launch_estimate_part(const Shape &sh, const Workspace &ws, const uint
     if (bias) window_stats_reduce_kernel<<<dim3(sh.Hq, kWin / 16), 1024, 0, st>>>(ws.part, sh.nchunks, sh.w, bias);
   }
   const int wu = what == EstimatePart::BlockMap ? 0 : (windows + 7) / 8;
-  const int units = wu + (what == EstimatePart::Windows ? 0 : (nstrips * sh.Hq + 7) / 8);
+  // Row blocks per workgroup of the block map: a strip's 16, or where those workgroups leave compute units without one, 8
+  // or 4, each with all column tiles of the strip.  A workgroup waits for the stream of its queries, which
+  // is twice as long with 128-row blocks: there up to two workgroups per compute unit.  4 heads at 1K and 4K tokens 17.5 ->
+  // 16.4 and 18.7 -> 17.2 us, with 128-row blocks 23.9 -> 17.1 at 4K and 73.5 -> 66.5 at 64K, 8 heads of one KV head at
+  // 8K 23.9 -> 18.9; beyond the line it costs (one workgroup more per unit: 16 heads at 16K 42.7 -> 45.9).
+  int rows_wg = 16;
+  while (rows_wg > 4 && nstrips * sh.Hq * (16 / rows_wg) * 2 * 64 <= sh.n_cu * sh.b) rows_wg /= 2;
+  const int units = wu + (what == EstimatePart::Windows ? 0 : (nstrips * sh.Hq * (16 / rows_wg) + 7) / 8);
   // 4/5: 364 us for the estimator at 128K tokens, 114 at 32K; all units 388 and 119 (pass 2 is left for the end), the
   // first ones 388 and 121 (it does not run beside the stream any more); 65, 65 and 62 at 16K
   int spread = units * 4 / 5;
@@ -825,7 +836,7 @@ hipError_t launch_estimate_part(const Shape &sh, const Workspace &ws, const uint
   const int tiles_per_wave = (nstrips + kMapWaves - 1) / kMapWaves;
 #define SA_SECOND(MT)                                                                                         \
   estimate_second_kernel<MT><<<8 * units, 256, 0, st>>>(Q, K, sh, c, ws.part, bias, ws.kblk, out, wu, spread, \
-                                                        only_block_cluster)
+                                                        rows_wg, only_block_cluster)
   if (tiles_per_wave <= 8) SA_SECOND(8);
   else if (tiles_per_wave <= 16) SA_SECOND(16);
   else if (tiles_per_wave <= 32) SA_SECOND(32);
