@@ -100,30 +100,31 @@ __device__ inline void plan_item(const AttnArgs &p, int id, uint32_t *k0, uint32
   const int xb = p.share & 15, rb = p.share >> 4;
   const int nslots = 8 >> xb, slot = qn >> xb, sub = qn & ((1 << xb) - 1);
   const int rows_q = tickets_per_head(p.nT, p.share), per_q = rows_q * p.g;
-  const int r = k % per_q, kvh = k / per_q * nslots + slot;
-  int h = -1, tidx = p.nT;
-  if (kvh < p.Hkv) {
-    // heads without diagonals, as two words (a group has at most kMaxHeads = 128 heads)
-    unsigned long long w[2];
+  // This wave's item: row `trow` of the queue's rows and head j of the group.  The ticket it gets follows from the heads
+  // before j and their kinds, which are needed last: the reads below do not wait for them.
+  const int kvh = k / per_q * nslots + slot, j = k % per_q / rows_q, trow = k % per_q % rows_q;
+  const bool head_ok = kvh < p.Hkv;
+  int n_offs[2];  // a group has at most kMaxHeads = 128 heads
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int j = 64 * i + lane;
-      w[i] = __ballot(j < p.g && p.n_offs[kvh * p.g + min(j, p.g - 1)] <= 0);
-    }
+  for (int i = 0; i < 2; ++i) n_offs[i] = head_ok && 64 * i + lane < p.g ? p.n_offs[kvh * p.g + 64 * i + lane] : 1;
+  const int h = kvh * p.g + j, rn = trow >> rb;
+  const int tidx = (((rn << xb) + ((rn & 1) ? (1 << xb) - 1 - sub : sub)) << rb) + (trow & ((1 << rb) - 1));
+  auto ticket_id = [&]() {
+    unsigned long long w[2];  // heads without diagonals
+#pragma unroll
+    for (int i = 0; i < 2; ++i) w[i] = __ballot(n_offs[i] <= 0);
     const int c = __popcll(w[0]) + __popcll(w[1]);
-    const bool plain = r < c * rows_q;
-    const int r2 = r - c * rows_q;
-    const int side = plain ? c : p.side_by_side ? p.g - c : 0;  // heads that take a row block together
-    const int rk = plain ? r : r2;
-    int nth = side ? rk % side : rk / rows_q;  // this many heads of its kind come before it
-    const int trow = side ? rk / side : rk % rows_q;
-    for (int j = 0; j < p.g; ++j)
-      if ((((w[j >> 6] >> (j & 63)) & 1ull) != 0ull) == plain && nth-- == 0) h = kvh * p.g + j;
-    const int rn = trow >> rb;
-    tidx = (((rn << xb) + ((rn & 1) ? (1 << xb) - 1 - sub : sub)) << rb) + (trow & ((1 << rb) - 1));
-  }
-  if (h < 0 || tidx >= p.nT) {
-    if (lane == 0) p.items[id] = make_uint4(0u, kNoItem, 0u, 0u);
+    const bool plain = ((j < 64 ? w[0] >> j : w[1] >> (j - 64)) & 1ull) != 0ull;
+    const int plain_before = j < 64 ? __popcll(w[0] & ((1ull << j) - 1ull)) : __popcll(w[0]) + __popcll(w[1] & ((1ull << (j - 64)) - 1ull));
+    const int nth = plain ? plain_before : j - plain_before;  // heads of its kind before it
+    const int r = plain               ? trow * c + nth
+                  : p.side_by_side ? c * rows_q + trow * (p.g - c) + nth
+                                   : (c + nth) * rows_q + trow;
+    return qn + 8 * (k / per_q * per_q + r);
+  };
+  if (!head_ok || tidx >= p.nT) {  // a hole (without a KV head all heads count as having diagonals: any order)
+    const int at = ticket_id();
+    if (lane == 0) p.items[at] = make_uint4(0u, kNoItem, 0u, 0u);
     return;
   }
   const int t128 = p.nT - 1 - tidx;
@@ -164,16 +165,38 @@ __device__ inline void plan_item(const AttnArgs &p, int id, uint32_t *k0, uint32
   __builtin_amdgcn_wave_barrier();
   // One tile per lane, 64 at a time: the kept ones in ascending order.  Stretches that keep none are passed
   // over by a mask of the others (a row of a long sequence has thousands of tiles and keeps some thirty:
-  // without it this launch took 46 us at 128K tokens and 32 heads, 34 with it).
+  // without it this launch took 46 us at 128K tokens and 32 heads, 34 with it).  Scattered
+  // ones, up to three in a stretch, are taken by the lanes beside each other, each its own: with that, and the heads' kinds
+  // read beside the row pointers and not before them, 29.6 us (64K tokens 19.6 -> 16.8, 32K 12.2 -> 11.0).
   const unsigned start = (unsigned)min(ea0, p.cap_b) * tpb;
   const unsigned room = p.tile_cap - start;
   uint16_t *out = p.tiles + (size_t)h * p.tile_cap + start;
   unsigned base = 0;
   static_assert(NWORDS <= 128, "one lane per pair of words");
-  uint32_t any = 0u;
-  if (2 * lane < nwords) any = k0[2 * lane] | k1[2 * lane];
-  if (2 * lane + 1 < nwords) any |= k0[2 * lane + 1] | k1[2 * lane + 1];
-  for (unsigned long long pairs = __ballot(any != 0u); pairs != 0ull; pairs &= pairs - 1ull) {
+  uint32_t mine[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) mine[i] = 2 * lane + i < nwords ? k0[2 * lane + i] | k1[2 * lane + i] : 0u;
+  unsigned long long pairs = __ballot((mine[0] | mine[1]) != 0u);
+  const unsigned count = __popc(mine[0]) + __popc(mine[1]), upto = wave_inclusive_sum(count);
+  const unsigned total = __builtin_amdgcn_readlane(upto, 63);
+  if (total <= 3u * __popcll(pairs)) {  // scattered tiles: each lane those of its own words
+    unsigned pos = upto - count;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int w = 2 * lane + i;
+      for (uint32_t m = mine[i]; m != 0u; m &= m - 1u, ++pos) {
+        const int bit = __ffs(m) - 1;
+        const uint16_t ent = (uint16_t)((w * 32 + bit) | ((k0[w] >> bit) & 1u) << 14 | ((k1[w] >> bit) & 1u) << 15);
+        if (pos < room) {
+          out[pos] = ent;
+          if (pos < 2) first2[pos] = ent;
+        }
+      }
+    }
+    base = total;
+    pairs = 0ull;
+  }
+  for (; pairs != 0ull; pairs &= pairs - 1ull) {
     const int w0 = 2 * (__ffsll(pairs) - 1), w = w0 + (lane >> 5);
     const uint32_t a = w < nwords ? (k0[w] >> (lane & 31)) & 1u : 0u, b = w < nwords ? (k1[w] >> (lane & 31)) & 1u : 0u;
     const unsigned long long m = __ballot((a | b) != 0u);
@@ -188,8 +211,9 @@ __device__ inline void plan_item(const AttnArgs &p, int id, uint32_t *k0, uint32
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
   const unsigned n = min(base, room);
+  const int at = ticket_id();
   if (lane == 0)
-    p.items[id] = make_uint4((unsigned)h | (unsigned)query_head(h, p.g, p.gq) << 7 | (unsigned)kvh << 14 | (unsigned)t128 << 21, n, start,
+    p.items[at] = make_uint4((unsigned)h | (unsigned)query_head(h, p.g, p.gq) << 7 | (unsigned)kvh << 14 | (unsigned)t128 << 21, n, start,
                              (n > 0 ? first2[0] : 0u) | (n > 1 ? (unsigned)first2[1] << 16 : 0u));
 }
 
@@ -250,15 +274,20 @@ __global__ __launch_bounds__(256) void index_prepare_kernel(AttnArgs p, unsigned
   }
   const int ntile = p.kvg_rows / BK, gb = (int)blockIdx.x - p.Hq - n_plan;
   const int h = gb / ntile, g = gb % ntile;
-  const int nc = min(max(p.n_cols[h], 0), p.k_v);
-  if (g * BK >= nc) return;
   const int kvh = h / p.g;
   const int lrow = tid >> 4, lcc = tid & 15;
+  int col[4];  // on their way before their number is known
 #pragma unroll
   for (int n = 0; n < 4; ++n) {
     const int ci = g * BK + lrow + 16 * n;
-    int src = ci < nc ? p.cols[(size_t)h * p.k_v + ci] : 0;
-    src = min(max(src, 0), p.N - 1);
+    col[n] = ci < p.k_v ? p.cols[(size_t)h * p.k_v + ci] : 0;
+  }
+  const int nc = min(max(p.n_cols[h], 0), p.k_v);
+  if (g * BK >= nc) return;
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    const int ci = g * BK + lrow + 16 * n;
+    const int src = min(max(ci < nc ? col[n] : 0, 0), p.N - 1);
     const size_t so = (size_t)kvh * p.kv_hs + (size_t)src * p.kv_rs + lcc * 8;
     const size_t dofs = ((size_t)h * p.kvg_rows + ci) * p.kv_rs + lcc * 8;  // same row stride as K / V
     *(uint4 *)(p.Kg + dofs) = *(const uint4 *)(p.K + so);
