@@ -36,9 +36,8 @@
 // the emission selects inside each row instead: one wave per row, keys in
 // registers, the threshold found by halving the range of the row's keys.
 //
-// With block-granular diagonals two launches after the emission turn the selected
-// offsets of the Interval-Slash heads into rows of the block CSR (bitmap per row,
-// count and prefix, ordered write).
+// With block-granular diagonals the selected offsets of the Interval-Slash heads become rows of
+// the block CSR, in the second launch of the held form or in one after the emission (diag_rows).
 #include <algorithm>
 #include <cstddef>
 
@@ -88,8 +87,6 @@ struct IdxScratch {
   unsigned thr[NSEL], need[NSEL];
   unsigned wgt[2][kMaxVsParts], weq[2][kMaxVsParts];  // v / s: counts per wave part, then exclusive prefixes
   unsigned bgt[kMaxBlkParts], beq[kMaxBlkParts];      // blk: likewise
-  unsigned ticket_rows;                   // block-granular diagonals: cleared by the emission
-  unsigned rowcnt[kMaxNb];                // block-granular diagonals: blocks per row
 };
 constexpr size_t kZeroBytes = offsetof(IdxScratch, psum);
 static_assert(kZeroBytes % 16 == 0, "cleared 16 bytes at a time");
@@ -1148,6 +1145,64 @@ __device__ __forceinline__ int emit_rows(const IdxArgs &a, const unsigned *hb, i
   return s_at[nb];
 }
 
+// ---- diagonals at block granularity -----------------------------------------------------------------
+// An offset o leads from row block R to the key blocks R - floor(o / b) and R - ceil(o / b): the same distances in every
+// row.  So the kept blocks of row R are R - d for the distances d <= R of one set, 0 among them, and row pointers
+// are sums of the counts up to each R.  Every workgroup of 64 NW threads forms the set for itself; a wave takes whole
+// rows (part of nparts).  (A bitmap per row from all offsets, in a launch that counted and one that wrote, took 10 us of a layer of
+// 10K tokens and 32 heads, like this nothing beside the columns' part of the placing launch.  32K, all 32 heads
+// diagonals, blocks of 128: 4.7 + 2 x 5.6 before, 9.4 now in one launch; 128K, in a launch of their own: 2 x 11.6 and 9.3.)
+template <int NB>
+struct DiagRows {
+  unsigned word[NB / 32];  // the set
+  int before[NB / 32];     // distances before each word
+  uint16_t dist[NB];       // in ascending order
+  int at[NB + 1];          // row pointers
+};
+template <int NW, int NB>
+__device__ __forceinline__ int diag_rows(const IdxArgs &a, const unsigned *offs, int n_offs, int part, int nparts, int32_t *rp,
+                                         int32_t *bc, DiagRows<NB> &l, unsigned *wsum) {
+  const int tid = threadIdx.x, lane = tid & 63, nb = a.sh.nb, words = (nb + 31) / 32, shift = a.sh.b == 128 ? 7 : 6;
+  static_assert(NB / 32 <= 64 * NW, "a word per thread");
+  if (tid < words) l.word[tid] = tid == 0 ? 1u : 0u;
+  __syncthreads();
+  for (int t = tid; t < n_offs; t += 64 * NW) {
+    const unsigned o = offs[t], near = o >> shift, far = (o + a.sh.b - 1) >> shift;
+    atomicOr(&l.word[near >> 5], 1u << (near & 31));
+    if (far != near && far < (unsigned)nb) atomicOr(&l.word[far >> 5], 1u << (far & 31));
+  }
+  __syncthreads();
+  unsigned bits = tid < words ? l.word[tid] : 0u, run = __popc(bits), unused = 0;
+  block_exclusive_scan2<NW>(run, unused, wsum);
+  if (tid < words) {
+    l.before[tid] = (int)run;
+    for (; bits; bits &= bits - 1u) l.dist[run++] = (uint16_t)(32 * tid + __ffs(bits) - 1);
+  }
+  __syncthreads();
+  auto count = [&](int R) { return l.before[R >> 5] + __popc(l.word[R >> 5] & (0xFFFFFFFFu >> (31 - (R & 31)))); };
+  const int per = (nb + 64 * NW - 1) / (64 * NW);
+  unsigned sum = 0;
+  for (int j = 0; j < per; ++j)
+    if (per * tid + j < nb) sum += (unsigned)count(per * tid + j);
+  run = sum;
+  block_exclusive_scan2<NW>(run, unused, wsum);
+  for (int j = 0; j < per; ++j) {
+    const int R = per * tid + j;
+    if (R < nb) {
+      l.at[R] = (int)run;
+      run += (unsigned)count(R);
+      if (R == nb - 1) l.at[nb] = (int)run;
+    }
+  }
+  __syncthreads();
+  for (int R = part; R < nb; R += nparts) {
+    const int at = l.at[R], n = l.at[R + 1] - at;
+    if (lane == 0) rp[R] = at;
+    for (int i = lane; i < n; i += 64) bc[at + i] = R - (int)l.dist[n - 1 - i];
+  }
+  return l.at[nb];
+}
+
 // Block CSR of a Triangular head (a wave takes whole rows) or an Interval-Slash head: the blocks of all rows.
 __device__ inline int emit_fixed(const IdxArgs &a, int h, int pat, int part, int nparts, int gtid, int gthreads,
                                  int32_t *rp, int32_t *bc) {
@@ -1202,7 +1257,6 @@ __global__ __launch_bounds__(BT) void idx_emit_kernel(IdxArgs a) {
     for (int i = shown + gtid; i < width; i += gthreads) idx[i] = -1;
     if (gtid == 0) {
       (ro.arr ? a.out.n_offs : a.out.n_cols)[h] = shown;
-      if (aside) G->ticket_rows = 0u;
     }
     return;
   }
@@ -1912,12 +1966,18 @@ __device__ __forceinline__ void best_of_segments(const Held<kHeldUnits> &x, unsi
 // them the time until the pattern is known and the keys are there (5 of 18 us).  With one workgroup per array and head,
 // which made a list of the keys that reach the bound, 32 heads at 32K tokens (29500 best of four segments) took 28 us,
 // like this 18; at 64K (19000 of four) 21 and 15.
+//
+// Diagonals at block granularity are written here where v and s are one segment, so that the selection has left the
+// offsets in their final order.  Every workgroup that takes part forms their set first, so few do: at 32K tokens and 32
+// heads with the per-row rule (64 workgroups a head, blocks of 64) 4, 8 and 16 of them take 11.0, 11.2 and 12.3 us, all 20.
+constexpr int kDiagWgs = 8;
 template <int ROWS, bool SEGS>
 __global__ __launch_bounds__(ST) void idx_place_kernel(IdxArgs a) {
   __shared__ TopShared s;
   __shared__ int s_pat, s_at[ROWS > 0 ? kMaxNb + 1 : 1];
   __shared__ __attribute__((aligned(16))) unsigned s_hist[SEGS ? kBins * kMapCopies : 4];
   __shared__ uint16_t s_row[ROWS > 0 ? 1 : kSlice];  // rows of the selected entries of the slice
+  __shared__ DiagRows<kSeg / 64> s_diag;             // v and s of one segment: up to kSeg / 64 row blocks
   const Shape &sh = a.sh;
   const int x0 = (int)blockIdx.x, h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, nb = sh.nb;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2068,11 +2128,13 @@ __global__ __launch_bounds__(ST) void idx_place_kernel(IdxArgs a) {
     for (int i = shown + wg * ST + tid; i < width; i += nwg * ST) idx[i] = -1;
     if (wg == 0 && tid == 0) {
       (arr ? a.out.n_offs : a.out.n_cols)[h] = shown;
-      if (aside) G->ticket_rows = 0u;
     }
     return;
   }
-  const int part = wg * SW + wv, nparts = nwg * SW, gtid = wg * ST + tid, gthreads = nwg * ST;
+  const bool diags = pat == SA_INTERVAL_SLASH && sh.diag_blocks && a.seg_vs == 1;  // the offsets are in order already
+  const int wgs = diags ? min(nwg, kDiagWgs) : nwg;
+  if (wg >= wgs) return;
+  const int part = wg * SW + wv, nparts = wgs * SW, gtid = wg * ST + tid, gthreads = wgs * ST;
   int32_t *rp = a.out.rowptr + (size_t)h * (nb + 1);
   int32_t *bc = a.out.blkcols + (size_t)h * sh.cap_b;
   int total;
@@ -2110,6 +2172,8 @@ __global__ __launch_bounds__(ST) void idx_place_kernel(IdxArgs a) {
     }
     if (gtid == 0) rp[0] = 0;
     total = k + nb;
+  } else if (diags) {
+    total = diag_rows<SW>(a, top_of(a, h, 1, false), ksel(a, h, 3), part, nparts, rp, bc, s_diag, s.wsum);
   } else {
     total = emit_fixed(a, h, pat, part, nparts, gtid, gthreads, rp, bc);
   }
@@ -2117,87 +2181,19 @@ __global__ __launch_bounds__(ST) void idx_place_kernel(IdxArgs a) {
   for (int i = total + gtid; i < sh.cap_b; i += gthreads) bc[i] = -1;
 }
 
-// ---- diagonals at block granularity -----------------------------------------------------------------
-// Interval-Slash heads when the selected diagonals are kept as whole blocks.  Runs after the
-// emission, which has left the selected offsets in doffs: one wave per row block R collects the
-// key blocks that hold a key i - o of a query i of the row (at most two per offset) and the diagonal
-// block in a bitmap (the wave's own LDS slice).  PASS 0 counts the blocks of the rows, and its last
-// workgroup turns the counts into row pointers; PASS 1 writes the blocks in ascending order.
-template <int PASS>
+// Interval-Slash heads when the selected diagonals are kept as whole blocks, where the launch before does not write
+// them itself: the emission has left the offsets in doffs.  grid (workgroups, Hq)
 __global__ __launch_bounds__(BT) void idx_diag_rows_kernel(IdxArgs a) {
-  __shared__ unsigned bm[WPB][kMaxNb / 32];
+  __shared__ DiagRows<kMaxNb> l;
   __shared__ unsigned s_wsum[2 * WPB];
   const Shape &sh = a.sh;
-  const int h = blockIdx.y, nb = sh.nb, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  IdxScratch *G = a.scratch + h;
+  const int h = blockIdx.y, nb = sh.nb;
   if (a.out.pattern[h] != SA_INTERVAL_SLASH) return;
-  const int n_offs = ksel(a, h, 3);
-  const int32_t *offs = a.doffs + (size_t)h * sh.k_s;
   int32_t *rp = a.out.rowptr + (size_t)h * (nb + 1);
-  int32_t *bc = a.out.blkcols + (size_t)h * sh.cap_b;
-  const int shift = sh.b == 128 ? 7 : 6;
-  unsigned *w = bm[wv];
-  for (int R = blockIdx.x * WPB + wv; R < nb; R += gridDim.x * WPB) {
-    const int words = (R >> 5) + 1;  // bits 0..R
-    for (int i = lane; i < words; i += 64) w[i] = 0u;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    const long long first = (long long)R << shift, last = first + sh.b - 1;  // queries of the row
-    for (int t = lane; t < n_offs; t += 64) {
-      const long long o = offs[t];
-      if (last - o < 0) continue;  // the diagonal starts below this row
-      const int c0 = (int)((first - o > 0 ? first - o : 0) >> shift), c1 = (int)((last - o) >> shift);
-      atomicOr(&w[c0 >> 5], 1u << (c0 & 31));
-      if (c1 != c0) atomicOr(&w[c1 >> 5], 1u << (c1 & 31));
-    }
-    if (lane == 0) atomicOr(&w[R >> 5], 1u << (R & 31));
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    int run = PASS == 1 ? rp[R] : 0;
-    for (int i0 = 0; i0 < words; i0 += 64) {
-      unsigned bits = i0 + lane < words ? w[i0 + lane] : 0u;
-      const int pc = __popc(bits);
-      int incl = pc;  // inclusive prefix over the lanes
-      for (int d = 1; d < 64; d <<= 1) {
-        const int o = __shfl_up(incl, d);
-        if (lane >= d) incl += o;
-      }
-      if (PASS == 1) {
-        int pos = run + incl - pc;
-        while (bits) {
-          const int bit = __ffs(bits) - 1;
-          bits &= bits - 1;
-          bc[pos++] = (i0 + lane) * 32 + bit;
-        }
-      }
-      run += __shfl(incl, 63);
-    }
-    if (PASS == 0 && lane == 0) agent_store(&G->rowcnt[R], (unsigned)run);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();  // the slice is cleared again for the next row
-  }
-  if (PASS == 1 || !arrives_last(&G->ticket_rows, gridDim.x)) return;
-  // row pointers: thread t owns RP consecutive rows
-  constexpr int RP = kMaxNb / BT;
-  const int per = (nb + BT - 1) / BT;  // <= RP
-  unsigned g[RP], sum = 0;
-#pragma unroll
-  for (int j = 0; j < RP; ++j) {
-    const int R = per * tid + j;
-    g[j] = j < per && R < nb ? agent_load(&G->rowcnt[R]) : 0u;
-    sum += g[j];
-  }
-  unsigned run = sum, unused = 0;
-  block_exclusive_scan2<WPB>(run, unused, s_wsum);
-#pragma unroll
-  for (int j = 0; j < RP; ++j) {
-    const int R = per * tid + j;
-    if (j < per && R < nb) {
-      rp[R] = (int)run;
-      run += g[j];
-      if (R == nb - 1) rp[nb] = (int)run;
-    }
-  }
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int total = diag_rows<WPB>(a, (const unsigned *)a.doffs + (size_t)h * sh.k_s, ksel(a, h, 3), (int)blockIdx.x * WPB + wv,
+                                   (int)gridDim.x * WPB, rp, a.out.blkcols + (size_t)h * sh.cap_b, l, s_wsum);
+  if (blockIdx.x == 0 && threadIdx.x == 0) rp[nb] = total;
 }
 
 // Boundary keys a list takes (8 bytes each).  The same memory holds the counts of a range whose keys are counted
@@ -2387,13 +2383,11 @@ void launch_finish(const IdxArgs &a, hipStream_t st) {
   else if (a.sh.nb <= 256) idx_emit_kernel<4><<<grid, BT, 0, st>>>(a);
   else if (a.sh.nb <= 1024) idx_emit_kernel<16><<<grid, BT, 0, st>>>(a);
   else idx_emit_kernel<kMaxNb / 64><<<grid, BT, 0, st>>>(a);
-  if (a.sh.diag_blocks) {
+  if (a.sh.diag_blocks && !(a.held && a.seg_vs == 1 && (one || !a.sh.row_select))) {  // not by the placing launch
     // a row per wave, up to 64 workgroups per head
     int P = (a.sh.nb + WPB - 1) / WPB;
     if (P > 64) P = 64;
-    const dim3 rows(P, a.sh.Hq);
-    idx_diag_rows_kernel<0><<<rows, BT, 0, st>>>(a);
-    idx_diag_rows_kernel<1><<<rows, BT, 0, st>>>(a);
+    idx_diag_rows_kernel<<<dim3(P, a.sh.Hq), BT, 0, st>>>(a);
   }
 }
 
