@@ -831,15 +831,14 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
           float sv = sd[0];
 #pragma unroll
           for (int r = 1; r < 16; ++r) sv = (r == rstar) ? sd[r] : sv;
-          const float sm = max_pair(holder && ((tk >> q) & 1u) ? sv : -INFINITY);  // both lanes of the pair know it
-          smax = fmaxf(smax, sm);
-          dsc[slot * BQ] = sm;
+          smax = fmaxf(smax, holder && ((tk >> q) & 1u) ? sv : -INFINITY);
+          if (holder) dsc[slot * BQ] = sv;  // as it is: a maximum would drop a NaN
           if constexpr (STATS) {
             st_kept += holder && ((tk >> q) & 1u) ? 1u : 0u;
             st_tiles += 1u;
           }
         }
-        const float m_new = fmaxf(m_run, smax * p.c);
+        const float m_new = fmaxf(m_run, max_pair(smax) * p.c);
         if (__any(m_new - m_run > 8.f)) {
           const float alpha = __builtin_amdgcn_exp2f(m_run - ((m_new == -INFINITY) ? 0.f : m_new));
           m_run = m_new;
