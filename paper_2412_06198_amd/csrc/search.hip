@@ -366,14 +366,14 @@ __global__ __launch_bounds__(kRankThreads) void slash_refine_kernel(const uint32
 }
 
 // Heads that go through the search together, and the scratch they take.
-struct Plan {
-  int heads, kv_heads;  // query heads of a batch (whole KV groups, or a part of one), their KV heads
-  sa_config cfg;        // of a batch's virtual heads: budgets as large as any candidate's
+struct Batch {
+  int heads, kv_heads;  // query heads (whole KV groups, or a part of one), their KV heads
+  sa_config cfg;        // of the virtual heads: budgets as large as any candidate's
   int64_t x_lo[3], x_hi[3];
   size_t off[11], total;
 };
 
-sa_status plan_batch(const sa_ctx *ctx, int heads, Plan *z) {
+sa_status plan_batch(const sa_ctx *ctx, int heads, Batch *z) {
   const sa_config &p = ctx->cfg;
   const int N = p.seq_len, nb = N / p.block, g = ctx->sh.g;
   z->heads = heads;
@@ -410,21 +410,78 @@ sa_status plan_batch(const sa_ctx *ctx, int heads, Plan *z) {
   return SA_OK;
 }
 
-// The largest batch whose scratch stays within kBatchBytes: whole KV groups, else an even part of one.
+// The batches of a search: all of one size, but the last one (of every group, where they are parts of one).
+struct Plan {
+  Batch full, last;  // last.heads = 0: every batch is full
+  int period;        // heads that are shared out: all, or a KV group's
+  size_t total;
+  int heads_from(int h0) const { return period - h0 % period < full.heads ? last.heads : full.heads; }
+};
+
+sa_status plan_batches(const sa_ctx *ctx, int heads, int period, Plan *z) {
+  z->period = period;
+  z->last.heads = 0;
+  sa_status st = plan_batch(ctx, heads, &z->full);
+  if (st == SA_OK && period % heads) st = plan_batch(ctx, period % heads, &z->last);
+  z->total = z->last.heads && z->last.total > z->full.total ? z->last.total : z->full.total;
+  return st;
+}
+
+// As few batches as the head limit and kBatchBytes allow, of equal sizes as far as that goes: of whole KV groups, else of
+// parts of one.  Equal parts alone are not enough: 37 heads on one KV head, a prime number above the 32 that four
+// indices each leave, would go head by head with a wait of the host after each (at 192, 1024 and 4096
+// tokens 3215, 3965 and 7072 us, in two batches 238, 339 and 909; 39 heads on 13 KV heads at 2048 tokens 1810 and 442).
 sa_status plan(const sa_ctx *ctx, Plan *z) {
-  const int g = ctx->sh.g;
+  const int g = ctx->sh.g, Hkv = ctx->sh.Hkv;
   sa_status st = SA_OK;
-  for (int kv = ctx->sh.Hkv; kv >= 1; --kv) {
-    if (ctx->sh.Hkv % kv || kSets * kv * g > sa::kMaxHeads) continue;
-    if ((st = plan_batch(ctx, kv * g, z)) != SA_OK) return st;
+  for (int n = 1; n <= Hkv; ++n) {
+    const int kv = (Hkv + n - 1) / n;
+    if ((n > 1 && kv == (Hkv + n - 2) / (n - 1)) || kSets * kv * g > sa::kMaxHeads) continue;
+    if ((st = plan_batches(ctx, kv * g, Hkv * g, z)) != SA_OK) return st;
     if (z->total <= kBatchBytes) return SA_OK;
   }
-  for (int n = g - 1; n >= 1; --n) {
-    if (g % n || kSets * n > sa::kMaxHeads) continue;
-    if ((st = plan_batch(ctx, n, z)) != SA_OK) return st;
+  for (int n = 2; n <= g; ++n) {
+    const int heads = (g + n - 1) / n;
+    if (heads == (g + n - 2) / (n - 1) || kSets * heads > sa::kMaxHeads) continue;
+    if ((st = plan_batches(ctx, heads, g, z)) != SA_OK) return st;
     if (z->total <= kBatchBytes) return SA_OK;
   }
   return SA_OK;  // one head at a time
+}
+
+// Where a batch's buffers lie in the scratch, and its shapes.
+struct Layout {
+  sa::Shape cs, ps;  // of the dense reference and the candidates; of a refinement step
+  sa::Workspace ws;
+  uint16_t *outputs;
+  sa::HeadBudget *budgets, *probes;  // of the virtual heads: dense and candidates, probes
+  Refine *state;                     // and the sums behind it: the results
+  double *partial;
+  sa_index ix;
+};
+
+sa_status lay_out(const Batch &z, char *base, Layout *l) {
+  const int B = z.heads, gb = B / z.kv_heads;
+  l->outputs = (uint16_t *)(base + z.off[1]);
+  l->budgets = (sa::HeadBudget *)(base + z.off[2]);
+  l->probes = l->budgets + (size_t)kSets * B;
+  l->state = (Refine *)(base + z.off[3]);
+  l->partial = (double *)(l->state + B);
+  int32_t **part[7] = {&l->ix.pattern, &l->ix.n_cols, &l->ix.cols, &l->ix.n_offs, &l->ix.offs, &l->ix.rowptr, &l->ix.blkcols};
+  for (int i = 0; i < 7; ++i) *part[i] = (int32_t *)(base + z.off[4 + i]);
+  sa_ctx *child = nullptr;
+  sa_status st = sa_create(&z.cfg, &child);
+  if (st != SA_OK) return st;
+  st = sa_set_workspace(child, base + z.off[0], child->ws_bytes);
+  l->cs = child->sh;
+  l->cs.gq = gb;
+  l->cs.o_rs = sa::kHeadDim;
+  l->cs.o_hs = (int64_t)l->cs.N * sa::kHeadDim;
+  l->ps = l->cs;
+  l->ps.Hq = kProbes * B; l->ps.g = kProbes * gb;
+  l->ws = child->ws;
+  sa_destroy(child);
+  return st;
 }
 
 sa_status failp(sa_ctx *c, sa_status st, const char *msg) {
@@ -460,71 +517,65 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
   if (scratch_bytes < z.total) return failp(ctx, SA_ERR_BUFFER_TOO_SMALL, "scratch smaller than sa_search_scratch_bytes");
   hipStream_t stream = (hipStream_t)hip_stream;
   const sa::Shape &sh = ctx->sh;
-  const int N = sh.N, nb = sh.nb, b = sh.b, B = z.heads;
-  char *base = (char *)scratch;
-  const int gb = B / z.kv_heads;  // heads of a KV head in the batch
-  uint16_t *outputs = (uint16_t *)(base + z.off[1]);
-  sa::HeadBudget *budgets = (sa::HeadBudget *)(base + z.off[2]);  // of the virtual heads: dense and candidates, probes
-  sa::HeadBudget *probes = budgets + (size_t)kSets * B;
-  Refine *state = (Refine *)(base + z.off[3]);  // and the sums behind it: the results
-  double *partial = (double *)(state + B);
-  sa_index ix;
-  int32_t **part[7] = {&ix.pattern, &ix.n_cols, &ix.cols, &ix.n_offs, &ix.offs, &ix.rowptr, &ix.blkcols};
-  for (int i = 0; i < 7; ++i) *part[i] = (int32_t *)(base + z.off[4 + i]);
-
-  sa_ctx *child = nullptr;
-  if ((st = sa_create(&z.cfg, &child)) != SA_OK) return failp(ctx, st, "search: batch rejected by sa_create");
-  st = sa_set_workspace(child, base + z.off[0], child->ws_bytes);
-  sa::Shape cs = child->sh;
-  cs.gq = gb;
-  cs.o_rs = sa::kHeadDim;
-  cs.o_hs = (int64_t)N * sa::kHeadDim;
-  sa::Shape ps = cs;  // of a refinement step
-  ps.Hq = kProbes * B; ps.g = kProbes * gb;
-  const sa::Workspace ws = child->ws;
-  sa_destroy(child);
-  if (st != SA_OK) return failp(ctx, st, "search: workspace");
+  const int N = sh.N, nb = sh.nb, b = sh.b;
+  Layout l;
 
   // pairs of an index made of whole blocks, the nb diagonal ones among them
   auto block_pairs = [&](int64_t blocks) { return (blocks - nb) * b * b + (int64_t)nb * b * (b + 1) / 2; };
   // The sizes of the candidates whose pairs are known without an index are the same for every head.
   Refine tri, clu;
-  tri.start(z.x_lo[0], z.x_hi[0]);
+  tri.start(z.full.x_lo[0], z.full.x_hi[0]);
   while (!tri.done) tri.step(block_pairs(sa::triangular_count(nb, sh.sink, (int)tri.x)), target_pairs, eps_pairs);
-  clu.start(z.x_lo[2], z.x_hi[2]);
+  clu.start(z.full.x_lo[2], z.full.x_hi[2]);
   while (!clu.done) clu.step(block_pairs(clu.x), target_pairs, eps_pairs);
   // A bisection evaluates the ends and a size per halving; the first step takes both ends and the middle, every
   // other one two sizes in a row.
+  const int64_t x_lo = z.full.x_lo[1], x_hi = z.full.x_hi[1];
   int halvings = 0;
-  for (int64_t w = z.x_hi[1] - z.x_lo[1]; w > 1; w = (w + 1) / 2) ++halvings;
+  for (int64_t w = x_hi - x_lo; w > 1; w = (w + 1) / 2) ++halvings;
   const int rounds = 1 + halvings / 2;
   const bool ranked = N <= kRankMaxSeq;  // all steps in one launch
 
   // host memory of the call: what goes to the device, what comes back
   const int nblocks = (N + 15) / 16 < kNormBlocks ? (N + 15) / 16 : kNormBlocks;
-  const size_t norms = (size_t)B * 3 * nblocks, n_budgets = (size_t)B * (kSets + kProbes);
   static_assert(sizeof(Refine) % sizeof(double) == 0, "the sums follow the states");
-  const std::unique_ptr<sa::HeadBudget[]> head(new (std::nothrow) sa::HeadBudget[n_budgets]);
-  const std::unique_ptr<Refine[]> begin(new (std::nothrow) Refine[B]);
-  const std::unique_ptr<double[]> back(new (std::nothrow) double[B * (sizeof(Refine) / sizeof(double)) + norms]);
+  const int most = z.full.heads;
+  const std::unique_ptr<sa::HeadBudget[]> head(new (std::nothrow) sa::HeadBudget[(size_t)most * (kSets + kProbes)]);
+  const std::unique_ptr<Refine[]> begin(new (std::nothrow) Refine[most]);
+  const std::unique_ptr<double[]> back(new (std::nothrow) double[most * (sizeof(Refine) / sizeof(double) + 3 * (size_t)nblocks)]);
   if (!head || !begin || !back) return failp(ctx, SA_ERR_INVALID_ARG, "search: out of host memory");
   sa::HeadBudget *hb = head.get();
   Refine *hr = begin.get();
-  const double *hp = back.get() + B * (sizeof(Refine) / sizeof(double));
-  for (int i = 0; i < B; ++i) {
-    hr[i].start(z.x_lo[1], z.x_hi[1]);
-    for (int p = 0; p < kProbes; ++p) hb[kSets * B + virtual_head(i, p, gb, kProbes)] = slash_budget(hr[i].probe(p), N, nb);
-    for (int k = 0; k < kSets; ++k) hb[virtual_head(i, k, gb, kSets)] = slash_budget(z.x_lo[1], N, nb);
-    hb[virtual_head(i, 0, gb, kSets)].local = nb;
-    hb[virtual_head(i, 1 + SA_TRIANGULAR, gb, kSets)].local = (int32_t)tri.x;
-    hb[virtual_head(i, 1 + SA_BLOCK_CLUSTER, gb, kSets)].k_b = (int32_t)clu.x;
-  }
+  for (int i = 0; i < most; ++i) hr[i].start(x_lo, x_hi);
   hipError_t he = hipSuccess;
   auto ok = [&](hipError_t e) {
     if (e != hipSuccess && he == hipSuccess) he = e;
     return he == hipSuccess;
   };
+  int B = 0, gb = 0;  // heads of the batch, and of a KV head in it
   for (int h0 = 0; h0 < sh.Hq && he == hipSuccess; h0 += B) {
+    if (B != z.heads_from(h0)) {  // the device and the host are done with the batch before
+      B = z.heads_from(h0);
+      const Batch &batch = B == z.full.heads ? z.full : z.last;
+      gb = B / batch.kv_heads;
+      if ((st = lay_out(batch, (char *)scratch, &l)) != SA_OK) return failp(ctx, st, "search: batch rejected");
+      for (int i = 0; i < B; ++i) {
+        for (int p = 0; p < kProbes; ++p) hb[kSets * B + virtual_head(i, p, gb, kProbes)] = slash_budget(hr[i].probe(p), N, nb);
+        for (int k = 0; k < kSets; ++k) hb[virtual_head(i, k, gb, kSets)] = slash_budget(x_lo, N, nb);
+        hb[virtual_head(i, 0, gb, kSets)].local = nb;
+        hb[virtual_head(i, 1 + SA_TRIANGULAR, gb, kSets)].local = (int32_t)tri.x;
+        hb[virtual_head(i, 1 + SA_BLOCK_CLUSTER, gb, kSets)].k_b = (int32_t)clu.x;
+      }
+    }
+    const size_t norms = (size_t)B * 3 * nblocks, n_budgets = (size_t)B * (kSets + kProbes);
+    const double *hp = back.get() + B * (sizeof(Refine) / sizeof(double));
+    const sa::Shape &cs = l.cs, &ps = l.ps;
+    const sa::Workspace &ws = l.ws;
+    const sa_index &ix = l.ix;
+    uint16_t *outputs = l.outputs;
+    sa::HeadBudget *budgets = l.budgets, *probes = l.probes;
+    Refine *state = l.state;
+    double *partial = l.partial;
     const uint16_t *Qh = (const uint16_t *)Q + (size_t)h0 * sh.q_hs;
     const uint16_t *Kh = (const uint16_t *)K + (size_t)(h0 / sh.g) * sh.kv_hs;
     const uint16_t *Vh = (const uint16_t *)V + (size_t)(h0 / sh.g) * sh.kv_hs;
@@ -536,7 +587,7 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
     sa::Override ov;
     for (int h = 0; h < sa::kMaxHeads; ++h) ov.pat[h] = SA_INTERVAL_SLASH;
     if (ranked && he == hipSuccess) {
-      slash_refine_kernel<<<B, kRankThreads, 0, stream>>>((const uint32_t *)sc.v, (const uint32_t *)sc.s, N, b, gb, z.x_lo[1], z.x_hi[1],
+      slash_refine_kernel<<<B, kRankThreads, 0, stream>>>((const uint32_t *)sc.v, (const uint32_t *)sc.s, N, b, gb, x_lo, x_hi,
                                                           state, budgets, target_pairs, eps_pairs);
       ok(hipGetLastError());
     }
