@@ -969,14 +969,24 @@ int queue_share(const Shape &sh) {
 // other at 1.4 us with a compute unit to itself; with two groups, two tiles take 1.9.  Where the items
 // are no more than the compute units, it is faster for every kind of head: layers of 4 to 8 heads at 1K to
 // 4K tokens 19.7 -> 18.8 us, 28.9 -> 25.3, 45.2 -> 36.9, 56 -> 45 at 8K, slash heads only 22.9 -> 22.9 to 57 -> 47.
-// With up to twice as many it depends on how unlike the items are, since two workgroups would share the unit anyway:
-// where the band of Triangular heads covers the sequence (plain causal attention) 2K to 16K tokens 56 -> 50, 97 -> 81,
-// 180 -> 141, 352 -> 263 us (at 2.25 items per unit 81 -> 90); slash heads 34 -> 41, a mix 62 -> 46, which
-// cannot be told apart here.  Heads taken with several indices (the offline search) stay whole: their results must not
+// With up to twice as many it depends on what the items hold, since two workgroups would share the unit anyway; the host
+// knows the budgets.  Where the band of Triangular heads covers the sequence they gain (plain causal attention of 2K
+// to 16K tokens 56 -> 50, 97 -> 81, 180 -> 141, 352 -> 263 us; at 2.25 items per unit 81 -> 90), and so do
+// Block-Cluster heads that keep every block.  Interval-Slash heads gain if their items are long too, which asks for a
+// quarter of the keys as columns, what sa_default_budgets gives for keep = 1: whole layers under the run-time rule, 8 heads
+// at 5120 and 8192 tokens (slash, and seven slash heads of eight) 121 -> 98, 173 -> 152, 145 -> 120, 214 -> 188, 32 heads
+// at 1280 and 2048 70.2 -> 71.6, 87.3 -> 86.7, 72.3 -> 73.3, 95.5 -> 95.0, 64 heads at 1024 71.5 -> 75.8 (all
+// Block-Cluster 75 -> 69).  With few columns under such a band they lose (a tenth of the keys kept, 8 heads at 5120
+// tokens 62 -> 69.5, 32 at 2048 60.8 -> 67, 24 at 2048 58 -> 64.5), so these stay whole, as do those without such a band
+// (slash heads 34 -> 41, a mix 62 -> 46, which cannot be told apart here).  To ask the index on the device instead, with
+// both kernels launched and one of them returning at once, cost 2 to 3 us a call.
+// Heads taken with several indices (the offline search) stay whole: their results must not
 // depend on how many heads are taken together.
 bool split_items(const Shape &sh) {
   const int n_items = (sh.N + BQ - 1) / BQ * sh.Hq;
-  return sh.gq == sh.g && n_items <= (sh.local >= sh.nb ? 2 : 1) * sh.n_cu;
+  // rounded to 64, a quarter of the keys can be half a tile short
+  const bool long_items = sh.local >= sh.nb && 4 * ((long long)sh.k_v + BK / 2) >= sh.N;
+  return sh.gq == sh.g && n_items <= (long_items ? 2 : 1) * sh.n_cu;
 }
 
 int queue_capacity(const Shape &sh) {
