@@ -18,6 +18,8 @@
 // ALU) spread among those of the block map (bound by the HBM stream of Q), which needs the K means of
 // pass 1.  One stream, no events: with five launches on two streams 4 heads of 4096 tokens took 55 us,
 // now 18; 32 heads at 10K, 16K, 32K, 64K and 128K tokens 59, 78, 122, 189 and 394, now 55, 65, 114, 183 and 364.
+#include <algorithm>
+
 #include "sa_internal.h"
 
 namespace sa {
@@ -827,7 +829,11 @@ hipError_t launch_estimate_part(const Shape &sh, const Workspace &ws, const uint
   // 8K 23.9 -> 18.9; beyond the line it costs (one workgroup more per unit: 16 heads at 16K 42.7 -> 45.9).
   int rows_wg = 16;
   while (rows_wg > 4 && nstrips * sh.Hq * (16 / rows_wg) * 2 * 64 <= sh.n_cu * sh.b) rows_wg /= 2;
-  const int units = wu + (what == EstimatePart::Windows ? 0 : (nstrips * sh.Hq * (16 / rows_wg) + 7) / 8);
+  // A single strip of less than 16 row blocks needs no workgroups for those it lacks: empty as they are, they push the
+  // windows' workgroups on to units that have one (128 heads on 8 KV heads at 384 and 512 tokens 21.4 and 19.8 us with
+  // them, 17.2 and 17.1 without, with 128-row blocks 19.1 and 21.1, 17.0 and 16.8; 64 at 1024 19.6, 16.9).
+  const int per_strip = (std::min(sh.nb, 16) + rows_wg - 1) / rows_wg;
+  const int units = wu + (what == EstimatePart::Windows ? 0 : (nstrips * sh.Hq * per_strip + 7) / 8);
   // 4/5: 364 us for the estimator at 128K tokens, 114 at 32K; all units 388 and 119 (pass 2 is left for the end), the
   // first ones 388 and 121 (it does not run beside the stream any more); 65, 65 and 62 at 16K
   int spread = units * 4 / 5;
