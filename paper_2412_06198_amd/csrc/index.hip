@@ -2218,7 +2218,10 @@ struct HeldPlan { bool held; int seg_vs, seg_blk, per_vs, per_blk, cap_vs, cap_b
 // pattern rule no more than a wave).  Two launches against five, 32 heads: 18 us and 22 at 8K tokens, 30 and 40 at 16K,
 // 44 and 55 at 32K with 7400 blocks selected below the diagonal, 32 and 53 with 2100, 41 and 60 at 64K.  A list
 // of more than 8192 blocks loses: 38.6 and 39.3 with 9400 at 16K tokens, 43.4 and 40.4 with 12600, 47 and 41 with 15300,
-// 42.5 and 36.8 with 8 heads.
+// 42.5 and 36.8 with 8 heads.  The five launches follow the number of heads, the two hardly: with up to 8 heads, Block-
+// Cluster ones among them, long lists of several segments already lose below that (4 heads at 32K tokens with 7368
+// blocks 40.1 and 34.6, with 3428 33.3 and 34.5; at 64K with 4741 37.6 and 35.2), while without such heads, which the host
+// cannot know, the two stay ahead (29.5 and 32.4, 28.5 and 33.2 with 5398).  So the line is not drawn by the heads.
 HeldPlan held_arrays(const Shape &sh) {
   HeldPlan p;
   const long long ncand = sh.row_select ? 0 : (long long)sh.nb * (sh.nb - 1) / 2;
