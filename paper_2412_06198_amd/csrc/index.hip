@@ -495,16 +495,15 @@ __device__ inline void count_keys(const Four &f, unsigned bits, unsigned lo, int
 
 // One workgroup narrows the ranges by walks over the whole array until at most kList keys are left or
 // a single one, ...
-template <int NT>
 __device__ inline void narrow(const IdxArgs &a, int arr, const unsigned *src, int nparts, int ns,
                               unsigned (*hist)[kSubWords], Pick *pick, unsigned *wsum, Ranges &r) {
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   while (r.open(0, kList) || r.open(1, kList)) {
     const bool want[2] = {r.open(0, kList), r.open(1, kList)};
     __syncthreads();
-    for (int i = threadIdx.x; i < 2 * kSubWords; i += NT) (&hist[0][0])[i] = 0u;
+    for (int i = threadIdx.x; i < 2 * kSubWords; i += BT) (&hist[0][0])[i] = 0u;
     __syncthreads();
-    for (int pt = wv; pt < nparts; pt += NT / 64)
+    for (int pt = wv; pt < nparts; pt += BT / 64)
       visit(a, arr, src, pt, [&](const Four &f) {
 #pragma unroll
         for (int k = 0; k < 2; ++k)
@@ -516,7 +515,7 @@ __device__ inline void narrow(const IdxArgs &a, int arr, const unsigned *src, in
             count_keys(f, bits, r.lo[k], digit_shift(r.last[k] - r.lo[k]), hist[k]);
           }
       });
-    narrow_step<NT>(ns, hist, pick, wsum, want, r);
+    narrow_step<BT>(ns, hist, pick, wsum, want, r);
   }
   __syncthreads();
 }
@@ -524,13 +523,12 @@ __device__ inline void narrow(const IdxArgs &a, int arr, const unsigned *src, in
 // ... and then, per part, counts the keys above them (up to `top`) and puts the keys inside them on
 // the lists.  A range of a single key needs no list, its keys are counted.  Selection ns - 1 is the
 // one whose entries are emitted; of the other, a probe, only the sum of the keys matters.
-template <int NT>
 __device__ inline void collect(const IdxArgs &a, int arr, const unsigned *src, int nparts, int ns, const Ranges &r,
                                const unsigned (&top)[2], u64 (*list)[kList], unsigned *n_list, unsigned *pgt,
                                unsigned *peq, u64 &ts) {
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), km = ns - 1;
   const unsigned lom = km ? r.lo[1] : r.lo[0], lastm = km ? r.last[1] : r.last[0], topm = km ? top[1] : top[0];
-  for (int pt = wv; pt < nparts; pt += NT / 64) {
+  for (int pt = wv; pt < nparts; pt += BT / 64) {
     unsigned gt = 0, eq = 0;
     visit(a, arr, src, pt, [&](const Four &f) {
 #pragma unroll
@@ -561,7 +559,7 @@ __device__ inline void collect(const IdxArgs &a, int arr, const unsigned *src, i
 // 2 tid + 1 counted elsewhere), and of v and s the sum of the probe best (ts: this thread's share of
 // the keys above the probe's list, above: the workgroup's).  Both selections step together: a step
 // is a chain of barriers and LDS round trips.
-template <int NT, class Each>
+template <class Each>
 __device__ inline u64 finish_array(const IdxArgs &a, IdxScratch *G, int arr, int nparts, int ns,
                                    const u64 (*list)[kList], Each each,
                                    unsigned (*hist)[kSubWords], Pick *pick, Ranges &r, const unsigned (&own)[2],
@@ -591,7 +589,7 @@ __device__ inline u64 finish_array(const IdxArgs &a, IdxScratch *G, int arr, int
   while (r.lo[0] != r.last[0] || r.lo[1] != r.last[1]) {
     const bool want[2] = {r.lo[0] != r.last[0], r.lo[1] != r.last[1]};
     __syncthreads();
-    for (int i = tid; i < ns * kSubWords; i += NT) (&hist[0][0])[i] = 0u;
+    for (int i = tid; i < ns * kSubWords; i += BT) (&hist[0][0])[i] = 0u;
     __syncthreads();
     for (int k = 0; k < ns; ++k) {
       const unsigned l = k ? r.lo[1] : r.lo[0], e = k ? r.last[1] : r.last[0];
@@ -601,7 +599,7 @@ __device__ inline u64 finish_array(const IdxArgs &a, IdxScratch *G, int arr, int
           if (key >= l && key <= e) atomicAdd(&hist[k][(key - l) >> shift], 1u);
         });
     }
-    narrow_step<NT>(ns, hist, pick, wsum, want, r);
+    narrow_step<BT>(ns, hist, pick, wsum, want, r);
   }
   const unsigned thr_p = r.lo[0], thr = ns > 1 ? r.lo[1] : r.lo[0], need = ns > 1 ? r.rank[1] : r.rank[0];
   for (int k = 0; k < ns; ++k) {
@@ -629,7 +627,7 @@ __device__ inline u64 finish_array(const IdxArgs &a, IdxScratch *G, int arr, int
     e[j] = in ? peq[2 * tid + j] : 0u;
   }
   unsigned xg = g[0] + g[1], xe = e[0] + e[1];
-  block_exclusive_scan2<NT / 64>(xg, xe, wsum);
+  block_exclusive_scan2<BT / 64>(xg, xe, wsum);
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     if (2 * tid + j < nparts) { wg[2 * tid + j] = xg; we[2 * tid + j] = xe; }
@@ -642,7 +640,7 @@ __device__ inline u64 finish_array(const IdxArgs &a, IdxScratch *G, int arr, int
   u64 sum = 0;
   if (arr < 2 && tid == 0) {
     sum = (u64)r.rank[0] * fx30(thr_p);  // ties at the threshold
-    for (int w = 0; w < NT / 64; ++w) sum += red[w];
+    for (int w = 0; w < BT / 64; ++w) sum += red[w];
   }
   return sum;
 }
@@ -936,8 +934,8 @@ __global__ __launch_bounds__(BT) void idx_count_kernel(IdxArgs a) {
   if (any_dense && !counted) {
     // A wide range of different keys, more than a list takes: below the lowest bin (or above the highest) only.
     const unsigned top[2] = {r.last[0], r.last[1]};
-    narrow<BT>(a, arr, src, nparts, ns, hist, pick, wsum, r);
-    collect<BT>(a, arr, src, nparts, ns, r, top, list, n_list, pgt, peq, ts);
+    narrow(a, arr, src, nparts, ns, hist, pick, wsum, r);
+    collect(a, arr, src, nparts, ns, r, top, list, n_list, pgt, peq, ts);
     m[0] = n_list[0]; m[1] = n_list[1];
   } else if (any_dense) {
 #pragma unroll 1
@@ -982,7 +980,7 @@ __global__ __launch_bounds__(BT) void idx_count_kernel(IdxArgs a) {
       fn((unsigned)(it >> 32), (int)(unsigned)it);
     }
   };
-  const u64 sum = finish_array<BT>(a, G, arr, nparts, ns, list, each, hist, pick, r, own, pgt, peq, wsum, red, ts);
+  const u64 sum = finish_array(a, G, arr, nparts, ns, list, each, hist, pick, r, own, pgt, peq, wsum, red, ts);
   if (arr == 2 || tid != 0) return;
   agent_store(&G->psum[arr], sum);
   finish_vs(a, G, arr, h);
