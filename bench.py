@@ -245,7 +245,8 @@ def run_workload(name, steps, warmup, layers, with_cpu, sample_rows, with_dense=
             "diagonals": {"ms": t_diag, "bytes": diag_bytes, "GBps": diag_bytes / t_diag / 1e6,
                           "frac_of_hbm_peak": diag_bytes / t_diag / 1e6 / PEAK_HBM_GBS,
                           "kept_pairs": c_full[1] - c_tile[1],
-                          "how": "difference to the full call; bytes = 32 K + 32 V rows per (wave, diagonal) tile"},
+                          "how": "difference to the full call, whose tile loops hide a part of the phase: a cost, not a rate of "
+                                 "the memory; bytes = 32 K + 32 V rows per (wave, diagonal) tile"},
         }
         log(f"[{name}] attention {t_full:.3f} ms = tile loop {t_tile:.3f} ms ({attn_phases['tile_loop']['TFLOPs_on_tiles']:.0f} TFLOP/s on tiles) "
             f"+ diagonals {t_diag:.3f} ms ({diag_bytes / 1e9:.2f} GB, {attn_phases['diagonals']['GBps']:.0f} GB/s)")

@@ -329,8 +329,8 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
   // Persistent workgroups pull (head, row block) items from eight queues, one per XCD
   // (consecutive workgroup ids land on consecutive XCDs).  1, 2, 4 or 8 queues share one KV head at a
   // time: alone, a queue keeps its KV head in a single L2; with more of them fewer KV heads are live at
-  // once, so that the rows the diagonal phase fetches (no reuse inside an L2) come out of the
-  // memory-side cache instead of HBM.  plan_item has written down what every ticket stands for.  A
+  // once, so that the rows the diagonal phase fetches (little reuse inside an L2) are in the
+  // memory-side cache rather than in HBM.  plan_item has written down what every ticket stands for.  A
   // workgroup whose own queue is empty takes from the others, then exits.  The first ticket is the
   // workgroup's number; the one for the next item of the home queue is drawn while the current item
   // finishes, so its round trip is off the critical path.
@@ -698,9 +698,13 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
   // and read from there like any tile, the copies of one running while the one before is multiplied.
   // An entry is dropped when its key block is kept by the CSR or its key is a selected column: those
   // tiles already counted it.
-  // The phase waits for its rows: copies of such tiles run at 33 TB/s out of an L2 on this chip and at 8 TB/s out
-  // of the memory-side cache, and little of what a row block reads is in its XCD's L2 (nearby row blocks reach
-  // the same keys at another offset and another time).  So the chain between two copies is kept short: which
+  // The phase waits for its rows, and these for the path from the L2s to the fabric: copies of such tiles, two a wave in
+  // flight as here, run at 35 TB/s out of an L2 and at 6.8 to 7.2 where they miss it, whatever the rows span beyond
+  // 128 MiB.  Little of what a row block reads is in its XCD's L2 (nearby row blocks reach the same keys at
+  // another offset and another time): an index of diagonals alone, 32 heads at 128K tokens, reads 35 GB of rows
+  // in 3.38 ms, 22.4 GB of it past the L2s, which is 6.6 TB/s.  In a mix of heads the tile loops of other workgroups
+  // run meanwhile: 14.7 GB cost 0.99 ms more than no diagonals, not the 2.1 they would take alone.
+  // So the chain between two copies is kept short: which
   // queries take an entry is worked out for 64 offsets at once, one per lane, and the scores of a batch of offsets
   // are taken from K before their products with V, so that the row maximum is exchanged and compared once a
   // batch and either copy has a whole step of the other buffer to land.  Against K and V of one offset after the
@@ -957,7 +961,10 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
 int queue_share(const Shape &sh) {
   const int nT = (sh.N + BQ - 1) / BQ;
   // KV heads in progress together: as many as there are queues, unless their K and V rows
-  // (what the diagonal phase streams) exceed the 256 MiB memory-side cache
+  // (what the diagonal phase streams) exceed the 256 MiB memory-side cache.  32 heads at 128K tokens, a queue to itself
+  // against two: a mix of heads 4.04 ms and 3.84, all Interval-Slash 3.73 and 3.66.  Not by fewer L2 misses (19.2 and 20.2
+  // GB), nor by the rate of misses, which 128 MiB and 1 GiB of rows share; diagonals alone 3.30 and 3.39.  The cause is
+  // not known.
   int xb = 0;
   while (xb < 3 && (8 >> xb) > sh.Hkv) ++xb;  // fewer than 8 KV heads: no idle queues
   while (xb < 3 && (size_t)(8 >> xb) * sh.N * kHeadDim * 2 * 2 > ((size_t)256 << 20)) ++xb;
