@@ -826,7 +826,10 @@ hipError_t launch_estimate_part(const Shape &sh, const Workspace &ws, const uint
   // or 4, each with all column tiles of the strip.  A workgroup waits for the stream of its queries, which
   // is twice as long with 128-row blocks: there up to two workgroups per compute unit.  4 heads at 1K and 4K tokens 17.5 ->
   // 16.4 and 18.7 -> 17.2 us, with 128-row blocks 23.9 -> 17.1 at 4K and 73.5 -> 66.5 at 64K, 8 heads of one KV head at
-  // 8K 23.9 -> 18.9; beyond the line it costs (one workgroup more per unit: 16 heads at 16K 42.7 -> 45.9).
+  // 8K 23.9 -> 18.9; beyond the line it costs (one workgroup more per unit: 16 heads at 16K 42.7 -> 45.9).  Over 568 sizes
+  // of 2 to 32 heads 9 % in the mean; 39 of them are up to 17 % slower than with whole strips, most where the map's
+  // workgroups and the windows' come to one more per unit (6 heads at 10K 21.2 -> 24.7, 4 at 14K 30.5 -> 34.6), but not
+  // halving there would give away as many gains as losses (8 heads at 24K, b = 128, 36.9 -> 31.9).
   int rows_wg = 16;
   while (rows_wg > 4 && nstrips * sh.Hq * (16 / rows_wg) * 2 * 64 <= sh.n_cu * sh.b) rows_wg /= 2;
   // A single strip of less than 16 row blocks needs no workgroups for those it lacks: empty as they are, they push the
