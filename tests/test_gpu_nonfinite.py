@@ -1,4 +1,4 @@
-"""NaN and infinities in K: a query whose softmax takes one in must show it, whatever part of the index keeps the key
+"""NaN and infinities in K, NaN in Q: a query whose softmax takes one in must show it, whatever part of the index keeps the key
 (a block, a column, a diagonal), and no other query may; against a softmax in fp64."""
 import numpy as np
 import pytest
@@ -50,3 +50,30 @@ def test_key_rows(H, value, by):
     got = host_f64(O)
     assert (np.isnan(got) == bad).all()
     check_attention(got[~takes], want[~takes], f"{by} {value}")
+
+
+@pytest.mark.parametrize("H", [2, 72])
+@pytest.mark.parametrize("N", [448, 64])
+def test_query_rows(H, N):
+    # a query with a NaN, one that keeps keys through its block, columns and diagonals and one in the first block
+    print(f"case non-finite queries heads {H} N={N}", flush=True)
+    b, row = 64, N - 3
+    nb = N // b
+    blk = np.arange(nb, dtype=np.int32)
+    index = orc.Index(np.full(H, 1, np.int32), np.full(H, 2, np.int32), np.tile(np.array([5, 50], np.int32), (H, 1)),
+                      np.full(H, 2, np.int32), np.tile(np.array([0, 60], np.int32), (H, 1)), np.tile(np.arange(nb + 1, dtype=np.int32), (H, 1)),
+                      np.tile(np.pad(blk, (0, nb * (nb + 1) // 2 - nb), constant_values=-1), (H, 1)))
+    Q, K, V = gen.random_qkv(H, 1, N, 128, seed=4)
+    clean = orc.masked_rows(Q, K, V, b, index)[0]
+    Q[H - 1, [9, row], 100] = 0x7FC0
+    ses = make_session(H, 1, N, b, 64, orc.Budgets(1, 1, 2, 2, nb * (nb + 1) // 2))
+    upload_index(ses, index)
+    Qd, Kd, Vd = dev_bf16(Q), dev_bf16(K), dev_bf16(V)
+    O = torch.full_like(Qd, 7.0)
+    ses.prefill(Qd, Kd, Vd, O)
+    torch.cuda.synchronize()
+    bad = np.zeros((H, N), bool)
+    bad[H - 1, [9, row]] = True
+    got = host_f64(O)
+    assert (np.isnan(got) == bad[..., None]).all()
+    check_attention(got[~bad], clean[~bad], f"queries {N}")

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 # (heads, keep: 1.0 = what the library takes for it, patterns, whether the items stay whole); None: the run-time rule
 @pytest.mark.parametrize("H,keep,pattern,whole", [(40, 0.1, [1], True), (64, 0.1, None, True), (33, 0.6, [1, 0, 2], True),
                                                   (40, 1.0, [0], False), (64, 1.0, None, False), (33, 1.0, [1, 0, 2], False)])
-@pytest.mark.parametrize("N,b", [(1024, 64), (960, 64), (896, 128)])
+@pytest.mark.parametrize("N,b", [(1024, 64), (960, 64), (1024, 128)])
 def test_choice(H, keep, pattern, whole, N, b):
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
     nb, items = N // b, -(-N // 128) * H
