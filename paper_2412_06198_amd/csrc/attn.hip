@@ -309,6 +309,12 @@ __device__ inline float max_pair(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// The sum of a lane's value and that of the lane 32 away, in both.
+__device__ inline float sum_pair(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // G groups of four waves share an item: group j takes every G-th tile and diagonal from the j-th on, with buffers of
 // its own, and the groups' sums are merged at the end.  With G = 1 two workgroups live on a compute unit, with G = 2
 // one: see split_items for where that pays.
@@ -722,27 +728,28 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
     // two 8 KB tiles per wave: waves 0, 1 in the V buffers, waves 2, 3 in the K buffers
     uint16_t *const tile0 = (wv < 2 ? &Vs[grp][0][0] : &Ks[grp][0][0]) + (wv & 1) * (2 * 32 * 128);
     const unsigned ldsT = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)tile0;
-    const int rstar = 4 * (q >> 3) + (q & 3);        // register of S^T that holds key_local == q
-    const bool holder = gg == ((q >> 2) & 1);        // ... in this half of the lane pair
     const int vrow = lane >> 4;                      // copies: one instruction moves rows 4n + vrow
-    const unsigned vchunk = (unsigned)(((lane & 15) ^ (vrow << 2)) << 4);  // swizzles applied on the global side
-    // K rows are swizzled by (row & 15) = (4n & 15) ^ vrow: four per-lane offsets serve the eight copies
+    // rows are swizzled by (row & 15) = (4n & 15) ^ vrow, on the global side: four per-lane offsets serve the eight copies
     const unsigned kchunk = (unsigned)(((lane & 15) ^ vrow) << 4);
+    // V (A operand of the 4x4 products, transposing read): the 16 lanes of a read supply four pieces of each of four blocks
+    // of four keys, lane s the piece of key 4 (s % 4) + s / 4, and lane r receives keys 4 (r / 4) .. + 3 of element r % 4
+    const int dvrow = (lane & 16) + 4 * (lane & 3) + ((lane >> 2) & 3);
+    const unsigned dvbase = (unsigned)(dvrow * 256) | (unsigned)((dvrow & 15) << 4) | (unsigned)(8 * gg);
     const unsigned krow = (unsigned)(vrow * (int)p.kv_rs * 2);
     const uint32_t *kw = wv < 2 ? kept0 : kept1;
     float *const dsc = dscore[grp] + 32 * wv + q;
-#define SA_DIAG_COPY(src, jb_, swzc, swzn, ldsb)                                                 \
+#define SA_DIAG_COPY(src, jb_, ldsb)                                                             \
   {                                                                                              \
     if ((jb_) >= 0) {                                                                            \
       const uint16_t *b_ = (src) + (size_t)(jb_) * p.kv_rs;                                      \
       _Pragma("unroll") for (int n_ = 0; n_ < 8; ++n_)                                           \
-        SA_DMA16(b_ + (size_t)(4 * n_) * p.kv_rs, krow + ((swzc) ^ (unsigned)(swzn)), (ldsb) + n_ * 1024); \
+        SA_DMA16(b_ + (size_t)(4 * n_) * p.kv_rs, krow + (kchunk ^ (unsigned)(((4 * n_) & 15) << 4)), (ldsb) + n_ * 1024); \
     } else { /* rows before the sequence: clamped copies, masked out by the validity test */     \
       _Pragma("unroll") for (int n_ = 0; n_ < 8; ++n_) {                                         \
         const int rb_ = max((jb_) + 4 * n_, 0);                                                  \
         const int dr_ = max((jb_) + 4 * n_ + vrow, 0) - rb_; /* >= 0 */                          \
         SA_DMA16((src) + (size_t)rb_ * p.kv_rs,                                                  \
-                 (unsigned)(dr_ * (int)p.kv_rs * 2) + ((swzc) ^ (unsigned)(swzn)), (ldsb) + n_ * 1024); \
+                 (unsigned)(dr_ * (int)p.kv_rs * 2) + (kchunk ^ (unsigned)(((4 * n_) & 15) << 4)), (ldsb) + n_ * 1024); \
       }                                                                                          \
     }                                                                                            \
   }
@@ -796,8 +803,8 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
         const int jb = r0 - __builtin_amdgcn_readlane(ov, __ffsll(i_left) - 1);
         i_left &= i_left - 1ull;
         const unsigned ldsb = ldsT + ibuf * (32 * 256);
-        if (i_v) SA_DIAG_COPY(Vh, jb, vchunk, 0, ldsb)
-        else SA_DIAG_COPY(Kh, jb, kchunk, ((4 * n_) & 15) << 4, ldsb)
+        const uint16_t *const src = i_v ? Vh : Kh;
+        SA_DIAG_COPY(src, jb, ldsb)
         ibuf ^= 1;
         ++n_out;
       };
@@ -826,19 +833,24 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
           __builtin_amdgcn_sched_barrier(0);
           cbuf ^= 1;
           issue();
-          f32x16 sd;
+          // a lane's key row times its query and those of its three neighbours, 8 of 16 elements of a k-step per lane
+          f32x4 sd[4] = {};
 #pragma unroll
-          for (int r = 0; r < 16; ++r) sd[r] = 0.f;
+          for (int ks = 0; ks < 8; ++ks) {
+            const s16x8 k8 = __builtin_bit_cast(s16x8, kf[ks]), q8 = __builtin_bit_cast(s16x8, qf[ks]);
+            sd[2 * (ks & 1)] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_shufflevector(k8, k8, 0, 1, 2, 3),
+                                                          __builtin_shufflevector(q8, q8, 0, 1, 2, 3), sd[2 * (ks & 1)], 0, 0, 0);
+            sd[2 * (ks & 1) + 1] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_shufflevector(k8, k8, 4, 5, 6, 7),
+                                                          __builtin_shufflevector(q8, q8, 4, 5, 6, 7), sd[2 * (ks & 1) + 1], 0, 0, 0);
+          }
+          float sv = (sd[0][0] + sd[2][0]) + (sd[1][0] + sd[3][0]);
 #pragma unroll
-          for (int ks = 0; ks < 8; ++ks)
-            sd = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], sd, 0, 0, 0);
-          float sv = sd[0];
-#pragma unroll
-          for (int r = 1; r < 16; ++r) sv = (r == rstar) ? sd[r] : sv;
-          smax = fmaxf(smax, holder && ((tk >> q) & 1u) ? sv : -INFINITY);
-          if (holder) dsc[slot * BQ] = sv;  // as it is: a maximum would drop a NaN
+          for (int r = 1; r < 4; ++r) sv = r == (q & 3) ? (sd[0][r] + sd[2][r]) + (sd[1][r] + sd[3][r]) : sv;
+          sv = sum_pair(sv);
+          smax = fmaxf(smax, (tk >> q) & 1u ? sv : -INFINITY);
+          dsc[slot * BQ] = sv;  // as it is: a maximum would drop a NaN
           if constexpr (STATS) {
-            st_kept += holder && ((tk >> q) & 1u) ? 1u : 0u;
+            st_kept += gg == 0 && ((tk >> q) & 1u) ? 1u : 0u;
             st_tiles += 1u;
           }
         }
@@ -857,30 +869,31 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
         for (unsigned long long left = batch; left != 0ull; left &= left - 1ull, ++slot) {
           const uint32_t tk = (uint32_t)__builtin_amdgcn_readlane((int)take, __ffsll(left) - 1);
           const float sv = dsc[slot * BQ];
-          const float pv = holder && ((tk >> q) & 1u) ? __builtin_amdgcn_exp2f(__builtin_fmaf(sv, p.c, -m_ref)) : 0.f;
-          const __bf16 pvb = (__bf16)pv, zb = (__bf16)0.f;
-          l_run += (float)pvb;  // the weight as the matrix pipe sees it (see the tile loop's normaliser)
+          const float pv = (tk >> q) & 1u ? __builtin_amdgcn_exp2f(__builtin_fmaf(sv, p.c, -m_ref)) : 0.f;
+          const __bf16 pvb = (__bf16)pv;
+          l_run += gg == 0 ? (float)pvb : 0.f;  // the weight as the matrix pipe sees it (see the tile loop's normaliser)
+          const uint32_t pw = (uint32_t)__builtin_bit_cast(uint16_t, pvb) << (16 * (q & 1));
+          const s16x4 pb = __builtin_bit_cast(s16x4, make_uint2(q & 2 ? 0u : pw, q & 2 ? pw : 0u));
           landed();
           const uint16_t *Vw = tile0 + cbuf * (32 * 128);
           s16x4 vf[16];
 #pragma unroll
-          for (int i = 0; i < 16; ++i) vf[i] = SA_VTR(Vw, (i >> 1) & 3, 16 * (i >> 3) + 8 * (i & 1));
+          for (int i = 0; i < 16; ++i)
+            vf[i] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)((const char *)Vw + (dvbase ^ (unsigned)(i << 4))));
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
           __builtin_amdgcn_sched_barrier(0);
           cbuf ^= 1;
           issue();
-          // P^T is diagonal: slot e2 of k-step u is register 8u+e2
+          // P^T is diagonal: slot q % 4 of the block of four queries; elements 8 i + 4 gg .. + 3 are registers 4 (i % 4) .. + 3
 #pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            bf16x8 pb;
-#pragma unroll
-            for (int e2 = 0; e2 < 8; ++e2) pb[e2] = (8 * u + e2 == rstar) ? pvb : zb;
-#pragma unroll
-            for (int db = 0; db < 4; ++db) {
-              const s16x8 av = __builtin_shufflevector(vf[8 * u + 2 * db], vf[8 * u + 2 * db + 1], 0, 1, 2, 3, 4, 5, 6, 7);
-              oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), pb,
-                                                                 oacc[db], 0, 0, 0);
-            }
+          for (int i = 0; i < 16; ++i) {
+            f32x16 &o = oacc[i >> 2];
+            const int r = 4 * (i & 3);
+            const f32x4 s4 = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(vf[i], pb, f32x4{o[r], o[r + 1], o[r + 2], o[r + 3]}, 0, 0, 0);
+            o[r] = s4[0];
+            o[r + 1] = s4[1];
+            o[r + 2] = s4[2];
+            o[r + 3] = s4[3];
           }
         }
       }
