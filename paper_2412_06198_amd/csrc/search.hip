@@ -128,6 +128,19 @@ __host__ __device__ inline sa::HeadBudget slash_budget(int64_t x, int N, int nb)
   return b;
 }
 
+// Sizes of a head's indices in the last launches, those known beforehand: the smallest Interval-Slash size, the refined
+// Triangular and Block-Cluster sizes.
+struct Sizes { int64_t slash, triangular, cluster; };
+
+// Budget of index `set` (0: dense, then the candidates) of a head.
+__host__ __device__ inline sa::HeadBudget set_budget(int set, const Sizes &x, int N, int nb) {
+  sa::HeadBudget b = slash_budget(x.slash, N, nb);
+  if (set == 0) b.local = nb;
+  if (set == 1 + SA_TRIANGULAR) b.local = (int32_t)x.triangular;
+  if (set == 1 + SA_BLOCK_CLUSTER) b.k_b = (int32_t)x.cluster;
+  return b;
+}
+
 // One workgroup per virtual head of a refinement step: the kept pairs of its Interval-Slash index (its diagonal blocks,
 // the selected columns, the selected diagonals; each pair once).  The workgroup that counts a head's last
 // probe takes the steps of its bisection that the probes answer.
@@ -283,7 +296,7 @@ __device__ __forceinline__ void rank_pass(unsigned long long *key, int P, int k,
 }
 
 __global__ __launch_bounds__(kRankThreads) void slash_refine_kernel(const uint32_t *v, const uint32_t *s, int N, int b, int gb,
-                                                                    int64_t x_lo, int64_t x_hi, Refine *state, sa::HeadBudget *last,
+                                                                    Sizes known, int64_t x_hi, Refine *state, sa::HeadBudget *last,
                                                                     int64_t target, int64_t eps) {
   typedef unsigned long long u64;
   __shared__ u64 key[2][kRankMaxSeq];
@@ -313,7 +326,7 @@ __global__ __launch_bounds__(kRankThreads) void slash_refine_kernel(const uint32
   for (int i = tid; i < N / 32; i += kRankThreads) offset[i] = (uint16_t)rank_index(key[1][rank_slot(i)]);
 
   Refine r;
-  r.start(x_lo, x_hi);
+  r.start(known.slash, x_hi);
   if (tid < 256) by_pos[tid >> 7][tid & 127] = 0;
   __syncthreads();
   for (int cur = 0; !r.done; cur ^= 1) {
@@ -360,9 +373,11 @@ __global__ __launch_bounds__(kRankThreads) void slash_refine_kernel(const uint32
     for (int i = 0; i < kRankThreads / 64; ++i) pairs += red[cur][i];
     r.step(pairs, target, eps);  // every thread the same
   }
-  if (tid != 0) return;
-  state[i0] = r;
-  last[virtual_head(i0, 1 + SA_INTERVAL_SLASH, gb, kSets)] = slash_budget(r.x, N, nb);
+  // The budgets of all of the head's indices, from here: a copy from the host's pageable memory before this launch held the
+  // host for its staging (8 heads of 4096 tokens 273 us a search with it, 243 without, 4 of 2048 153 and 128, 8 of 1024
+  // 131 and 110).
+  if (tid < kSets) last[virtual_head(i0, tid, gb, kSets)] = tid == 1 + SA_INTERVAL_SLASH ? slash_budget(r.x, N, nb) : set_budget(tid, known, N, nb);
+  if (tid == 0) state[i0] = r;
 }
 
 // Heads that go through the search together, and the scratch they take.
@@ -531,6 +546,7 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
   // A bisection evaluates the ends and a size per halving; the first step takes both ends and the middle, every
   // other one two sizes in a row.
   const int64_t x_lo = z.full.x_lo[1], x_hi = z.full.x_hi[1];
+  const Sizes known = {x_lo, tri.x, clu.x};
   int halvings = 0;
   for (int64_t w = x_hi - x_lo; w > 1; w = (w + 1) / 2) ++halvings;
   const int rounds = 1 + halvings / 2;
@@ -559,12 +575,9 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
       const Batch &batch = B == z.full.heads ? z.full : z.last;
       gb = B / batch.kv_heads;
       if ((st = lay_out(batch, (char *)scratch, &l)) != SA_OK) return failp(ctx, st, "search: batch rejected");
-      for (int i = 0; i < B; ++i) {
+      for (int i = 0; !ranked && i < B; ++i) {
         for (int p = 0; p < kProbes; ++p) hb[kSets * B + virtual_head(i, p, gb, kProbes)] = slash_budget(hr[i].probe(p), N, nb);
-        for (int k = 0; k < kSets; ++k) hb[virtual_head(i, k, gb, kSets)] = slash_budget(x_lo, N, nb);
-        hb[virtual_head(i, 0, gb, kSets)].local = nb;
-        hb[virtual_head(i, 1 + SA_TRIANGULAR, gb, kSets)].local = (int32_t)tri.x;
-        hb[virtual_head(i, 1 + SA_BLOCK_CLUSTER, gb, kSets)].k_b = (int32_t)clu.x;
+        for (int k = 0; k < kSets; ++k) hb[virtual_head(i, k, gb, kSets)] = set_budget(k, known, N, nb);
       }
     }
     const size_t norms = (size_t)B * 3 * nblocks, n_budgets = (size_t)B * (kSets + kProbes);
@@ -580,14 +593,14 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
     const uint16_t *Kh = (const uint16_t *)K + (size_t)(h0 / sh.g) * sh.kv_hs;
     const uint16_t *Vh = (const uint16_t *)V + (size_t)(h0 / sh.g) * sh.kv_hs;
     const sa_scores sc{scores.v + (size_t)h0 * N, scores.s + (size_t)h0 * N, scores.blk + (size_t)h0 * nb * nb};
-    ok(hipMemcpyAsync(budgets, hb, n_budgets * sizeof(sa::HeadBudget), hipMemcpyHostToDevice, stream));
+    if (!ranked) ok(hipMemcpyAsync(budgets, hb, n_budgets * sizeof(sa::HeadBudget), hipMemcpyHostToDevice, stream));
     if (!ranked) ok(hipMemcpyAsync(state, hr, (size_t)B * sizeof(Refine), hipMemcpyHostToDevice, stream));
     // RefineSearchSpace of the Interval-Slash candidate, all heads a step per round (a head that is done
     // repeats its last index)
     sa::Override ov;
     for (int h = 0; h < sa::kMaxHeads; ++h) ov.pat[h] = SA_INTERVAL_SLASH;
     if (ranked && he == hipSuccess) {
-      slash_refine_kernel<<<B, kRankThreads, 0, stream>>>((const uint32_t *)sc.v, (const uint32_t *)sc.s, N, b, gb, x_lo, x_hi,
+      slash_refine_kernel<<<B, kRankThreads, 0, stream>>>((const uint32_t *)sc.v, (const uint32_t *)sc.s, N, b, gb, known, x_hi,
                                                           state, budgets, target_pairs, eps_pairs);
       ok(hipGetLastError());
     }
