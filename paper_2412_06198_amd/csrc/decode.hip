@@ -12,6 +12,7 @@
 // 8 heads, 4096-token prompt: 10.9 -> 6.7 us (an empty launch is 2.2); 32 heads, 128K-token prompt, 29 MB
 // of rows out of the memory-side cache: 16.3 -> 10.8 us, and 26.7 -> 15.0 (the kernels alone) where K and V
 // have been pushed out of it, as they are where a step reads other layers in between.
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 
@@ -400,6 +401,28 @@ int decode_splits(const Shape &sh) {
   return s < 1 ? 1 : (s > 64 ? 64 : s);
 }
 
+namespace {
+
+// Workgroups per head of one step, at most decode_splits.  Those without keys of their own only read how long the list
+// is, but 512 of them are still 0.4 us of a step of 7.  What a list holds is known on the device; the
+// host knows the budgets: one workgroup per compute unit where a single step of each (64 keys) covers an
+// Interval-Slash and a Triangular list (8 heads at 1.2K tokens with 744 generated ones 6.71 -> 6.23 us, 32 heads at 2K
+// 7.26 -> 6.84, 8 heads at 93K 6.67 -> 6.25), else two (16 heads at 64K 7.95 us, with one 8.75).  No
+// more than an even list of a Block-Cluster head needs four times over: a hot last row holds more than its share (twice
+// its share: 4 heads at 60K 6.62 -> 6.84).  A list that is longer is taken in larger chunks.
+int splits_of_step(const Shape &sh, int pos) {
+  const int64_t own = (int64_t)pos - sh.N + 1;
+  const int64_t slash = (int64_t)sh.k_v + sh.k_s + sh.b, band = (int64_t)std::min(sh.sink + sh.local, sh.nb) * sh.b;
+  const int64_t cluster = std::min<int64_t>(4 * (int64_t)sh.k_b / sh.nb + 1, sh.nb) * sh.b;
+  const int64_t list = std::max(slash, band) + own, most = std::max(list, cluster + own);
+  const int half = std::max(256 / std::max(sh.Hq, 1), 1);
+  int64_t s = decode_splits(sh);
+  if (list <= (int64_t)half * kMinChunk) s = std::min<int64_t>(s, half);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(s, (most + kMinChunk - 1) / kMinChunk));
+}
+
+}  // namespace
+
 size_t decode_partial_bytes(const Shape &sh) { return (size_t)sh.Hq * decode_splits(sh) * kPartStride * 4; }
 
 size_t decode_static_bytes() { return sizeof(float) * kStaticPartials * kPartStride; }
@@ -433,7 +456,7 @@ hipError_t launch_sparse_decode(const Shape &sh, float *partials, const uint16_t
   a.rowptr = idx.rowptr; a.blkcols = idx.blkcols;
   a.part = partials;
   a.Hq = sh.Hq; a.g = sh.g; a.N = sh.N; a.b = sh.b; a.nb = sh.nb; a.k_v = sh.k_v; a.k_s = sh.k_s;
-  a.cap_b = sh.cap_b; a.S = decode_splits(sh); a.pos = pos;
+  a.cap_b = sh.cap_b; a.S = splits_of_step(sh, pos); a.pos = pos;
   a.kv_hs = sh.kv_hs; a.kv_rs = sh.kv_rs;
   a.c = sh.scale * 1.4426950408889634f;
   a.token = next_token();
