@@ -765,8 +765,11 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
   l_run = lacc[0][0] + lacc[1][0];
 
   // ---- selected diagonals: one 32-key tile per (wave, offset), no workgroup barriers -----------
-  // For offset o the 32 queries of this wave need the 32 keys r0-o .. r0-o+31, and in
-  // S^T = K Q^T (32 keys x 32 queries) the wanted entries are the main diagonal.  K and V tiles are
+  // For offset o the 32 queries of this wave need the 32 keys r0-o .. r0-o+31, row q for query q.  A lane holds half of
+  // a key's row and of its query, which is what v_mfma_f32_4x4x4_16b takes of each of its 16 blocks: it multiplies four
+  // neighbours with each other and three of four results are not used, where a product of 32x32x16 used one of 32 and the
+  // diagonals were 17 % of the matrix work of a launch that runs at the card's power limit (layers of 128K tokens 4351
+  // -> 4266 us, 64K 1609 -> 1580, 32K 695 -> 681, 16K 378 -> 371, 4K 53.1 -> 53.3).  K and V tiles are
   // copied by the LDS DMA into two wave-private 8 KB buffers in turn (swizzled like the shared tiles)
   // and read from there like any tile, the copies of one running while the one before is multiplied.
   // An entry is dropped when its key block is kept by the CSR or its key is a selected column: those
@@ -1082,7 +1085,8 @@ bool split_items(const Shape &sh) {
 // such a tile occupies two of the four waves, and with them two of the four SIMDs, and takes 0.7 of the time of one that
 // all multiply; in pairs the waves of both blocks multiply 32 keys of their own tile in each of two steps.  A layer of 10K
 // tokens whose diagonals are whole blocks (two thirds of its tiles are kept by one block) 317 -> 302 us, 16K 382 -> 373,
-// 32K (a fifth) 682 -> 680; with two groups of waves per item 8 heads at 2K tokens, no two rows alike, 57.1 -> 55.9.  With 128-row blocks every tile is kept by the whole item, and where every block is kept beside
+// 32K (a fifth) 682 -> 680; with two groups of waves per item 8 heads at 2K tokens, no two rows alike,
+// 57.1 -> 55.9, and 4 Interval-Slash heads at 4K, whose items have one pair, 53.0 -> 53.2.  With 128-row blocks every tile is kept by the whole item, and where every block is kept beside
 // a quarter of the keys as columns (what sa_default_budgets gives for keep = 1) only the diagonal ones of Interval-Slash
 // heads are not: there the kernel without the second loop stays (dense at 16K tokens 1925 us, 1940 with it).
 bool pair_tiles(const Shape &sh) {
