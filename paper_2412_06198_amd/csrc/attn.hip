@@ -4,8 +4,7 @@
 // One workgroup = 128 query rows of one head (4 waves x 32 rows), two workgroups
 // per compute unit, fed from work queues.  A (head, row block) item has two phases:
 //   * tiles of 64 keys through LDS, shared by the four waves:
-//       range tiles  - aligned key tiles of the key blocks the CSR keeps; those that only one of an item's two 64-row
-//                      blocks keeps in pairs, half of the keys of either a step;
+//       range tiles  - aligned key tiles of the key blocks the CSR keeps;
 //       gather tiles - 64 selected key columns, gathered once per call into
 //                      contiguous buffers, so that they are read like any tile;
 //   * selected diagonals, one 32-key tile per wave and offset, without barriers.
@@ -16,8 +15,6 @@
 // needs a single cross-lane exchange, and the probabilities are already laid out
 // as the B operand of O^T += V^T P^T.
 #include "sa_internal.h"
-
-#include <type_traits>
 
 namespace sa {
 namespace {
@@ -61,13 +58,12 @@ struct AttnArgs {
   int share;    // log2 of the queues (XCDs) that share one KV head at a time (1, 2, 4 or 8), and from bit 4 on
                 // log2 of the consecutive row blocks a queue takes in a row (kRun or 1)
   int qcap;     // tickets per queue, holes of the id space included
-  int pairs;    // whether the tiles that one row block of an item keeps alone are listed in pairs, see pair_tiles
   int side_by_side;  // also the heads with diagonals take a row block together, see plan_item
   unsigned long long *counters;  // instrumentation only: {32x32 sub-tiles multiplied, kept (query,key) pairs}
   // Written by index_prepare_kernel.  items[queue + 8 * ticket] = {head | its query head << 7 | its KV head << 14 |
-  // row block << 21, key tiles in the list | pairs << 16 (kNoItem: a hole of the id space), list start inside the head's share
+  // row block << 21, key tiles in the list (kNoItem: a hole of the id space), list start inside the head's share
   // of tiles, first two entries}; tiles [Hq][tile_cap] list entries: key tile (bits 0..11), kept by waves 0, 1
-  // (bit 14) / by waves 2, 3 (bit 15); pairs first, one of either kind each.
+  // (bit 14) / by waves 2, 3 (bit 15).
   uint4 *items;
   uint16_t *tiles;
   unsigned tile_cap;
@@ -167,9 +163,7 @@ __device__ inline void plan_item(const AttnArgs &p, int id, uint32_t *k0, uint32
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  // The list: first the tiles that one row block alone keeps, in pairs (one of the upper row block, one of the lower:
-  // see the attention kernel's paired steps), then those that both keep, then what found no partner; each kind in
-  // ascending order.  One tile per lane, 64 at a time.  Stretches that keep none are passed
+  // One tile per lane, 64 at a time: the kept ones in ascending order.  Stretches that keep none are passed
   // over by a mask of the others (a row of a long sequence has thousands of tiles and keeps some thirty:
   // without it this launch took 46 us at 128K tokens and 32 heads, 34 with it).  Scattered
   // ones, up to three in a stretch, are taken by the lanes beside each other, each its own: with that, and the heads' kinds
@@ -177,66 +171,49 @@ __device__ inline void plan_item(const AttnArgs &p, int id, uint32_t *k0, uint32
   const unsigned start = (unsigned)min(ea0, p.cap_b) * tpb;
   const unsigned room = p.tile_cap - start;
   uint16_t *out = p.tiles + (size_t)h * p.tile_cap + start;
+  unsigned base = 0;
   static_assert(NWORDS <= 128, "one lane per pair of words");
-  uint32_t m0[2], m1[2];
+  uint32_t mine[2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    m0[i] = 2 * lane + i < nwords ? k0[2 * lane + i] : 0u;
-    m1[i] = 2 * lane + i < nwords ? k1[2 * lane + i] : 0u;
-  }
-  unsigned long long words = __ballot((m0[0] | m0[1] | m1[0] | m1[1]) != 0u);
-  const unsigned cb = __popc(m0[0] & m1[0]) + __popc(m0[1] & m1[1]);  // kept by both; by one of them, 16 bits each
-  const unsigned cs = (unsigned)(__popc(m0[0] & ~m1[0]) + __popc(m0[1] & ~m1[1])) | (unsigned)(__popc(m1[0] & ~m0[0]) + __popc(m1[1] & ~m0[1])) << 16;
-  const unsigned ub = wave_inclusive_sum(cb), us = p.b != BQ ? wave_inclusive_sum(cs) : 0u;
-  const unsigned nb2 = __builtin_amdgcn_readlane(ub, 63), ns = __builtin_amdgcn_readlane(us, 63);
-  const unsigned n1 = ns & 0xFFFFu, n2 = ns >> 16, pairs = p.pairs ? min(n1, n2) : 0u, total = nb2 + n1 + n2;
-  // place of a tile that is the r-th of its kind: 3 both, 1 the upper row block alone, 2 the lower one alone
-  auto place = [&](unsigned kind, unsigned r) {
-    return kind == 3u ? 2u * pairs + r : r < pairs ? 2u * r + (kind >> 1) : pairs + nb2 + r + (kind == 2u ? n1 - pairs : 0u);
-  };
-  auto put = [&](unsigned tile, unsigned kind, unsigned r) {
-    const unsigned pos = place(kind, r);
-    const uint16_t ent = (uint16_t)(tile | kind << 14);
-    if (pos < room) {
-      out[pos] = ent;
-      if (pos < 2u) first2[pos] = ent;
-    }
-  };
-  if (total <= 3u * __popcll(words)) {  // scattered tiles: each lane those of its own words
-    unsigned rb_ = ub - cb, r1 = (us & 0xFFFFu) - (cs & 0xFFFFu), r2 = (us >> 16) - (cs >> 16);
+  for (int i = 0; i < 2; ++i) mine[i] = 2 * lane + i < nwords ? k0[2 * lane + i] | k1[2 * lane + i] : 0u;
+  unsigned long long pairs = __ballot((mine[0] | mine[1]) != 0u);
+  const unsigned count = __popc(mine[0]) + __popc(mine[1]), upto = wave_inclusive_sum(count);
+  const unsigned total = __builtin_amdgcn_readlane(upto, 63);
+  if (total <= 3u * __popcll(pairs)) {  // scattered tiles: each lane those of its own words
+    unsigned pos = upto - count;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      for (uint32_t m = m0[i] | m1[i]; m != 0u; m &= m - 1u) {
+      const int w = 2 * lane + i;
+      for (uint32_t m = mine[i]; m != 0u; m &= m - 1u, ++pos) {
         const int bit = __ffs(m) - 1;
-        const unsigned kind = ((m0[i] >> bit) & 1u) | ((m1[i] >> bit) & 1u) << 1;
-        put((unsigned)((2 * lane + i) * 32 + bit), kind, kind == 3u ? rb_ : kind == 1u ? r1 : r2);
-        rb_ += kind == 3u;
-        r1 += kind == 1u;
-        r2 += kind == 2u;
+        const uint16_t ent = (uint16_t)((w * 32 + bit) | ((k0[w] >> bit) & 1u) << 14 | ((k1[w] >> bit) & 1u) << 15);
+        if (pos < room) {
+          out[pos] = ent;
+          if (pos < 2) first2[pos] = ent;
+        }
       }
     }
-  } else {
-    unsigned base[3] = {0u, 0u, 0u};  // of kinds 1, 2, 3
-    for (; words != 0ull; words &= words - 1ull) {
-      const int w0 = 2 * (__ffsll(words) - 1), w = w0 + (lane >> 5);
-      const unsigned kind = w < nwords ? ((k0[w] >> (lane & 31)) & 1u) | ((k1[w] >> (lane & 31)) & 1u) << 1 : 0u;
-      const unsigned long long below = (1ull << lane) - 1ull;
-      unsigned r = 0u;
-#pragma unroll
-      for (unsigned u = 1; u <= 3u; ++u) {
-        const unsigned long long m = __ballot(kind == u);
-        if (kind == u) r = base[u - 1] + (unsigned)__popcll(m & below);
-        base[u - 1] += (unsigned)__popcll(m);
-      }
-      if (kind != 0u) put((unsigned)(w0 * 32 + lane), kind, r);
+    base = total;
+    pairs = 0ull;
+  }
+  for (; pairs != 0ull; pairs &= pairs - 1ull) {
+    const int w0 = 2 * (__ffsll(pairs) - 1), w = w0 + (lane >> 5);
+    const uint32_t a = w < nwords ? (k0[w] >> (lane & 31)) & 1u : 0u, b = w < nwords ? (k1[w] >> (lane & 31)) & 1u : 0u;
+    const unsigned long long m = __ballot((a | b) != 0u);
+    const unsigned pos = base + (unsigned)__popcll(m & ((1ull << lane) - 1ull));
+    if ((a | b) != 0u && pos < room) {
+      const uint16_t ent = (uint16_t)((w0 * 32 + lane) | (a << 14) | (b << 15));
+      out[pos] = ent;
+      if (pos < 2) first2[pos] = ent;
     }
+    base += (unsigned)__popcll(m);
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  const unsigned n = min(total, room);
+  const unsigned n = min(base, room);
   const int at = ticket_id();
   if (lane == 0)
-    p.items[at] = make_uint4((unsigned)h | (unsigned)query_head(h, p.g, p.gq) << 7 | (unsigned)kvh << 14 | (unsigned)t128 << 21, n | min(pairs, n / 2u) << 16, start,
+    p.items[at] = make_uint4((unsigned)h | (unsigned)query_head(h, p.g, p.gq) << 7 | (unsigned)kvh << 14 | (unsigned)t128 << 21, n, start,
                              (n > 0 ? first2[0] : 0u) | (n > 1 ? (unsigned)first2[1] << 16 : 0u));
 }
 
@@ -340,8 +317,8 @@ __device__ inline float sum_pair(float x) {
 
 // G groups of four waves share an item: group j takes every G-th tile and diagonal from the j-th on, with buffers of
 // its own, and the groups' sums are merged at the end.  With G = 1 two workgroups live on a compute unit, with G = 2
-// one: see split_items for where that pays.  PAIRS: the lists may hold paired tiles, see pair_tiles.
-template <bool STATS, int G, bool PAIRS>
+// one: see split_items for where that pays.
+template <bool STATS, int G>
 __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) {
   __shared__ __attribute__((aligned(16))) uint16_t Ks[G][2][BK * 128];
   __shared__ __attribute__((aligned(16))) uint16_t Vs[G][2][BK * 128];
@@ -405,7 +382,7 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
     continue;
   }
   const int h = (int)(it_w & 127u), qh = (int)(it_w >> 7 & 127u), kvh = (int)(it_w >> 14 & 127u), t128 = (int)(it_w >> 21);
-  const int ntr = (int)(it_n & 0xFFFFu), npair = PAIRS ? 2 * (int)(it_n >> 16) : 0;  // key tiles; those of them in pairs, first
+  const int ntr = (int)it_n;
   const int i0 = t128 * BQ;
   const int r0 = i0 + 32 * wv;
   const int iq = r0 + q;  // this lane's query row
@@ -459,21 +436,6 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
     SA_DMA16(vb, dmaV, lv); SA_DMA16(vb + row16, dmaV, lv + 16 * 256);                           \
     SA_DMA16(vb + 2 * row16, dmaV, lv + 32 * 256); SA_DMA16(vb + 3 * row16, dmaV, lv + 48 * 256); \
   }
-#define SA_ISSUE_PAIR(t, buf, ents)                                                                 \
-  {                                                                                              \
-    const int a_ = (int)((ents) & 0xFFFu), b_ = (int)((ents) >> 16 & 0xFFFu);                    \
-    const int64_t j0_ = (int64_t)(a_ * BK + 32 * ((t) & 1)) * p.kv_rs;                           \
-    const int64_t hi_ = (int64_t)((b_ - a_) * BK) * p.kv_rs;                                     \
-    const uint16_t *kb = Kh + j0_, *vb = Vh + j0_;                                               \
-    const unsigned lk = ldsK0 + (buf) * (BK * 256), lv = ldsV0 + (buf) * (BK * 256);             \
-    SA_DMA16(kb, dmaK, lk); SA_DMA16(kb + row16, dmaK, lk + 16 * 256);                           \
-    SA_DMA16(vb, dmaV, lv); SA_DMA16(vb + row16, dmaV, lv + 16 * 256);                           \
-    kb += hi_; vb += hi_;                                                                        \
-    SA_DMA16(kb, dmaK, lk + 32 * 256); SA_DMA16(kb + row16, dmaK, lk + 48 * 256);                \
-    SA_DMA16(vb, dmaV, lv + 32 * 256); SA_DMA16(vb + row16, dmaV, lv + 48 * 256);                \
-  }
-  // entry t of the list out of the word that holds it and its neighbour
-#define SA_ENTRY(t, ents) ((int)((ents) >> (16 * ((t) & 1)) & 0xFFFFu))
 
   // per-lane LDS byte offsets of the operand reads.  The swizzles only touch address bits 4..7,
   // so every access is (one per-lane base) XOR (a compile-time constant):
@@ -497,11 +459,9 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
 
   // list entries travel one tile ahead in scalar registers, so that neither the copy of the next
   // tile nor this tile's keep test waits for an LDS read behind the barrier
-  // (two entries at a time, a tile's and its partner's)
-  uint32_t w_cur = it_e;
-  uint32_t w_nxt = it_e;  // from LDS later on: made scalar only where it is used, a tile later
-  if (grp < npair) SA_ISSUE_PAIR(grp, 0, w_cur)
-  else if (grp < ntr) SA_ISSUE_TILE(grp, 0, SA_ENTRY(grp, w_cur));
+  int e_cur = (int)((grp ? it_e >> 16 : it_e) & 0xFFFFu);
+  int r_nxt = (int)(it_e >> 16);  // from LDS later on: made scalar only where it is used, a tile later
+  if (grp < ntr) SA_ISSUE_TILE(grp, 0, e_cur);
 
   // the item's other reads, all in flight together with the first tile's copies
   bf16x8 qf[8];  // Q^T fragments: B operand, lane = query, 8 consecutive d per k-step half
@@ -530,11 +490,11 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
   }
   const int ng = (call + BK - 1) / BK;
   const int ntot = ntr + ng;
-  if (grp >= ntr && grp < ntot) SA_ISSUE_TILE(grp, 0, 0);
+  if (grp >= ntr && grp < ntot) SA_ISSUE_TILE(grp, 0, e_cur);
   {
     // the list, for the tile loop (read behind its first barrier), and the kept tiles as bitmaps, for the diagonals
     const uint16_t *tl = p.tiles + (size_t)h * p.tile_cap + it_at;
-    if (G > 1) w_nxt = ntr > 2 ? (uint32_t)tl[2] | (uint32_t)tl[min(3, ntr - 1)] << 16 : 0u;
+    if (G > 1) r_nxt = G + grp < ntr ? tl[G + grp] : 0;
     for (int i = tid + 256 * grp; i < ntr; i += 256 * G) {
       const int ent = tl[i];
       tlist[i] = (uint16_t)ent;
@@ -546,25 +506,63 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
     }
   }
 
-  const int n_step = (ntot + G - 1) / G, n_pair_step = npair / G;
-  // One step's products.  NH = 2: a tile of 64 keys.  NH = 1, a paired step: 32 keys of a tile that only the upper row
-  // block keeps for waves 0 and 1, in rows 0..31 of the buffers, and 32 of one that only the lower keeps for waves 2 and 3.
-  // The mask of a lane over the key slots: slot c (0..59 used) stands for key_local = c + 4*gg; see the accumulator layout
-  // below.  Without selected columns inside the tile it is a threshold (slot c kept iff c <= lim),
-  // applied with one compare per element; km is then only needed by the counted variant.
-  auto products = [&](auto halves, int cur, bool needmask, bool bits, uint64_t km, int lim) __attribute__((always_inline)) {
-    constexpr int NH = decltype(halves)::value;
+  const int n_step = (ntot + G - 1) / G;
+  for (int step = 0; step < n_step; ++step) {
+    const int t = G * step + grp, cur = step & 1;
+    // this wave's share of tile t has landed (nothing else is in flight); after the barrier the
+    // whole tile is in LDS[cur] and every wave has finished reading LDS[cur^1] (tile t-1)
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    __syncthreads();
+    const int e_nxt = __builtin_amdgcn_readfirstlane(r_nxt);
+    if (t + G < ntot) SA_ISSUE_TILE(t + G, cur ^ 1, e_nxt);
+    const int e_this = e_cur;
+    e_cur = e_nxt;
+    r_nxt = (int)tlist[min(t + 2 * G, kMaxSeq / BK - 1)];
+
+    // ---- what this wave keeps of the tile: a 64-bit mask per lane over the key slots ---------
+    // slot c (0..59 used) stands for key_local = c + 4*gg; see the accumulator layout below.
+    // Without selected columns inside the tile the mask is a threshold (slot c kept iff c <= lim),
+    // applied with one compare per element; km is then only needed by the counted variant.
+    bool active, needmask, bits = false;
+    uint64_t km;
+    int lim = 63;
+    if (t < ntr) {
+      const int kt = e_this & 0xFFF;
+      const int j0 = kt * BK;
+      const bool bk = ((e_this >> (wv < 2 ? 14 : 15)) & 1) != 0;
+      const bool beyond = j0 > min(r0 + 31, N - 1);
+      active = !beyond && bk;
+      const uint64_t vm = has_cols ? ((uint64_t)uload(colbm, 2 * kt) | ((uint64_t)uload(colbm, 2 * kt + 1) << 32)) : 0ull;
+      needmask = !(vm == 0 && j0 + 63 <= r0);
+      km = ~0ull;
+      bits = vm != 0;
+      if (active && needmask) {
+        lim = iq - j0 - 4 * gg;  // causal: slot c kept iff c <= lim
+        const uint64_t cm = lim < 0 ? 0ull : (lim >= 63 ? ~0ull : ((2ull << lim) - 1ull));
+        km = cm & ~(vm >> (4 * gg));  // selected columns are served by the gather tiles
+      }
+    } else {
+      const int gi = t - ntr;
+      active = cwave > gi * BK;
+      needmask = cwmin < (gi + 1) * BK;  // some query of the wave sees only a part of this tile
+      km = ~0ull;
+      if (needmask) {
+        lim = cle - gi * BK - 1 - 4 * gg;  // visible columns of this tile for this query, as a slot limit
+        km = lim < 0 ? 0ull : (lim >= 63 ? ~0ull : ((2ull << lim) - 1ull));
+      }
+    }
+    if (!active) continue;
     if constexpr (STATS) {
       // slots this lane owns: c = 32hf + 8(r/4) + r%4
       st_kept += iq < N ? (unsigned)__popcll(km & 0x0F0F0F0F0F0F0F0Full) : 0u;
-      st_tiles += NH;
+      st_tiles += 2u;
     }
 
     // ---- S^T = K Q^T : lane = query (q), accumulator r of half hf <-> key 32hf + 8(r/4) + 4gg + r%4
-    const uint16_t *Kt = Ks[grp][cur] + (NH == 1 ? (wv >> 1) * (32 * 128) : 0);
-    f32x16 sacc[NH];
+    const uint16_t *Kt = Ks[grp][cur];
+    f32x16 sacc[2];
 #pragma unroll
-    for (int hf = 0; hf < NH; ++hf)
+    for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
       for (int r = 0; r < 16; ++r) sacc[hf][r] = 0.f;
     {
@@ -574,20 +572,20 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
       // The two key halves take turns, so that a product does not follow the one whose sums it adds to.
       bf16x8 kf[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) kf[i] = SA_KFRAG(Kt, i % NH, i / NH);
+      for (int i = 0; i < 4; ++i) kf[i] = SA_KFRAG(Kt, i & 1, i >> 1);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < 8 * NH; ++i) {
-        const int hf = i % NH, ks = i / NH;
+      for (int i = 0; i < 16; ++i) {
+        const int hf = i & 1, ks = i >> 1;
         sacc[hf] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i & 3], qf[ks], sacc[hf], 0, 0, 0);
-        if (i + 4 < 8 * NH) kf[i & 3] = SA_KFRAG(Kt, (i + 4) % NH, (i + 4) / NH);
+        if (i + 4 < 16) kf[i & 3] = SA_KFRAG(Kt, (i + 4) & 1, (i + 4) >> 1);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
     if (needmask) {
       if (bits) {
 #pragma unroll
-        for (int hf = 0; hf < NH; ++hf)
+        for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int c = 32 * hf + 8 * (r / 4) + (r % 4);
@@ -595,7 +593,7 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
           }
       } else {
 #pragma unroll
-        for (int hf = 0; hf < NH; ++hf)
+        for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int c = 32 * hf + 8 * (r / 4) + (r % 4);
@@ -609,7 +607,7 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
     __builtin_amdgcn_s_setprio(0);
     float tmax = -INFINITY;
 #pragma unroll
-    for (int hf = 0; hf < NH; ++hf)
+    for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
       for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, sacc[hf][r]);
     tmax = max_pair(tmax);
@@ -650,7 +648,7 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
     // (2 passes each) replace eight additions on the vector ALU.
     const s16x4 ones4 = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
     // ---- O^T += V^T P^T : k-slot (gg,e) of step (hf,u) <-> key 32hf + 16u + 8(e/4) + 4gg + e%4 ----
-    const uint16_t *Vt = Vs[grp][cur] + (NH == 1 ? (wv >> 1) * (32 * 128) : 0);
+    const uint16_t *Vt = Vs[grp][cur];
     {
       // 16 V^T fragments (4 key steps x 4 d blocks), each two transposing reads; same ring of four
       s16x4 vlo[4], vhi[4];
@@ -669,7 +667,7 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
       // before.  Vector-ALU and matrix instructions of one wave overlap only when they alternate
       // in its instruction stream.
 #pragma unroll
-      for (int i = 0; i < 8 * NH; ++i) {
+      for (int i = 0; i < 16; ++i) {
         const int g = i >> 2, db = i & 3;  // key step g = 2*hf + u covers keys 16g .. 16g+15
         if (db == 0) {
           cvt2(g, 3);
@@ -685,82 +683,17 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
           if (db == 3)
             lacc[1] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones4, __builtin_shufflevector(ps, ps, 4, 5, 6, 7), lacc[1], 0, 0, 0);
         }
-        if (i + 4 < 8 * NH) {
+        if (i + 4 < 16) {
           vlo[i & 3] = SA_VTR(Vt, (i + 4) & 3, 16 * ((i + 4) >> 2));
           vhi[i & 3] = SA_VTR(Vt, (i + 4) & 3, 16 * ((i + 4) >> 2) + 8);
         }
-        if (g + 1 < 2 * NH) {
+        if (g + 1 < 4) {
           soft2(g + 1, db);
           if (db > 0) cvt2(g + 1, db - 1);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-  };
-  for (int step = 0; step < n_pair_step; ++step) {
-    const int t = G * step + grp, cur = step & 1;
-    // this wave's share of tile t has landed (nothing else is in flight); after the barrier the
-    // whole tile is in LDS[cur] and every wave has finished reading LDS[cur^1] (tile t-1)
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    __syncthreads();
-    const uint32_t w_new = (uint32_t)__builtin_amdgcn_readfirstlane((int)w_nxt);
-    if (t + G < npair) SA_ISSUE_PAIR(t + G, cur ^ 1, w_new)
-    else if (t + G < ntot) SA_ISSUE_TILE(t + G, cur ^ 1, SA_ENTRY(t + G, w_new));
-    const int j0 = (int)(w_cur >> (wv < 2 ? 0 : 16) & 0xFFFu) * BK + 32 * (t & 1);
-    w_cur = w_new;
-    w_nxt = ((const uint32_t *)tlist)[min(t + 2 * G, kMaxSeq / BK - 1) >> 1];
-    if (j0 > min(r0 + 31, N - 1)) continue;
-    const uint32_t vm = has_cols ? uload(colbm, j0 >> 5) : 0u;
-    const bool needmask = vm != 0u || j0 + 31 > r0;
-    uint32_t km = ~0u;
-    int lim = 31;
-    if (needmask) {
-      lim = iq - j0 - 4 * gg;  // causal: slot c kept iff c <= lim
-      km = (lim < 0 ? 0u : (lim >= 31 ? ~0u : ((2u << lim) - 1u))) & ~(vm >> (4 * gg));  // selected columns: gather tiles
-    }
-    products(std::integral_constant<int, 1>{}, cur, needmask, vm != 0u, km, lim);
-  }
-  int e_cur = SA_ENTRY(npair + grp, w_cur);  // one entry at a time from here on
-  int r_nxt = SA_ENTRY(npair + grp + G, w_nxt);
-  for (int step = n_pair_step; step < n_step; ++step) {
-    const int t = G * step + grp, cur = step & 1;
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // as above
-    __syncthreads();
-    const int e_nxt = __builtin_amdgcn_readfirstlane(r_nxt);
-    if (t + G < ntot) SA_ISSUE_TILE(t + G, cur ^ 1, e_nxt);
-    const int e_this = e_cur;
-    e_cur = e_nxt;
-    r_nxt = (int)tlist[min(t + 2 * G, kMaxSeq / BK - 1)];
-
-    bool active, needmask, bits = false;
-    uint64_t km;
-    int lim = 63;
-    if (t < ntr) {
-      const int kt = e_this & 0xFFF;
-      const int j0 = kt * BK;
-      const bool bk = ((e_this >> (wv < 2 ? 14 : 15)) & 1) != 0;
-      const bool beyond = j0 > min(r0 + 31, N - 1);
-      active = !beyond && bk;
-      const uint64_t vm = has_cols ? ((uint64_t)uload(colbm, 2 * kt) | ((uint64_t)uload(colbm, 2 * kt + 1) << 32)) : 0ull;
-      needmask = !(vm == 0 && j0 + 63 <= r0);
-      km = ~0ull;
-      bits = vm != 0;
-      if (active && needmask) {
-        lim = iq - j0 - 4 * gg;
-        const uint64_t cm = lim < 0 ? 0ull : (lim >= 63 ? ~0ull : ((2ull << lim) - 1ull));
-        km = cm & ~(vm >> (4 * gg));
-      }
-    } else {
-      const int gi = t - ntr;
-      active = cwave > gi * BK;
-      needmask = cwmin < (gi + 1) * BK;  // some query of the wave sees only a part of this tile
-      km = ~0ull;
-      if (needmask) {
-        lim = cle - gi * BK - 1 - 4 * gg;  // visible columns of this tile for this query, as a slot limit
-        km = lim < 0 ? 0ull : (lim >= 63 ? ~0ull : ((2ull << lim) - 1ull));
-      }
-    }
-    if (active) products(std::integral_constant<int, 2>{}, cur, needmask, bits, km, lim);
   }
   l_run = lacc[0][0] + lacc[1][0];
 
@@ -1038,8 +971,6 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
 #undef SA_KFRAG
 #undef SA_VTR
 #undef SA_ISSUE_TILE
-#undef SA_ISSUE_PAIR
-#undef SA_ENTRY
 #undef SA_DMA16
 
 // log2 of the queues that share a KV head, and from bit 4 on log2 of the row blocks a queue takes in a row
@@ -1081,18 +1012,6 @@ bool split_items(const Shape &sh) {
   return sh.gq == sh.g && n_items <= (long_items ? 2 : 1) * sh.n_cu;
 }
 
-// Whether the tiles that one of an item's two row blocks keeps alone are taken in pairs, one of either block.  By itself
-// such a tile occupies two of the four waves, and with them two of the four SIMDs, and takes 0.7 of the time of one that
-// all multiply; in pairs the waves of both blocks multiply 32 keys of their own tile in each of two steps.  A layer of 10K
-// tokens whose diagonals are whole blocks (two thirds of its tiles are kept by one block) 317 -> 302 us, 16K 382 -> 373,
-// 32K (a fifth) 682 -> 680; with two groups of waves per item 8 heads at 2K tokens, no two rows alike,
-// 57.1 -> 55.9, and 4 Interval-Slash heads at 4K, whose items have one pair, 53.0 -> 53.2.  With 128-row blocks every tile is kept by the whole item, and where every block is kept beside
-// a quarter of the keys as columns (what sa_default_budgets gives for keep = 1) only the diagonal ones of Interval-Slash
-// heads are not: there the kernel without the second loop stays (dense at 16K tokens 1925 us, 1940 with it).
-bool pair_tiles(const Shape &sh) {
-  return sh.b != BQ && !(4 * ((long long)sh.k_v + BK / 2) >= sh.N && (long long)sh.k_b >= (long long)sh.nb * (sh.nb + 1) / 2);
-}
-
 int queue_capacity(const Shape &sh) {
   const int share = queue_share(sh), slots = 8 >> (share & 15);
   return tickets_per_head((sh.N + BQ - 1) / BQ, share) * sh.g * ((sh.Hkv + slots - 1) / slots);
@@ -1123,7 +1042,6 @@ hipError_t launch_sparse_prefill(const Shape &sh, const Workspace &ws, const uin
   a.n_items = a.nT * sh.Hq;
   a.share = queue_share(sh);
   a.qcap = queue_capacity(sh);
-  a.pairs = pair_tiles(sh);
   a.side_by_side = a.n_items <= 8 * sh.n_cu;
   a.items = (uint4 *)ws.attn_items;
   a.tiles = ws.attn_tiles;
@@ -1141,18 +1059,14 @@ hipError_t launch_sparse_prefill(const Shape &sh, const Workspace &ws, const uin
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int grid = a.grid;
-  auto launch = [&](auto stats, auto groups) {
-    constexpr bool S = decltype(stats)::value;
-    constexpr int G = decltype(groups)::value;
-    if (a.pairs) sparse_prefill_kernel<S, G, true><<<grid, 256 * G, 0, st>>>(a);
-    else sparse_prefill_kernel<S, G, false><<<grid, 256 * G, 0, st>>>(a);
-  };
-  using One = std::integral_constant<int, 1>;
-  using Two = std::integral_constant<int, 2>;
-  if (counters && split) launch(std::true_type{}, Two{});
-  else if (counters) launch(std::true_type{}, One{});
-  else if (split) launch(std::false_type{}, Two{});
-  else launch(std::false_type{}, One{});
+  if (counters && split)
+    sparse_prefill_kernel<true, 2><<<grid, 512, 0, st>>>(a);
+  else if (counters)
+    sparse_prefill_kernel<true, 1><<<grid, 256, 0, st>>>(a);
+  else if (split)
+    sparse_prefill_kernel<false, 2><<<grid, 512, 0, st>>>(a);
+  else
+    sparse_prefill_kernel<false, 1><<<grid, 256, 0, st>>>(a);
   return hipGetLastError();
 }
 

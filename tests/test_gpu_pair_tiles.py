@@ -1,6 +1,5 @@
-"""Key tiles that one of an item's two row blocks keeps alone, taken in pairs (64-row blocks): as many for either block,
-more for one of them, none for one, a last row block without a partner; with selected columns and diagonals inside
-such tiles.  Against the oracle, with items whole (many heads) and shared by two groups of waves (few)."""
+"""Key tiles that one of an item's two row blocks keeps alone (64-row blocks): as many for either block, more for one of
+them, none for one, a last row block without a partner; with selected columns and diagonals inside such tiles.  Against the oracle, with items whole (many heads) and shared by two groups of waves (few)."""
 import numpy as np
 import pytest
 import torch
@@ -28,7 +27,7 @@ def _kept(rng, kind, R):
     return np.sort(rng.choice(R + 1, rng.integers(0, R + 2), replace=False))
 
 
-# with a budget of a quarter of the keys as columns beside every block, the lists hold no pairs
+# full: a budget of a quarter of the keys as columns beside every block, with which twice as many items are shared
 @pytest.mark.parametrize("Hq,Hkv,N,full", [(64, 8, 576, 0), (64, 8, 640, 0), (64, 8, 576, 1), (6, 2, 64, 1), (6, 2, 192, 0),
                                            (6, 2, 192, 1), (12, 4, 1344, 0), (12, 4, 4224, 0), (12, 4, 4224, 1)])
 def test_tiles_of_one_row_block(Hq, Hkv, N, full):
