@@ -403,22 +403,15 @@ int decode_splits(const Shape &sh) {
 
 namespace {
 
-// Workgroups per head of one step, at most decode_splits.  Those without keys of their own only read how long the list
-// is, but 512 of them are still 0.4 us of a step of 7.  What a list holds is known on the device; the
-// host knows the budgets: one workgroup per compute unit where a single step of each (64 keys) covers an
-// Interval-Slash and a Triangular list (8 heads at 1.2K tokens with 744 generated ones 6.71 -> 6.23 us, 32 heads at 2K
-// 7.26 -> 6.84, 8 heads at 93K 6.67 -> 6.25), else two (16 heads at 64K 7.95 us, with one 8.75).  No
-// more than an even list of a Block-Cluster head needs four times over: a hot last row holds more than its share (twice
-// its share: 4 heads at 60K 6.62 -> 6.84).  A list that is longer is taken in larger chunks.
+// Workgroups per head of one step: decode_splits, but no more than have a step's 64 keys in the longest list that the
+// budgets allow.  Those without keys only read how long the list is, but 512 of them are still 0.4 us of a step of 7 (8
+// heads at 1.2K tokens with 744 generated ones 6.97 -> 6.67 us, 6.74 -> 6.19 with few blocks).  What a list does hold is
+// known on the device alone, and k_blocks >= nb lets any head keep every block of the last row.  The line is not drawn by
+// what the budgets give on average: 256 workgroups wherever such lists fit them took 0.4 us from those, but rows of twice
+// the mean lost (24 heads at 3K 6.6 -> 7.9 us, 8 at 64K 7.1 -> 8.2) and whole rows more (8 heads at 64K 23 -> 31, at 128K 38 -> 54).
 int splits_of_step(const Shape &sh, int pos) {
-  const int64_t own = (int64_t)pos - sh.N + 1;
-  const int64_t slash = (int64_t)sh.k_v + sh.k_s + sh.b, band = (int64_t)std::min(sh.sink + sh.local, sh.nb) * sh.b;
-  const int64_t cluster = std::min<int64_t>(4 * (int64_t)sh.k_b / sh.nb + 1, sh.nb) * sh.b;
-  const int64_t list = std::max(slash, band) + own, most = std::max(list, cluster + own);
-  const int half = std::max(256 / std::max(sh.Hq, 1), 1);
-  int64_t s = decode_splits(sh);
-  if (list <= (int64_t)half * kMinChunk) s = std::min<int64_t>(s, half);
-  return (int)std::max<int64_t>(1, std::min<int64_t>(s, (most + kMinChunk - 1) / kMinChunk));
+  const int64_t longest = (int64_t)pos + 1 + sh.k_v + sh.k_s;  // every key, and the columns and offsets beside them
+  return (int)std::min<int64_t>(decode_splits(sh), (longest + kMinChunk - 1) / kMinChunk);
 }
 
 }  // namespace
