@@ -53,6 +53,12 @@ def cpu_baseline(orc, data, wl, bud, sample_rows):
     }
 
 
+def matrix_flop(tiles, diagonals, d):
+    """FLOP of the matrix products behind a count of 32x32 sub-tiles, `diagonals` of them diagonals, which are
+    multiplied in 4x4 pieces (32 products of 2048 FLOP at d = 128): an eighth of a sub-tile."""
+    return 4.0 * d * 32 * 32 * (tiles - diagonals * 7 / 8)
+
+
 def run_workload(name, steps, warmup, layers, with_cpu, sample_rows, with_dense=False, block_select=0,
                  diagonal_select=0, prewarm_s=PREWARM_S, lazy_block_map=0, force_pattern=None, plain=False):
     import numpy as np
@@ -195,13 +201,15 @@ def run_workload(name, steps, warmup, layers, with_cpu, sample_rows, with_dense=
         log(f"[{name}] graph replay skipped: {e!r}")
         torch.cuda.synchronize()
 
-    # work accounting (untimed): tiles multiplied and kept pairs per layer, pattern choices
-    tiles, kept, confusion = [], [], np.zeros((3, 3), int)
+    # work accounting (untimed): tiles computed, diagonals among them, and kept pairs per layer, pattern choices
+    tiles, diagonals, kept, confusion = [], [], [], np.zeros((3, 3), int)
     for l in range(layers):
         Q, K, V, planted = resident[l]
         ses.estimate(Q, K)
         ses.build_index(ov)
         c = ses.prefill_counted(Q, K, V, O)
+        ses.n_offs.zero_()
+        diagonals.append(c[0] - ses.prefill_counted(Q, K, V, O)[0])
         tiles.append(c[0]); kept.append(c[1])
         for pp, ch in zip(planted, ses.pattern.cpu().tolist()):
             if pp >= 0:
@@ -235,7 +243,7 @@ def run_workload(name, steps, warmup, layers, with_cpu, sample_rows, with_dense=
         ses.n_offs.copy_(saved_n_offs)
         diag_tiles = c_full[0] - c_tile[0]                 # one 32-key tile per (wave, diagonal)
         diag_bytes = diag_tiles * 32 * 2 * d * 2           # 32 K rows + 32 V rows of d bf16 each
-        f_tile_loop = 4.0 * d * c_tile[0] * 32 * 32
+        f_tile_loop = matrix_flop(c_tile[0], 0, d)
         t_diag = max(t_full - t_tile, 1e-6)
         attn_phases = {
             "layer": 0, "attention_ms": t_full,
@@ -251,7 +259,7 @@ def run_workload(name, steps, warmup, layers, with_cpu, sample_rows, with_dense=
         log(f"[{name}] attention {t_full:.3f} ms = tile loop {t_tile:.3f} ms ({attn_phases['tile_loop']['TFLOPs_on_tiles']:.0f} TFLOP/s on tiles) "
             f"+ diagonals {t_diag:.3f} ms ({diag_bytes / 1e9:.2f} GB, {attn_phases['diagonals']['GBps']:.0f} GB/s)")
     f_mask = 4.0 * d * float(np.mean(kept))
-    f_tiles = 4.0 * d * float(np.mean(tiles)) * 32 * 32   # counter unit: one 32 x 32 sub-tile
+    f_tiles = matrix_flop(float(np.mean(tiles)), float(np.mean(diagonals)), d)
     f_dense = 4.0 * d * Hq * N * (N + 1) / 2.0
     nb = N // b
     est_bytes = 2 * Hkv * N * d + 2 * Hq * N * d + 2 * Hq * w * d + 8 * Hq * N + 4 * Hq * nb * nb

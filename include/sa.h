@@ -173,10 +173,12 @@ sa_status sa_sparse_prefill(sa_ctx *ctx, const void *Q, const void *K, const voi
 
 /* Same computation and output as sa_sparse_prefill, plus work accounting for
  * the FLOP figures of a benchmark: adds to counters_dev[0] the number of
- * 32-query x 32-key sub-tiles the kernel multiplied (a 64-key tile of one wave
- * counts 2, a selected diagonal of one wave counts 1; 4*head_dim*32*32 FLOP
- * each) and to counters_dev[1] the number of kept (query, key) pairs, |M| of the sparse
- * softmax of Alg. 2 / Alg. 3.  counters_dev: DEVICE uint64[2], zeroed by the
+ * 32-query x 32-key sub-tiles the kernel computed (a 64-key tile of one wave
+ * counts 2, a selected diagonal of one wave counts 1) and to counters_dev[1] the
+ * number of kept (query, key) pairs, |M| of the sparse softmax of Alg. 2 /
+ * Alg. 3.  Half a 64-key tile is 4*head_dim*32*32 FLOP; a diagonal is an eighth of
+ * that, since only the 4x4 pieces along its sub-tile's diagonal are multiplied.  The
+ * count without diagonals is that of the same index with n_offs = 0.  counters_dev: DEVICE uint64[2], zeroed by the
  * caller.  A benchmark times sa_sparse_prefill, not this variant. */
 sa_status sa_sparse_prefill_counted(sa_ctx *ctx, const void *Q, const void *K, const void *V,
                                     sa_index idx, void *O, uint64_t *counters_dev,

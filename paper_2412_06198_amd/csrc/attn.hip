@@ -59,7 +59,8 @@ struct AttnArgs {
                 // log2 of the consecutive row blocks a queue takes in a row (kRun or 1)
   int qcap;     // tickets per queue, holes of the id space included
   int side_by_side;  // also the heads with diagonals take a row block together, see plan_item
-  unsigned long long *counters;  // instrumentation only: {32x32 sub-tiles multiplied, kept (query,key) pairs}
+  unsigned long long *counters;  // instrumentation only: {32x32 sub-tiles computed (a diagonal is one, and an eighth of
+                                 // its products), kept (query,key) pairs}
   // Written by index_prepare_kernel.  items[queue + 8 * ticket] = {head | its query head << 7 | its KV head << 14 |
   // row block << 21, key tiles in the list (kNoItem: a hole of the id space), list start inside the head's share
   // of tiles, first two entries}; tiles [Hq][tile_cap] list entries: key tile (bits 0..11), kept by waves 0, 1
