@@ -552,17 +552,17 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
   const int rounds = 1 + halvings / 2;
   const bool ranked = N <= kRankMaxSeq;  // all steps in one launch
 
-  // host memory of the call: what goes to the device, what comes back
+  // host memory of the call: what goes to the device (nothing where one launch takes all steps), what comes back
   const int nblocks = (N + 15) / 16 < kNormBlocks ? (N + 15) / 16 : kNormBlocks;
   static_assert(sizeof(Refine) % sizeof(double) == 0, "the sums follow the states");
   const int most = z.full.heads;
-  const std::unique_ptr<sa::HeadBudget[]> head(new (std::nothrow) sa::HeadBudget[(size_t)most * (kSets + kProbes)]);
-  const std::unique_ptr<Refine[]> begin(new (std::nothrow) Refine[most]);
+  const std::unique_ptr<sa::HeadBudget[]> head(ranked ? nullptr : new (std::nothrow) sa::HeadBudget[(size_t)most * (kSets + kProbes)]);
+  const std::unique_ptr<Refine[]> begin(ranked ? nullptr : new (std::nothrow) Refine[most]);
   const std::unique_ptr<double[]> back(new (std::nothrow) double[most * (sizeof(Refine) / sizeof(double) + 3 * (size_t)nblocks)]);
-  if (!head || !begin || !back) return failp(ctx, SA_ERR_INVALID_ARG, "search: out of host memory");
+  if (!back || (!ranked && (!head || !begin))) return failp(ctx, SA_ERR_INVALID_ARG, "search: out of host memory");
   sa::HeadBudget *hb = head.get();
   Refine *hr = begin.get();
-  for (int i = 0; i < most; ++i) hr[i].start(x_lo, x_hi);
+  for (int i = 0; !ranked && i < most; ++i) hr[i].start(x_lo, x_hi);
   hipError_t he = hipSuccess;
   auto ok = [&](hipError_t e) {
     if (e != hipSuccess && he == hipSuccess) he = e;
@@ -580,7 +580,7 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
         for (int k = 0; k < kSets; ++k) hb[virtual_head(i, k, gb, kSets)] = set_budget(k, known, N, nb);
       }
     }
-    const size_t norms = (size_t)B * 3 * nblocks, n_budgets = (size_t)B * (kSets + kProbes);
+    const size_t norms = (size_t)B * 3 * nblocks;
     const double *hp = back.get() + B * (sizeof(Refine) / sizeof(double));
     const sa::Shape &cs = l.cs, &ps = l.ps;
     const sa::Workspace &ws = l.ws;
@@ -593,8 +593,10 @@ sa_status sa_search_patterns(sa_ctx *ctx, const void *Q, const void *K, const vo
     const uint16_t *Kh = (const uint16_t *)K + (size_t)(h0 / sh.g) * sh.kv_hs;
     const uint16_t *Vh = (const uint16_t *)V + (size_t)(h0 / sh.g) * sh.kv_hs;
     const sa_scores sc{scores.v + (size_t)h0 * N, scores.s + (size_t)h0 * N, scores.blk + (size_t)h0 * nb * nb};
-    if (!ranked) ok(hipMemcpyAsync(budgets, hb, n_budgets * sizeof(sa::HeadBudget), hipMemcpyHostToDevice, stream));
-    if (!ranked) ok(hipMemcpyAsync(state, hr, (size_t)B * sizeof(Refine), hipMemcpyHostToDevice, stream));
+    if (!ranked) {
+      ok(hipMemcpyAsync(budgets, hb, (size_t)B * (kSets + kProbes) * sizeof(sa::HeadBudget), hipMemcpyHostToDevice, stream));
+      ok(hipMemcpyAsync(state, hr, (size_t)B * sizeof(Refine), hipMemcpyHostToDevice, stream));
+    }
     // RefineSearchSpace of the Interval-Slash candidate, all heads a step per round (a head that is done
     // repeats its last index)
     sa::Override ov;
