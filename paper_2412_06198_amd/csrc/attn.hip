@@ -299,7 +299,6 @@ __global__ __launch_bounds__(256) void index_prepare_kernel(AttnArgs p, unsigned
 // LDS tiles are 64 rows x 256 B with the 16-byte chunks of a row XOR-swizzled (no padding):
 //   K: chunk c of row r sits at chunk c ^ (r & 15)      -> b128 reads of 16 rows hit 64 banks
 //   V: chunk c of row r sits at chunk c ^ ((r & 3) << 2) -> the transposing b64 reads do
-__device__ inline int vswz(int row, int chunk) { return row * 128 + ((chunk ^ ((row & 3) << 2)) << 3); }
 
 // The larger of a lane's value and that of the lane 32 away, in both.  A shuffle through LDS queues behind
 // the operand reads of eight waves and every tile waits for it: with the half-wave swap and the order of
