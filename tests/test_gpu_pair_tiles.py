@@ -1,5 +1,6 @@
 """Key tiles that one of an item's two row blocks keeps alone (64-row blocks): as many for either block, more for one of
-them, none for one, a last row block without a partner; with selected columns and diagonals inside such tiles.  Against the oracle, with items whole (many heads) and shared by two groups of waves (few)."""
+them, none for one, a last row block without a partner; with selected columns and diagonals inside such tiles.  Against
+the oracle, with items whole (many heads) and shared by two groups of waves (few)."""
 import numpy as np
 import pytest
 import torch
@@ -27,11 +28,12 @@ def _kept(rng, kind, R):
     return np.sort(rng.choice(R + 1, rng.integers(0, R + 2), replace=False))
 
 
-# full: a budget of a quarter of the keys as columns beside every block, with which twice as many items are shared
-@pytest.mark.parametrize("Hq,Hkv,N,full", [(64, 8, 576, 0), (64, 8, 640, 0), (64, 8, 576, 1), (6, 2, 64, 1), (6, 2, 192, 0),
-                                           (6, 2, 192, 1), (12, 4, 1344, 0), (12, 4, 4224, 0), (12, 4, 4224, 1)])
+# items of 128 rows: 64 heads and 12 heads of 4224 tokens have more than the 256 compute units and stay whole, the others are shared, down to
+# lists of no, one or two tiles for a group; full: a quarter more of the keys as columns
+@pytest.mark.parametrize("Hq,Hkv,N,full", [(64, 8, 576, 0), (64, 8, 640, 0), (64, 8, 576, 1), (6, 2, 64, 1), (6, 2, 128, 0), (6, 2, 192, 0),
+                                           (6, 2, 192, 1), (6, 2, 320, 0), (6, 2, 448, 1), (12, 4, 1344, 0), (12, 4, 4224, 0), (12, 4, 4224, 1)])
 def test_tiles_of_one_row_block(Hq, Hkv, N, full):
-    print(f"case pairs of tiles {Hq}/{Hkv} heads N={N} full {full}", flush=True)
+    print(f"case tiles of one row block {Hq}/{Hkv} heads N={N} full {full}", flush=True)
     b, nb, k_v, k_s = 64, N // 64, min(N, 70 + full * N // 4), 5
     rng = np.random.default_rng(N + Hq)
     ses = make_session(Hq, Hkv, N, b, min(64, N), orc.Budgets(1, 1, k_v, k_s, nb * (nb + 1) // 2))
@@ -55,6 +57,6 @@ def test_tiles_of_one_row_block(Hq, Hkv, N, full):
         ses.prefill(Qd, Kd, Vd, O)
     _, kept = ses.prefill_counted(Qd, Kd, Vd, counted)
     torch.cuda.synchronize()
-    check_attention(host_f64(O), orc.masked_rows(Q, K, V, b, index)[0], f"pairs {N}")
+    check_attention(host_f64(O), orc.masked_rows(Q, K, V, b, index)[0], f"tiles of one row block {N}")
     assert torch.equal(O, counted)
     assert kept == sum(orc.mask_count(N, b, h, index) for h in range(Hq))
