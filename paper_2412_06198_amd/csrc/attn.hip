@@ -701,8 +701,9 @@ __global__ __launch_bounds__(256 * G, 2) void sparse_prefill_kernel(AttnArgs p) 
   // For offset o the 32 queries of this wave need the 32 keys r0-o .. r0-o+31, row q for query q.  A lane holds half of
   // a key's row and of its query, which is what v_mfma_f32_4x4x4_16b takes of each of its 16 blocks: it multiplies four
   // neighbours with each other and three of four results are not used, where a product of 32x32x16 used one of 32 and the
-  // diagonals were 17 % of the matrix work of a launch that runs at the card's power limit (layers of 128K tokens 4351
-  // -> 4266 us, 64K 1609 -> 1580, 32K 695 -> 681, 16K 378 -> 371, 4K 53.1 -> 53.3).  K and V tiles are
+  // diagonals were 17 % of the matrix work of a launch that runs at the card's power limit (layers of 128K tokens 4378
+  // -> 4290 us, 64K 1595 -> 1556, 32K 684 -> 673, 16K 376 -> 372; of 8 heads at 4K this launch 19.5 -> 19.2, but the
+  // layer 56.5 -> 56.8, since two others of it take longer).  K and V tiles are
   // copied by the LDS DMA into two wave-private 8 KB buffers in turn (swizzled like the shared tiles)
   // and read from there like any tile, the copies of one running while the one before is multiplied.
   // An entry is dropped when its key block is kept by the CSR or its key is a selected column: those

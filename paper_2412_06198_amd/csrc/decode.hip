@@ -9,7 +9,7 @@
 // memory round trips (list lengths, list, rows, partial (max, sum, output) triple, arrival counter, all
 // triples of the head) and what a single wave issues in between: the workgroup that arrives last merges
 // instead of a second launch, and a list place is resolved by one lane, not by the 16 that read its row.
-// 8 heads, 4096-token prompt: 10.9 -> 6.7 us (an empty launch is 2.2); 32 heads, 128K-token prompt, 29 MB
+// 8 heads, 4096-token prompt: 10.9 -> 6.8 us (an empty launch is 2.2); 32 heads, 128K-token prompt, 29 MB
 // of rows out of the memory-side cache: 16.3 -> 10.8 us, and 26.7 -> 15.0 (the kernels alone) where K and V
 // have been pushed out of it, as they are where a step reads other layers in between.
 #include <algorithm>
